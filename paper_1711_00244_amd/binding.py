@@ -156,6 +156,10 @@ def _want(t, shape, what):
                          f"got {t.dtype} {tuple(t.shape)}")
 
 
+_new_bytes = C.pythonapi.PyBytes_FromStringAndSize
+_new_bytes.restype, _new_bytes.argtypes = C.py_object, [C.c_void_p, C.c_ssize_t]
+
+
 class Layer:
     """Owns a cl_layer handle."""
 
@@ -225,9 +229,9 @@ class Layer:
     def serialize(self) -> bytes:
         n = C.c_size_t(0)
         _check(lib().cl_layer_serialize(self.handle, None, C.byref(n)))
-        buf = C.create_string_buffer(n.value)
+        buf = _new_bytes(None, n.value)          # written by the library before anything else sees it: no zeroing, no copy
         _check(lib().cl_layer_serialize(self.handle, buf, C.byref(n)))
-        return buf.raw[:n.value]
+        return buf
 
 
 def conv_block_h(out_channels: int, groups: int, block_h: int = 128) -> int:

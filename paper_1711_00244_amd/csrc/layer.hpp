@@ -91,7 +91,8 @@ void build_lut(const std::vector<uint8_t> &len, const std::vector<uint32_t> &cod
 // compress.cpp
 // Derive codes and decode tables from the stored lengths, then decode every record
 // on the host and check every table against what the decode finds.
-int32_t finalize_and_validate(cl_layer *L);
+class Team;
+int32_t finalize_and_validate(cl_layer *L, Team &team);
 
 // device.hip
 void release_device(cl_layer *L);

@@ -55,11 +55,11 @@ enum {
 /* Kernel selection for the forward entry points. */
 enum {
     CL_PATH_AUTO = 0,     /* CL_PATH_SPARSE for up to 8 images and for blocks above      */
-                          /*   128 x 128; else whichever of CL_PATH_MFMA_F32 and        */
-                          /*   CL_PATH_SPARSE_WIDE the library's launch models price    */
-                          /*   lower for this layer and batch (the dense tile multiplies */
-                          /*   every zero of a block: at 9 % density the sparse product  */
-                          /*   wins from about 100 images on, at 25 % it does not)       */
+                          /*   128 x 128; else whichever of CL_PATH_SPARSE,             */
+                          /*   CL_PATH_MFMA_F32 and CL_PATH_SPARSE_WIDE the library's    */
+                          /*   launch models price lower for this layer and batch (the   */
+                          /*   dense tile multiplies every zero of a block: at 9 %       */
+                          /*   density the sparse products win, at 25 % it does)         */
     CL_PATH_SPARSE = 1,   /* fused decode + sparse multiply on the vector ALUs      */
     CL_PATH_MFMA_F32 = 2, /* decode blocks to dense LDS tiles, fp32 MFMA; needs blocks */
                           /*   of at most 128 x 128, else CL_EUNSUPPORTED            */
@@ -250,9 +250,10 @@ int32_t cl_fc_resolved_path(const cl_layer *layer, int32_t batch, int32_t path, 
  *  d_X     batch x K fp32        d_bias  M fp32 or NULL
  *  d_Y     batch x M fp32, overwritten
  *  relu    non-zero applies max(0, .)
- *  path    CL_PATH_*.  CL_PATH_SPARSE takes up to 8 images per launch in a fixed
- *          summation order when block_h <= 256 (run-to-run identical); a launch for
- *          9-16 images at once, or a layer with taller blocks, adds lane sums into
+ *  path    CL_PATH_*.  CL_PATH_SPARSE is run-to-run identical (any batch with blocks of
+ *          at most 128 x 128; taller blocks take up to 8 images per launch in a fixed
+ *          summation order when block_h <= 256); a layer with blocks above 256 rows
+ *          adds lane sums into
  *          a shared LDS tile with floating-point atomics, so the last bits of Y can
  *          differ between runs.  The tiles of a block row are added up in a fixed
  *          order either way.  The other paths are run-to-run identical.

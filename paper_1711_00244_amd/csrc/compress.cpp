@@ -115,9 +115,9 @@ struct Scanner {
     uint32_t vmask, imask;
 
     // Decodes chunk c (records r0 .. r1 - 1, first position pos0 of a block of bwp columns and np
-    // cells).  With cnt, surviving weights are counted per half and group of eight rows (16 groups a half).
+    // cells).  With cnt, surviving weights are counted per half and row (128 rows a half).
     template <bool COUNT>
-    ChunkScan chunk(uint64_t r0, uint64_t r1, uint64_t pos0, uint32_t bwp, uint64_t np, uint32_t *cnt) const
+    ChunkScan chunk(uint64_t r0, uint64_t r1, uint64_t pos0, uint32_t bwp, uint64_t np, uint16_t *cnt) const
     {
         ChunkScan s;
         const int shift = (bwp & (bwp - 1)) == 0 ? __builtin_ctz(bwp) : -1;
@@ -143,7 +143,7 @@ struct Scanner {
                     const uint32_t row = shift >= 0 ? at >> shift : at / bwp, col = at - row * bwp;
                     const uint32_t h = col >= 64u;
                     s.right += h;
-                    ++cnt[h * 16u + (row >> 3)];
+                    ++cnt[h * 128u + row];
                 }
             }
             // the bits between the two spans must be zero
@@ -276,14 +276,20 @@ int32_t finalize_and_validate(cl_layer *L, Team &team)
                        (1u << L->val_lut_bits) - 1u, (1u << L->idx_lut_bits) - 1u};
     // the half-by-half order of the wide path (blocks of at most 128 x 128 only): per block, counts
     // first, list positions once the weights of all blocks before it are known
-    constexpr int kGroups = 16, kPer = 2 * (kGroups + 1);
+    constexpr int kGroups = 16, kPer = 2 * (kGroups + 1), kRows = 128;
     const bool halves = d.block_h <= 128 && d.block_w <= 128;
     L->chunk_nz.assign((size_t)L->n_chunks + 1, 0u);
+    L->slot.clear();
     L->chunk_half.clear();
     L->group_ptr.clear();
+    L->row_ptr.clear();
     if (halves) {
         L->chunk_half.assign((size_t)L->n_chunks * 2, 0u);
         L->group_ptr.assign((size_t)g.n_blocks * kPer, 0u);
+        L->row_ptr.assign((size_t)g.n_blocks * kRowPtrs, 0u);
+        L->block_slots = 1;
+        for (int64_t b = 0; b < g.n_blocks; ++b) L->block_slots = std::max<int32_t>(L->block_slots, (int32_t)(L->block_chunk[b + 1] - L->block_chunk[b]));
+        L->slot.assign((size_t)g.n_blocks * L->block_slots, ChunkSlot{});
     }
     std::atomic<int64_t> vbits{0}, ibits{0}, bad_chunk{L->n_chunks};
     auto report = [&](int64_t c) {
@@ -296,7 +302,8 @@ int32_t finalize_and_validate(cl_layer *L, Team &team)
         for (int64_t b = g.n_blocks * u / units; b < g.n_blocks * (u + 1) / units; ++b) {
             int row_id, col_id, bhp, bwp;
             g.block(b, row_id, col_id, bhp, bwp);
-            uint32_t cnt[2 * kGroups] = {0}, left = 0, right = 0;
+            uint16_t cnt[2 * kRows] = {0};
+            uint32_t left = 0, right = 0;
             for (uint32_t c = L->block_chunk[b]; c < L->block_chunk[b + 1]; ++c) {
                 const cl_chunk_meta &m = L->meta[c], &m1 = L->meta[(size_t)c + 1];
                 const ChunkScan s = halves ? scan.chunk<true>(m.rec_off, m1.rec_off, m.pos0, (uint32_t)bwp, (uint64_t)bhp * bwp, cnt)
@@ -309,6 +316,7 @@ int32_t finalize_and_validate(cl_layer *L, Team &team)
                 my_v += s.vbits;
                 my_i += s.ibits;
                 L->chunk_nz[c] = s.weights;
+                if (halves) L->slot[(size_t)b * L->block_slots + (c - L->block_chunk[b])] = ChunkSlot{m.rec_off, m1.rec_off - m.rec_off, m.pos0, left + right};
                 if (halves) {
                     L->chunk_half[2 * (size_t)c] = left;
                     L->chunk_half[2 * (size_t)c + 1] = right;
@@ -322,10 +330,16 @@ int32_t finalize_and_validate(cl_layer *L, Team &team)
                     uint32_t *gp = &L->group_ptr[(size_t)b * kPer + (size_t)h * (kGroups + 1)];
                     for (int q = 0; q < kGroups; ++q) {
                         gp[q] = at;
-                        at += cnt[h * kGroups + q];
+                        for (int r = q * kRows / kGroups; r < (q + 1) * kRows / kGroups; ++r) at += cnt[h * kRows + r];
                     }
                     gp[kGroups] = at;
                 }
+                uint16_t *rp = &L->row_ptr[(size_t)b * kRowPtrs], row_at = 0;
+                for (int r = 0; r < kRows; ++r) {
+                    rp[r] = row_at;
+                    row_at = (uint16_t)(row_at + cnt[r] + cnt[kRows + r]);
+                }
+                rp[kRows] = row_at;
             }
         }
         vbits += my_v;

@@ -15,7 +15,7 @@
 //
 // One translation unit: this file holds the host side (device image of a layer, launch
 // shapes, the entry points) and includes the kernels - decode.hpp (wavefront primitives,
-// decoding and placement passes), sparse_kernels.hpp, mfma_kernels.hpp, wide_kernels.hpp, bf16_kernels.hpp,
+// decoding and placement passes), sparse_kernels.hpp, mfma_kernels.hpp, wide_kernels.hpp, rows_kernels.hpp, bf16_kernels.hpp,
 // conv_kernels.hpp, finish_kernels.hpp, layer_kernels.hpp.
 #include <hip/hip_runtime.h>
 #include <type_traits>
@@ -57,20 +57,22 @@ struct LayerDev {
     const cl_chunk_meta *meta;
     const uint32_t *panel_chunk;
     const uint32_t *block_chunk;
-    const uint32_t *chunk_nz;
+    const ChunkSlot *slot;               // null unless the blocks are at most 128 x 128 (with row_ptr)
     const uint32_t *chunk_half;          // null unless the blocks are at most 128 x 128 (with group_ptr)
     const uint32_t *group_ptr;
+    const uint16_t *row_ptr;             // null unless the blocks are at most 128 x 128
     const float *codebook;
-    const lut_t *val_lut;
-    const lut_t *idx_lut;
+    const uint4 *tables;                 // both decode tables and the codebook as they lie in LDS (carve)
     int M, K, bh, bw, nbw;
     int val_bits, idx_bits, ncode;       // index widths of the decode tables, codebook entries
+    int block_slots;                     // slots of a block in `slot`
     int table_rows;                      // 16-byte rows of the table image (tables + codebook)
     uint32_t n_chunks;
     int panel0;                          // first block row of a launch that covers only some (a filter group); else 0
 };
 
-// Bytes of the table image: both decode tables, then the codebook, each padded to 16 bytes.
+// Bytes of the table image: both decode tables - the larger one first, so that each starts at
+// a multiple of its size - then the codebook, each padded to 16 bytes.
 static size_t table_image_bytes(int vbits, int ibits, int ncode)
 {
     const size_t tb = (((size_t)1 << vbits) + ((size_t)1 << ibits)) * sizeof(lut_t);
@@ -84,12 +86,13 @@ static LayerDev make_dev(const cl_layer *L)
     d.meta = L->dev.meta;
     d.panel_chunk = L->dev.panel_chunk;
     d.block_chunk = L->dev.block_chunk;
-    d.chunk_nz = L->dev.chunk_nz;
+    d.slot = L->dev.slot;
+    d.block_slots = L->block_slots;
     d.chunk_half = L->dev.chunk_half;
     d.group_ptr = L->dev.group_ptr;
     d.codebook = L->dev.codebook;
-    d.val_lut = L->dev.val_lut;
-    d.idx_lut = L->dev.idx_lut;
+    d.row_ptr = L->dev.row_ptr;
+    d.tables = (const uint4 *)L->dev.tables;
     d.M = L->desc.M;
     d.K = L->desc.K;
     d.bh = L->desc.block_h;
@@ -108,6 +111,7 @@ static LayerDev make_dev(const cl_layer *L)
 #include "sparse_kernels.hpp"
 #include "mfma_kernels.hpp"
 #include "wide_kernels.hpp"
+#include "rows_kernels.hpp"
 #include "bf16_kernels.hpp"
 #include "conv_kernels.hpp"
 #include "finish_kernels.hpp"
@@ -231,20 +235,22 @@ extern "C" int32_t cl_layer_upload(cl_layer *L)
     std::vector<char> image(table_image_bytes(L->val_lut_bits, L->idx_lut_bits, ncode), 0);
     {
         const size_t vb = L->val_lut.size() * sizeof(lut_t), ib = L->idx_lut.size() * sizeof(lut_t);
-        std::memcpy(image.data(), L->val_lut.data(), vb);
-        std::memcpy(image.data() + vb, L->idx_lut.data(), ib);
+        const bool values_first = vb >= ib;
+        std::memcpy(image.data() + (values_first ? 0 : ib), L->val_lut.data(), vb);
+        std::memcpy(image.data() + (values_first ? vb : 0), L->idx_lut.data(), ib);
         std::memcpy(image.data() + ((vb + ib + 15) & ~(size_t)15), L->codebook.data(), L->codebook.size() * 4);
     }
-    Sec secs[9] = {
+    Sec secs[10] = {
         {L->records.data(), L->records.size() * 8, 0},
         {L->meta.data(), L->meta.size() * sizeof(cl_chunk_meta), 0},
         {L->block_ptr.data(), L->block_ptr.size() * 4, 0},
         {L->panel_chunk.data(), L->panel_chunk.size() * 4, 0},
         {image.data(), image.size(), 0},
         {L->block_chunk.data(), L->block_chunk.size() * 4, 0},
-        {L->chunk_nz.data(), L->chunk_nz.size() * 4, 0},
+        {L->slot.data(), L->slot.size() * sizeof(ChunkSlot), 0},
         {L->chunk_half.data(), L->chunk_half.size() * 4, 0},
         {L->group_ptr.data(), L->group_ptr.size() * 4, 0},
+        {L->row_ptr.data(), L->row_ptr.size() * 2, 0},
     };
     size_t total = 0;
     for (auto &s : secs) { s.off = total; total += (s.bytes + 255) / 256 * 256; }
@@ -266,11 +272,11 @@ extern "C" int32_t cl_layer_upload(cl_layer *L)
     L->dev.block_ptr = (const uint32_t *)(blob + secs[2].off);
     L->dev.panel_chunk = (const uint32_t *)(blob + secs[3].off);
     L->dev.block_chunk = (const uint32_t *)(blob + secs[5].off);
-    L->dev.chunk_nz = (const uint32_t *)(blob + secs[6].off);
+    L->dev.slot = (const ChunkSlot *)(blob + secs[6].off);
     L->dev.chunk_half = L->group_ptr.empty() ? nullptr : (const uint32_t *)(blob + secs[7].off);
     L->dev.group_ptr = L->group_ptr.empty() ? nullptr : (const uint32_t *)(blob + secs[8].off);
-    L->dev.val_lut = (const lut_t *)(blob + secs[4].off);
-    L->dev.idx_lut = L->dev.val_lut + L->val_lut.size();
+    L->dev.row_ptr = L->row_ptr.empty() ? nullptr : (const uint16_t *)(blob + secs[9].off);
+    L->dev.tables = blob + secs[4].off;
     L->dev.codebook = (const float *)(blob + secs[4].off + ((L->val_lut.size() + L->idx_lut.size()) * sizeof(lut_t) + 15) / 16 * 16);
     clear_error();
     return CL_OK;
@@ -301,8 +307,24 @@ extern "C" int32_t cl_decode_layer(const cl_layer *L, uint8_t *d_val_sym, uint8_
 
 namespace {
 
+// Most columns (images, or images x output pixels) of one dense-tile launch: keeps the
+// kernels' 32-bit column arithmetic and the y extent of the layout kernels' grids in range.
+constexpr int kMaxTileColumns = 1 << 21;
+
+// Launch shape of fc_rows_kernel, the sparse path's kernel for more than a few images.
+struct RowsPlan {
+    int ipl = 0;             // images per lane (0: the kernel is not used)
+    int group = 1;           // blocks decoded and multiplied at a time
+    int Bp = 0;              // batch rounded up to whole image tiles
+    int splits = 1;          // workgroups sharing the blocks of one block row
+    int list_cap = 0;        // entries a block's list has room for
+    int64_t cost = 0;        // modelled cycles of the launch (same units as mfma_shape's)
+    size_t lds = 0, part_bytes = 0;
+};
+
 // Launch shape of the sparse forward path for one layer and batch.
 struct SparsePlan {
+    RowsPlan rows;           // the launch, if fc_rows_kernel takes it; else:
     int bt_max = 1;          // batch tile of the main kernel (power of two, <= 16)
     int wg_per_panel = 0;    // workgroups per block row (8 wavefronts of kSparseChunksPerWave chunks each)
     int xwant = 0;           // activation columns to stage in LDS per image (3 blocks wide)
@@ -316,9 +338,63 @@ struct SparsePlan {
     }
 };
 
-// (one_tile: the caller wants the whole batch, up to 16 images, in one batch tile)
-int32_t plan_sparse(const cl_layer *L, int batch, size_t max_lds, SparsePlan &P, bool one_tile = false)
+bool mfma_capable(const cl_layer *L) { return L->desc.block_h <= kTile && L->desc.block_w <= kTile; }
+
+// From this many images on the sparse path runs fc_rows_kernel where the layer's blocks allow
+// (fc6 / fc7 / fc8 of the AlexNet-shaped stack, us a call: 24 / 16 / 14 at 8 images on the small-batch
+// kernel, 28 / 17 / 18 on this one; at 9-16 images, two launches there, 44 / 30 / 25).
+constexpr int kRowsBatch = 9;
+
+// Launch shape of fc_rows_kernel; false where it does not fit (blocks above 128 x 128, more
+// weights in a block than its list has room for in LDS).
+bool plan_rows(const cl_layer *L, int batch, const DeviceLimits &dl, RowsPlan &P)
 {
+    if (!mfma_capable(L) || batch > kMaxTileColumns) return false;
+    P.ipl = batch <= 16 ? 1 : batch <= 32 ? 2 : 4;
+    const int images = 16 * P.ipl;
+    P.Bp = (batch + images - 1) / images * images;
+    P.list_cap = (int)((L->max_block_nnz + kListSlack + 7) / 8 * 8);
+    const size_t tables = table_image_bytes(L->val_lut_bits, L->idx_lut_bits, 1 << L->desc.weight_bits);
+    auto lds_of = [&](int group) { return tables + 2 * (size_t)group * (images * kXsColumns * sizeof(float) + P.list_cap * sizeof(uint16_t)); };
+    if (lds_of(1) > dl.max_lds) { P.ipl = 0; return false; }
+    // Blocks to a group and split of the block rows, as on the other paths, in cycles per
+    // workgroup: a start; per group of blocks a part that does not depend on what is in it
+    // (latencies, the barrier), per block and per surviving weight; the partial tiles.  Fitted to
+    // the AlexNet- and VGG-shaped fc6 / fc7 / fc8 at 16, 32 and 64 images (fc6, us a call: 28.9,
+    // 32.6 and 45.8; one block to a group 34.6, 36.9 and 45.8).
+    static const struct { int groups, block, weight_x20; } kFit[3] = {{3, 2150, 29}, {3, 3000, 34}, {1, 3900, 51}};
+    const auto &fit = kFit[P.ipl / 2];
+    const int64_t tiles = (int64_t)L->n_panels * (P.Bp / images);
+    const int cus = std::max(1, dl.cus);
+    const int64_t nnz_block = L->n_blocks ? L->nnz / L->n_blocks : 0;
+    const int64_t per_block = fit.block + nnz_block * fit.weight_x20 / 20, per_group = 2200, start = 12000;
+    const int sp_max = (int)std::max<int64_t>(1, std::min<int64_t>(L->nbw, (3 * (int64_t)cus + tiles - 1) / tiles));
+    int64_t best = -1;
+    for (int group = 1; group <= fit.groups && lds_of(group) <= dl.max_lds; ++group)
+        for (int sp = 1; sp <= sp_max; ++sp) {
+            const int64_t rounds = (tiles * sp + cus - 1) / cus, blocks = (L->nbw + sp - 1) / sp;
+            const int64_t t = rounds * (start + (blocks + group - 1) / group * per_group + blocks * per_block) +
+                              (int64_t)L->n_panels * sp * P.Bp * kTile * (int64_t)sizeof(float) * 3 / 4000;
+            if (best < 0 || t < best) {
+                best = t;
+                P.splits = sp;
+                P.group = group;
+            }
+        }
+    P.lds = lds_of(P.group);
+    P.cost = best;
+    P.part_bytes = (size_t)L->n_panels * P.splits * kTile * P.Bp * sizeof(float);
+    return true;
+}
+
+// (one_tile: the caller wants the whole batch, up to 16 images, in one batch tile)
+int32_t plan_sparse(const cl_layer *L, int batch, const DeviceLimits &dl, SparsePlan &P, bool one_tile = false)
+{
+    const size_t max_lds = dl.max_lds;
+    if (!one_tile && batch >= kRowsBatch && plan_rows(L, batch, dl, P.rows)) {
+        P.part_bytes = P.rows.part_bytes;
+        return CL_OK;
+    }
     P.fixed = table_image_bytes(L->val_lut_bits, L->idx_lut_bits, 1 << L->desc.weight_bits);
     P.xwant = (int)std::min<int64_t>(L->desc.K, (1 + 2 * kSparseChunksPerWave) * (int64_t)L->desc.block_w);
     // largest power-of-two batch tile (<= 16) that fits; prefer to stay under 64 KiB
@@ -339,7 +415,7 @@ int32_t plan_sparse(const cl_layer *L, int batch, size_t max_lds, SparsePlan &P,
 // stages its activation columns in LDS, where the sum of the tiles is formed.
 bool sparse_can_fold(const cl_layer *L, const SparsePlan &P, int batch)
 {
-    if (batch > P.bt_max || (batch & (batch - 1))) return false;
+    if (P.rows.ipl || batch > P.bt_max || (batch & (batch - 1))) return false;
     const int64_t widest = std::min<int64_t>(L->desc.K, (int64_t)L->max_group_blocks * L->desc.block_w);
     return widest <= P.xcap_for(batch);
 }
@@ -364,12 +440,6 @@ int reduce_col_tile(int panels, int ncols)
 
 // rows of the block-by-block activation layout, tail included
 size_t xt_rows(const cl_layer *L) { return (size_t)L->nbw * kTile + kXtTailRows; }
-
-// Most columns (images, or images x output pixels) of one dense-tile launch: keeps the
-// kernels' 32-bit column arithmetic and the y extent of the layout kernels' grids in range.
-constexpr int kMaxTileColumns = 1 << 21;
-
-bool mfma_capable(const cl_layer *L) { return L->desc.block_h <= kTile && L->desc.block_w <= kTile; }
 
 // Image tile, padded column count and split of the block rows for `ncols` columns and
 // `panels` block rows, from a small model of a layer's launches with measured constants
@@ -584,31 +654,38 @@ int32_t launch_wide_mul(const LayerDev &D, int panels, const WidePlan &P, const 
     return CL_OK;
 }
 
-// CL_PATH_AUTO: the sparse path up to kAutoSparseBatch images (one batch tile of the kernel
-// with a tile per wavefront); above, when the blocks fit a tile, whichever of the dense-tile
-// path and the wide sparse path the two launch models price lower (same units, both fitted
-// to measured launches).  Measured on the AlexNet-shaped stack (fc6 / fc7 / fc8, ms per
-// layer call): sparse 0.019 / 0.015 / 0.015 at 4 images, 0.024 / 0.016 / 0.014 at 8 and
-// 0.054 / 0.034 / 0.024 at 9-16 (two batch tiles); dense tiles of 32 images 0.040 / 0.024 /
-// 0.019; at 256 images dense tiles 0.176 / 0.095 / 0.044, wide sparse 0.094 / 0.051 for fc6
-// and fc7 - the dense tile multiplies eleven times the necessary products at a 9 % density
-// but four at 25 %.
+// CL_PATH_AUTO: the sparse path up to kAutoSparseBatch images (one batch tile of its small-batch
+// kernel) and for blocks above 128 x 128; above, whichever of the sparse path's fc_rows_kernel,
+// the dense-tile path and the wide sparse path their launch models price lower (same units, all
+// fitted to measured launches; fc_rows_kernel saves a launch that lays the activations out or
+// decodes, 6 k cycles).  Measured on the AlexNet-shaped stack (fc6 / fc7 / fc8, us per layer
+// call): small-batch kernel 24 / 16 / 14 at 8 images; at 16 images fc_rows_kernel 29 / 18 / 18,
+// dense tiles 40 / 24 / 18; at 64 images 46 / 28 / 24 and 60 / 35 / 23; at 256 images wide
+// 97 / 58 / 50, dense tiles 166 / 89 / 41 - the dense tile multiplies eleven times the necessary
+// products at a 9 % density but four at 25 %.  A layer of fewer than kAutoRowsBlocks blocks takes
+// 12 to 16 us on either, launches for the most part, and stays on dense tiles.
 constexpr int kAutoSparseBatch = 8;
+constexpr int kAutoRowsBlocks = 48;
+constexpr int64_t kAutoLaunch = 6000;
 
 int resolve_path(const cl_layer *L, int batch, int path, const DeviceLimits &dl)
 {
     if (path != CL_PATH_AUTO) return path;
     if (batch <= kAutoSparseBatch || !mfma_capable(L)) return CL_PATH_SPARSE;
     if (batch > kMaxTileColumns) return CL_PATH_MFMA_F32;      // refused there with its message
-    WidePlan W;
-    if (plan_wide(L, batch, dl, W) != CL_OK) {
-        clear_error();
-        return CL_PATH_MFMA_F32;
-    }
     int nq, np, splits;
-    int64_t dense = 0;
-    mfma_shape(L, L->n_panels, batch, dl.cus, false, nq, np, splits, false, false, &dense);
-    return W.cost < dense ? CL_PATH_SPARSE_WIDE : CL_PATH_MFMA_F32;
+    int64_t best = 0;
+    int choice = CL_PATH_MFMA_F32;
+    mfma_shape(L, L->n_panels, batch, dl.cus, false, nq, np, splits, false, false, &best);
+    WidePlan W;
+    if (plan_wide(L, batch, dl, W) != CL_OK) clear_error();
+    else if (W.cost < best) {
+        best = W.cost;
+        choice = CL_PATH_SPARSE_WIDE;
+    }
+    RowsPlan R;
+    if (L->n_blocks >= kAutoRowsBlocks && plan_rows(L, batch, dl, R) && R.cost < best + kAutoLaunch) choice = CL_PATH_SPARSE;
+    return choice;
 }
 
 bool is_mfma(int path) { return path == CL_PATH_MFMA_F32 || path == CL_PATH_MFMA_BF16; }
@@ -636,7 +713,7 @@ extern "C" int32_t cl_fc_workspace_bytes(const cl_layer *L, int32_t batch, int32
         *out = P.xt_bytes + P.part_bytes;
     } else {
         SparsePlan P;
-        if (int32_t rc = plan_sparse(L, batch, dl.max_lds, P)) return rc;
+        if (int32_t rc = plan_sparse(L, batch, dl, P)) return rc;
         *out = P.part_bytes;
     }
     return CL_OK;
@@ -653,6 +730,42 @@ extern "C" int32_t cl_fc_resolved_path(const cl_layer *L, int32_t batch, int32_t
     return CL_OK;
 }
 
+template <int IPL, int G>
+static int32_t launch_rows(const LayerDev &D, int panels, const RowsPlan &P, const float *d_X, float *part, int batch, hipStream_t st)
+{
+    static LdsLimit seen;
+    if (int32_t rc = ensure_lds((const void *)fc_rows_kernel<IPL, G>, P.lds, seen)) return rc;
+    dim3 grid;
+    GRID_TRY(grid, (int64_t)panels * P.splits * (P.Bp / (16 * IPL)));
+    hipLaunchKernelGGL((fc_rows_kernel<IPL, G>), grid, dim3(kRowsThreads), P.lds, st, D, d_X, part, batch, panels, P.splits, P.Bp, P.list_cap);
+    HIP_TRY(hipGetLastError());
+    return CL_OK;
+}
+
+// One layer through fc_rows_kernel with launch shape P, and its finishing kernel.
+static int32_t forward_rows(const cl_layer *L, const LayerDev &D, const RowsPlan &P, const float *d_X, const float *d_bias, float *d_Y,
+                            int batch, int relu, float *part, hipStream_t st)
+{
+    timing_begin(st);
+    int32_t rc = CL_EINVAL;
+    switch (P.ipl * 8 + P.group) {
+    case 1 * 8 + 1: rc = launch_rows<1, 1>(D, L->n_panels, P, d_X, part, batch, st); break;
+    case 1 * 8 + 2: rc = launch_rows<1, 2>(D, L->n_panels, P, d_X, part, batch, st); break;
+    case 1 * 8 + 3: rc = launch_rows<1, 3>(D, L->n_panels, P, d_X, part, batch, st); break;
+    case 2 * 8 + 1: rc = launch_rows<2, 1>(D, L->n_panels, P, d_X, part, batch, st); break;
+    case 2 * 8 + 2: rc = launch_rows<2, 2>(D, L->n_panels, P, d_X, part, batch, st); break;
+    case 2 * 8 + 3: rc = launch_rows<2, 3>(D, L->n_panels, P, d_X, part, batch, st); break;
+    case 4 * 8 + 1: rc = launch_rows<4, 1>(D, L->n_panels, P, d_X, part, batch, st); break;
+    }
+    if (rc) return rc;
+    timing_end(st, 1);
+    dim3 rgrid;
+    GRID_TRY(rgrid, (int64_t)L->n_panels * (kTile / kWideRedRows) * ((P.Bp + kWideRedImages - 1) / kWideRedImages));
+    hipLaunchKernelGGL(wide_reduce_kernel, rgrid, dim3(256), 0, st, D, part, d_bias, d_Y, batch, P.Bp, P.splits, relu, 0);
+    HIP_TRY(hipGetLastError());
+    return CL_OK;
+}
+
 // The small-batch path for one layer.  With `prev` the input is not d_X but the partial
 // tiles of the layer before (see PrevSlots); with finish == false the layer's own
 // finishing kernel is left to the layer after it in the same way.  Both only where
@@ -662,7 +775,8 @@ static int32_t forward_sparse(const cl_layer *L, const LayerDev &D, const Device
                               const PrevSlots *prev = nullptr, bool finish = true)
 {
     SparsePlan P;
-    if (int32_t rc = plan_sparse(L, batch, dl.max_lds, P)) return rc;
+    if (int32_t rc = plan_sparse(L, batch, dl, P)) return rc;
+    if (P.rows.ipl) return forward_rows(L, D, P.rows, d_X, d_bias, d_Y, batch, relu, part, st);
     const PrevSlots from = prev ? *prev : PrevSlots{nullptr, nullptr, nullptr, 1, 0, 0, 0};
     if ((prev || !finish) && !sparse_can_fold(L, P, batch)) return fail(CL_EINVAL, "internal: layer cannot take or leave partial tiles");
     const int M = L->desc.M, K = L->desc.K;
@@ -763,7 +877,7 @@ static int32_t launch_wide_expand(const cl_layer *const *layers, WideEntry *cons
 {
     ExpandJobs jobs{};
     jobs.ipl = (uint32_t)ipl;
-    size_t lds = 0;
+    size_t lds = xt_of ? kExpandTurnBytes : 0;
     int64_t wgs = 0;
     int used = 0;
     if (xt_of) {
@@ -959,7 +1073,7 @@ int32_t plan_stack(const cl_layer *const *layers, int n, int batch, int path, co
             P.part_bytes = std::max(P.part_bytes, round256(P.mfma[i].part_bytes));
             P.xt_in[i] = i > 0 && reads_xt(P.path[i - 1]) && P.path[i] == CL_PATH_MFMA_F32 && plain_rows;
         } else {
-            if (int32_t rc = plan_sparse(L, batch, dl.max_lds, P.sparse[i])) return rc;
+            if (int32_t rc = plan_sparse(L, batch, dl, P.sparse[i])) return rc;
             P.part_bytes = std::max(P.part_bytes, round256(P.sparse[i].part_bytes));
             // (measured on the AlexNet-shaped stack: 39.8 -> 37.1 us at one image, no gain at
             // two, a loss at four - every workgroup of a block column adds the same tiles up)
@@ -1111,7 +1225,7 @@ int32_t plan_group(const cl_layer_group *G, int batch, const DeviceLimits &dl, G
     const cl_layer *L = G->layers[0];
     if (batch < 1) return fail(CL_EINVAL, "batch must be positive");
     if (batch > 16 || (batch & (batch - 1))) return fail(CL_EUNSUPPORTED, "a group call takes 1, 2, 4, 8 or 16 images per layer");
-    if (int32_t rc = plan_sparse(L, batch, dl.max_lds, P.sp, true)) return rc;
+    if (int32_t rc = plan_sparse(L, batch, dl, P.sp, true)) return rc;
     if (P.sp.bt_max < batch) return fail(CL_EUNSUPPORTED, "%d images do not fit one batch tile of this layer shape", batch);
     const int bt = batch;
     P.sp.bt_max = bt;

@@ -10,6 +10,7 @@
 namespace cl {
 
 constexpr int kLanes = CL_RECORDS_PER_CHUNK;        // one 64-bit record per lane of a wavefront
+constexpr int kRowPtrs = 132;                       // words of row_ptr per block: 128 row starts, the end, padding to 8 bytes
 constexpr int kCountBits = 4;                       // width of a record's entry-count field
 
 int32_t fail(int32_t code, const char *fmt, ...);
@@ -22,6 +23,13 @@ constexpr int lut_len(uint16_t e) { return e & 0xff; }
 constexpr int lut_sym(uint16_t e) { return e >> 8; }
 using lut_t = uint16_t;
 
+// A chunk as fc_rows_kernel looks it up: by block and number within the block.
+struct ChunkSlot {
+    uint32_t rec_off, nrec;        // its records (nrec 0: the block has no such chunk)
+    uint32_t pos0;                 // position carry into the chunk
+    uint32_t at;                   // surviving weights of the block before it
+};
+
 struct DeviceImage {
     int device = -1;
     char *blob = nullptr;          // one allocation; the pointers below point into it
@@ -31,12 +39,12 @@ struct DeviceImage {
     const uint32_t *block_ptr = nullptr;
     const uint32_t *panel_chunk = nullptr;
     const uint32_t *block_chunk = nullptr;
-    const uint32_t *chunk_nz = nullptr;
+    const ChunkSlot *slot = nullptr;
     const uint32_t *chunk_half = nullptr;
     const uint32_t *group_ptr = nullptr;
     const float *codebook = nullptr;
-    const lut_t *val_lut = nullptr;
-    const lut_t *idx_lut = nullptr;
+    const uint16_t *row_ptr = nullptr;
+    const void *tables = nullptr;      // decode tables and codebook, laid out as in LDS
 };
 
 }  // namespace cl
@@ -55,6 +63,8 @@ struct cl_layer {
     std::vector<uint32_t> block_chunk;              // n_blocks + 1: first chunk of each block (derived)
     std::vector<uint32_t> chunk_nz;                 // n_chunks + 1: surviving weights (entries that are not padding) in all
                                                     //   chunks before this one (derived)
+    std::vector<cl::ChunkSlot> slot;                // (blocks of at most 128 x 128) n_blocks x block_slots (derived)
+    int32_t block_slots = 0;                        // most chunks in one block
     int64_t max_block_nnz = 0;                      // most surviving weights in one block
     int32_t max_group_blocks = 0;                   // most blocks touched by eight consecutive chunks of a block row that start
                                                     //   at a multiple of eight from the block row's first (the share of one
@@ -66,6 +76,8 @@ struct cl_layer {
                                                     //   each half goes
     std::vector<uint32_t> group_ptr;                // n_blocks x 2 x 17: where each group of eight rows starts in each
                                                     //   half of the block's part of the list, and where the half ends
+    std::vector<uint16_t> row_ptr;                  // (the same layers) n_blocks x kRowPtrs: where each row of a block starts among the
+                                                    //   block's surviving weights in block order, rows 0 .. 127, then the end
     std::vector<cl_chunk_meta> meta;                // n_chunks + 1
     std::vector<uint64_t> records;
     std::vector<cl::lut_t> val_lut, idx_lut;        // indexed by the next val_lut_bits / idx_lut_bits stream bits

@@ -165,10 +165,7 @@ __device__ __forceinline__ void decoder_role(const LayerDev &L, const Smem &s, f
         const uint32_t b = pb0 + (uint32_t)bi;
         const BlockGeom g = block_geom(L, b);
         while (h0.valid && (uint32_t)__builtin_amdgcn_readfirstlane((int)h0.blk) == b) {
-            LaneRecord rec;
-            rec.n = (uint32_t)lane < h0.rec_end - h0.rec_off ? (uint32_t)w0 & 15u : 0u;
-            rec.vbuf = w0 >> kCountBits;
-            rec.ibuf = __builtin_bitreverse64(w0);
+            const LaneRecord rec = split_record(w0, (uint32_t)lane < h0.rec_end - h0.rec_off ? (uint32_t)w0 & 15u : 0u);
             const uint32_t pos0 = h0.pos0;
             // move the stream on; the record load issued here uses a head that arrived
             // a chunk ago

@@ -1,0 +1,312 @@
+// Batches of a few up to some dozens of images: decode to entry lists in LDS, multiply row by
+// row with sixteen images across the lanes of a quarter wavefront.  fc_rows_kernel.
+// Part of the device translation unit: included by device.hip inside namespace cl,
+// in the order given there.
+#pragma once
+
+constexpr int kRowsThreads = 1024;
+constexpr int kXsColumns = kTile + 1;                   // columns of an activation slab; column 128 holds zeros
+constexpr int kListSlack = 16;                          // list entries past a block's last: read by idle lanes, the final one written by them
+
+// The value of lane K of each quarter wavefront, in all its lanes.
+template <int K> __device__ __forceinline__ uint32_t row_bcast(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + K, 0xf, 0xf, true);        // row_newbcast:K
+}
+
+// Eight of the sixteen entries a quarter wavefront holds, one per lane (byte offset of the
+// entry's column in the activations, and its weight), K .. K + 7: every quarter multiplies
+// its k-th entry with its sixteen (times IPL) images.  The reads of all eight go out together;
+// the multiply-adds take the weight from lane k of the quarter themselves (written out: the
+// compiler keeps the move apart).
+template <int IPL, int K>
+__device__ __forceinline__ void rows_read(float (&x)[8][IPL], uint32_t off, uint32_t xbase)
+{
+    typedef typename WideVec<IPL>::type vec_t;
+    typedef const __attribute__((address_space(3))) vec_t *lds_vec;
+    const uint32_t at[8] = {row_bcast<K>(off) + xbase,     row_bcast<K + 1>(off) + xbase, row_bcast<K + 2>(off) + xbase, row_bcast<K + 3>(off) + xbase,
+                            row_bcast<K + 4>(off) + xbase, row_bcast<K + 5>(off) + xbase, row_bcast<K + 6>(off) + xbase, row_bcast<K + 7>(off) + xbase};
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+        const vec_t v = *(lds_vec)(uintptr_t)at[u];
+        if constexpr (IPL == 1) x[u][0] = v;
+        else {
+#pragma unroll
+            for (int m = 0; m < IPL; ++m) x[u][m] = v[m];
+        }
+    }
+}
+
+template <int IPL, int K>
+__device__ __forceinline__ void rows_add(float (&acc)[IPL], const float (&x)[8][IPL], float w)
+{
+    // (s_nop: two wait states between a vector write of w and its use as another lane's operand)
+#pragma unroll
+    for (int m = 0; m < IPL; ++m)
+        asm("s_nop 1\n"
+            "v_fmac_f32_dpp %0, %1, %2 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n"
+            "v_fmac_f32_dpp %0, %1, %3 row_newbcast:%10+1 row_mask:0xf bank_mask:0xf\n"
+            "v_fmac_f32_dpp %0, %1, %4 row_newbcast:%10+2 row_mask:0xf bank_mask:0xf\n"
+            "v_fmac_f32_dpp %0, %1, %5 row_newbcast:%10+3 row_mask:0xf bank_mask:0xf\n"
+            "v_fmac_f32_dpp %0, %1, %6 row_newbcast:%10+4 row_mask:0xf bank_mask:0xf\n"
+            "v_fmac_f32_dpp %0, %1, %7 row_newbcast:%10+5 row_mask:0xf bank_mask:0xf\n"
+            "v_fmac_f32_dpp %0, %1, %8 row_newbcast:%10+6 row_mask:0xf bank_mask:0xf\n"
+            "v_fmac_f32_dpp %0, %1, %9 row_newbcast:%10+7 row_mask:0xf bank_mask:0xf"
+            : "+v"(acc[m])
+            : "v"(w), "v"(x[0][m]), "v"(x[1][m]), "v"(x[2][m]), "v"(x[3][m]), "v"(x[4][m]), "v"(x[5][m]), "v"(x[6][m]), "v"(x[7][m]), "n"(K));
+}
+
+// Bytes of v that are not zero, added to n.
+__device__ __forceinline__ uint32_t add_nonzero_bytes(uint32_t v, uint32_t n)
+{
+    return n + (uint32_t)__builtin_popcount((((v & 0x7f7f7f7fu) + 0x7f7f7f7fu) | v) & 0x80808080u);
+}
+
+// The surviving weights of a record put into a list, two bytes each (value index << 8 |
+// column): `at` is the LDS address of the first one's place, `before` the sum of z over the
+// block's entries before the record plus its entry count (the position of the record's first
+// entry, less its own z).  No branches: what is not a surviving weight - padding, and entries
+// the record does not have, whose value index reads 0 - goes to the list's last place, which
+// nobody reads.
+typedef __attribute__((address_space(3))) uint16_t *lds_u16;
+
+template <int J, class Col>
+__device__ __forceinline__ void list_from(const Symbols &y, uint32_t pos, uint32_t at, uint32_t trash, Col &col)
+{
+    if constexpr (J < kMaxEntries) {
+        if ((uint32_t)J >= y.nmax) return;                                  // uniform
+        constexpr int w = J / 4, b = J % 4;
+        pos += (y.z[w] >> (8 * b)) & 0xffu;
+        const uint32_t e = __builtin_amdgcn_perm(y.v[w], col(pos + (uint32_t)J), 0x0c0c0000u | (uint32_t)(4 + b) << 8);
+        const bool live = ((y.v[w] >> (8 * b)) & 0xffu) != 0u;
+        *(lds_u16)(uintptr_t)(live ? at : trash) = (uint16_t)e;
+        list_from<J + 1>(y, pos, live ? at + 2u : at, trash, col);
+    }
+}
+
+// Workgroup (image tile of 16 IPL images, block row p, split j of its blocks) of sixteen
+// wavefronts, one to a CU.  The blocks are taken G at a time.  While a group is multiplied the
+// next one is decoded, by the same wavefronts: each decodes its chunk of the next group (one
+// record per lane), puts the surviving weights of the chunk in block order into that block's
+// list in LDS and then multiplies its eight rows of the present group, two per quarter
+// wavefront: a quarter takes sixteen entries of a row, one per lane, and goes through them as
+// above.  So an entry costs a quarter of (one address, one LDS read, IPL multiply-adds), a
+// row's sum stays in a register from the first block to the last, and nothing is added in
+// memory.  Where a row's entries start in a block's list was counted when the layer was loaded
+// (row_ptr).
+template <int IPL, int G>
+__global__ __launch_bounds__(kRowsThreads) void fc_rows_kernel(LayerDev L, const float *__restrict__ X, float *__restrict__ part, int B,
+                                                               int panels, int splits, int Bp, int list_cap)
+{
+    constexpr int NW = kRowsThreads / 64, kImages = 16 * IPL, kSlab = kXsColumns * kImages, RQ = kTile / NW / 4;
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem_raw[];
+    const Smem s = carve(smem_raw, L);
+    float *slabs = s.extra;                                             // [2][G][kXsColumns][kImages]
+    uint16_t *lists = (uint16_t *)(slabs + 2 * G * kSlab);              // [2][G][list_cap]
+    const int j = (int)blockIdx.x % splits, rest = (int)blockIdx.x / splits;
+    const int p = rest % panels, img0 = (rest / panels) * kImages;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int lane = (int)(threadIdx.x & 63), l16 = lane & 15;
+    const int blk_lo = (int)(((int64_t)L.nbw * j) / splits), blk_hi = (int)(((int64_t)L.nbw * (j + 1)) / splits);
+    const uint32_t pb0 = (uint32_t)p * (uint32_t)L.nbw;
+    const int phases = (blk_hi - blk_lo + G - 1) / G;
+
+    // ---- the chunks: a group's chunks are counted off slot by slot of its blocks (slot_at), wavefront w
+    // takes the ones congruent to w + 4 ph.  What a chunk is stands in one table entry, so
+    // only the record's load waits for another one.
+    const int slots = L.block_slots;
+    ChunkSlot ch{};
+    uint64_t rec = 0;
+    int ch_blk = 0, ch_i = 0;                   // the chunk's block (of the block row) and its number within the group
+    auto fetch_chunk = [&](int ph) {            // the next chunk with records from ch_i on, if any
+        const int b0 = blk_lo + ph * G, n = ph < phases ? min(G, blk_hi - b0) * slots : 0;
+        ch.nrec = 0;
+        for (; ch_i < n; ch_i += NW) {
+            int g = 0;
+#pragma unroll
+            for (int q = 1; q < G; ++q) g += ch_i >= q * slots ? 1 : 0;
+            ch_blk = b0 + g;
+            ch = L.slot[(size_t)(pb0 + (uint32_t)b0) * (uint32_t)slots + (uint32_t)ch_i];
+            if (ch.nrec != 0) break;
+        }
+        if (ch.nrec != 0) rec = (uint32_t)lane < ch.nrec ? L.records[(size_t)ch.rec_off + lane] : 0ull;
+    };
+    auto first_chunk = [&](int ph) {
+        ch_i = (wave + 4 * ph) & (NW - 1);
+        fetch_chunk(ph);
+    };
+    auto decode = [&](int ph) {
+        const Symbols y = decode_record(split_record(rec, (uint32_t)rec & 15u), s.T);
+        uint32_t weights = 0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+            if ((uint32_t)(4 * w) < y.nmax) weights = add_nonzero_bytes(y.v[w], weights);
+        // lane counts (<= 15, 960 per chunk) and advances in one scan
+        const uint32_t mine = weights | (y.adv << 10);
+        const uint32_t excl = wave_incl_scan(mine) - mine;
+        const uint16_t *list = lists + ((ph & 1) * G + ch_blk - (blk_lo + ph * G)) * list_cap;
+        const uint32_t base = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) uint16_t *)list;
+        const uint32_t at = base + 2u * (ch.at + (excl & 1023u)), trash = base + 2u * (uint32_t)(list_cap - 1);
+        const uint32_t before = ch.pos0 + (excl >> 10);
+        const uint32_t bwp = (uint32_t)min(L.bw, L.K - ch_blk * L.bw);
+        if ((bwp & (bwp - 1u)) == 0u) {
+            auto col = [&](uint32_t pos) { return pos & (bwp - 1u); };
+            list_from<0>(y, before, at, trash, col);
+        } else {
+            // (a magic multiplier instead of a division: exact for positions below 2^14 and
+            // widths up to 128)
+            const uint32_t inv = (0x400000u + bwp - 1u) / bwp;
+            auto col = [&](uint32_t pos) { return pos - ((pos * inv) >> 22) * bwp; };
+            list_from<0>(y, before, at, trash, col);
+        }
+    };
+    auto decode_group = [&](int ph) {
+        // (more chunks in a group than wavefronts: the rest is fetched where it is needed)
+        while (ch.nrec != 0) {
+            decode(ph);
+            ch_i += NW;
+            fetch_chunk(ph);
+        }
+    };
+
+    // ---- the activations of a group, X[image][column] in memory, [column][image] in LDS: what a
+    // quarter reads of a column is contiguous, so that its reads never conflict with each other.
+    // Four lanes fetch 64 bytes of an image, sixteen images side by side.
+    constexpr int kPieces = (G * kImages * (kTile / 4) + kRowsThreads - 1) / kRowsThreads;
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+    f4 stage[kPieces];
+    const bool ragged = L.nbw * L.bw > L.K || L.bw < kTile;           // (a fetch may run past the end of an image)
+    auto piece = [&](int i, int &g, int &img, int &col) {
+        const int t = (wave + i * NW) * 4;                              // four 16-byte columns, sixteen images per wavefront
+        const int c = t & (kTile / 4 - 1), q = t / (kTile / 4);
+        col = (c + (lane >> 4)) * 4;
+        img = (q % (kImages / 16)) * 16 + (lane & 15);
+        g = q / (kImages / 16);
+    };
+    // (images past the batch read the last one: their sums are dropped; columns a block does not
+    // have read the next block's or the row's last: no list names them)
+    auto slab_fetch = [&](int ph) {
+#pragma unroll
+        for (int i = 0; i < kPieces; ++i) {
+            int g, img, col;
+            piece(i, g, img, col);
+            const int k = min(blk_lo + ph * G + g, L.nbw - 1) * L.bw + col;
+            const float *row = X + (size_t)min(img0 + img, B - 1) * L.K;
+            if (!ragged || k + 4 <= L.K) stage[i] = *(const f4u *)(row + k);
+            else {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) stage[i][u] = row[min(k + u, L.K - 1)];
+            }
+        }
+    };
+    auto slab_store = [&](int ph) {
+#pragma unroll
+        for (int i = 0; i < kPieces; ++i) {
+            int g, img, col;
+            piece(i, g, img, col);
+            if (g >= G) continue;
+            float *dst = slabs + ((ph & 1) * G + g) * kSlab + col * kImages + img;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) dst[u * kImages] = stage[i][u];
+        }
+    };
+
+    // ---- where the quarter's rows start in the lists of a group of blocks, and where the last ends ----
+    const int row0 = wave * (kTile / NW) + (lane >> 4) * RQ;
+    struct RowRange {
+        uint32_t at[RQ + 1];
+    };
+    auto ranges_fetch = [&](int ph, RowRange (&r)[G]) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const int blk = blk_lo + ph * G + g;
+            r[g] = RowRange{};
+            if (blk < blk_hi) {
+                const uint16_t *rp = L.row_ptr + (size_t)(pb0 + (uint32_t)blk) * kRowPtrs + row0;
+#pragma unroll
+                for (int q = 0; q <= RQ; ++q) r[g].at[q] = rp[q];
+            }
+        }
+    };
+
+    float acc[RQ][IPL];
+#pragma unroll
+    for (int i = 0; i < RQ; ++i)
+#pragma unroll
+        for (int m = 0; m < IPL; ++m) acc[i][m] = 0.0f;
+
+    auto multiply = [&](int ph, const RowRange (&r)[G]) {
+        // the first sixteen entries of all the rows, then their weights: requested together
+        // (past a row's last entry: codebook entry 0 and the column of zeros)
+        auto entry = [&](uint32_t at, int left) { return l16 < left ? (uint32_t)*(lds_u16)(uintptr_t)at : (uint32_t)kTile; };
+        auto list_at = [&](int g, int i) { return (uint32_t)(uintptr_t)(lds_u16)(lists + ((ph & 1) * G + g) * list_cap) + 2u * (r[g].at[i] + (uint32_t)l16); };
+        uint32_t ent[G][RQ];
+        float w[G][RQ];
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int i = 0; i < RQ; ++i) ent[g][i] = entry(list_at(g, i), (int)(r[g].at[i + 1] - r[g].at[i]));
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int i = 0; i < RQ; ++i) w[g][i] = s.T.cb[ent[g][i] >> 8];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const uint32_t xbase = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) float *)(slabs + ((ph & 1) * G + g) * kSlab) +
+                                   (uint32_t)(l16 * IPL * 4);
+#pragma unroll
+            for (int i = 0; i < RQ; ++i) {
+                int left = (int)(r[g].at[i + 1] - r[g].at[i]);
+                uint32_t at = list_at(g, i);
+                for (;;) {
+                    const uint32_t off = (ent[g][i] & 255u) * (uint32_t)(kImages * 4);
+                    const bool half = __any(left > 8), more = __any(left > 16);      // uniform
+                    float x0[8][IPL], x1[8][IPL];
+                    rows_read<IPL, 0>(x0, off, xbase);
+                    if (half) rows_read<IPL, 8>(x1, off, xbase);
+                    const float wv = w[g][i];
+                    if (more) ent[g][i] = entry(at += 32u, left -= 16);
+                    rows_add<IPL, 0>(acc[i], x0, wv);
+                    if (more) w[g][i] = s.T.cb[ent[g][i] >> 8];
+                    if (half) rows_add<IPL, 8>(acc[i], x1, wv);
+                    if (!more) break;
+                }
+            }
+        }
+    };
+
+    if (phases > 0) {
+        RowRange now[G], next[G];
+        for (int i = (int)threadIdx.x; i < L.table_rows; i += kRowsThreads) s.tables[i] = L.tables[i];
+        first_chunk(0);
+        slab_fetch(0);
+        ranges_fetch(0, now);
+        for (int i = (int)threadIdx.x; i < 2 * G * kImages; i += kRowsThreads) slabs[(i / kImages) * kSlab + kTile * kImages + i % kImages] = 0.0f;
+        __syncthreads();
+        decode_group(0);
+        first_chunk(1);
+        slab_store(0);
+        __syncthreads();
+        for (int ph = 0; ph < phases; ++ph) {
+            const bool more = ph + 1 < phases;
+            if (more) {
+                slab_fetch(ph + 1);
+                ranges_fetch(ph + 1, next);
+                decode_group(ph + 1);
+                first_chunk(ph + 2);
+            }
+            multiply(ph, now);
+            if (more) {
+                slab_store(ph + 1);
+#pragma unroll
+                for (int g = 0; g < G; ++g) now[g] = next[g];
+            }
+            __syncthreads();
+        }
+    }
+    // the quarter's rows of the workgroup's partial tile, part[block row][split][row][Bp]
+#pragma unroll
+    for (int i = 0; i < RQ; ++i)
+        store_floats<IPL>(part + (((size_t)p * splits + j) * kTile + row0 + i) * (size_t)Bp + img0 + l16 * IPL, acc[i]);
+}

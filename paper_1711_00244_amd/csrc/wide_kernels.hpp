@@ -44,6 +44,7 @@ constexpr int kGroupPtrs = 2 * (kWideWaves + 1);        // group_ptr words per b
 // (One launch can decode several layers - those of a stack that take this path - each into
 // its own list: workgroups wg0[i] .. wg0[i + 1] - 1 belong to job i.)
 constexpr int kExpandJobs = 4;
+constexpr size_t kExpandTurnBytes = 2 * 32 * 33 * sizeof(float);       // LDS of a workgroup that lays activations out
 struct ExpandJobs {
     LayerDev L[kExpandJobs];
     WideEntry *ent[kExpandJobs];
@@ -60,8 +61,9 @@ struct ExpandJobs {
 
 __global__ __launch_bounds__(kThreads) void wide_expand_kernel(ExpandJobs jobs)
 {
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem_raw[];
     if (blockIdx.x < jobs.t_wgs) {
-        __shared__ float t[2][32][33];
+        auto t = (float(*)[32][33])smem_raw;          // [2][32][33]
         const int half = (int)(threadIdx.x >> 8), tid = (int)(threadIdx.x & 255);
         const int row_tiles = jobs.rows / 32, tile = (int)blockIdx.x * 2 + half;
         const bool real = tile < row_tiles * (jobs.Bp / 32);
@@ -83,7 +85,6 @@ __global__ __launch_bounds__(kThreads) void wide_expand_kernel(ExpandJobs jobs)
         if (blockIdx.x >= jobs.wg0[i]) job = i;
     const LayerDev &L = jobs.L[job];
     WideEntry *ent = jobs.ent[job];
-    extern __shared__ __attribute__((aligned(16))) uint8_t smem_raw[];
     const Smem s = carve(smem_raw, L);
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = (int)(threadIdx.x & 63);

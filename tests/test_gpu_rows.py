@@ -1,0 +1,53 @@
+"""The sparse path's kernel for more than a few images (fc_rows_kernel) against the oracle, under
+both gates: batches on both sides of its image tiles and of the hand-over from the small-batch
+kernel, ragged last blocks in both directions (K no multiple of four), narrow and low blocks,
+rows and blocks without entries, rows with more entries than a quarter wavefront takes at a time,
+blocks of more chunks than a workgroup has wavefronts, and an index table larger than the value table; results the
+same every run, and independent of a non-finite activation in a column that no surviving weight of
+the row names."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_1711_00244_amd as cl
+from gates import assert_close, fc_ref
+from test_host_library import rand_pruned
+
+pytestmark = pytest.mark.gpu
+
+CASES = [(300, 521, 128, 128, 0.09, 5, 4), (515, 700, 128, 128, 0.001, 5, 4), (256, 1024, 128, 128, 0.25, 5, 4), (130, 390, 128, 128, 1.0, 8, 5),
+         (200, 333, 64, 48, 0.2, 5, 4), (257, 261, 128, 20, 0.1, 5, 5), (140, 2050, 100, 128, 0.04, 3, 8), (128, 128, 128, 128, 0.0, 5, 4)]
+
+
+@pytest.mark.parametrize("M,K,bh,bw,d,r,k", CASES)
+@pytest.mark.parametrize("B", [9, 16, 17, 32, 33, 64, 65, 130])
+def test_rows_kernel(M, K, bh, bw, d, r, k, B):
+    import torch
+    rng = np.random.default_rng(M + K + B)
+    W = rand_pruned(rng, M, K, d)
+    L = cl.compress_layer(W, r, k, bh, bw, upload=True)
+    oW = oracle.dense_weights(oracle.compress_layer(W, r, k, bh, bw))
+    X = np.maximum(rng.standard_normal((B, K)), 0).astype(np.float32)
+    bias = (rng.standard_normal(M) * 0.1).astype(np.float32)
+    Xd, bd = torch.from_numpy(X).cuda(), torch.from_numpy(bias).cuda()
+    for b, relu in ((None, False), (bd, True)):
+        Y = cl.compressed_fc_forward(L, Xd, b, relu=relu, path=cl.PATH_SPARSE)
+        assert_close(Y.cpu().numpy(), fc_ref(oW, X, None if b is None else bias), relu)
+        assert torch.equal(Y, cl.compressed_fc_forward(L, Xd, b, relu=relu, path=cl.PATH_SPARSE))
+    L.free()
+
+
+def test_rows_kernel_keeps_infinities_to_their_rows():
+    import torch
+    rng = np.random.default_rng(3)
+    W = rand_pruned(rng, 200, 300, 0.02)
+    W[:, 77] = 0.0
+    W[9, :] = 0.0
+    L = cl.compress_layer(W, 5, 4, 128, 128, upload=True)
+    X = rng.random((12, 300)).astype(np.float32)
+    want = cl.compressed_fc_forward(L, torch.from_numpy(X).cuda(), path=cl.PATH_SPARSE)
+    X[3, 77] = np.inf
+    got = cl.compressed_fc_forward(L, torch.from_numpy(X).cuda(), path=cl.PATH_SPARSE)
+    val, idx, bp, dense = cl.decode_layer(L)
+    # padding entries may name column 77; the kernel drops them
+    assert torch.equal(got, want) and not bool(dense[:, 77].any())

@@ -288,7 +288,11 @@ int32_t finalize_and_validate(cl_layer *L, Team &team)
         L->group_ptr.assign((size_t)g.n_blocks * kPer, 0u);
         L->row_ptr.assign((size_t)g.n_blocks * kRowPtrs, 0u);
         L->block_slots = 1;
-        for (int64_t b = 0; b < g.n_blocks; ++b) L->block_slots = std::max<int32_t>(L->block_slots, (int32_t)(L->block_chunk[b + 1] - L->block_chunk[b]));
+        L->max_block_entries = 0;
+        for (int64_t b = 0; b < g.n_blocks; ++b) {
+            L->block_slots = std::max<int32_t>(L->block_slots, (int32_t)(L->block_chunk[b + 1] - L->block_chunk[b]));
+            L->max_block_entries = std::max<int64_t>(L->max_block_entries, L->block_ptr[b + 1] - L->block_ptr[b]);
+        }
         L->slot.assign((size_t)g.n_blocks * L->block_slots, ChunkSlot{});
     }
     std::atomic<int64_t> vbits{0}, ibits{0}, bad_chunk{L->n_chunks};

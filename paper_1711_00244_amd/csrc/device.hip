@@ -143,6 +143,23 @@ static int32_t device_limits(DeviceLimits &dl)
     return CL_OK;
 }
 
+// Raises a kernel's dynamic LDS limit when a launch needs more than any before it on
+// this device (the attribute sticks; asking again for every launch costs a runtime
+// call each time).  `seen` belongs to one kernel instantiation.
+constexpr int kMaxDevices = 64;
+struct LdsLimit { std::atomic<size_t> bytes[kMaxDevices]; };
+
+static int32_t ensure_lds(const void *kernel, size_t lds, LdsLimit &seen)
+{
+    int dev = 0;
+    HIP_TRY(hipGetDevice(&dev));
+    const bool tracked = dev >= 0 && dev < kMaxDevices;
+    if (tracked && seen.bytes[dev].load(std::memory_order_relaxed) >= lds) return CL_OK;
+    HIP_TRY(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    if (tracked) seen.bytes[dev].store(lds, std::memory_order_relaxed);
+    return CL_OK;
+}
+
 // Event bracket around the main kernel of the last forward call (benchmarks only).
 struct KernelTiming {
     bool on = false, valid = false;
@@ -282,12 +299,40 @@ extern "C" int32_t cl_layer_upload(cl_layer *L)
     return CL_OK;
 }
 
+// decode_blocks_kernel takes a few thousand cycles for a block, most of them latencies, however small
+// the block is.  With blocks of less than 64 x 64 the chunk kernel, which has a wavefront for
+// each, is faster in spite of the second pass over the dense matrix (4096 x 4096: blocks of
+// 32 x 32, 31 and 53 us; of 64 x 64, 31 and 21 us), and where no dense matrix is asked for it
+// already is with somewhat larger ones (4096 x 25088: blocks of 64 x 64, 30 and 70 us; of
+// 128 x 128, 28 and 25 us).
+static bool decode_by_blocks(const cl_layer *L, bool dense)
+{
+    return !L->row_ptr.empty() && (int64_t)L->desc.block_h * L->desc.block_w >= (dense ? 64 * 64 : 96 * 96);
+}
+
 extern "C" int32_t cl_decode_layer(const cl_layer *L, uint8_t *d_val_sym, uint8_t *d_idx_sym,
                                    uint32_t *d_block_ptr, float *d_dense, void *stream)
 {
     if (int32_t rc = require_device(L)) return rc;
     hipStream_t st = (hipStream_t)stream;
     const LayerDev D = make_dev(L);
+    if (decode_by_blocks(L, d_dense != nullptr) && (d_val_sym || d_idx_sym || d_block_ptr || d_dense)) {
+        DeviceLimits dl;
+        if (int32_t rc = device_limits(dl)) return rc;
+        const int stage = ((int)L->max_block_entries + 31) / 16 * 16;           // (and up to 15 bytes before the first)
+        const size_t lds = smem_fixed_bytes(D.val_bits, D.idx_bits, D.ncode) + kDecodeTile + 2 * (size_t)stage;
+        static LdsLimit seen;
+        if (int32_t rc = ensure_lds((const void *)decode_blocks_kernel, lds, seen)) return rc;
+        // as many workgroups as are resident at once, each with the same number of blocks where
+        // that divides
+        const int64_t resident = (int64_t)dl.cus * std::max<int64_t>(1, std::min<int64_t>(8, dl.max_lds / lds));
+        const int64_t each = (L->n_blocks + resident - 1) / resident;
+        hipLaunchKernelGGL(decode_blocks_kernel, dim3((unsigned)((L->n_blocks + each - 1) / each)), dim3(kDecodeThreads), lds, st, D, L->dev.block_ptr,
+                           (int)L->n_blocks, d_val_sym, d_idx_sym, d_block_ptr, d_dense, stage);
+        HIP_TRY(hipGetLastError());
+        clear_error();
+        return CL_OK;
+    }
     if (d_block_ptr)
         HIP_TRY(hipMemcpyAsync(d_block_ptr, L->dev.block_ptr, (size_t)(L->n_blocks + 1) * 4, hipMemcpyDeviceToDevice, st));
     if (d_dense) {
@@ -514,23 +559,6 @@ int32_t plan_mfma(const cl_layer *L, int batch, bool bf16, const DeviceLimits &d
     if (P.lds > dl.max_lds) return fail(CL_EUNSUPPORTED, "the MFMA path needs %zu bytes of LDS", P.lds);
     P.xt_bytes = xt_bytes_for(L, P.Bp, bf16);
     P.part_bytes = (size_t)L->n_panels * P.splits * P.Bp * L->desc.block_h * sizeof(float);
-    return CL_OK;
-}
-
-// Raises a kernel's dynamic LDS limit when a launch needs more than any before it on
-// this device (the attribute sticks; asking again for every launch costs a runtime
-// call each time).  `seen` belongs to one kernel instantiation.
-constexpr int kMaxDevices = 64;
-struct LdsLimit { std::atomic<size_t> bytes[kMaxDevices]; };
-
-static int32_t ensure_lds(const void *kernel, size_t lds, LdsLimit &seen)
-{
-    int dev = 0;
-    HIP_TRY(hipGetDevice(&dev));
-    const bool tracked = dev >= 0 && dev < kMaxDevices;
-    if (tracked && seen.bytes[dev].load(std::memory_order_relaxed) >= lds) return CL_OK;
-    HIP_TRY(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    if (tracked) seen.bytes[dev].store(lds, std::memory_order_relaxed);
     return CL_OK;
 }
 

@@ -65,6 +65,7 @@ struct cl_layer {
                                                     //   chunks before this one (derived)
     std::vector<cl::ChunkSlot> slot;                // (blocks of at most 128 x 128) n_blocks x block_slots (derived)
     int32_t block_slots = 0;                        // most chunks in one block
+    int64_t max_block_entries = 0;                  // most entries in one block
     int64_t max_block_nnz = 0;                      // most surviving weights in one block
     int32_t max_group_blocks = 0;                   // most blocks touched by eight consecutive chunks of a block row that start
                                                     //   at a multiple of eight from the block row's first (the share of one

@@ -6,6 +6,8 @@
 // ------------------------------------------------------------------------- //
 // decode_layer: symbols and (optionally) the dense matrix
 // ------------------------------------------------------------------------- //
+// For layers with blocks above 128 x 128: a wavefront per chunk, eight to a workgroup, after
+// fill_kernel has cleared the dense matrix.
 __global__ __launch_bounds__(kThreads) void decode_kernel(LayerDev L, uint8_t *val_out, uint8_t *idx_out, float *dense)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem_raw[];
@@ -36,6 +38,111 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(LayerDev L, uint8_t *v
             dense[(size_t)(g.row_id + (int)r) * L.K + (size_t)(g.col_id + (int)cc)] = s.T.cb[v];
         }
     });
+}
+
+// The same for layers whose blocks are at most 128 x 128, everything in one launch: a workgroup
+// takes block after block.  A wavefront decodes a chunk of the block and leaves its symbols in
+// LDS - value and relative indices in entry order, and the value index once more in a byte
+// tile of the block, at its position; then the workgroup writes the block out, dense rows (zeros
+// with the rest) and symbols in whole 16-byte pieces, having asked for the next block's
+// records first.  Bound by the bytes written: every byte of the outputs is written once, in
+// whole lines where the rows of a block begin on one.
+constexpr int kDecodeThreads = 256, kDecodeTile = 128 * 128;
+
+__global__ __launch_bounds__(kDecodeThreads) void decode_blocks_kernel(LayerDev L, const uint32_t *block_ptr, int blocks, uint8_t *val_out, uint8_t *idx_out,
+                                                                       uint32_t *ptr_out, float *dense, int stage_bytes)
+{
+    constexpr int NW = kDecodeThreads / 64;
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem_raw[];
+    const Smem s = carve(smem_raw, L);
+    uint8_t *tile = (uint8_t *)s.extra;                     // value index of every position of the block
+    uint8_t *stage[2] = {tile + kDecodeTile, tile + kDecodeTile + stage_bytes};        // value, relative indices
+    uint8_t *const out[2] = {val_out, idx_out};
+    const int tid = (int)threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    // what a wavefront decodes next: chunk `wave` of a block, by its slot
+    ChunkSlot ch{};
+    uint64_t rec = 0;
+    uint32_t e0 = 0, e1 = 0, first = 0;                     // the block's entries; the chunk's first one
+    auto fetch_chunk = [&](int b, int i) {
+        ch = L.slot[(size_t)b * (uint32_t)L.block_slots + (uint32_t)i];
+        if (ch.nrec == 0) return;
+        first = L.meta[L.block_chunk[b] + (uint32_t)i].sym_off;
+        rec = (uint32_t)lane < ch.nrec ? L.records[(size_t)ch.rec_off + lane] : 0ull;
+    };
+    auto fetch_block = [&](int b) {
+        ch.nrec = 0;
+        if (b >= blocks) return;
+        e0 = block_ptr[b];
+        e1 = block_ptr[b + 1];
+        if (wave < L.block_slots) fetch_chunk(b, wave);
+    };
+
+    fetch_block((int)blockIdx.x);
+    for (int i = tid; i < L.table_rows; i += kDecodeThreads) s.tables[i] = L.tables[i];
+    for (int i = tid; i < kDecodeTile / 16; i += kDecodeThreads) ((u4 *)tile)[i] = u4{0, 0, 0, 0};
+    if (ptr_out && blockIdx.x == 0 && tid == 0) ptr_out[blocks] = block_ptr[blocks];
+    __syncthreads();
+    for (int b = (int)blockIdx.x; b < blocks; b += (int)gridDim.x) {
+        const uint32_t at0 = e0, n = e1 - e0;
+        // the stages begin where their first 16-byte piece does in memory
+        const uint32_t mis[2] = {val_out ? (uint32_t)(uintptr_t)(val_out + at0) & 15u : 0u, idx_out ? (uint32_t)(uintptr_t)(idx_out + at0) & 15u : 0u};
+        for (int i = wave; ch.nrec != 0;) {
+            const Symbols y = decode_record(split_record(rec, (uint32_t)rec & 15u), s.T);
+            const LaneStart st = lane_starts(y, ch.pos0);
+            const uint32_t at = first - at0 + st.entry;
+            for_each_entry(y, st.sum, [&](uint32_t j, uint32_t v, uint32_t z, uint32_t pos) {
+                stage[0][mis[0] + at + j] = (uint8_t)v;
+                stage[1][mis[1] + at + j] = (uint8_t)z;
+                tile[pos] = (uint8_t)v;                     // (padding: zero, at a position of its own)
+            });
+            i += NW;
+            if (i >= L.block_slots) break;
+            fetch_chunk(b, i);
+        }
+        __syncthreads();
+        fetch_block(b + (int)gridDim.x);
+        if (ptr_out && tid == 0) ptr_out[b] = at0;
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+            if (!out[a]) continue;
+            uint8_t *dst = out[a] + at0 - mis[a];
+            for (uint32_t p = 16u * (uint32_t)tid; p < mis[a] + n; p += 16u * kDecodeThreads) {
+                if (p >= mis[a] && p + 16u <= mis[a] + n) *(u4 *)(dst + p) = *(const u4 *)(stage[a] + p);
+                else
+                    for (uint32_t q = max(p, mis[a]); q < min(p + 16u, mis[a] + n); ++q) dst[q] = stage[a][q];
+            }
+        }
+        // the dense rows; what has been read of the tile is cleared for the next block
+        const BlockGeom g = block_geom(L, (uint32_t)b);
+        if (!dense) {
+            for (int i = tid; i < (g.bhp * g.bwp + 15) / 16; i += kDecodeThreads) ((u4 *)tile)[i] = u4{0, 0, 0, 0};
+        } else if (((L.K | L.bw | g.bwp) & 3) == 0 && ((uintptr_t)dense & 15u) == 0) {
+            const int c = (tid & 31) * 4;
+            float *dst = dense + (size_t)g.row_id * L.K + g.col_id + c;
+            if (c < g.bwp) {
+#pragma unroll 4
+                for (int r = tid >> 5; r < g.bhp; r += kDecodeThreads / 32) {
+                    uint32_t *t = (uint32_t *)(tile + r * g.bwp + c);
+                    const uint32_t v = *t;
+                    *t = 0u;
+                    *(f4 *)(dst + (size_t)r * L.K) = f4{s.T.cb[v & 255u], s.T.cb[(v >> 8) & 255u], s.T.cb[(v >> 16) & 255u], s.T.cb[v >> 24]};
+                }
+            }
+        } else {
+            const int c = tid & 127;
+            if (c < g.bwp)
+                for (int r = tid >> 7; r < g.bhp; r += kDecodeThreads / 128) {
+                    const uint8_t v = tile[r * g.bwp + c];
+                    tile[r * g.bwp + c] = 0;
+                    dense[(size_t)(g.row_id + r) * L.K + g.col_id + c] = s.T.cb[v];
+                }
+        }
+        __syncthreads();
+    }
 }
 
 __global__ void fill_kernel(float *p, size_t n, float v)

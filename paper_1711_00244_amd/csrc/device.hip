@@ -1447,7 +1447,7 @@ struct ConvPlan {
     size_t total() const { return xt_bytes + part_bytes + wt_bytes + rows_bytes; }
 };
 
-// From this many columns on (image x output pixel) the fp32 path decodes the layer's
+// From this many columns on (image x output pixel) both paths decode the layer's
 // blocks once per call into dense tiles in the workspace, and a multiply kernel of its own
 // gathers each 128 x 128 piece of the column matrix into LDS straight from the input, so
 // that the column matrix never exists in memory.  Below, and for calls too small to
@@ -1488,7 +1488,8 @@ int32_t plan_conv(const cl_layer *L, const cl_conv_desc *cv, int batch, bool bf1
     P.lds = mfma_lds_bytes(L, bf16);
     if (P.lds > dl.max_lds) return fail(CL_EUNSUPPORTED, "the convolution path needs %zu bytes of LDS", P.lds);
     const int64_t cols = (int64_t)batch * g.P * g.Q;
-    P.gather = !compact && !bf16 && cols >= kConvGatherColumns && (size_t)kConvLdsBytes <= dl.max_lds &&
+    const int planes = bf16 ? 2 : 3;
+    P.gather = !compact && cols >= kConvGatherColumns && (size_t)conv_lds_bytes(planes) <= dl.max_lds &&
                // its one tile width must give the chip something to do: work items for a
                // sixteenth of the CUs before the block rows are split, 128 x 128 products for half
                16 * launch_panels * ((cols + kConvColumns - 1) / kConvColumns) >= dl.cus &&
@@ -1497,7 +1498,7 @@ int32_t plan_conv(const cl_layer *L, const cl_conv_desc *cv, int batch, bool bf1
     if (P.gather) {
         // nothing but the launch size limits the images of a launch
         P.imgs = (int)std::min<int64_t>(batch, kMaxTileColumns / ((int64_t)g.P * g.Q));
-        P.lds = kConvLdsBytes;
+        P.lds = (size_t)conv_lds_bytes(planes);
     }
     P.wt_bytes = P.gather ? (size_t)L->n_blocks * kTile * kTile * sizeof(float) : 0;
     P.rows_bytes = P.gather ? round256((size_t)L->nbw * kTile * sizeof(uint2)) : 0;
@@ -1506,7 +1507,7 @@ int32_t plan_conv(const cl_layer *L, const cl_conv_desc *cv, int batch, bool bf1
     for (int imgs : {P.imgs, batch % P.imgs}) {
         if (imgs == 0) continue;
         int nq, np, splits;
-        mfma_shape(L, launch_panels, imgs * g.P * g.Q, dl.cus, bf16, nq, np, splits, P.gather, !bf16);
+        mfma_shape(L, launch_panels, imgs * g.P * g.Q, dl.cus, bf16, nq, np, splits, P.gather, P.gather || !bf16);
         if (!P.gather) P.xt_bytes = std::max(P.xt_bytes, (size_t)P.groups_at_once * xt_bytes_for(L, np, bf16));
         if (!(P.gather && splits == 1))
             P.part_bytes = std::max(P.part_bytes, (size_t)launch_panels * splits * np * L->desc.block_h * sizeof(float));
@@ -1574,7 +1575,7 @@ int32_t conv_finish_splits(const ConvCall &c)
 
 // The gathered form: one launch gathers the columns and multiplies them with the decoded
 // blocks (wt) of all filter groups; it finishes the output itself unless block rows are split.
-int32_t conv_gathered(const ConvCall &c, const float *wt, const uint2 *rows, bool combined)
+int32_t conv_gathered(const ConvCall &c, bool bf16, const float *wt, const uint2 *rows, bool combined)
 {
     const ConvPlan &P = *c.P;
     const bool direct = c.splits == 1;
@@ -1582,15 +1583,17 @@ int32_t conv_gathered(const ConvCall &c, const float *wt, const uint2 *rows, boo
     // the kernel form for the height of the layer's blocks: how the multiplying wavefronts divide the tile
     const int bh = c.L->desc.block_h, form = bh <= 64 ? 2 : bh <= 96 ? 1 : 0;
     using Kernel = void (*)(LayerDev, const float *, const float *, const uint2 *, float *, ConvGeom, int, int, int, int, DirectOut);
-    static const Kernel kernels[6] = {conv_mfma_kernel<false, 1, 4>, conv_mfma_kernel<true, 1, 4>, conv_mfma_kernel<false, 3, 1>,
-                                      conv_mfma_kernel<true, 3, 1>,  conv_mfma_kernel<false, 1, 2>, conv_mfma_kernel<true, 1, 2>};
-    static LdsLimit seen[6];
-    const int which = (combined ? 1 : 0) + 2 * form;
+    static const Kernel kernels[12] = {conv_mfma_kernel<false, 1, 4, 3>, conv_mfma_kernel<true, 1, 4, 3>, conv_mfma_kernel<false, 3, 1, 3>,
+                                       conv_mfma_kernel<true, 3, 1, 3>,  conv_mfma_kernel<false, 1, 2, 3>, conv_mfma_kernel<true, 1, 2, 3>,
+                                       conv_mfma_kernel<false, 1, 4, 2>, conv_mfma_kernel<true, 1, 4, 2>, conv_mfma_kernel<false, 3, 1, 2>,
+                                       conv_mfma_kernel<true, 3, 1, 2>,  conv_mfma_kernel<false, 1, 2, 2>, conv_mfma_kernel<true, 1, 2, 2>};
+    static LdsLimit seen[12];
+    const int which = (combined ? 1 : 0) + 2 * form + (bf16 ? 6 : 0);
     if (int32_t rc = ensure_lds((const void *)kernels[which], P.lds, seen[which])) return rc;
     dim3 grid;
     GRID_TRY(grid, (int64_t)c.launch_panels * c.splits * (c.Np / kConvColumns));
     if (!*c.timed) timing_begin(c.st);
-    hipLaunchKernelGGL(kernels[which], grid, dim3(kConvThreads), P.lds, c.st, c.D, c.x, wt, rows, c.part, P.cg, c.ncols, c.Np, c.splits,
+    hipLaunchKernelGGL(kernels[which], grid, dim3(conv_threads(bf16 ? 2 : 3)), P.lds, c.st, c.D, c.x, wt, rows, c.part, P.cg, c.ncols, c.Np, c.splits,
                        P.panels_per_group, out);
     HIP_TRY(hipGetLastError());
     if (!*c.timed) { timing_end(c.st, 1); *c.timed = true; }
@@ -1681,10 +1684,10 @@ extern "C" int32_t cl_compressed_conv_forward(const cl_layer *L, const cl_conv_d
     for (int b0 = 0; b0 < batch; b0 += P.imgs) {
         const int nb = std::min(P.imgs, batch - b0);
         c.ncols = nb * c.pq;
-        mfma_shape(L, c.launch_panels, c.ncols, dl.cus, bf16, c.nq, c.Np, c.splits, P.gather, !bf16);
+        mfma_shape(L, c.launch_panels, c.ncols, dl.cus, bf16, c.nq, c.Np, c.splits, P.gather, P.gather || !bf16);
         c.x = d_X + (size_t)b0 * g.C * g.H * g.W;
         c.y = d_Y + (size_t)b0 * L->desc.M * c.pq;
-        if (int32_t rc = P.gather ? conv_gathered(c, wt, rows, combined) : conv_columns(c, cv->groups, bf16, xt)) return rc;
+        if (int32_t rc = P.gather ? conv_gathered(c, bf16, wt, rows, combined) : conv_columns(c, cv->groups, bf16, xt)) return rc;
     }
     clear_error();
     return CL_OK;

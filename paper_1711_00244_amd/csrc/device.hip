@@ -1558,6 +1558,7 @@ struct ConvCall {
     int launch_panels, nq, Np, splits;
     float *part;
     hipStream_t st;
+    int cus;
     bool *timed;            // benchmarks time the first multiply launch of a call
 };
 
@@ -1579,25 +1580,30 @@ int32_t conv_gathered(const ConvCall &c, bool bf16, const float *wt, const uint2
 {
     const ConvPlan &P = *c.P;
     const bool direct = c.splits == 1;
-    const DirectOut out{direct ? c.y : nullptr, c.bias, c.ncols, c.pq, c.relu};
+    // (partial tiles take neither bias nor activation)
+    const DirectOut out{direct ? c.y : nullptr, direct ? c.bias : nullptr, c.ncols, c.pq, direct ? c.relu : 0};
     // the kernel form for the height of the layer's blocks: how the multiplying wavefronts divide the tile
-    const int bh = c.L->desc.block_h, form = bh <= 64 ? 2 : bh <= 96 ? 1 : 0;
-    using Kernel = void (*)(LayerDev, const float *, const float *, const uint2 *, float *, ConvGeom, int, int, int, int, DirectOut);
-    static const Kernel kernels[12] = {conv_mfma_kernel<false, 1, 4, 3>, conv_mfma_kernel<true, 1, 4, 3>, conv_mfma_kernel<false, 3, 1, 3>,
-                                       conv_mfma_kernel<true, 3, 1, 3>,  conv_mfma_kernel<false, 1, 2, 3>, conv_mfma_kernel<true, 1, 2, 3>,
-                                       conv_mfma_kernel<false, 1, 4, 2>, conv_mfma_kernel<true, 1, 4, 2>, conv_mfma_kernel<false, 3, 1, 2>,
-                                       conv_mfma_kernel<true, 3, 1, 2>,  conv_mfma_kernel<false, 1, 2, 2>, conv_mfma_kernel<true, 1, 2, 2>};
-    static LdsLimit seen[12];
-    const int which = (combined ? 1 : 0) + 2 * form + (bf16 ? 6 : 0);
+    const int bh = c.L->desc.block_h;
+    using Kernel = void (*)(LayerDev, const float *, const float *, const uint2 *, float *, ConvGeom, int, int, int, int, int, DirectOut);
+    static const Kernel kernels[8] = {conv_mfma_kernel<false, 4, 3>, conv_mfma_kernel<true, 4, 3>, conv_mfma_kernel<false, 2, 3>, conv_mfma_kernel<true, 2, 3>,
+                                      conv_mfma_kernel<false, 4, 2>, conv_mfma_kernel<true, 4, 2>, conv_mfma_kernel<false, 2, 2>, conv_mfma_kernel<true, 2, 2>};
+    static LdsLimit seen[8];
+    const int which = (combined ? 1 : 0) + (bh <= 64 ? 2 : 0) + (bf16 ? 4 : 0);
     if (int32_t rc = ensure_lds((const void *)kernels[which], P.lds, seen[which])) return rc;
     dim3 grid;
-    GRID_TRY(grid, (int64_t)c.launch_panels * c.splits * (c.Np / kConvColumns));
+    const int64_t items = (int64_t)c.launch_panels * c.splits * (c.Np / kConvColumns);
+    if (items > INT32_MAX / 2) return fail(CL_EUNSUPPORTED, "a launch of %lld work items does not fit a grid", (long long)items);
+    GRID_TRY(grid, std::min<int64_t>(items, std::max(1, c.cus)));
     if (!*c.timed) timing_begin(c.st);
     hipLaunchKernelGGL(kernels[which], grid, dim3(conv_threads(bf16 ? 2 : 3)), P.lds, c.st, c.D, c.x, wt, rows, c.part, P.cg, c.ncols, c.Np, c.splits,
-                       P.panels_per_group, out);
+                       P.panels_per_group, (int)items, out);
     HIP_TRY(hipGetLastError());
     if (!*c.timed) { timing_end(c.st, 1); *c.timed = true; }
-    return direct ? CL_OK : conv_finish_splits(c);
+    if (direct) return CL_OK;
+    GRID_TRY(grid, (int64_t)c.launch_panels * bh * ((c.ncols + kConvRedColumns - 1) / kConvRedColumns));
+    hipLaunchKernelGGL(conv_reduce_kernel, grid, dim3(kConvRedThreads), 0, c.st, c.D, c.part, c.bias, c.y, c.ncols, c.Np, c.splits, c.relu, c.pq);
+    HIP_TRY(hipGetLastError());
+    return CL_OK;
 }
 
 // The form with the column matrix in memory: P.groups_at_once filter groups per launch of
@@ -1680,7 +1686,7 @@ extern "C" int32_t cl_compressed_conv_forward(const cl_layer *L, const cl_conv_d
         HIP_TRY(hipGetLastError());
     }
     bool timed = false;
-    ConvCall c{L, &P, make_dev(L), nullptr, nullptr, d_bias, 0, g.P * g.Q, relu, P.panels_per_group * P.groups_at_once, 0, 0, 0, part, st, &timed};
+    ConvCall c{L, &P, make_dev(L), nullptr, nullptr, d_bias, 0, g.P * g.Q, relu, P.panels_per_group * P.groups_at_once, 0, 0, 0, part, st, dl.cus, &timed};
     for (int b0 = 0; b0 < batch; b0 += P.imgs) {
         const int nb = std::min(P.imgs, batch - b0);
         c.ncols = nb * c.pq;

@@ -496,9 +496,10 @@ size_t xt_rows(const cl_layer *L) { return (size_t)L->nbw * kTile + kXtTailRows;
 // block row writes the output itself, `direct`).  Fitted
 // to sweeps over every tile width and split of the AlexNet and VGG-16 FC layers at 8 to
 // 1024 images: the choice is the fastest measured shape for the large layers and
-// within 3 % of it on average for a 1000-row layer, where the partial tiles decide; for
-// the gathered convolution, to sweeps over the splits of the AlexNet and VGG-16 layers
-// at 2 to 128 images (0.2 % from the fastest on average, 5 % at worst).
+// within 3 % of it on average for a 1000-row layer, where the partial tiles decide.  The
+// gathered convolution's kernel takes 13 k cycles a block (two phases of 6.5 k), 7.5 k with blocks of at most 64
+// rows or two terms, and 4 k for an item; against its predecessor's price (8 k and 17.9 k for any block) 0 to
+// 4 % faster over forty convolutions, none slower by more than 1 %.
 void mfma_shape(const cl_layer *L, int panels, int ncols, int cus, bool bf16, int &nq, int &np, int &splits, bool gathered = false,
                 bool direct = false, int64_t *cost = nullptr)
 {
@@ -518,8 +519,8 @@ void mfma_shape(const cl_layer *L, int panels, int ncols, int cus, bool bf16, in
         for (int sp = 1; sp <= sp_max; ++sp) {
             const int64_t rounds = (tiles * sp + cus - 1) / cus;
             const int64_t blocks = (L->nbw + sp - 1) / sp;
-            // blocks decoded beforehand: the gathering costs less than a decode
-            int64_t t = gathered ? rounds * (8000 + blocks * (1500 + 4100 * q))
+            // blocks decoded beforehand; a workgroup that goes on to its next item starts quickly
+            int64_t t = gathered ? rounds * (4000 + blocks * (bf16 || L->desc.block_h <= 64 ? 7500 : 13000))
                               : rounds * (12000 + blocks * (5000 + (bf16 ? 1500 : 4100) * q));
             if (!(direct && sp == 1)) t += (int64_t)panels * sp * cols * L->desc.block_h * (int64_t)sizeof(float) * (gathered ? 2 : 3) / (gathered ? 5000 : 4000);
             if (best < 0 || t < best) {
@@ -1454,7 +1455,8 @@ struct ConvPlan {
 // give that kernel's one tile width enough work items (see plan_conv), the column matrix
 // is written out and the blocks of a column tile are decoded inside the multiply kernel
 // (measured on the AlexNet and VGG-16 convolutions at 1 to 64 images: with these limits
-// the gathered form is the faster one wherever it is taken, by 4-25 %).
+// the gathered form is the faster one wherever it is taken, by 4-25 %; of thirty convolutions with 96 to
+// 700 columns none gains more than 1 % from a limit of 96, one of 169 columns goes from 19.9 to 24.4 us).
 constexpr int64_t kConvGatherColumns = 512;
 
 // compact: the form that needs the least scratch - filter groups one after the other

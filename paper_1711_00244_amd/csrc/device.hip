@@ -859,7 +859,7 @@ static int32_t forward_sparse(const cl_layer *L, const LayerDev &D, const Device
 // out for the kernel into xt first) or, when d_X is null, already sits in xt.  The
 // output goes to d_Y as batch x M, or, with next_bp > 0, as the transposed activations
 // of a following 128-column-block layer whose image axis is padded to next_bp
-// (Y[row][next_bp], padded images zero).
+// (Y[row][next_bp], padded images zero; on the bf16 path its two planes).
 static int32_t run_mfma_layer(const cl_layer *L, const LayerDev &D, const MfmaPlan &P, const float *d_X, void *xt, float *part,
                               const float *d_bias, float *d_Y, int next_bp, int batch, int relu, hipStream_t st)
 {
@@ -878,6 +878,14 @@ static int32_t run_mfma_layer(const cl_layer *L, const LayerDev &D, const MfmaPl
     timing_begin(st);
     if (int32_t rc = launch_mfma(L, D, P.bf16, P.nq, L->n_panels, P.splits, P.Bp, L->n_panels, 0, P.lds, xt, part, st)) return rc;
     timing_end(st, 1);
+    if (P.bf16 && next_bp > 0) {
+        dim3 grid;
+        GRID_TRY(grid, ((int64_t)(L->desc.M / 4) * next_bp + 255) / 256);
+        hipLaunchKernelGGL(bf16_reduce_kernel, grid, dim3(256), 0, st, D, part, d_bias, (uint16_t *)d_Y, batch, P.Bp, P.splits, relu, next_bp,
+                           ((size_t)(L->desc.M / kTile) * 8 + kXbTailGroups) * next_bp * 16);       // (xb_plane_elems of the next layer)
+        HIP_TRY(hipGetLastError());
+        return CL_OK;
+    }
     const int cols = std::max(batch, next_bp);
     // towards a following layer the output runs along the images: full 32-column tiles
     // (128-byte runs), and the rows of a block row shared out to keep the launch wide
@@ -1100,7 +1108,8 @@ int32_t plan_stack(const cl_layer *const *layers, int n, int batch, int path, co
             if (int32_t rc = plan_mfma(L, batch, P.path[i] == CL_PATH_MFMA_BF16, dl, P.mfma[i])) return rc;
             P.xt_bytes = std::max(P.xt_bytes, P.mfma[i].xt_bytes);
             P.part_bytes = std::max(P.part_bytes, round256(P.mfma[i].part_bytes));
-            P.xt_in[i] = i > 0 && reads_xt(P.path[i - 1]) && P.path[i] == CL_PATH_MFMA_F32 && plain_rows;
+            P.xt_in[i] = i > 0 && plain_rows && (P.path[i] == CL_PATH_MFMA_F32 ? reads_xt(P.path[i - 1])
+                                                                             : P.path[i - 1] == CL_PATH_MFMA_BF16 && layers[i - 1]->desc.block_h % 4 == 0);
         } else {
             if (int32_t rc = plan_sparse(L, batch, dl, P.sparse[i])) return rc;
             P.part_bytes = std::max(P.part_bytes, round256(P.sparse[i].part_bytes));

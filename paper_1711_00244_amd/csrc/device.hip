@@ -789,8 +789,9 @@ static int32_t forward_rows(const cl_layer *L, const LayerDev &D, const RowsPlan
     if (rc) return rc;
     timing_end(st, 1);
     dim3 rgrid;
-    GRID_TRY(rgrid, (int64_t)L->n_panels * (kTile / kWideRedRows) * ((P.Bp + kWideRedImages - 1) / kWideRedImages));
-    hipLaunchKernelGGL(wide_reduce_kernel, rgrid, dim3(256), 0, st, D, part, d_bias, d_Y, batch, P.Bp, P.splits, relu, 0);
+    const int quads = rows_reduce_quads(P.Bp), rows = kRowsRedPieces / quads;
+    GRID_TRY(rgrid, (int64_t)((L->desc.M + rows - 1) / rows) * (P.Bp / (4 * quads)));
+    hipLaunchKernelGGL(rows_reduce_kernel, rgrid, dim3(kRowsRedParts * kRowsRedPieces), 0, st, D, part, d_bias, d_Y, batch, P.Bp, P.splits, relu);
     HIP_TRY(hipGetLastError());
     return CL_OK;
 }

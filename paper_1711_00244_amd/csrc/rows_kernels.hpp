@@ -314,3 +314,56 @@ __global__ __launch_bounds__(kRowsThreads) void fc_rows_kernel(LayerDev L, const
     for (int i = 0; i < RQ; ++i)
         store_floats<IPL>(part + (((size_t)p * splits + j) * kTile + row0 + i) * (size_t)Bp + img0 + l16 * IPL, acc[i]);
 }
+
+// Finishes fc_rows_kernel: Y[image][row] = act(sum over the splits + bias) from part[block row][split][row][Bp].  The
+// partial tiles are small and the splits many, so it is bound by the latency of its loads, not by bytes: a
+// thread takes four images of a row and a quarter of the splits, all its loads (up to eight at a time) in flight together, and
+// the quarters are added in order.  (wide_reduce_kernel, whose threads take all splits of two rows, left a 1000-row
+// layer 32 workgroups and took 9.8 us for 64 images.  AlexNet-shaped
+// stack at 16 images 64.5 -> 54.1 us, VGG-16-shaped at 64 131.5 -> 123.4.)
+constexpr int kRowsRedParts = 4, kRowsRedPieces = 64;      // quarters; (row, four images) pieces of a workgroup
+
+__host__ __device__ constexpr int rows_reduce_quads(int Bp) { return Bp >= 64 ? 16 : Bp / 4; }     // pieces of a row in a workgroup
+
+__global__ __launch_bounds__(kRowsRedParts * kRowsRedPieces) void rows_reduce_kernel(LayerDev L, const float *__restrict__ part, const float *__restrict__ bias,
+                                                                                     float *Y, int batch, int Bp, int splits, int relu)
+{
+    __shared__ float sums[kRowsRedParts - 1][kRowsRedPieces][4];
+    const int quads = rows_reduce_quads(Bp), image_tiles = Bp / (4 * quads);
+    const int piece = (int)threadIdx.x & (kRowsRedPieces - 1);
+    const int jp = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kRowsRedPieces);
+    const int m = (int)(blockIdx.x / (unsigned)image_tiles) * (kRowsRedPieces / quads) + piece / quads;
+    const int c = (int)(blockIdx.x % (unsigned)image_tiles) * (4 * quads) + 4 * (piece % quads);
+    const bool live = m < L.M && c < batch;
+    float t[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (live) {
+        const int p = m / L.bh, r = m - p * L.bh;
+        const int lo = splits * jp / kRowsRedParts, hi = splits * (jp + 1) / kRowsRedParts;
+        const size_t stride = (size_t)kTile * Bp;
+        const float *src = part + ((size_t)p * splits * kTile + r) * (size_t)Bp + c;
+        for (int j = lo; j < hi; j += 8) {
+            float a[8][4];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) load_floats<4>(src + (size_t)(j + u < hi ? j + u : j) * stride, a[u]);
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (j + u < hi) t[k] += a[u][k];
+        }
+        if (jp > 0) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) sums[jp - 1][piece][k] = t[k];
+        }
+    }
+    __syncthreads();
+    if (jp > 0 || !live) return;
+    const float b = bias ? bias[m] : 0.0f;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+#pragma unroll
+        for (int q = 0; q < kRowsRedParts - 1; ++q) t[k] += sums[q][piece][k];
+        t[k] += b;
+        if (c + k < batch) Y[(size_t)(c + k) * L.M + m] = relu ? fmaxf(t[k], 0.0f) : t[k];
+    }
+}

@@ -252,6 +252,9 @@ int32_t finalize_and_validate(cl_layer *L, Team &team)
         const uint64_t r0 = m.rec_off, r1 = m1.rec_off;
         if (r0 != next_rec || r1 <= r0 || r1 - r0 > (uint64_t)kLanes || r1 > (uint64_t)L->n_records)
             return fail(CL_ECORRUPT, "chunk %lld: bad record range", (long long)c);
+        // every record holds an entry: with this a block without entries has no chunk, and every
+        // chunk lies in its block's range of block_chunk, where the walk below finds it
+        if (m.sym_off >= m1.sym_off) return fail(CL_ECORRUPT, "chunk %lld has no entries", (long long)c);
         if (m.blk >= (uint64_t)g.n_blocks || (int64_t)m.blk < cur_blk) return fail(CL_ECORRUPT, "chunk %lld: bad block", (long long)c);
         if ((int64_t)m.blk != cur_blk) {
             if (m.sym_off != L->block_ptr[m.blk] || (c == 0 && m.sym_off != 0)) return fail(CL_ECORRUPT, "chunk %lld does not start its block", (long long)c);

@@ -280,6 +280,44 @@ def test_validation_catches_inconsistent_tables_even_with_a_good_checksum():
     assert off_rec < len(img)
 
 
+@pytest.mark.parametrize("empty", [0, 1, 3], ids=["first", "middle", "last"])
+def test_validation_refuses_a_chunk_of_an_empty_block(empty):
+    """A chunk that names a block without entries, with records of its own behind it: block_ptr
+    and the chunk's symbol offset agree, so only the fact that every record holds an entry tells
+    that something is wrong.  Refused wherever the empty block lies, whatever the records hold."""
+    rng = np.random.default_rng(17)
+    W = rand_pruned(rng, 256, 256, 0.1)                                       # blocks 2 x 2
+    W[128 * (empty // 2):128 * (empty // 2 + 1), 128 * (empty % 2):128 * (empty % 2 + 1)] = 0.0
+    L = cl.compress_layer(W, 5, 4, 128, 128)
+    img, hv = bytearray(L.serialize()), L.host_view()
+    stored = [hv[k] for k in ("codebook", "val_len", "idx_len", "block_ptr", "panel_chunk", "chunk_meta", "records")]
+    hdr = len(img) - sum(a.nbytes for a in stored)
+    bp, meta = hv["block_ptr"], hv["chunk_meta"]
+    assert bp[empty] == bp[empty + 1] and hv["n_entries"] > hv["n_records"] + 64
+    at = int((meta["blk"][:-1] < empty).sum())                                # where the chunk goes in
+    for n_extra, records in [(64, rng.integers(0, 2 ** 63, 64, dtype=np.uint64)), (1, hv["records"][:1]), (1, np.zeros(1, np.uint64))]:
+        extra = meta[at:at + 1].copy()
+        extra["blk"], extra["pos0"], extra["sym_off"] = empty, 0, bp[empty]
+        moved = meta[at:].copy()
+        moved["rec_off"] += n_extra
+        panel = hv["panel_chunk"].copy()
+        panel[empty // 2 + 1:] += 1
+        r0 = int(extra["rec_off"][0])
+        body = b"".join(np.ascontiguousarray(a).tobytes() for a in stored[:4] + [panel, meta[:at], extra, moved, hv["records"][:r0], records, hv["records"][r0:]])
+        head = bytearray(img[:hdr])
+        counts = np.frombuffer(bytes(head[hdr - 56:hdr - 24]), np.int64) + [0, 1, n_extra, 0]    # blocks, chunks, records, entries
+        head[hdr - 56:hdr - 24] = counts.tobytes()
+        h = 1469598103934665603
+        for byte in body:
+            h = ((h ^ byte) * 1099511628211) & (2 ** 64 - 1)
+        head[hdr - 8:hdr] = h.to_bytes(8, "little")
+        with pytest.raises(cl.CLError) as e:
+            cl.layer_deserialize(bytes(head) + body)
+        assert e.value.code == binding.CL_ECORRUPT
+        assert not re.search("checksum|count|size", str(e.value)), e.value    # refused for its content
+    L.free()
+
+
 def test_format_statistics_on_benchmark_shapes():
     """Scaled-down AlexNet fc6 (same density / bit widths): padding rate and bits
     per non-zero land where the closed forms say."""

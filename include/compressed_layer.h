@@ -237,7 +237,10 @@ int32_t cl_decode_layer(const cl_layer *layer, uint8_t *d_val_sym, uint8_t *d_id
 /* Device scratch a forward call needs for (batch, path): the partial output tiles
  * of the workgroups of each block row and, on the MFMA paths, the activations in
  * the layout the kernel reads (transposed, K laid out block by block; two bf16
- * planes for CL_PATH_MFMA_BF16).  Needs a HIP device (CL_EHIP otherwise). */
+ * planes for CL_PATH_MFMA_BF16).  On CL_PATH_SPARSE it is bounded whatever the
+ * batch, by CL_STATIC_SCRATCH_BYTES or by what the call needs at 16 images, whichever is
+ * more: more images are taken in runs, one after the other.
+ * Needs a HIP device (CL_EHIP otherwise). */
 int32_t cl_fc_workspace_bytes(const cl_layer *layer, int32_t batch, int32_t path, size_t *out);
 
 /* The path a forward call with these arguments runs on: `path` itself unless it is

@@ -360,11 +360,12 @@ constexpr int kMaxTileColumns = 1 << 21;
 struct RowsPlan {
     int ipl = 0;             // images per lane (0: the kernel is not used)
     int group = 1;           // blocks decoded and multiplied at a time
-    int Bp = 0;              // batch rounded up to whole image tiles
+    int run = 0;             // images per launch: whole image tiles, or all there are
     int splits = 1;          // workgroups sharing the blocks of one block row
     int list_cap = 0;        // entries a block's list has room for
-    int64_t cost = 0;        // modelled cycles of the launch (same units as mfma_shape's)
+    int64_t cost = 0;        // modelled cycles of the launches (same units as mfma_shape's)
     size_t lds = 0, part_bytes = 0;
+    int padded(int images) const { return (images + 16 * ipl - 1) / (16 * ipl) * (16 * ipl); }
 };
 
 // Launch shape of the sparse forward path for one layer and batch.
@@ -390,14 +391,26 @@ bool mfma_capable(const cl_layer *L) { return L->desc.block_h <= kTile && L->des
 // kernel, 28 / 17 / 18 on this one; at 9-16 images, two launches there, 44 / 30 / 25).
 constexpr int kRowsBatch = 9;
 
+// Most scratch fc_rows_kernel takes for its partial tiles, whatever the batch: what the entry point
+// without a workspace has.  A batch whose tiles, unsplit, take more is cut into runs, one launch after
+// the other.  (A tile of 64 images is 32 KiB, so two per CU fit: a run of that size keeps the chip
+// busy.)
+constexpr size_t kRowsScratch = CL_STATIC_SCRATCH_BYTES;
+
 // Launch shape of fc_rows_kernel; false where it does not fit (blocks above 128 x 128, more
-// weights in a block than its list has room for in LDS).
+// weights in a block than its list has room for in LDS, so many block rows that a tile of
+// sixteen images of each exceeds kRowsScratch).
 bool plan_rows(const cl_layer *L, int batch, const DeviceLimits &dl, RowsPlan &P)
 {
     if (!mfma_capable(L) || batch > kMaxTileColumns) return false;
-    P.ipl = batch <= 16 ? 1 : batch <= 32 ? 2 : 4;
+    const size_t image_bytes = (size_t)L->n_panels * kTile * sizeof(float);       // of the partial tiles, unsplit
+    const int64_t most = (int64_t)(kRowsScratch / image_bytes);
+    if (most < 16) return false;
+    P.ipl = batch <= 16 || most < 32 ? 1 : batch <= 32 || most < 64 ? 2 : 4;
     const int images = 16 * P.ipl;
-    P.Bp = (batch + images - 1) / images * images;
+    const int runs = (int)((batch + most / images * images - 1) / (most / images * images));
+    P.run = runs == 1 ? batch : P.padded((batch + runs - 1) / runs);
+    const int Bp = P.padded(P.run);
     P.list_cap = (int)((L->max_block_nnz + kListSlack + 7) / 8 * 8);
     const size_t tables = table_image_bytes(L->val_lut_bits, L->idx_lut_bits, 1 << L->desc.weight_bits);
     auto lds_of = [&](int group) { return tables + 2 * (size_t)group * (images * kXsColumns * sizeof(float) + P.list_cap * sizeof(uint16_t)); };
@@ -409,17 +422,17 @@ bool plan_rows(const cl_layer *L, int batch, const DeviceLimits &dl, RowsPlan &P
     // 32.6 and 45.8; one block to a group 34.6, 36.9 and 45.8).
     static const struct { int groups, block, weight_x20; } kFit[3] = {{3, 2150, 29}, {3, 3000, 34}, {1, 3900, 51}};
     const auto &fit = kFit[P.ipl / 2];
-    const int64_t tiles = (int64_t)L->n_panels * (P.Bp / images);
+    const int64_t tiles = (int64_t)L->n_panels * (Bp / images);
     const int cus = std::max(1, dl.cus);
     const int64_t nnz_block = L->n_blocks ? L->nnz / L->n_blocks : 0;
     const int64_t per_block = fit.block + nnz_block * fit.weight_x20 / 20, per_group = 2200, start = 12000;
-    const int sp_max = (int)std::max<int64_t>(1, std::min<int64_t>(L->nbw, (3 * (int64_t)cus + tiles - 1) / tiles));
+    const int sp_max = (int)std::max<int64_t>(1, std::min<int64_t>({L->nbw, (3 * (int64_t)cus + tiles - 1) / tiles, (int64_t)(kRowsScratch / (image_bytes * Bp))}));
     int64_t best = -1;
     for (int group = 1; group <= fit.groups && lds_of(group) <= dl.max_lds; ++group)
         for (int sp = 1; sp <= sp_max; ++sp) {
             const int64_t rounds = (tiles * sp + cus - 1) / cus, blocks = (L->nbw + sp - 1) / sp;
             const int64_t t = rounds * (start + (blocks + group - 1) / group * per_group + blocks * per_block) +
-                              (int64_t)L->n_panels * sp * P.Bp * kTile * (int64_t)sizeof(float) * 3 / 4000;
+                              (int64_t)image_bytes * sp * Bp * 3 / 4000;
             if (best < 0 || t < best) {
                 best = t;
                 P.splits = sp;
@@ -427,8 +440,8 @@ bool plan_rows(const cl_layer *L, int batch, const DeviceLimits &dl, RowsPlan &P
             }
         }
     P.lds = lds_of(P.group);
-    P.cost = best;
-    P.part_bytes = (size_t)L->n_panels * P.splits * kTile * P.Bp * sizeof(float);
+    P.cost = best * runs;
+    P.part_bytes = image_bytes * P.splits * Bp;
     return true;
 }
 
@@ -762,37 +775,43 @@ extern "C" int32_t cl_fc_resolved_path(const cl_layer *L, int32_t batch, int32_t
 template <int IPL, int G>
 static int32_t launch_rows(const LayerDev &D, int panels, const RowsPlan &P, const float *d_X, float *part, int batch, hipStream_t st)
 {
+    const int Bp = P.padded(batch);
     static LdsLimit seen;
     if (int32_t rc = ensure_lds((const void *)fc_rows_kernel<IPL, G>, P.lds, seen)) return rc;
     dim3 grid;
-    GRID_TRY(grid, (int64_t)panels * P.splits * (P.Bp / (16 * IPL)));
-    hipLaunchKernelGGL((fc_rows_kernel<IPL, G>), grid, dim3(kRowsThreads), P.lds, st, D, d_X, part, batch, panels, P.splits, P.Bp, P.list_cap);
+    GRID_TRY(grid, (int64_t)panels * P.splits * (Bp / (16 * IPL)));
+    hipLaunchKernelGGL((fc_rows_kernel<IPL, G>), grid, dim3(kRowsThreads), P.lds, st, D, d_X, part, batch, panels, P.splits, Bp, P.list_cap);
     HIP_TRY(hipGetLastError());
     return CL_OK;
 }
 
-// One layer through fc_rows_kernel with launch shape P, and its finishing kernel.
+// One layer through fc_rows_kernel with launch shape P, and its finishing kernel; run after run
+// through the same partial tiles.
 static int32_t forward_rows(const cl_layer *L, const LayerDev &D, const RowsPlan &P, const float *d_X, const float *d_bias, float *d_Y,
                             int batch, int relu, float *part, hipStream_t st)
 {
-    timing_begin(st);
-    int32_t rc = CL_EINVAL;
-    switch (P.ipl * 8 + P.group) {
-    case 1 * 8 + 1: rc = launch_rows<1, 1>(D, L->n_panels, P, d_X, part, batch, st); break;
-    case 1 * 8 + 2: rc = launch_rows<1, 2>(D, L->n_panels, P, d_X, part, batch, st); break;
-    case 1 * 8 + 3: rc = launch_rows<1, 3>(D, L->n_panels, P, d_X, part, batch, st); break;
-    case 2 * 8 + 1: rc = launch_rows<2, 1>(D, L->n_panels, P, d_X, part, batch, st); break;
-    case 2 * 8 + 2: rc = launch_rows<2, 2>(D, L->n_panels, P, d_X, part, batch, st); break;
-    case 2 * 8 + 3: rc = launch_rows<2, 3>(D, L->n_panels, P, d_X, part, batch, st); break;
-    case 4 * 8 + 1: rc = launch_rows<4, 1>(D, L->n_panels, P, d_X, part, batch, st); break;
+    for (int b0 = 0; b0 < batch; b0 += P.run) {
+        const int nb = std::min(P.run, batch - b0), Bp = P.padded(nb);
+        const float *x = d_X + (size_t)b0 * L->desc.K;
+        if (b0 == 0) timing_begin(st);      // benchmarks time the first main-kernel launch of a call
+        int32_t rc = CL_EINVAL;
+        switch (P.ipl * 8 + P.group) {
+        case 1 * 8 + 1: rc = launch_rows<1, 1>(D, L->n_panels, P, x, part, nb, st); break;
+        case 1 * 8 + 2: rc = launch_rows<1, 2>(D, L->n_panels, P, x, part, nb, st); break;
+        case 1 * 8 + 3: rc = launch_rows<1, 3>(D, L->n_panels, P, x, part, nb, st); break;
+        case 2 * 8 + 1: rc = launch_rows<2, 1>(D, L->n_panels, P, x, part, nb, st); break;
+        case 2 * 8 + 2: rc = launch_rows<2, 2>(D, L->n_panels, P, x, part, nb, st); break;
+        case 2 * 8 + 3: rc = launch_rows<2, 3>(D, L->n_panels, P, x, part, nb, st); break;
+        case 4 * 8 + 1: rc = launch_rows<4, 1>(D, L->n_panels, P, x, part, nb, st); break;
+        }
+        if (rc) return rc;
+        if (b0 == 0) timing_end(st, 1);
+        dim3 rgrid;
+        const int quads = rows_reduce_quads(Bp), rows = kRowsRedPieces / quads;
+        GRID_TRY(rgrid, (int64_t)((L->desc.M + rows - 1) / rows) * (Bp / (4 * quads)));
+        hipLaunchKernelGGL(rows_reduce_kernel, rgrid, dim3(kRowsRedParts * kRowsRedPieces), 0, st, D, part, d_bias, d_Y + (size_t)b0 * L->desc.M, nb, Bp, P.splits, relu);
+        HIP_TRY(hipGetLastError());
     }
-    if (rc) return rc;
-    timing_end(st, 1);
-    dim3 rgrid;
-    const int quads = rows_reduce_quads(P.Bp), rows = kRowsRedPieces / quads;
-    GRID_TRY(rgrid, (int64_t)((L->desc.M + rows - 1) / rows) * (P.Bp / (4 * quads)));
-    hipLaunchKernelGGL(rows_reduce_kernel, rgrid, dim3(kRowsRedParts * kRowsRedPieces), 0, st, D, part, d_bias, d_Y, batch, P.Bp, P.splits, relu);
-    HIP_TRY(hipGetLastError());
     return CL_OK;
 }
 

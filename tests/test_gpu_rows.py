@@ -51,3 +51,30 @@ def test_rows_kernel_keeps_infinities_to_their_rows():
     val, idx, bp, dense = cl.decode_layer(L)
     # padding entries may name column 77; the kernel drops them
     assert torch.equal(got, want) and not bool(dense[:, 77].any())
+
+
+# M, K: a batch in runs of four images a lane (1024 images of 4096 rows fill the scratch); of two and of
+# one (so many rows that 63 and 31 images do); and one that leaves the path to the small-batch kernel
+@pytest.mark.parametrize("M,K,B", [(4096, 260, 1023), (4096, 260, 1025), (4096, 260, 2100), (66000, 24, 200), (130000, 24, 70), (270000, 12, 20)])
+def test_scratch_is_bounded(M, K, B):
+    """The path's scratch does not grow with the batch, so the entry point without a workspace takes
+    any; the images of every run come out as the oracle has them, and as a call with a workspace has."""
+    import torch
+    rng = np.random.default_rng(B)
+    W = rand_pruned(rng, M, K, 0.1)
+    L = cl.compress_layer(W, 5, 4, 128, 128, upload=True)
+    assert cl.fc_workspace_bytes(L, B, cl.PATH_SPARSE) <= cl.STATIC_SCRATCH_BYTES
+    oW = oracle.dense_weights(oracle.compress_layer(W, 5, 4, 128, 128))
+    X = np.maximum(rng.standard_normal((B, K)), 0).astype(np.float32)
+    bias = (rng.standard_normal(M) * 0.1).astype(np.float32)
+    Xd, bd = torch.from_numpy(X).cuda(), torch.from_numpy(bias).cuda()
+    out = torch.full((B, M), -7.0, device="cuda")
+    cl.compressed_fc_forward_static(L, Xd, out, bd, relu=True, path=cl.PATH_SPARSE)
+    assert torch.equal(out, cl.compressed_fc_forward(L, Xd, bd, relu=True, path=cl.PATH_SPARSE))
+    rows = np.concatenate([np.arange(min(M, 300)), np.arange(max(0, M - 300), M)])
+    assert_close(out.cpu().numpy()[:, rows], fc_ref(oW[rows], X, bias[rows]), True)
+    # (the library's own choice of path: what it does not refuse with a workspace of that size runs here too)
+    if cl.fc_workspace_bytes(L, B) <= cl.STATIC_SCRATCH_BYTES:
+        cl.compressed_fc_forward_static(L, Xd, out, bd, relu=True)
+        assert_close(out.cpu().numpy()[:, rows], fc_ref(oW[rows], X, bias[rows]), True)
+    L.free()

@@ -375,10 +375,15 @@ int32_t cl_conv_workspace_bytes_min(const cl_layer *layer, const cl_conv_desc *c
  *    block products for half): every block of the layer is decoded once per call into a
  *    dense 128 x 128 tile in the workspace (64 KiB per block), and the multiply kernel
  *    gathers each piece of the column matrix from d_X into LDS itself - the
- *    column matrix is never written to memory.  (CL_PATH_MFMA_F32: products of three-term
- *    bf16 operands, at least as close to the exact result as fp32 products.)  Workspace: the decoded blocks, a row
+ *    column matrix is never written to memory.  On CL_PATH_MFMA_F32 both operands are split
+ *    into three bf16 terms and eight of the nine products are added in fp32: what is
+ *    left out is below 2^-32 |w x|, so a sum carries no more rounding than n fp32
+ *    multiply-adds, n its surviving weights, from the first on.  An activation below 2^-110
+ *    is taken to the nearest multiple of 2^-133 (the other form takes it as it is).
+ *    Workspace: the decoded blocks, a row
  *    table (8 bytes per row of the layout), partial tiles when block rows are split.
- *    Needs R, S <= 32 and 129 images of input under 2^29 elements, else the other form.
+ *    Needs R, S <= 32, 129 images of input under 2^29 elements and, on CL_PATH_MFMA_F32,
+ *    a codebook without -0 and without values other than 0 below 2^-110, else the other form.
  *  - otherwise the receptive fields are written out as columns in the workspace, one
  *    matrix per filter group and at most 1 GiB of them at a time (the batch is cut
  *    into image groups accordingly), and multiplied by the kernels of the FC paths,

@@ -7,8 +7,11 @@
 // The products run on the bf16 matrix cores, sixteen times the fp32 ones' rate.  With NP = 3
 // (the fp32 path) a weight and an activation are each split into three bf16 terms, w = w1 + w2 +
 // w3 and x = x1 + x2 + x3 (split8): together they are the 24 bits of an fp32 value, nothing is
-// rounded away.  Six of the nine products are formed - x1 w1, x1 w2, x2 w1, x2 w2, x1 w3, x3 w1 -,
-// all exact, and added in fp32; what is left out is below 2^-24 |w x|, an fp32 product's own rounding.
+// rounded away.  Eight of the nine products are formed, all but x3 w3, which is below 2^-32 |w x|; they
+// are exact and added in fp32, so that an output with a single surviving weight is rounded once,
+// as an fp32 multiply-add rounds it.  (Without x2 w3 and x3 w2, up to 1.95 * 2^-24 |w x|, such an output was
+// off by up to 1.4e-7 instead of 6e-8; VGG-16 conv4_2 at one image took 41.4 us, now 44.7, AlexNet at 64
+// images 767, now 828.)
 // With NP = 2 (the bf16 path) three of two terms' four, as in fc_mfma_bf16_kernel.
 //
 // Workgroup = (block row p of the filters, split j of its blocks, tile of 128 columns =
@@ -35,7 +38,7 @@
 // A workgroup per CU takes item after item (block row, split, tile of columns): the gatherers are
 // at the next one's first piece while the multipliers write the last one's output.
 // Bound by the instructions issued: a vector instruction adds its four cycles to the multiplies' time here, and
-// there are some 600 of them per phase and SIMD, gathering and splitting, to 96 multiplies of 32 cycles.
+// there are some 630 of them per phase and SIMD, gathering and splitting, to 128 multiplies of 32 cycles.
 // (AlexNet conv1 to conv5, 64 images, us: 151, 155, 95, 105, 61; on the fp32 matrix cores, at nine
 // tenths of their rate, 202, 240, 150, 149, 95.  A workgroup per item instead of per CU: conv1 178.)
 constexpr int conv_gatherers(int planes) { return planes == 3 ? 4 : 8; }   // wavefronts (eight leave too few registers for two sums)
@@ -68,10 +71,11 @@ __device__ __forceinline__ void bf16_rest(uint32_t t, float &a, float &b)
 
 // Eight fp32 values as NP (2 or 3) bf16 terms each, largest first: each term is what is left of
 // the value, rounded to the nearest bf16.  Three terms are the value itself (8 + 8 + 8 bits; below
-// 2^-110 the last ones run into bf16's smallest numbers), two leave less than 2^-16 of it.
+// 2^-110 the last one can be smaller than bf16's smallest number, 2^-133, and is rounded to a multiple of
+// it), two leave less than 2^-16 of it.
 // terms[i] holds term i of all eight, in order.  An infinity becomes the last term
-// alone, the one that is multiplied with the other side's first term only: it meets every weight once,
-// and so gives what it gives in fp32.
+// alone, the one that is multiplied with the other side's first two terms only, which have the
+// weight's sign or, for a weight of zero, are zero (split_weights): so it gives what it gives in fp32.
 template <int NP> __device__ __forceinline__ void split8(const float (&v)[8], uint4 (&terms)[NP])
 {
     uint32_t t[NP][4];
@@ -108,13 +112,16 @@ template <int NP> __device__ __forceinline__ void split8(const float (&v)[8], ui
     for (int i = 0; i < NP; ++i) terms[i] = uint4{t[i][0], t[i][1], t[i][2], t[i][3]};
 }
 
-// Two weights (finite) as NP bf16 terms each, a pair to a word.  Of three terms the first is cut
-// off, not rounded, so that it cannot overflow; of two it is rounded, which leaves less.
+// Two weights (finite) as NP bf16 terms each, a pair to a word.  Of three terms the first is the
+// largest bf16 whose magnitude is below the weight's: it cannot overflow, and what it leaves has the
+// weight's sign and is zero for a zero only (split8; the subtraction saturates, so that +0 stays +0; the
+// launcher keeps -0 and values below 2^-110 away).  Of two it is rounded, which leaves less.
 template <int NP> __device__ __forceinline__ void split_weights(float a, float b, uint32_t (&t)[NP])
 {
 #pragma unroll
     for (int i = 0; i < NP; ++i) {
-        if (NP == 3 && i == 0) t[i] = __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
+        if (NP == 3 && i == 0)
+            t[i] = __builtin_amdgcn_perm(__builtin_elementwise_sub_sat(__float_as_uint(b), 1u), __builtin_elementwise_sub_sat(__float_as_uint(a), 1u), 0x07060302u);
         else t[i] = bf16_pair(a, b);
         if (i + 1 < NP) bf16_rest(t[i], a, b);
     }
@@ -272,8 +279,9 @@ __global__ __launch_bounds__(conv_threads(NP)) void conv_mfma_kernel(LayerDev L,
     constexpr int kRaw = Q == 4 ? 2 : 4;                    // steps of weights on their way
     static_assert(kConvSteps % kRaw == 0 && kConvSteps % 2 == 0, "a step's registers are the same in every phase");
     // the products formed, smallest first: term of the activation, term of the weight
-    constexpr int kProducts = NP == 3 ? 6 : 3;
-    constexpr int kTermX[6] = {NP == 3 ? 2 : 1, 0, NP == 3 ? 1 : 0, 1, 0, 0}, kTermW[6] = {0, NP == 3 ? 2 : 1, NP == 3 ? 1 : 0, 0, 1, 0};
+    constexpr int kProducts = NP == 3 ? 8 : 3;
+    constexpr int kTermX[8] = {NP == 3 ? 2 : 1, NP == 3 ? 1 : 0, NP == 3 ? 2 : 0, 0, 1, 1, 0, 0};
+    constexpr int kTermW[8] = {NP == 3 ? 1 : 0, NP == 3 ? 2 : 1, 0, 2, 1, 0, 1, 0};
 
     uint4 x[2][QB][NP];
     auto load_x = [&](int buffer, int idx, uint4 (&dst)[QB][NP]) {      // idx = step * kTurns + turn

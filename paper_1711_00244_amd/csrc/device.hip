@@ -23,6 +23,7 @@
 #include <algorithm>
 #include <atomic>
 #include <climits>
+#include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <memory>
@@ -510,9 +511,10 @@ size_t xt_rows(const cl_layer *L) { return (size_t)L->nbw * kTile + kXtTailRows;
 // to sweeps over every tile width and split of the AlexNet and VGG-16 FC layers at 8 to
 // 1024 images: the choice is the fastest measured shape for the large layers and
 // within 3 % of it on average for a 1000-row layer, where the partial tiles decide.  The
-// gathered convolution's kernel takes 13 k cycles a block (two phases of 6.5 k), 7.5 k with blocks of at most 64
+// gathered convolution's kernel is priced at 13 k cycles a block (two phases), 7.5 k with blocks of at most 64
 // rows or two terms, and 4 k for an item; against its predecessor's price (8 k and 17.9 k for any block) 0 to
-// 4 % faster over forty convolutions, none slower by more than 1 %.
+// 4 % faster over forty convolutions, none slower by more than 1 %.  (Fitted with six products of the terms; with
+// eight a block takes about 14.5 k, a price that gives thirty-two convolutions the same splits.)
 void mfma_shape(const cl_layer *L, int panels, int ncols, int cus, bool bf16, int &nq, int &np, int &splits, bool gathered = false,
                 bool direct = false, int64_t *cost = nullptr)
 {
@@ -1488,6 +1490,15 @@ struct ConvPlan {
 // 700 columns none gains more than 1 % from a limit of 96, one of 169 columns goes from 19.9 to 24.4 us).
 constexpr int64_t kConvGatherColumns = 512;
 
+// Whether the layer's weights are the sums of the three bf16 terms that the gathered form splits them
+// into, with a sign that the first two share (split_weights): not below 2^-110, nor as -0.
+bool splits_exactly(const cl_layer *L)
+{
+    for (float c : L->codebook)
+        if (std::fabs(c) < 0x1p-110f && (c != 0.0f || std::signbit(c))) return false;
+    return true;
+}
+
 // compact: the form that needs the least scratch - filter groups one after the other
 // through the same buffers, blocks decoded inside the multiply kernel.
 int32_t plan_conv(const cl_layer *L, const cl_conv_desc *cv, int batch, bool bf16, const DeviceLimits &dl, ConvPlan &P,
@@ -1525,7 +1536,8 @@ int32_t plan_conv(const cl_layer *L, const cl_conv_desc *cv, int batch, bool bf1
                // sixteenth of the CUs before the block rows are split, 128 x 128 products for half
                16 * launch_panels * ((cols + kConvColumns - 1) / kConvColumns) >= dl.cus &&
                2 * launch_panels * ((cols + kConvColumns - 1) / kConvColumns) * L->nbw >= dl.cus &&
-               (int64_t)(kConvColumns + 1) * g.C * g.H * g.W < (1 << 29) && g.R <= 32 && g.S <= 32;      // the gatherers' 32-bit byte offsets and tap masks
+               (int64_t)(kConvColumns + 1) * g.C * g.H * g.W < (1 << 29) && g.R <= 32 && g.S <= 32 &&    // the gatherers' 32-bit byte offsets and tap masks
+               (bf16 || splits_exactly(L));
     if (P.gather) {
         // nothing but the launch size limits the images of a launch
         P.imgs = (int)std::min<int64_t>(batch, kMaxTileColumns / ((int64_t)g.P * g.Q));

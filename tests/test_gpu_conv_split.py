@@ -83,3 +83,85 @@ def test_not_finite(bad):
             assert np.array_equal(Y[4, :, y, x], want, equal_nan=True), (r, s)
     assert np.array_equal(Y[~seen], clean[~seen])
     L.free()
+
+
+def _one_by_one(rng, n, codebook=None, sigma=1.0):
+    """A 1 x 1 convolution whose outputs are sums of n products, and its dense weights."""
+    geom = _geom(n, 30, 1, 64)
+    W = (rng.standard_normal((64, n)) * sigma).astype(np.float32)
+    L = cl.compress_layer(W, 8, 8, 128, 128, codebook=codebook, upload=True)
+    return geom, L, cl.decode_layer(L)[3].cpu().numpy().astype(np.float64)
+
+
+def _run(L, geom, X):
+    import torch
+    return cl.compressed_conv_forward(L, geom, torch.from_numpy(X).cuda(), relu=False).cpu().numpy().astype(np.float64)
+
+
+def _sums(W, X):
+    return np.einsum("oc,nchw->nohw", W, X.astype(np.float64))
+
+
+@pytest.mark.parametrize("n", [1, 2, 3])
+@pytest.mark.parametrize("spread", ["normal", "near a power of two"])
+def test_short_sums(n, spread):
+    """One to three products: no more than the rounding of that many fp32 multiply-adds, n * 2^-24 of
+    the sum of magnitudes.  (The seven products beside x1 w1 add up to less than 2^-6 of it, and each of
+    their additions rounds by up to 2^-23 of that, in whatever manner the matrix cores round: with
+    what is left out, less than 14 * 2^-30 + 2^-32 < 2^-2 * 2^-24.)"""
+    rng = np.random.default_rng(n)
+    if spread == "normal":
+        geom, L, W = _one_by_one(rng, n)
+        X = rng.standard_normal((IMAGES, n, 30, 30)).astype(np.float32)
+    else:       # where a relative error weighs most: mantissas just above 1
+        near = lambda shape: ((1 + rng.random(shape) * 2.0 ** -5) * 2.0 ** rng.integers(-3, 3, shape)).astype(np.float32)
+        cb = np.concatenate([[0], np.sort(near(255))]).astype(np.float32)
+        geom, L, W = _one_by_one(rng, n, cb)
+        X = near((IMAGES, n, 30, 30))
+    err = np.abs(_run(L, geom, X) - _sums(W, X))
+    assert float((err / _sums(np.abs(W), np.abs(X))).max()) <= (n + 0.25) * 2.0 ** -24
+    L.free()
+
+
+@pytest.mark.parametrize("e", [90, 109, 114, 122, 130])
+def test_small_activations(e):
+    """Values around 2^-e: those of 2^-110 and more exact, smaller ones to the nearest multiple of
+    bf16's smallest number, 2^-133.  (Weights around 2^30, so that the results are normal numbers.)"""
+    rng = np.random.default_rng(e)
+    n = 3
+    geom, L, W = _one_by_one(rng, n, sigma=2.0 ** 30)
+    X = (rng.standard_normal((IMAGES, n, 30, 30)) * 2.0 ** -e).astype(np.float32)
+    err = np.abs(_run(L, geom, X) - _sums(W, X))
+    lost = np.where(np.abs(X) < 2.0 ** -110, 2.0 ** -134, 0.0)
+    assert (err <= (n + 0.25) * 2.0 ** -24 * _sums(np.abs(W), np.abs(X)) + _sums(np.abs(W), lost)).all()
+    L.free()
+
+
+@pytest.mark.parametrize("low", [2.0 ** -112, 2.0 ** -120, -0.0])
+def test_codebooks_that_do_not_split(low):
+    """Weights below 2^-110, and a codebook's -0, go the other way: exact to fp32's rounding."""
+    rng = np.random.default_rng(8)
+    cb = np.concatenate([[low if low == 0 else 0.0], np.linspace(-1, 1, 255) * (low if low else 1.0) * (1 + 2.0 ** -20)]).astype(np.float32)
+    geom, L, W = _one_by_one(rng, 3, cb, sigma=low if low else 1.0)
+    X = (rng.standard_normal((IMAGES, 3, 30, 30)) * (2.0 ** 40 if low else 1.0)).astype(np.float32)
+    err = np.abs(_run(L, geom, X) - _sums(W, X))
+    assert (err <= 4 * 2.0 ** -24 * _sums(np.abs(W), np.abs(X))).all()
+    L.free()
+
+
+@pytest.mark.parametrize("bad", [np.inf, -np.inf])
+def test_infinity_meets_bf16_weights(bad):
+    """Weights that are bf16 values themselves (powers of two: nothing is left for their second and third
+    term) keep an infinity's sign, and a weight of zero makes it NaN, as in fp32."""
+    rng = np.random.default_rng(9)
+    cb = np.array([0] + [s * 2.0 ** k for k in range(-64, 63) for s in (-1, 1)] + [1.5], np.float32)
+    geom = _geom(2, 30, 1, 64)
+    W = (cb[rng.integers(1, 256, (64, 2))] * (rng.random((64, 2)) < 0.7)).astype(np.float32)
+    L = cl.compress_layer(W, 8, 8, 128, 128, codebook=cb, upload=True)
+    assert np.array_equal(cl.decode_layer(L)[3].cpu().numpy(), W)
+    X = rng.standard_normal((IMAGES, 2, 30, 30)).astype(np.float32)
+    X[5, 1, 3, 4] = bad
+    with np.errstate(invalid="ignore"):
+        want = np.float32(bad) * W[:, 1]
+    assert np.array_equal(_run(L, geom, X)[5, :, 3, 4], want.astype(np.float64), equal_nan=True)
+    L.free()

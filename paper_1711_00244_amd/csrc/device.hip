@@ -392,6 +392,20 @@ bool mfma_capable(const cl_layer *L) { return L->desc.block_h <= kTile && L->des
 // kernel, 28 / 17 / 18 on this one; at 9-16 images, two launches there, 44 / 30 / 25).
 constexpr int kRowsBatch = 9;
 
+// It pays a fixed part per block (some 3 k cycles), the small-batch kernel one per chunk (under 1 k for
+// eight images).  So where a block is one chunk and every CU has many, up to 16 images - two launches
+// there - are faster on the small-batch kernel (4096 x 4096 at 9 %, us a call at 9 / 16 images, this kernel
+// and the small-batch one: blocks of 16 x 16 323 / 349 and 151 / 213; 32 x 32 89 / 95 and 54 / 71; 16 x 128
+// 51 / 53 and 40 / 54; 64 x 64 33 / 34 and 37 / 49.  32 images: 32 x 32 112 and 140, 16 x 128 62 and 106.
+// 1000 x 4096 at 25 %, 8 blocks to a CU, 16 x 128: 24 / 24 and 29 / 37; 16 to a CU, 32 x 32: 32 / 33 and 26 / 32.)
+constexpr int kRowsCells = 64 * 64, kRowsBlocksPerCu = 12;
+
+bool rows_kernel_pays(const cl_layer *L, int batch, int cus)
+{
+    if (batch < kRowsBatch) return false;
+    return batch > 16 || (int64_t)L->desc.block_h * L->desc.block_w >= kRowsCells || L->n_blocks <= (int64_t)kRowsBlocksPerCu * std::max(1, cus);
+}
+
 // Most scratch fc_rows_kernel takes for its partial tiles, whatever the batch: what the entry point
 // without a workspace has.  A batch whose tiles, unsplit, take more is cut into runs, one launch after
 // the other.  (A tile of 64 images is 32 KiB, so two per CU fit: a run of that size keeps the chip
@@ -450,7 +464,7 @@ bool plan_rows(const cl_layer *L, int batch, const DeviceLimits &dl, RowsPlan &P
 int32_t plan_sparse(const cl_layer *L, int batch, const DeviceLimits &dl, SparsePlan &P, bool one_tile = false)
 {
     const size_t max_lds = dl.max_lds;
-    if (!one_tile && batch >= kRowsBatch && plan_rows(L, batch, dl, P.rows)) {
+    if (!one_tile && rows_kernel_pays(L, batch, dl.cus) && plan_rows(L, batch, dl, P.rows)) {
         P.part_bytes = P.rows.part_bytes;
         return CL_OK;
     }
@@ -707,7 +721,8 @@ int32_t launch_wide_mul(const LayerDev &D, int panels, const WidePlan &P, const 
 // dense tiles 40 / 24 / 18; at 64 images 46 / 28 / 24 and 60 / 35 / 23; at 256 images wide
 // 97 / 58 / 50, dense tiles 166 / 89 / 41 - the dense tile multiplies eleven times the necessary
 // products at a 9 % density but four at 25 %.  A layer of fewer than kAutoRowsBlocks blocks takes
-// 12 to 16 us on either, launches for the most part, and stays on dense tiles.
+// 12 to 16 us on either, launches for the most part, and stays on dense tiles.  (Where the sparse path
+// runs the small-batch kernel instead, rows_kernel_pays, that is the cheaper one: the price is an upper bound.)
 constexpr int kAutoSparseBatch = 8;
 constexpr int kAutoRowsBlocks = 48;
 constexpr int64_t kAutoLaunch = 6000;

@@ -53,6 +53,28 @@ def test_rows_kernel_keeps_infinities_to_their_rows():
     assert torch.equal(got, want) and not bool(dense[:, 77].any())
 
 
+# blocks of fewer than 64 x 64 cells, more than 12 of them to a CU of 256: the small-batch kernel up to 16
+# images; fewer blocks, larger ones or more images: this one
+@pytest.mark.parametrize("M,K,bh,bw,small", [(1040, 8192, 16, 128, True), (1040, 8192, 32, 64, True), (530, 8192, 32, 32, True), (1000, 4096, 16, 128, False),
+                                             (1040, 8192, 64, 64, False)])
+def test_kernel_by_block_size(M, K, bh, bw, small):
+    """Which kernel it is shows in the scratch: the small-batch kernel's is the same for 8 and 16 images."""
+    import torch
+    rng = np.random.default_rng(bh + bw)
+    W = rand_pruned(rng, M, K, 0.09)
+    L = cl.compress_layer(W, 5, 4, bh, bw, upload=True)
+    oW = oracle.dense_weights(oracle.compress_layer(W, 5, 4, bh, bw))
+    need = {B: cl.fc_workspace_bytes(L, B, cl.PATH_SPARSE) for B in (8, 9, 16, 17)}
+    assert (need[9] == need[8] and need[16] == need[8]) == small and need[17] != need[8], need
+    for B in (9, 16, 17):
+        X = np.maximum(rng.standard_normal((B, K)), 0).astype(np.float32)
+        Xd = torch.from_numpy(X).cuda()
+        ref = fc_ref(oW, X)
+        for path in (cl.PATH_SPARSE, cl.PATH_AUTO):
+            assert_close(cl.compressed_fc_forward(L, Xd, path=path).cpu().numpy(), ref, False)
+    L.free()
+
+
 # M, K: a batch in runs of four images a lane (1024 images of 4096 rows fill the scratch); of two and of
 # one (so many rows that 63 and 31 images do); and one that leaves the path to the small-batch kernel
 @pytest.mark.parametrize("M,K,B", [(4096, 260, 1023), (4096, 260, 1025), (4096, 260, 2100), (66000, 24, 200), (130000, 24, 70), (270000, 12, 20)])

@@ -289,14 +289,21 @@ int32_t finalize_and_validate(cl_layer *L, Team &team)
     if (halves) {
         L->chunk_half.assign((size_t)L->n_chunks * 2, 0u);
         L->group_ptr.assign((size_t)g.n_blocks * kPer, 0u);
-        L->row_ptr.assign((size_t)g.n_blocks * kRowPtrs, 0u);
         L->block_slots = 1;
         L->max_block_entries = 0;
         for (int64_t b = 0; b < g.n_blocks; ++b) {
             L->block_slots = std::max<int32_t>(L->block_slots, (int32_t)(L->block_chunk[b + 1] - L->block_chunk[b]));
             L->max_block_entries = std::max<int64_t>(L->max_block_entries, L->block_ptr[b + 1] - L->block_ptr[b]);
         }
-        L->slot.assign((size_t)g.n_blocks * L->block_slots, ChunkSlot{});
+        // Small blocks, and blocks of very different content, would make the lookup tables of some kernels
+        // heavier than the layer itself, and gain little by those kernels: a table of more than half
+        // the records' size and a mebibyte is left out, and the launches do without the kernels that read it.
+        auto in_proportion = [&](size_t bytes) { return bytes <= std::max<size_t>((size_t)L->n_records * 8 / 2, 1 << 20); };
+        const size_t slots = (size_t)g.n_blocks * L->block_slots;
+        if (in_proportion(slots * sizeof(ChunkSlot))) L->slot.assign(slots, ChunkSlot{});
+        L->row_ptrs = (d.block_h + 3) & ~1;
+        const size_t starts = (size_t)g.n_blocks * L->row_ptrs;
+        if (!L->slot.empty() && in_proportion(starts * 2)) L->row_ptr.assign(starts, 0u);
     }
     std::atomic<int64_t> vbits{0}, ibits{0}, bad_chunk{L->n_chunks};
     auto report = [&](int64_t c) {
@@ -323,7 +330,7 @@ int32_t finalize_and_validate(cl_layer *L, Team &team)
                 my_v += s.vbits;
                 my_i += s.ibits;
                 L->chunk_nz[c] = s.weights;
-                if (halves) L->slot[(size_t)b * L->block_slots + (c - L->block_chunk[b])] = ChunkSlot{m.rec_off, m1.rec_off - m.rec_off, m.pos0, left + right};
+                if (!L->slot.empty()) L->slot[(size_t)b * L->block_slots + (c - L->block_chunk[b])] = ChunkSlot{m.rec_off, m1.rec_off - m.rec_off, m.pos0, left + right};
                 if (halves) {
                     L->chunk_half[2 * (size_t)c] = left;
                     L->chunk_half[2 * (size_t)c + 1] = right;
@@ -341,12 +348,13 @@ int32_t finalize_and_validate(cl_layer *L, Team &team)
                     }
                     gp[kGroups] = at;
                 }
-                uint16_t *rp = &L->row_ptr[(size_t)b * kRowPtrs], row_at = 0;
-                for (int r = 0; r < kRows; ++r) {
-                    rp[r] = row_at;
-                    row_at = (uint16_t)(row_at + cnt[r] + cnt[kRows + r]);
+                if (!L->row_ptr.empty()) {
+                    uint16_t *rp = &L->row_ptr[(size_t)b * L->row_ptrs], row_at = 0;
+                    for (int r = 0; r < L->row_ptrs; ++r) {
+                        rp[r] = row_at;
+                        if (r < d.block_h) row_at = (uint16_t)(row_at + cnt[r] + cnt[kRows + r]);
+                    }
                 }
-                rp[kRows] = row_at;
             }
         }
         vbits += my_v;

@@ -58,15 +58,15 @@ struct LayerDev {
     const cl_chunk_meta *meta;
     const uint32_t *panel_chunk;
     const uint32_t *block_chunk;
-    const ChunkSlot *slot;               // null unless the blocks are at most 128 x 128 (with row_ptr)
+    const ChunkSlot *slot;               // may be null, as row_ptr (cl_layer::slot)
     const uint32_t *chunk_half;          // null unless the blocks are at most 128 x 128 (with group_ptr)
     const uint32_t *group_ptr;
-    const uint16_t *row_ptr;             // null unless the blocks are at most 128 x 128
+    const uint16_t *row_ptr;
     const float *codebook;
     const uint4 *tables;                 // both decode tables and the codebook as they lie in LDS (carve)
     int M, K, bh, bw, nbw;
     int val_bits, idx_bits, ncode;       // index widths of the decode tables, codebook entries
-    int block_slots;                     // slots of a block in `slot`
+    int block_slots, row_ptrs;           // slots of a block in `slot`, entries of a block in row_ptr
     int table_rows;                      // 16-byte rows of the table image (tables + codebook)
     uint32_t n_chunks;
     int panel0;                          // first block row of a launch that covers only some (a filter group); else 0
@@ -89,6 +89,7 @@ static LayerDev make_dev(const cl_layer *L)
     d.block_chunk = L->dev.block_chunk;
     d.slot = L->dev.slot;
     d.block_slots = L->block_slots;
+    d.row_ptrs = L->row_ptrs;
     d.chunk_half = L->dev.chunk_half;
     d.group_ptr = L->dev.group_ptr;
     d.codebook = L->dev.codebook;
@@ -290,7 +291,7 @@ extern "C" int32_t cl_layer_upload(cl_layer *L)
     L->dev.block_ptr = (const uint32_t *)(blob + secs[2].off);
     L->dev.panel_chunk = (const uint32_t *)(blob + secs[3].off);
     L->dev.block_chunk = (const uint32_t *)(blob + secs[5].off);
-    L->dev.slot = (const ChunkSlot *)(blob + secs[6].off);
+    L->dev.slot = L->slot.empty() ? nullptr : (const ChunkSlot *)(blob + secs[6].off);
     L->dev.chunk_half = L->group_ptr.empty() ? nullptr : (const uint32_t *)(blob + secs[7].off);
     L->dev.group_ptr = L->group_ptr.empty() ? nullptr : (const uint32_t *)(blob + secs[8].off);
     L->dev.row_ptr = L->row_ptr.empty() ? nullptr : (const uint16_t *)(blob + secs[9].off);
@@ -308,7 +309,7 @@ extern "C" int32_t cl_layer_upload(cl_layer *L)
 // 128 x 128, 28 and 25 us).
 static bool decode_by_blocks(const cl_layer *L, bool dense)
 {
-    return !L->row_ptr.empty() && (int64_t)L->desc.block_h * L->desc.block_w >= (dense ? 64 * 64 : 96 * 96);
+    return !L->slot.empty() && (int64_t)L->desc.block_h * L->desc.block_w >= (dense ? 64 * 64 : 96 * 96);
 }
 
 extern "C" int32_t cl_decode_layer(const cl_layer *L, uint8_t *d_val_sym, uint8_t *d_idx_sym,
@@ -412,12 +413,12 @@ bool rows_kernel_pays(const cl_layer *L, int batch, int cus)
 // busy.)
 constexpr size_t kRowsScratch = CL_STATIC_SCRATCH_BYTES;
 
-// Launch shape of fc_rows_kernel; false where it does not fit (blocks above 128 x 128, more
-// weights in a block than its list has room for in LDS, so many block rows that a tile of
-// sixteen images of each exceeds kRowsScratch).
+// Launch shape of fc_rows_kernel; false where it does not fit (blocks above 128 x 128, a layer
+// without the tables it reads, more weights in a block than its list has room for in LDS, so many
+// block rows that a tile of sixteen images of each exceeds kRowsScratch).
 bool plan_rows(const cl_layer *L, int batch, const DeviceLimits &dl, RowsPlan &P)
 {
-    if (!mfma_capable(L) || batch > kMaxTileColumns) return false;
+    if (L->row_ptr.empty() || batch > kMaxTileColumns) return false;
     const size_t image_bytes = (size_t)L->n_panels * kTile * sizeof(float);       // of the partial tiles, unsplit
     const int64_t most = (int64_t)(kRowsScratch / image_bytes);
     if (most < 16) return false;

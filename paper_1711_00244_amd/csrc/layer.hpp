@@ -10,7 +10,6 @@
 namespace cl {
 
 constexpr int kLanes = CL_RECORDS_PER_CHUNK;        // one 64-bit record per lane of a wavefront
-constexpr int kRowPtrs = 132;                       // words of row_ptr per block: 128 row starts, the end, padding to 8 bytes
 constexpr int kCountBits = 4;                       // width of a record's entry-count field
 
 int32_t fail(int32_t code, const char *fmt, ...);
@@ -63,7 +62,9 @@ struct cl_layer {
     std::vector<uint32_t> block_chunk;              // n_blocks + 1: first chunk of each block (derived)
     std::vector<uint32_t> chunk_nz;                 // n_chunks + 1: surviving weights (entries that are not padding) in all
                                                     //   chunks before this one (derived)
-    std::vector<cl::ChunkSlot> slot;                // (blocks of at most 128 x 128) n_blocks x block_slots (derived)
+    // What fc_rows_kernel and decode_blocks_kernel look up (blocks of at most 128 x 128, and where it is
+    // in proportion to the layer, else empty: see finalize_and_validate) (derived).
+    std::vector<cl::ChunkSlot> slot;                // n_blocks x block_slots
     int32_t block_slots = 0;                        // most chunks in one block
     int64_t max_block_entries = 0;                  // most entries in one block
     int64_t max_block_nnz = 0;                      // most surviving weights in one block
@@ -77,8 +78,11 @@ struct cl_layer {
                                                     //   each half goes
     std::vector<uint32_t> group_ptr;                // n_blocks x 2 x 17: where each group of eight rows starts in each
                                                     //   half of the block's part of the list, and where the half ends
-    std::vector<uint16_t> row_ptr;                  // (the same layers) n_blocks x kRowPtrs: where each row of a block starts among the
-                                                    //   block's surviving weights in block order, rows 0 .. 127, then the end
+    std::vector<uint16_t> row_ptr;                  // n_blocks x row_ptrs: where each row of a block starts among the block's
+                                                    //   surviving weights in block order, and where the last ends (with slot
+                                                    //   only, and again in proportion to the layer) (derived)
+    int32_t row_ptrs = 0;                           // block_h and the end, which the last two entries both hold: an even
+                                                    //   number, so that a block's begin at a whole word
     std::vector<cl_chunk_meta> meta;                // n_chunks + 1
     std::vector<uint64_t> records;
     std::vector<cl::lut_t> val_lut, idx_lut;        // indexed by the next val_lut_bits / idx_lut_bits stream bits

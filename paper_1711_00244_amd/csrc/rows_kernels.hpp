@@ -217,7 +217,10 @@ __global__ __launch_bounds__(kRowsThreads) void fc_rows_kernel(LayerDev L, const
     };
 
     // ---- where the quarter's rows start in the lists of a group of blocks, and where the last ends ----
+    // (rows the blocks do not have start and end where the last row ends: the table's last two entries)
     const int row0 = wave * (kTile / NW) + (lane >> 4) * RQ;
+    static_assert(RQ == 2, "a quarter's two rows are one word of row_ptr and the half after it");
+    const int row_at = min(row0, L.row_ptrs - 2), row_end = min(row0 + RQ, L.row_ptrs - 1);
     struct RowRange {
         uint32_t at[RQ + 1];
     };
@@ -227,9 +230,9 @@ __global__ __launch_bounds__(kRowsThreads) void fc_rows_kernel(LayerDev L, const
             const int blk = blk_lo + ph * G + g;
             r[g] = RowRange{};
             if (blk < blk_hi) {
-                const uint16_t *rp = L.row_ptr + (size_t)(pb0 + (uint32_t)blk) * kRowPtrs + row0;
-#pragma unroll
-                for (int q = 0; q <= RQ; ++q) r[g].at[q] = rp[q];
+                const uint16_t *rp = L.row_ptr + (size_t)(pb0 + (uint32_t)blk) * (uint32_t)L.row_ptrs;
+                const uint32_t starts = *(const uint32_t *)(rp + row_at);
+                r[g] = RowRange{{starts & 0xffffu, starts >> 16, rp[row_end]}};
             }
         }
     };

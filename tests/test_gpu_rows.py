@@ -75,6 +75,61 @@ def test_kernel_by_block_size(M, K, bh, bw, small):
     L.free()
 
 
+def _device_bytes(L):
+    import torch
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    L.upload()
+    return before - torch.cuda.mem_get_info()[0]
+
+
+@pytest.mark.parametrize("block", [(128, 128), (32, 128), (16, 16), (8, 8)])
+def test_tables_in_proportion(block):
+    """What a layer takes on the device beside its stored form: per block the 34 list positions of the
+    large-batch path, its first entry and first chunk, and the lookup tables, which are left out
+    above half the records' size (and a mebibyte); per chunk two list positions."""
+    import torch
+    W = rand_pruned(np.random.default_rng(4), 4096, 4096, 0.09)
+    L = cl.compress_layer(W, 5, 4, *block)
+    st = L.stats()
+    tables = st["n_blocks"] * (34 * 4 + 4) + st["n_chunks"] * 8 + 2 * max(st["payload_bytes"] // 2, 1 << 20) + st["lut_bytes"]
+    assert _device_bytes(L) <= st["model_bytes"] + tables + (2 << 20)          # (allocations come in pieces of 2 MiB)
+    L.free()
+
+
+def _one_full_block():
+    """A layer whose blocks hold next to nothing, but for one that is full."""
+    rng = np.random.default_rng(11)
+    W = np.zeros((33 * 128, 100 * 128), np.float32)
+    W[rng.integers(0, W.shape[0], 20000), rng.integers(0, W.shape[1], 20000)] = 0.02
+    W[:128, 256:384] = rng.standard_normal((128, 128)) * 0.02
+    return W
+
+
+@pytest.mark.parametrize("make,block", [(lambda: rand_pruned(np.random.default_rng(5), 1040, 4096, 0.09), (8, 8)), (_one_full_block, (128, 128))],
+                         ids=["small blocks", "one full block"])
+def test_layers_without_the_lookup_tables(make, block):
+    """They run on the small-batch kernel (its scratch is the same for any batch from 8 on), decode chunk
+    by chunk, and give what the oracle gives."""
+    import torch
+    W = make()
+    L = cl.compress_layer(W, 5, 4, *block, upload=True)
+    m = oracle.compress_layer(W, 5, 4, *block)
+    oW = oracle.dense_weights(m)
+    assert len({cl.fc_workspace_bytes(L, B, cl.PATH_SPARSE) for B in (8, 9, 64)}) == 1
+    val, idx, bp, dense = cl.decode_layer(L)
+    oval, oidx, obp = oracle.decode_layer(m)
+    assert np.array_equal(val.cpu().numpy(), oval) and np.array_equal(idx.cpu().numpy(), oidx) and np.array_equal(bp.cpu().numpy(), obp)
+    assert np.array_equal(dense.cpu().numpy(), oW)
+    rng = np.random.default_rng(6)
+    X = np.maximum(rng.standard_normal((20, W.shape[1])), 0).astype(np.float32)
+    Xd = torch.from_numpy(X).cuda()
+    ref = fc_ref(oW, X)
+    for path in (cl.PATH_SPARSE, cl.PATH_AUTO):
+        assert_close(cl.compressed_fc_forward(L, Xd, path=path).cpu().numpy(), ref, False)
+    L.free()
+
+
 # M, K: a batch in runs of four images a lane (1024 images of 4096 rows fill the scratch); of two and of
 # one (so many rows that 63 and 31 images do); and one that leaves the path to the small-batch kernel
 @pytest.mark.parametrize("M,K,B", [(4096, 260, 1023), (4096, 260, 1025), (4096, 260, 2100), (66000, 24, 200), (130000, 24, 70), (270000, 12, 20)])

@@ -8,7 +8,6 @@
 #include <cstdint>
 #include <exception>
 #include <mutex>
-#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -35,7 +34,7 @@ public:
         threads_.reserve((size_t)std::max<int64_t>(0, n - 1));
         try {
             for (int64_t i = 1; i < n; ++i) threads_.emplace_back([this] { serve(); });
-        } catch (const std::system_error &) {      // fewer threads than asked for: the work is shared among those there are
+        } catch (...) {      // (no thread, no memory for one) fewer than asked for: the work is shared among those there are
         }
     }
 

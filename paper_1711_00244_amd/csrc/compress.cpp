@@ -16,20 +16,34 @@
 
 namespace cl {
 
-static thread_local std::string g_error;
+// (of fixed size: reporting that there is no memory takes none)
+static thread_local char g_error[512];
 
-int32_t fail(int32_t code, const char *fmt, ...)
+int32_t fail(int32_t code, const char *fmt, ...) noexcept
 {
-    char buf[512];
+    char buf[sizeof g_error];                   // (an argument may be the message before)
     va_list ap;
     va_start(ap, fmt);
     vsnprintf(buf, sizeof buf, fmt, ap);
     va_end(ap);
-    g_error = buf;
+    std::memcpy(g_error, buf, sizeof buf);
     return code;
 }
 
-void clear_error() { g_error.clear(); }
+void clear_error() noexcept { g_error[0] = 0; }
+
+int32_t fail_with_exception() noexcept
+{
+    try {
+        throw;
+    } catch (const std::bad_alloc &) {
+        return fail(CL_ENOMEM, "out of memory");
+    } catch (const std::exception &e) {
+        return fail(CL_ENOMEM, "out of a host resource: %s", e.what());
+    } catch (...) {
+        return fail(CL_ENOMEM, "out of a host resource");
+    }
+}
 
 namespace {
 
@@ -405,7 +419,7 @@ int32_t finalize_and_validate(cl_layer *L, Team &team)
 
 using namespace cl;
 
-extern "C" const char *cl_last_error(void) { return g_error.c_str(); }
+extern "C" const char *cl_last_error(void) { return g_error; }
 
 namespace {
 
@@ -682,8 +696,8 @@ extern "C" int32_t cl_compress_layer(const cl_layer_desc *desc, const float *W, 
         if (int32_t rc = finalize_and_validate(L.get(), team)) return fail(rc == CL_ECORRUPT ? CL_EINVAL : rc, "internal: self-check failed: %s", cl_last_error());
         L->val_bits_unlimited = vu;
         L->idx_bits_unlimited = iu;
-    } catch (const std::bad_alloc &) {
-        return fail(CL_ENOMEM, "out of memory");
+    } catch (...) {
+        return fail_with_exception();
     }
     *out = L.release();
     clear_error();
@@ -869,8 +883,12 @@ extern "C" int32_t cl_layer_serialize(const cl_layer *L, void *buf, size_t *byte
     put(L->panel_chunk.data(), section_bytes(L->panel_chunk));
     put(L->meta.data(), section_bytes(L->meta));
     put(L->records.data(), section_bytes(L->records));
-    Team team((int64_t)need, kBytesPerThread);
-    h.checksum = fnv1a_team((const uint8_t *)buf + sizeof h, need - sizeof h, team);
+    try {
+        Team team((int64_t)need, kBytesPerThread);
+        h.checksum = fnv1a_team((const uint8_t *)buf + sizeof h, need - sizeof h, team);
+    } catch (...) {
+        return fail_with_exception();
+    }
     std::memcpy(buf, &h, sizeof h);
     *bytes = need;
     return CL_OK;
@@ -916,8 +934,8 @@ extern "C" int32_t cl_layer_deserialize(const void *buf, size_t bytes, cl_layer 
         get(L->records, (size_t)h.n_records);
         if (L->meta[(size_t)h.n_chunks].sym_off != (uint64_t)h.n_entries) return fail(CL_ECORRUPT, "entry count mismatch");
         if (int32_t rc = finalize_and_validate(L.get(), team)) return rc;
-    } catch (const std::bad_alloc &) {
-        return fail(CL_ENOMEM, "out of memory");
+    } catch (...) {
+        return fail_with_exception();
     }
     L->val_bits_unlimited = h.val_bits_unlimited;
     L->idx_bits_unlimited = h.idx_bits_unlimited;

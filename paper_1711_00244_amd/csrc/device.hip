@@ -232,7 +232,7 @@ static int32_t require_device(const cl_layer *L)
 using namespace cl;
 
 extern "C" int32_t cl_layer_upload(cl_layer *L)
-{
+try {
     if (!L) return fail(CL_EINVAL, "null layer");
     int ndev = 0;
     if (hipGetDeviceCount(&ndev) != hipSuccess || ndev < 1) return fail(CL_EHIP, "no HIP device");
@@ -299,6 +299,8 @@ extern "C" int32_t cl_layer_upload(cl_layer *L)
     L->dev.codebook = (const float *)(blob + secs[4].off + ((L->val_lut.size() + L->idx_lut.size()) * sizeof(lut_t) + 15) / 16 * 16);
     clear_error();
     return CL_OK;
+} catch (...) {
+    return fail_with_exception();
 }
 
 // decode_blocks_kernel takes a few thousand cycles for a block, most of them latencies, however small
@@ -1166,7 +1168,7 @@ int32_t plan_stack(const cl_layer *const *layers, int n, int batch, int path, co
 
 extern "C" int32_t cl_fc_stack_workspace_bytes(const cl_layer *const *layers, int32_t n_layers, int32_t batch, int32_t path,
                                                size_t *out)
-{
+try {
     if (!out) return fail(CL_EINVAL, "null argument");
     DeviceLimits dl;
     if (int32_t rc = device_limits(dl)) return rc;
@@ -1174,13 +1176,15 @@ extern "C" int32_t cl_fc_stack_workspace_bytes(const cl_layer *const *layers, in
     if (int32_t rc = plan_stack(layers, n_layers, batch, path, dl, P)) return rc;
     *out = P.total();
     return CL_OK;
+} catch (...) {
+    return fail_with_exception();
 }
 
 extern "C" int32_t cl_compressed_fc_stack_forward(const cl_layer *const *layers, int32_t n_layers, const float *d_X,
                                                   const float *const *d_bias_or_null, float *d_Y, int32_t batch,
                                                   int32_t relu_hidden, int32_t relu_last, int32_t path, void *d_workspace,
                                                   size_t workspace_bytes, void *stream)
-{
+try {
     if (!d_X || !d_Y) return fail(CL_EINVAL, "null activation pointer");
     DeviceLimits dl;
     if (int32_t rc = device_limits(dl)) return rc;
@@ -1272,6 +1276,8 @@ extern "C" int32_t cl_compressed_fc_stack_forward(const cl_layer *const *layers,
     }
     clear_error();
     return CL_OK;
+} catch (...) {
+    return fail_with_exception();
 }
 
 // ------------------------------------------------------------------------- //
@@ -1318,7 +1324,7 @@ int32_t plan_group(const cl_layer_group *G, int batch, const DeviceLimits &dl, G
 }  // namespace
 
 extern "C" int32_t cl_layer_group_create(const cl_layer *const *layers, int32_t n_layers, cl_layer_group **out)
-{
+try {
     if (!layers || !out || n_layers < 1) return fail(CL_EINVAL, "a group needs at least one layer");
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev));
@@ -1346,6 +1352,8 @@ extern "C" int32_t cl_layer_group_create(const cl_layer *const *layers, int32_t 
     *out = G.release();
     clear_error();
     return CL_OK;
+} catch (...) {
+    return fail_with_exception();
 }
 
 extern "C" void cl_layer_group_free(cl_layer_group *G)

@@ -2,7 +2,6 @@
 #pragma once
 #include <cstdarg>
 #include <cstdint>
-#include <string>
 #include <vector>
 
 #include "compressed_layer.h"
@@ -12,8 +11,11 @@ namespace cl {
 constexpr int kLanes = CL_RECORDS_PER_CHUNK;        // one 64-bit record per lane of a wavefront
 constexpr int kCountBits = 4;                       // width of a record's entry-count field
 
-int32_t fail(int32_t code, const char *fmt, ...);
-void clear_error();
+int32_t fail(int32_t code, const char *fmt, ...) noexcept;
+void clear_error() noexcept;
+// The status and message of the exception being handled: an entry point that may allocate ends with
+// catch (...) { return fail_with_exception(); }
+int32_t fail_with_exception() noexcept;
 
 // Entry of a decode table: low byte = codeword length (>= 1, <= CL_MAX_CODE_LEN, so
 // the entry can feed a 64-bit shift, which looks at the low six bits only), next byte

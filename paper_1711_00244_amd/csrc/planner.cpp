@@ -70,7 +70,7 @@ extern "C" int32_t cl_plan_batches(int32_t n_layers, const int32_t *batch_set, i
                                    const int64_t *out_bytes_per_image, const int64_t *ws_bytes,
                                    int64_t tot_bytes, int64_t mem_step_bytes, double latency_cap_ms,
                                    int32_t *out_batch_per_layer, double *out_ms_per_image)
-{
+try {
     using cl::fail;
     if (!batch_set || !time_ms || !in_bytes_per_image || !out_bytes_per_image || !ws_bytes || !out_batch_per_layer || !out_ms_per_image)
         return fail(CL_EINVAL, "null argument");
@@ -112,4 +112,6 @@ extern "C" int32_t cl_plan_batches(int32_t n_layers, const int32_t *batch_set, i
     }
     cl::clear_error();
     return CL_OK;
+} catch (...) {
+    return cl::fail_with_exception();
 }

@@ -76,5 +76,46 @@ int main(int, char **argv)
                 return CL_ENOMEM;
             }
         });
-    return 2;
+    const int M = 1024, K = 2048;           // enough weights, records and bytes for several threads
+    std::vector<float> W((size_t)M * K);
+    uint32_t x = 1;
+    for (float &w : W) {
+        x = x * 1664525u + 1013904223u;
+        w = x >> 30 ? 0.0f : (float)((x >> 8) & 0xffff) * 1e-5f - 0.3f;
+    }
+    const cl_layer_desc d{M, K, 5, 4, 128, 128, 0, 0};
+    cl_layer *L = nullptr;
+    if (cl_compress_layer(&d, W.data(), nullptr, &L) != CL_OK) return 2;
+    size_t bytes = 0;
+    if (cl_layer_serialize(L, nullptr, &bytes) != CL_OK) return 2;
+    std::vector<char> image(bytes), again(bytes);
+    if (cl_layer_serialize(L, image.data(), &bytes) != CL_OK) return 2;
+    if (!std::strcmp(argv[1], "serialize"))
+        return each_failure([&] {
+            size_t n = bytes;
+            const int32_t rc = cl_layer_serialize(L, again.data(), &n);
+            return rc == CL_OK && again != image ? (int32_t)CL_ECORRUPT : rc;
+        });
+    if (!std::strcmp(argv[1], "deserialize"))
+        return each_failure([&] {
+            cl_layer *out = nullptr;
+            const int32_t rc = cl_layer_deserialize(image.data(), bytes, &out);
+            cl_layer_free(out);
+            return rc;
+        });
+    if (!std::strcmp(argv[1], "compress"))
+        return each_failure([&] {
+            cl_layer *out = nullptr;
+            const int32_t rc = cl_compress_layer(&d, W.data(), nullptr, &out);
+            cl_layer_free(out);
+            return rc;
+        });
+    const int32_t batches[3] = {1, 2, 4};
+    const double ms[6] = {1, 2, 3, 1, 2, 3};
+    const int64_t some[2] = {100, 100};
+    return each_failure([&] {
+        int32_t plan[2];
+        double best;
+        return cl_plan_batches(2, batches, 3, ms, some, some, some, 10000, 100, 0.0, plan, &best);
+    });
 }

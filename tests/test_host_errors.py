@@ -17,7 +17,7 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("what", ["team"])
+@pytest.mark.parametrize("what", ["team", "serialize", "deserialize", "compress", "plan"])
 def test_every_allocation_may_fail(program, what):
     r = subprocess.run([program, what], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, (r.returncode, r.stdout, r.stderr)

@@ -156,8 +156,8 @@ def _want(t, shape, what):
                          f"got {t.dtype} {tuple(t.shape)}")
 
 
-_new_bytes = C.pythonapi.PyBytes_FromStringAndSize
-_new_bytes.restype, _new_bytes.argtypes = C.py_object, [C.c_void_p, C.c_ssize_t]
+# (a function object of its own: the attribute of ctypes.pythonapi is shared by the whole process)
+_new_bytes = C.PYFUNCTYPE(C.py_object, C.c_void_p, C.c_ssize_t)(("PyBytes_FromStringAndSize", C.pythonapi))
 
 
 class Layer:

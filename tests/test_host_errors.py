@@ -1,6 +1,8 @@
-"""The library's host side when memory runs out: every entry point returns a status."""
+"""The library's host side when memory runs out: every entry point returns a status.  And what
+importing the package leaves alone."""
 import os
 import subprocess
+import sys
 
 import pytest
 
@@ -21,3 +23,11 @@ def program(tmp_path_factory):
 def test_every_allocation_may_fail(program, what):
     r = subprocess.run([program, what], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, (r.returncode, r.stdout, r.stderr)
+
+
+def test_the_import_leaves_ctypes_pythonapi_alone():
+    code = ("import ctypes; f = ctypes.pythonapi.PyBytes_FromStringAndSize; before = f.restype, f.argtypes\n"
+            "from paper_1711_00244_amd import binding\n"
+            "assert (f.restype, f.argtypes) == before, (f.restype, f.argtypes)")
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr

@@ -329,7 +329,8 @@ __device__ __forceinline__ Smem carve(uint8_t *base, const LayerDev &L)
     lut_t *v = (lut_t *)base + (values_first ? 0 : 1 << L.idx_bits);
     lut_t *i = (lut_t *)base + (values_first ? 1 << L.val_bits : 0);
     // both tables have at least two entries, so they end 4-byte aligned; round up to 16
-    // (base is where the dynamic LDS starts: at 0, in kernels that have no other)
+    // (base is where the dynamic LDS starts: at 0, in kernels that have no other - as all that call this
+    // must be, which tests/test_kernel_lds.py checks in the built library)
     const size_t tb = (((size_t)1 << L.val_bits) + ((size_t)1 << L.idx_bits)) * sizeof(lut_t);
     float *cb = (float *)(base + ((tb + 15) & ~(size_t)15));
     s.T.vbase = (uint32_t)(uintptr_t)(lds_lut)v;

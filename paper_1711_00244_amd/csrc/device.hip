@@ -463,13 +463,17 @@ bool plan_rows(const cl_layer *L, int batch, const DeviceLimits &dl, RowsPlan &P
     return true;
 }
 
-// (one_tile: the caller wants the whole batch, up to 16 images, in one batch tile)
-int32_t plan_sparse(const cl_layer *L, int batch, const DeviceLimits &dl, SparsePlan &P, bool one_tile = false)
+// (one_tile: the caller wants the whole batch, up to 16 images, in one batch tile; rows: the launch shape
+// of fc_rows_kernel where the caller has it already)
+int32_t plan_sparse(const cl_layer *L, int batch, const DeviceLimits &dl, SparsePlan &P, bool one_tile = false, const RowsPlan *rows = nullptr)
 {
     const size_t max_lds = dl.max_lds;
-    if (!one_tile && rows_kernel_pays(L, batch, dl.cus) && plan_rows(L, batch, dl, P.rows)) {
-        P.part_bytes = P.rows.part_bytes;
-        return CL_OK;
+    if (!one_tile && rows_kernel_pays(L, batch, dl.cus)) {
+        if (rows) P.rows = *rows;
+        if (rows || plan_rows(L, batch, dl, P.rows)) {
+            P.part_bytes = P.rows.part_bytes;
+            return CL_OK;
+        }
     }
     P.fixed = table_image_bytes(L->val_lut_bits, L->idx_lut_bits, 1 << L->desc.weight_bits);
     P.xwant = (int)std::min<int64_t>(L->desc.K, (1 + 2 * kSparseChunksPerWave) * (int64_t)L->desc.block_w);
@@ -730,30 +734,54 @@ constexpr int kAutoSparseBatch = 8;
 constexpr int kAutoRowsBlocks = 48;
 constexpr int64_t kAutoLaunch = 6000;
 
-int resolve_path(const cl_layer *L, int batch, int path, const DeviceLimits &dl)
+// How one layer runs for a batch: the path, and that path's launch shape.  Made once per call (what
+// the choice of a path has worked out for it is kept).
+struct FcPlan {
+    int path = 0;
+    bool have_wide = false, have_rows = false;      // left by the choice: wide, sparse.rows
+    SparsePlan sparse;
+    MfmaPlan mfma;
+    WidePlan wide;
+    size_t bytes() const { return path == CL_PATH_SPARSE ? sparse.part_bytes : path == CL_PATH_SPARSE_WIDE ? wide.xt_bytes + wide.part_bytes : mfma.xt_bytes + mfma.part_bytes; }
+};
+
+void choose_path(const cl_layer *L, int batch, int path, const DeviceLimits &dl, FcPlan &P)
 {
-    if (path != CL_PATH_AUTO) return path;
-    if (batch <= kAutoSparseBatch || !mfma_capable(L)) return CL_PATH_SPARSE;
-    if (batch > kMaxTileColumns) return CL_PATH_MFMA_F32;      // refused there with its message
+    P.path = path;
+    if (path != CL_PATH_AUTO) return;
+    P.path = CL_PATH_SPARSE;
+    if (batch <= kAutoSparseBatch || !mfma_capable(L)) return;
+    P.path = CL_PATH_MFMA_F32;
+    if (batch > kMaxTileColumns) return;                    // refused there with its message
     int nq, np, splits;
     int64_t best = 0;
-    int choice = CL_PATH_MFMA_F32;
     mfma_shape(L, L->n_panels, batch, dl.cus, false, nq, np, splits, false, false, &best);
-    WidePlan W;
-    if (plan_wide(L, batch, dl, W) != CL_OK) clear_error();
-    else if (W.cost < best) {
-        best = W.cost;
-        choice = CL_PATH_SPARSE_WIDE;
+    P.have_wide = plan_wide(L, batch, dl, P.wide) == CL_OK;
+    if (!P.have_wide) clear_error();
+    else if (P.wide.cost < best) {
+        best = P.wide.cost;
+        P.path = CL_PATH_SPARSE_WIDE;
     }
-    RowsPlan R;
-    if (L->n_blocks >= kAutoRowsBlocks && plan_rows(L, batch, dl, R) && R.cost < best + kAutoLaunch) choice = CL_PATH_SPARSE;
-    return choice;
+    P.have_rows = L->n_blocks >= kAutoRowsBlocks && plan_rows(L, batch, dl, P.sparse.rows);
+    if (P.have_rows && P.sparse.rows.cost < best + kAutoLaunch) P.path = CL_PATH_SPARSE;
 }
 
 bool is_mfma(int path) { return path == CL_PATH_MFMA_F32 || path == CL_PATH_MFMA_BF16; }
 
 // the paths that read the activations transposed and laid out block by block
 bool reads_xt(int path) { return is_mfma(path) || path == CL_PATH_SPARSE_WIDE; }
+
+int32_t plan_fc(const cl_layer *L, int batch, int path, const DeviceLimits &dl, FcPlan &P)
+{
+    if (batch < 1) return fail(CL_EINVAL, "batch must be positive");
+    if (path < CL_PATH_AUTO || path > CL_PATH_SPARSE_WIDE) return fail(CL_EINVAL, "unknown path %d", path);
+    choose_path(L, batch, path, dl, P);
+    if (P.path == CL_PATH_SPARSE_WIDE) return P.have_wide ? (int32_t)CL_OK : plan_wide(L, batch, dl, P.wide);
+    if (is_mfma(P.path)) return plan_mfma(L, batch, P.path == CL_PATH_MFMA_BF16, dl, P.mfma);
+    const RowsPlan rows = P.sparse.rows;
+    P.sparse = SparsePlan{};
+    return plan_sparse(L, batch, dl, P.sparse, false, P.have_rows ? &rows : nullptr);
+}
 
 }  // namespace
 
@@ -764,20 +792,9 @@ extern "C" int32_t cl_fc_workspace_bytes(const cl_layer *L, int32_t batch, int32
     if (path < CL_PATH_AUTO || path > CL_PATH_SPARSE_WIDE) return fail(CL_EINVAL, "unknown path %d", path);
     DeviceLimits dl;
     if (int32_t rc = device_limits(dl)) return rc;
-    const int chosen = resolve_path(L, batch, path, dl);
-    if (chosen == CL_PATH_SPARSE_WIDE) {
-        WidePlan P;
-        if (int32_t rc = plan_wide(L, batch, dl, P)) return rc;
-        *out = P.xt_bytes + P.part_bytes;
-    } else if (is_mfma(chosen)) {
-        MfmaPlan P;
-        if (int32_t rc = plan_mfma(L, batch, chosen == CL_PATH_MFMA_BF16, dl, P)) return rc;
-        *out = P.xt_bytes + P.part_bytes;
-    } else {
-        SparsePlan P;
-        if (int32_t rc = plan_sparse(L, batch, dl, P)) return rc;
-        *out = P.part_bytes;
-    }
+    FcPlan P;
+    if (int32_t rc = plan_fc(L, batch, path, dl, P)) return rc;
+    *out = P.bytes();
     return CL_OK;
 }
 
@@ -788,7 +805,9 @@ extern "C" int32_t cl_fc_resolved_path(const cl_layer *L, int32_t batch, int32_t
     if (path < CL_PATH_AUTO || path > CL_PATH_SPARSE_WIDE) return fail(CL_EINVAL, "unknown path %d", path);
     DeviceLimits dl;
     if (int32_t rc = device_limits(dl)) return rc;
-    *out = resolve_path(L, batch, path, dl);
+    FcPlan P;
+    choose_path(L, batch, path, dl, P);
+    *out = P.path;
     return CL_OK;
 }
 
@@ -835,16 +854,14 @@ static int32_t forward_rows(const cl_layer *L, const LayerDev &D, const RowsPlan
     return CL_OK;
 }
 
-// The small-batch path for one layer.  With `prev` the input is not d_X but the partial
+// One layer on the sparse path with launch shape P.  With `prev` the input is not d_X but the partial
 // tiles of the layer before (see PrevSlots); with finish == false the layer's own
 // finishing kernel is left to the layer after it in the same way.  Both only where
 // sparse_can_fold allows.
-static int32_t forward_sparse(const cl_layer *L, const LayerDev &D, const DeviceLimits &dl, const float *d_X,
+static int32_t forward_sparse(const cl_layer *L, const LayerDev &D, const SparsePlan &P, const float *d_X,
                               const float *d_bias, float *d_Y, int batch, int relu, float *part, hipStream_t st,
                               const PrevSlots *prev = nullptr, bool finish = true)
 {
-    SparsePlan P;
-    if (int32_t rc = plan_sparse(L, batch, dl, P)) return rc;
     if (P.rows.ipl) return forward_rows(L, D, P.rows, d_X, d_bias, d_Y, batch, relu, part, st);
     const PrevSlots from = prev ? *prev : PrevSlots{nullptr, nullptr, nullptr, 1, 0, 0, 0};
     if ((prev || !finish) && !sparse_can_fold(L, P, batch)) return fail(CL_EINVAL, "internal: layer cannot take or leave partial tiles");
@@ -1029,44 +1046,31 @@ static int32_t run_wide_layer(const cl_layer *L, const LayerDev &D, const WidePl
     return CL_OK;
 }
 
-static int32_t forward_wide(const cl_layer *L, const LayerDev &D, const DeviceLimits &dl, const float *d_X, const float *d_bias,
-                            float *d_Y, int batch, int relu, char *ws, hipStream_t st)
-{
-    WidePlan P;
-    if (int32_t rc = plan_wide(L, batch, dl, P)) return rc;
-    return run_wide_layer(L, D, P, d_X, (float *)ws, (float *)(ws + P.xt_bytes), (WideEntry *)(ws + P.xt_bytes + P.tile_bytes), false,
-                          d_bias, d_Y, 0, batch, relu, st);
-}
-
-static int32_t forward_mfma(const cl_layer *L, const LayerDev &D, const DeviceLimits &dl, bool bf16, const float *d_X,
-                            const float *d_bias, float *d_Y, int batch, int relu, char *ws, hipStream_t st)
-{
-    MfmaPlan P;
-    if (int32_t rc = plan_mfma(L, batch, bf16, dl, P)) return rc;
-    return run_mfma_layer(L, D, P, d_X, ws, (float *)(ws + P.xt_bytes), d_bias, d_Y, 0, batch, relu, st);
-}
-
-static int32_t fc_forward_checked(const cl_layer *L, const float *d_X, const float *d_bias, float *d_Y, int32_t batch,
-                                  int32_t relu, int32_t path, void *d_workspace, size_t workspace_bytes, void *stream)
+// The checks of a single-layer call (before anything is planned), then its launches with plan P.
+static int32_t check_fc_call(const cl_layer *L, const float *d_X, const float *d_Y, int32_t batch)
 {
     if (int32_t rc = require_device(L)) return rc;
     if (!d_X || !d_Y) return fail(CL_EINVAL, "null activation pointer");
     if (batch < 1) return fail(CL_EINVAL, "batch must be positive");
-    size_t need = 0;
-    if (int32_t rc = cl_fc_workspace_bytes(L, batch, path, &need)) return rc;
+    return CL_OK;
+}
+
+static int32_t forward_planned(const cl_layer *L, const FcPlan &P, const float *d_X, const float *d_bias, float *d_Y, int32_t batch,
+                               int32_t relu, void *d_workspace, size_t workspace_bytes, hipStream_t st)
+{
+    const size_t need = P.bytes();
     if (workspace_bytes < need || (need && !d_workspace)) return fail(CL_EINVAL, "workspace too small: %zu < %zu", workspace_bytes, need);
     if ((uintptr_t)d_workspace % 256) return fail(CL_EINVAL, "workspace must be 256-byte aligned");
-    DeviceLimits dl;
-    if (int32_t rc = device_limits(dl)) return rc;
     const LayerDev D = make_dev(L);
+    char *ws = (char *)d_workspace;
     int32_t rc;
-    const int chosen = resolve_path(L, batch, path, dl);
-    if (chosen == CL_PATH_SPARSE_WIDE)
-        rc = forward_wide(L, D, dl, d_X, d_bias, d_Y, batch, relu, (char *)d_workspace, (hipStream_t)stream);
-    else if (is_mfma(chosen))
-        rc = forward_mfma(L, D, dl, chosen == CL_PATH_MFMA_BF16, d_X, d_bias, d_Y, batch, relu, (char *)d_workspace, (hipStream_t)stream);
+    if (P.path == CL_PATH_SPARSE_WIDE)
+        rc = run_wide_layer(L, D, P.wide, d_X, (float *)ws, (float *)(ws + P.wide.xt_bytes), (WideEntry *)(ws + P.wide.xt_bytes + P.wide.tile_bytes), false,
+                            d_bias, d_Y, 0, batch, relu, st);
+    else if (is_mfma(P.path))
+        rc = run_mfma_layer(L, D, P.mfma, d_X, ws, (float *)(ws + P.mfma.xt_bytes), d_bias, d_Y, 0, batch, relu, st);
     else
-        rc = forward_sparse(L, D, dl, d_X, d_bias, d_Y, batch, relu, (float *)d_workspace, (hipStream_t)stream);
+        rc = forward_sparse(L, D, P.sparse, d_X, d_bias, d_Y, batch, relu, (float *)ws, st);
     if (rc == CL_OK) clear_error();
     return rc;
 }
@@ -1075,22 +1079,28 @@ extern "C" int32_t cl_compressed_fc_forward(const cl_layer *L, const float *d_X,
                                             float *d_Y, int32_t batch, int32_t relu, int32_t path,
                                             void *d_workspace, size_t workspace_bytes, void *stream)
 {
-    return fc_forward_checked(L, d_X, d_bias, d_Y, batch, relu, path, d_workspace, workspace_bytes, stream);
+    if (int32_t rc = check_fc_call(L, d_X, d_Y, batch)) return rc;
+    DeviceLimits dl;
+    if (int32_t rc = device_limits(dl)) return rc;
+    FcPlan P;
+    if (int32_t rc = plan_fc(L, batch, path, dl, P)) return rc;
+    return forward_planned(L, P, d_X, d_bias, d_Y, batch, relu, d_workspace, workspace_bytes, (hipStream_t)stream);
 }
 
 extern "C" int32_t cl_compressed_fc_forward_static(const cl_layer *L, const float *d_X, const float *d_bias,
                                                    float *d_Y, int32_t batch, int32_t relu, int32_t path, void *stream)
 {
-    if (int32_t rc = require_device(L)) return rc;
-    if (batch < 1) return fail(CL_EINVAL, "batch must be positive");
-    size_t need = 0;
-    if (int32_t rc = cl_fc_workspace_bytes(L, batch, path, &need)) return rc;
-    if (need > (size_t)CL_STATIC_SCRATCH_BYTES)
+    if (int32_t rc = check_fc_call(L, d_X, d_Y, batch)) return rc;
+    DeviceLimits dl;
+    if (int32_t rc = device_limits(dl)) return rc;
+    FcPlan P;
+    if (int32_t rc = plan_fc(L, batch, path, dl, P)) return rc;
+    if (P.bytes() > (size_t)CL_STATIC_SCRATCH_BYTES)
         return fail(CL_EUNSUPPORTED, "this call needs %zu bytes of scratch, the static scratch area holds %zu: use cl_compressed_fc_forward with a workspace",
-                    need, (size_t)CL_STATIC_SCRATCH_BYTES);
+                    P.bytes(), (size_t)CL_STATIC_SCRATCH_BYTES);
     void *scratch = nullptr;
     if (int32_t rc = static_scratch(&scratch)) return rc;
-    return fc_forward_checked(L, d_X, d_bias, d_Y, batch, relu, path, scratch, (size_t)CL_STATIC_SCRATCH_BYTES, stream);
+    return forward_planned(L, P, d_X, d_bias, d_Y, batch, relu, scratch, (size_t)CL_STATIC_SCRATCH_BYTES, (hipStream_t)stream);
 }
 
 // ------------------------------------------------------------------------- //
@@ -1099,10 +1109,7 @@ extern "C" int32_t cl_compressed_fc_forward_static(const cl_layer *L, const floa
 namespace {
 
 struct StackPlan {
-    std::vector<int> path;            // per layer: the path it runs on
-    std::vector<MfmaPlan> mfma;       // per layer on a dense-tile path
-    std::vector<WidePlan> wide;       // per layer on the wide sparse path
-    std::vector<SparsePlan> sparse;   // per layer on the sparse path
+    std::vector<FcPlan> fc;           // per layer: the path it runs on, and its launch shape
     std::vector<char> xt_in;          // layer reads its transposed activations straight from the layer before
     std::vector<char> fold_in;        // layer adds up the partial tiles of the layer before itself (both on the sparse path)
     std::vector<size_t> ent_off;      // per layer on the wide path: its entry list in the area behind the rotating buffers
@@ -1120,10 +1127,7 @@ int32_t plan_stack(const cl_layer *const *layers, int n, int batch, int path, co
     if (!layers || n < 1) return fail(CL_EINVAL, "a stack needs at least one layer");
     if (batch < 1) return fail(CL_EINVAL, "batch must be positive");
     if (path < CL_PATH_AUTO || path > CL_PATH_SPARSE_WIDE) return fail(CL_EINVAL, "unknown path %d", path);
-    P.path.assign(n, 0);
-    P.wide.assign(n, WidePlan{});
-    P.mfma.assign(n, MfmaPlan{});
-    P.sparse.assign(n, SparsePlan{});
+    P.fc.assign(n, FcPlan{});
     P.xt_in.assign(n, 0);
     P.fold_in.assign(n, 0);
     P.ent_off.assign(n, 0);
@@ -1132,31 +1136,28 @@ int32_t plan_stack(const cl_layer *const *layers, int n, int batch, int path, co
         if (!L) return fail(CL_EINVAL, "layer %d is null", i);
         if (i > 0 && L->desc.K != layers[i - 1]->desc.M)
             return fail(CL_EINVAL, "layer %d takes %d inputs, layer %d gives %d outputs", i, L->desc.K, i - 1, layers[i - 1]->desc.M);
-        P.path[i] = resolve_path(L, batch, path, dl);
+        if (int32_t rc = plan_fc(L, batch, path, dl, P.fc[i])) return rc;
+        const int mine = P.fc[i].path, before = i > 0 ? P.fc[i - 1].path : 0;
         // the finishing kernel of the layer before can write this layer's transposed
         // activations itself when their row order is the plain one (128-column blocks,
         // no ragged last block): 2-3 % of a step on the AlexNet-shaped stack
         const bool plain_rows = L->desc.block_w == kTile && L->desc.K % kTile == 0;
-        if (P.path[i] == CL_PATH_SPARSE_WIDE) {
-            if (int32_t rc = plan_wide(L, batch, dl, P.wide[i])) return rc;
-            P.xt_bytes = std::max(P.xt_bytes, P.wide[i].xt_bytes);
-            P.part_bytes = std::max(P.part_bytes, round256(P.wide[i].tile_bytes));
+        if (mine == CL_PATH_SPARSE_WIDE) {
+            P.xt_bytes = std::max(P.xt_bytes, P.fc[i].wide.xt_bytes);
+            P.part_bytes = std::max(P.part_bytes, round256(P.fc[i].wide.tile_bytes));
             P.ent_off[i] = P.ent_bytes;
-            P.ent_bytes += round256(P.wide[i].ent_bytes);
-            P.xt_in[i] = i > 0 && reads_xt(P.path[i - 1]) && plain_rows;
-        } else if (is_mfma(P.path[i])) {
-            if (int32_t rc = plan_mfma(L, batch, P.path[i] == CL_PATH_MFMA_BF16, dl, P.mfma[i])) return rc;
-            P.xt_bytes = std::max(P.xt_bytes, P.mfma[i].xt_bytes);
-            P.part_bytes = std::max(P.part_bytes, round256(P.mfma[i].part_bytes));
-            P.xt_in[i] = i > 0 && plain_rows && (P.path[i] == CL_PATH_MFMA_F32 ? reads_xt(P.path[i - 1])
-                                                                             : P.path[i - 1] == CL_PATH_MFMA_BF16 && layers[i - 1]->desc.block_h % 4 == 0);
+            P.ent_bytes += round256(P.fc[i].wide.ent_bytes);
+            P.xt_in[i] = i > 0 && reads_xt(before) && plain_rows;
+        } else if (is_mfma(mine)) {
+            P.xt_bytes = std::max(P.xt_bytes, P.fc[i].mfma.xt_bytes);
+            P.part_bytes = std::max(P.part_bytes, round256(P.fc[i].mfma.part_bytes));
+            P.xt_in[i] = i > 0 && plain_rows && (mine == CL_PATH_MFMA_F32 ? reads_xt(before) : before == CL_PATH_MFMA_BF16 && layers[i - 1]->desc.block_h % 4 == 0);
         } else {
-            if (int32_t rc = plan_sparse(L, batch, dl, P.sparse[i])) return rc;
-            P.part_bytes = std::max(P.part_bytes, round256(P.sparse[i].part_bytes));
+            P.part_bytes = std::max(P.part_bytes, round256(P.fc[i].sparse.part_bytes));
             // (measured on the AlexNet-shaped stack: 39.8 -> 37.1 us at one image, no gain at
             // two, a loss at four - every workgroup of a block column adds the same tiles up)
-            P.fold_in[i] = batch == 1 && i > 0 && P.path[i - 1] == CL_PATH_SPARSE && sparse_can_fold(layers[i - 1], P.sparse[i - 1], batch) &&
-                           sparse_can_fold(L, P.sparse[i], batch);
+            P.fold_in[i] = batch == 1 && i > 0 && before == CL_PATH_SPARSE && sparse_can_fold(layers[i - 1], P.fc[i - 1].sparse, batch) &&
+                           sparse_can_fold(L, P.fc[i].sparse, batch);
         }
         if (i + 1 < n) P.act_bytes = std::max(P.act_bytes, round256((size_t)batch * L->desc.M * sizeof(float)));
     }
@@ -1218,17 +1219,17 @@ try {
         WideEntry *ents[kExpandJobs];
         int n = 0, ipl_of_stack = 4;                 // (the images per lane follow from the batch: the same for every layer)
         for (int i = 0; i <= n_layers; ++i) {
-            const bool mine = i < n_layers && P.path[i] == CL_PATH_SPARSE_WIDE;
+            const bool mine = i < n_layers && P.fc[i].path == CL_PATH_SPARSE_WIDE;
             if (mine) {
                 todo[n] = layers[i];
                 ents[n] = ent_of(i);
-                ipl_of_stack = P.wide[i].ipl;
+                ipl_of_stack = P.fc[i].wide.ipl;
                 ++n;
             }
             if (n == kExpandJobs || (i == n_layers && n > 0)) {
-                const bool with_x = !x_laid_out && P.path[0] == CL_PATH_SPARSE_WIDE;
+                const bool with_x = !x_laid_out && P.fc[0].path == CL_PATH_SPARSE_WIDE;
                 if (int32_t rc = launch_wide_expand(todo, ents, n, ipl_of_stack, st, with_x ? layers[0] : nullptr, d_X,
-                                                    (float *)region(xt0, P.xt_bytes, 0), batch, P.wide[0].Bp))
+                                                    (float *)region(xt0, P.xt_bytes, 0), batch, P.fc[0].wide.Bp))
                     return rc;
                 x_laid_out = x_laid_out || with_x;
                 n = 0;
@@ -1243,18 +1244,18 @@ try {
         const float *bias = d_bias_or_null ? d_bias_or_null[i] : nullptr;
         const int relu = last ? relu_last : relu_hidden;
         float *out = last ? d_Y : (float *)region(act0, P.act_bytes, i);
-        if (reads_xt(P.path[i])) {
+        if (reads_xt(P.fc[i].path)) {
             // towards a following layer that takes its activations transposed, this layer's finishing
             // kernel writes them so, the image axis padded to that layer's tile
             const bool to_xt = !last && P.xt_in[i + 1];
             float *dst = to_xt ? (float *)region(xt0, P.xt_bytes, i + 1) : out;
-            const int next_bp = !to_xt ? 0 : P.path[i + 1] == CL_PATH_SPARSE_WIDE ? P.wide[i + 1].Bp : P.mfma[i + 1].Bp;
+            const int next_bp = !to_xt ? 0 : P.fc[i + 1].path == CL_PATH_SPARSE_WIDE ? P.fc[i + 1].wide.Bp : P.fc[i + 1].mfma.Bp;
             int32_t rc;
-            if (P.path[i] == CL_PATH_SPARSE_WIDE)
-                rc = run_wide_layer(L, D, P.wide[i], in, (float *)region(xt0, P.xt_bytes, i), (float *)region(part0, P.part_bytes, i),
+            if (P.fc[i].path == CL_PATH_SPARSE_WIDE)
+                rc = run_wide_layer(L, D, P.fc[i].wide, in, (float *)region(xt0, P.xt_bytes, i), (float *)region(part0, P.part_bytes, i),
                                     ent_of(i), true, bias, dst, next_bp, batch, relu, st);
             else
-                rc = run_mfma_layer(L, D, P.mfma[i], in, region(xt0, P.xt_bytes, i), (float *)region(part0, P.part_bytes, i), bias, dst, next_bp, batch, relu, st);
+                rc = run_mfma_layer(L, D, P.fc[i].mfma, in, region(xt0, P.xt_bytes, i), (float *)region(part0, P.part_bytes, i), bias, dst, next_bp, batch, relu, st);
             if (rc) return rc;
             in = to_xt ? nullptr : out;
         } else {
@@ -1264,11 +1265,11 @@ try {
             if (P.fold_in[i]) {
                 const cl_layer *Lp = layers[i - 1];
                 prev = PrevSlots{(const float *)region(part0, P.part_bytes, i - 1), make_dev(Lp).panel_chunk,
-                                 d_bias_or_null ? d_bias_or_null[i - 1] : nullptr, Lp->desc.block_h, P.sparse[i - 1].wg_per_panel,
+                                 d_bias_or_null ? d_bias_or_null[i - 1] : nullptr, Lp->desc.block_h, P.fc[i - 1].sparse.wg_per_panel,
                                  batch, relu_hidden};
             }
             const bool finish = last || !P.fold_in[i + 1];
-            if (int32_t rc = forward_sparse(L, D, dl, in, bias, out, batch, relu, (float *)region(part0, P.part_bytes, i), st,
+            if (int32_t rc = forward_sparse(L, D, P.fc[i].sparse, in, bias, out, batch, relu, (float *)region(part0, P.part_bytes, i), st,
                                             P.fold_in[i] ? &prev : nullptr, finish))
                 return rc;
             in = out;

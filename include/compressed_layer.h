@@ -121,7 +121,15 @@ typedef struct {
     int64_t payload_bytes;  /* lane records (8 B each): counts, codewords, padding   */
     int64_t table_bytes;    /* chunk table + block_ptr + panel table                 */
     int64_t model_bytes;    /* payload + tables + codebook + code lengths: the bytes */
-                            /*   a forward pass has to fetch                         */
+                            /*   a forward pass has to fetch.  What is derived from  */
+                            /*   them at load time and kept on the device beside is  */
+                            /*   not counted: decode tables (lut_bytes); 4 B a block */
+                            /*   (its first chunk); with blocks of at most 128 x 128 */
+                            /*   136 B a block and 8 B a chunk (the order of the     */
+                            /*   large-batch path) and two lookup tables (16 B a     */
+                            /*   block and chunk of the block with most; 2 B a row   */
+                            /*   of a block), each left out above half the payload   */
+                            /*   and 1 MiB                                           */
     int64_t lut_bytes;      /* decode tables derived at load time (not stored)       */
     int32_t val_max_len, idx_max_len;
 } cl_stats;

@@ -94,8 +94,8 @@ __device__ __forceinline__ void list_from(const Symbols &y, uint32_t pos, uint32
 // row's sum stays in a register from the first block to the last, and nothing is added in
 // memory.  Where a row's entries start in a block's list was counted when the layer was loaded
 // (row_ptr).
-// Bound by vector issue (61 % of the cycles at 16 images of the AlexNet-shaped fc6) and by the
-// latencies of a group's turn, which is why small tiles take several blocks to a group.  There (us per
+// Bound by vector issue (52 % of the cycles at 16 images of the AlexNet-shaped fc6, 40 % over the
+// VGG-shaped stack at 64) and by the latencies of a group's turn, which is why small tiles take several blocks to a group.  There (us per
 // layer call, dense tiles before): 16 images 40 -> 29, 32 images 41 -> 32, 64 images 60 -> 46;
 // VGG-shaped fc6 91 -> 50, 92 -> 57, 139 -> 87.
 template <int IPL, int G>

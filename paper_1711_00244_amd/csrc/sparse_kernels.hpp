@@ -6,8 +6,9 @@
 // ------------------------------------------------------------------------- //
 // decode_layer: symbols and (optionally) the dense matrix
 // ------------------------------------------------------------------------- //
-// For layers with blocks above 128 x 128: a wavefront per chunk, eight to a workgroup, after
-// fill_kernel has cleared the dense matrix.
+// For layers with blocks above 128 x 128, blocks that decode_blocks_kernel gains nothing by (small ones:
+// decode_by_blocks) and layers without the chunk slots it reads: a wavefront per chunk, eight to a
+// workgroup, after fill_kernel has cleared the dense matrix.
 __global__ __launch_bounds__(kThreads) void decode_kernel(LayerDev L, uint8_t *val_out, uint8_t *idx_out, float *dense)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem_raw[];
@@ -40,7 +41,7 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(LayerDev L, uint8_t *v
     });
 }
 
-// The same for layers whose blocks are at most 128 x 128, everything in one launch: a workgroup
+// The same for the other layers, whose blocks are at most 128 x 128, everything in one launch: a workgroup
 // takes block after block.  A wavefront decodes a chunk of the block and leaves its symbols in
 // LDS - value and relative indices in entry order, and the value index once more in a byte
 // tile of the block, at its position; then the workgroup writes the block out, dense rows (zeros

@@ -38,9 +38,10 @@
 // A workgroup per CU takes item after item (block row, split, tile of columns): the gatherers are
 // at the next one's first piece while the multipliers write the last one's output.
 // Bound by the instructions issued: a vector instruction adds its four cycles to the multiplies' time here, and
-// there are some 630 of them per phase and SIMD, gathering and splitting, to 128 multiplies of 32 cycles.
-// (AlexNet conv1 to conv5, 64 images, us: 151, 155, 95, 105, 61; on the fp32 matrix cores, at nine
-// tenths of their rate, 202, 240, 150, 149, 95.  A workgroup per item instead of per CU: conv1 178.)
+// there are some 600 of them per phase and SIMD, gathering and splitting, to 128 multiplies of 32 cycles.
+// (AlexNet conv1 to conv5, 64 images, us: 156, 182, 111, 118, 68, with six products 149, 155, 96, 105, 60; on
+// the fp32 matrix cores, at nine tenths of their rate, 202, 240, 150, 149, 95.  A workgroup per item instead
+// of per CU, six products: conv1 178 for 151.)
 constexpr int conv_gatherers(int planes) { return planes == 3 ? 4 : 8; }   // wavefronts (eight leave too few registers for two sums)
 constexpr int conv_threads(int planes) { return (4 + conv_gatherers(planes)) * 64; }
 constexpr int kConvColumns = kTile;                        // columns per workgroup

@@ -312,7 +312,11 @@ int32_t cl_compressed_fc_forward_static(const cl_layer *layer, const float *d_X,
  *  d_Y             batch x layers[n_layers-1]->M fp32, overwritten
  *  relu_hidden     non-zero applies max(0, .) after every layer but the last
  *  relu_last       the same for the last layer
- *  path            CL_PATH_*, resolved per layer as in cl_compressed_fc_forward
+ *  path            CL_PATH_*; CL_PATH_AUTO is resolved per layer as in
+ *                  cl_compressed_fc_forward, but where some layers would run on
+ *                  CL_PATH_SPARSE and some not, all together: a layer may then leave
+ *                  CL_PATH_SPARSE for the path that is next best for it alone (and give that
+ *                  path's last bits)
  *  d_workspace     at least cl_fc_stack_workspace_bytes(), 256-byte aligned
  * Errors: CL_EINVAL (null pointers, n_layers < 1, layer sizes that do not chain,
  * workspace too small, a layer not uploaded) - nothing is launched then. */

@@ -739,6 +739,8 @@ constexpr int64_t kAutoLaunch = 6000;
 struct FcPlan {
     int path = 0;
     bool have_wide = false, have_rows = false;      // left by the choice: wide, sparse.rows
+    int no_rows = 0;                                // and the path it would be without fc_rows_kernel (0: it is not that kernel)
+    int64_t mfma_cost = 0;
     SparsePlan sparse;
     MfmaPlan mfma;
     WidePlan wide;
@@ -756,6 +758,7 @@ void choose_path(const cl_layer *L, int batch, int path, const DeviceLimits &dl,
     int nq, np, splits;
     int64_t best = 0;
     mfma_shape(L, L->n_panels, batch, dl.cus, false, nq, np, splits, false, false, &best);
+    P.mfma_cost = best;
     P.have_wide = plan_wide(L, batch, dl, P.wide) == CL_OK;
     if (!P.have_wide) clear_error();
     else if (P.wide.cost < best) {
@@ -763,7 +766,10 @@ void choose_path(const cl_layer *L, int batch, int path, const DeviceLimits &dl,
         P.path = CL_PATH_SPARSE_WIDE;
     }
     P.have_rows = L->n_blocks >= kAutoRowsBlocks && plan_rows(L, batch, dl, P.sparse.rows);
-    if (P.have_rows && P.sparse.rows.cost < best + kAutoLaunch) P.path = CL_PATH_SPARSE;
+    if (P.have_rows && P.sparse.rows.cost < best + kAutoLaunch) {
+        P.no_rows = P.path;
+        P.path = CL_PATH_SPARSE;
+    }
 }
 
 bool is_mfma(int path) { return path == CL_PATH_MFMA_F32 || path == CL_PATH_MFMA_BF16; }
@@ -1122,6 +1128,49 @@ size_t round256(size_t n) { return (n + 255) / 256 * 256; }
 
 constexpr int kStackRegions = 4;
 
+// Whether the finishing kernel of the layer before can write this layer's transposed
+// activations itself: when their row order is the plain one (128-column blocks, no ragged
+// last block): 2-3 % of a step on the AlexNet-shaped stack.
+bool plain_rows(const cl_layer *L) { return L->desc.block_w == kTile && L->desc.K % kTile == 0; }
+
+// CL_PATH_AUTO for the layers of a stack.  What fc_rows_kernel saves a single layer - the launch that
+// lays the activations out, or decodes - a layer between two on the other paths does not pay: its
+// neighbour hands the activations over, and one launch decodes all layers on the wide path.  So where
+// some layers run on fc_rows_kernel and some do not, the modelled cycles of the whole stack decide
+// whether the former do without it (us a step, AlexNet- and VGG-shaped stack: at 128 images, fc6 wide
+// either way, 148 and 167 with fc_rows_kernel for fc7, 135 and 156 without; at 64, all three layers on it, 87 and
+// 125, 114 and 136 without).
+constexpr int64_t kWideShared = 13000;          // the decoding launch's fixed part (plan_wide)
+
+int32_t choose_stack_paths(const cl_layer *const *layers, int n, int batch, const DeviceLimits &dl, std::vector<FcPlan> &fc)
+{
+    bool some = false, others = false;
+    for (const FcPlan &P : fc) (P.no_rows ? some : others) = true;
+    if (!some || !others) return CL_OK;
+    auto cost = [&](bool rows) {
+        int64_t t = 0;
+        bool wide = false, before = false;      // a wide layer yet; the layer before hands activations over
+        for (int i = 0; i < n; ++i) {
+            const FcPlan &P = fc[i];
+            const int path = rows || !P.no_rows ? P.path : P.no_rows;
+            const bool handed = before && plain_rows(layers[i]);
+            if (path == CL_PATH_SPARSE) t += P.no_rows ? P.sparse.rows.cost : 0;
+            else if (path == CL_PATH_SPARSE_WIDE) t += P.wide.cost - (wide ? kWideShared : 0) + (i > 0 && !handed ? kAutoLaunch : 0);
+            else t += P.mfma_cost + (handed ? 0 : kAutoLaunch);
+            wide = wide || path == CL_PATH_SPARSE_WIDE;
+            before = reads_xt(path);
+        }
+        return t;
+    };
+    if (cost(true) <= cost(false)) return CL_OK;
+    for (int i = 0; i < n; ++i)
+        if (const int path = fc[i].no_rows) {
+            fc[i] = FcPlan{};
+            if (int32_t rc = plan_fc(layers[i], batch, path, dl, fc[i])) return rc;
+        }
+    return CL_OK;
+}
+
 int32_t plan_stack(const cl_layer *const *layers, int n, int batch, int path, const DeviceLimits &dl, StackPlan &P)
 {
     if (!layers || n < 1) return fail(CL_EINVAL, "a stack needs at least one layer");
@@ -1137,21 +1186,22 @@ int32_t plan_stack(const cl_layer *const *layers, int n, int batch, int path, co
         if (i > 0 && L->desc.K != layers[i - 1]->desc.M)
             return fail(CL_EINVAL, "layer %d takes %d inputs, layer %d gives %d outputs", i, L->desc.K, i - 1, layers[i - 1]->desc.M);
         if (int32_t rc = plan_fc(L, batch, path, dl, P.fc[i])) return rc;
+    }
+    if (path == CL_PATH_AUTO)
+        if (int32_t rc = choose_stack_paths(layers, n, batch, dl, P.fc)) return rc;
+    for (int i = 0; i < n; ++i) {
+        const cl_layer *L = layers[i];
         const int mine = P.fc[i].path, before = i > 0 ? P.fc[i - 1].path : 0;
-        // the finishing kernel of the layer before can write this layer's transposed
-        // activations itself when their row order is the plain one (128-column blocks,
-        // no ragged last block): 2-3 % of a step on the AlexNet-shaped stack
-        const bool plain_rows = L->desc.block_w == kTile && L->desc.K % kTile == 0;
         if (mine == CL_PATH_SPARSE_WIDE) {
             P.xt_bytes = std::max(P.xt_bytes, P.fc[i].wide.xt_bytes);
             P.part_bytes = std::max(P.part_bytes, round256(P.fc[i].wide.tile_bytes));
             P.ent_off[i] = P.ent_bytes;
             P.ent_bytes += round256(P.fc[i].wide.ent_bytes);
-            P.xt_in[i] = i > 0 && reads_xt(before) && plain_rows;
+            P.xt_in[i] = i > 0 && reads_xt(before) && plain_rows(L);
         } else if (is_mfma(mine)) {
             P.xt_bytes = std::max(P.xt_bytes, P.fc[i].mfma.xt_bytes);
             P.part_bytes = std::max(P.part_bytes, round256(P.fc[i].mfma.part_bytes));
-            P.xt_in[i] = i > 0 && plain_rows && (mine == CL_PATH_MFMA_F32 ? reads_xt(before) : before == CL_PATH_MFMA_BF16 && layers[i - 1]->desc.block_h % 4 == 0);
+            P.xt_in[i] = i > 0 && plain_rows(L) && (mine == CL_PATH_MFMA_F32 ? reads_xt(before) : before == CL_PATH_MFMA_BF16 && layers[i - 1]->desc.block_h % 4 == 0);
         } else {
             P.part_bytes = std::max(P.part_bytes, round256(P.fc[i].sparse.part_bytes));
             // (measured on the AlexNet-shaped stack: 39.8 -> 37.1 us at one image, no gain at

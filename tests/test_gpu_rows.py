@@ -155,3 +155,24 @@ def test_scratch_is_bounded(M, K, B):
         cl.compressed_fc_forward_static(L, Xd, out, bd, relu=True)
         assert_close(out.cpu().numpy()[:, rows], fc_ref(oW[rows], X, bias[rows]), True)
     L.free()
+
+
+def test_a_stack_chooses_its_paths_together():
+    """Where the first layer of a stack is on the wide path, the second hands and is handed its
+    activations and shares the decoding launch there: it stays on that path, which alone it would
+    leave for this kernel.  Bit for bit the chain of the paths named; all layers on this kernel at 64."""
+    import torch
+    from paper_1711_00244_amd import workloads as wl
+    layers = []
+    for li in range(3):
+        spec, W = wl.layer_weights(3, li)
+        layers.append(cl.compress_layer(W, spec.r, spec.k, 128, 128, upload=True))
+    for B, paths in ((64, [cl.PATH_SPARSE] * 3), (96, [cl.PATH_SPARSE_WIDE, cl.PATH_SPARSE_WIDE, cl.PATH_MFMA_F32]),
+                     (128, [cl.PATH_SPARSE_WIDE, cl.PATH_SPARSE_WIDE, cl.PATH_MFMA_F32])):
+        a = torch.from_numpy(wl.activations(3, B)).cuda()
+        Y = cl.compressed_fc_stack_forward(layers, a)
+        for li in range(3):
+            a = cl.compressed_fc_forward(layers[li], a, relu=li < 2, path=paths[li])
+        assert torch.equal(Y, a), B
+    for L in layers:
+        L.free()

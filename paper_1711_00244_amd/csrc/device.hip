@@ -740,7 +740,7 @@ struct FcPlan {
     int path = 0;
     bool have_wide = false, have_rows = false;      // left by the choice: wide, sparse.rows
     int no_rows = 0;                                // and the path it would be without fc_rows_kernel (0: it is not that kernel)
-    int64_t mfma_cost = 0;
+    int64_t mfma_cost = 0, rows_cost = 0;
     SparsePlan sparse;
     MfmaPlan mfma;
     WidePlan wide;
@@ -766,7 +766,8 @@ void choose_path(const cl_layer *L, int batch, int path, const DeviceLimits &dl,
         P.path = CL_PATH_SPARSE_WIDE;
     }
     P.have_rows = L->n_blocks >= kAutoRowsBlocks && plan_rows(L, batch, dl, P.sparse.rows);
-    if (P.have_rows && P.sparse.rows.cost < best + kAutoLaunch) {
+    P.rows_cost = P.sparse.rows.cost;
+    if (P.have_rows && P.rows_cost < best + kAutoLaunch) {
         P.no_rows = P.path;
         P.path = CL_PATH_SPARSE;
     }
@@ -1142,11 +1143,11 @@ bool plain_rows(const cl_layer *L) { return L->desc.block_w == kTile && L->desc.
 // 125, 114 and 136 without).
 constexpr int64_t kWideShared = 13000;          // the decoding launch's fixed part (plan_wide)
 
-int32_t choose_stack_paths(const cl_layer *const *layers, int n, int batch, const DeviceLimits &dl, std::vector<FcPlan> &fc)
+void choose_stack_paths(const cl_layer *const *layers, int n, int batch, const DeviceLimits &dl, std::vector<FcPlan> &fc)
 {
     bool some = false, others = false;
     for (const FcPlan &P : fc) (P.no_rows ? some : others) = true;
-    if (!some || !others) return CL_OK;
+    if (!some || !others) return;
     auto cost = [&](bool rows) {
         int64_t t = 0;
         bool wide = false, before = false;      // a wide layer yet; the layer before hands activations over
@@ -1154,7 +1155,7 @@ int32_t choose_stack_paths(const cl_layer *const *layers, int n, int batch, cons
             const FcPlan &P = fc[i];
             const int path = rows || !P.no_rows ? P.path : P.no_rows;
             const bool handed = before && plain_rows(layers[i]);
-            if (path == CL_PATH_SPARSE) t += P.no_rows ? P.sparse.rows.cost : 0;
+            if (path == CL_PATH_SPARSE) t += P.no_rows ? P.rows_cost : 0;
             else if (path == CL_PATH_SPARSE_WIDE) t += P.wide.cost - (wide ? kWideShared : 0) + (i > 0 && !handed ? kAutoLaunch : 0);
             else t += P.mfma_cost + (handed ? 0 : kAutoLaunch);
             wide = wide || path == CL_PATH_SPARSE_WIDE;
@@ -1162,13 +1163,13 @@ int32_t choose_stack_paths(const cl_layer *const *layers, int n, int batch, cons
         }
         return t;
     };
-    if (cost(true) <= cost(false)) return CL_OK;
+    if (cost(true) <= cost(false)) return;
     for (int i = 0; i < n; ++i)
         if (const int path = fc[i].no_rows) {
-            fc[i] = FcPlan{};
-            if (int32_t rc = plan_fc(layers[i], batch, path, dl, fc[i])) return rc;
+            FcPlan without;
+            if (plan_fc(layers[i], batch, path, dl, without) == CL_OK) fc[i] = without;
+            else clear_error();                 // (a layer that path does not fit: it stays)
         }
-    return CL_OK;
 }
 
 int32_t plan_stack(const cl_layer *const *layers, int n, int batch, int path, const DeviceLimits &dl, StackPlan &P)
@@ -1187,8 +1188,7 @@ int32_t plan_stack(const cl_layer *const *layers, int n, int batch, int path, co
             return fail(CL_EINVAL, "layer %d takes %d inputs, layer %d gives %d outputs", i, L->desc.K, i - 1, layers[i - 1]->desc.M);
         if (int32_t rc = plan_fc(L, batch, path, dl, P.fc[i])) return rc;
     }
-    if (path == CL_PATH_AUTO)
-        if (int32_t rc = choose_stack_paths(layers, n, batch, dl, P.fc)) return rc;
+    if (path == CL_PATH_AUTO) choose_stack_paths(layers, n, batch, dl, P.fc);
     for (int i = 0; i < n; ++i) {
         const cl_layer *L = layers[i];
         const int mine = P.fc[i].path, before = i > 0 ? P.fc[i - 1].path : 0;

@@ -129,7 +129,9 @@ typedef struct {
                             /*   large-batch path) and two lookup tables (16 B a     */
                             /*   block and chunk of the block with most; 2 B a row   */
                             /*   of a block), each left out above half the payload   */
-                            /*   and 1 MiB                                           */
+                            /*   and 1 MiB; with blocks of at most 256 rows 2 B a    */
+                            /*   record (where it starts in its block; 4 B with      */
+                            /*   blocks of more than 65536 cells)                    */
     int64_t lut_bytes;      /* decode tables derived at load time (not stored)       */
     int32_t val_max_len, idx_max_len;
 } cl_stats;

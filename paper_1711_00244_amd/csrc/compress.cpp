@@ -127,6 +127,8 @@ struct Scanner {
     const cl_layer *L;
     std::vector<uint32_t> vt, it;
     uint32_t vmask, imask;
+    uint16_t *pos16;                   // where the records' first positions go (one of the two, or neither)
+    uint32_t *pos32;
 
     // Decodes chunk c (records r0 .. r1 - 1, first position pos0 of a block of bwp columns and np
     // cells).  With cnt, surviving weights are counted per half and row (128 rows a half).
@@ -139,6 +141,8 @@ struct Scanner {
         for (uint64_t r = r0; r < r1; ++r) {
             const uint64_t w = L->records[r];
             const int n = (int)(w & 15u);
+            if (pos16) pos16[r] = (uint16_t)pos;
+            else if (pos32) pos32[r] = (uint32_t)pos;
             uint64_t vbuf = w >> kCountBits, ibuf = bit_reverse64(w);
             uint32_t vused = 0, iused = 0, flags = n < 1 ? kSlotBad : 0;
             for (int j = 0; j < n; ++j) {
@@ -289,8 +293,15 @@ int32_t finalize_and_validate(cl_layer *L, Team &team)
         if (L->block_ptr[b] == L->block_ptr[b + 1]) L->block_chunk[b] = L->block_chunk[b + 1];
 
     // ---- the records, block by block ----
+    L->rec_pos16.clear();
+    L->rec_pos32.clear();
+    if (d.block_h <= kPrivateTileRows) {
+        if ((int64_t)d.block_h * d.block_w <= 1 << 16) L->rec_pos16.resize((size_t)L->n_records);
+        else L->rec_pos32.resize((size_t)L->n_records);
+    }
     const Scanner scan{L, check_table(L->val_lut, L->val_len, true, 0), check_table(L->idx_lut, L->idx_len, false, nidx - 1),
-                       (1u << L->val_lut_bits) - 1u, (1u << L->idx_lut_bits) - 1u};
+                       (1u << L->val_lut_bits) - 1u, (1u << L->idx_lut_bits) - 1u,
+                       L->rec_pos16.empty() ? nullptr : L->rec_pos16.data(), L->rec_pos32.empty() ? nullptr : L->rec_pos32.data()};
     // the half-by-half order of the wide path (blocks of at most 128 x 128 only): per block, counts
     // first, list positions once the weights of all blocks before it are known
     constexpr int kGroups = 16, kPer = 2 * (kGroups + 1), kRows = 128;

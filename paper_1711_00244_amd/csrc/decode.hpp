@@ -32,6 +32,25 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v)
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
+// n / d for a divisor known on the host, in four scalar instructions (a division of uniform values the compiler
+// works out in vector registers, and takes what follows from it for different in every lane).  Granlund and
+// Montgomery's round-up method, exact for every 32-bit n.
+struct Divisor {
+    uint32_t mul, shift, d;
+    __device__ __forceinline__ uint32_t quotient(uint32_t n) const
+    {
+        const uint32_t t = __umulhi(n, mul);
+        return (t + ((n - t) >> (shift > 0 ? 1 : 0))) >> (shift > 0 ? shift - 1 : 0);
+    }
+};
+
+static Divisor divisor(uint32_t d)
+{
+    uint32_t s = 0;
+    while (s < 32 && (1ull << s) < d) ++s;
+    return Divisor{(uint32_t)((((1ull << s) - d) << 32) / d + 1), s, d};
+}
+
 // W consecutive floats (W * 4-byte aligned) with one load.
 template <int W> __device__ __forceinline__ void load_floats(const float *p, float *dst)
 {
@@ -152,13 +171,21 @@ __device__ __forceinline__ void decode_from(LaneRecord &rec, const Tables &T, Sy
 // touching the tables again.  The pass is written out for the fifteen possible entries
 // (it ends after the wavefront's longest record), so every byte position is a constant.
 // All lanes of the wavefront must be active.
-__device__ __forceinline__ Symbols decode_record(LaneRecord rec, const Tables &T)
+// (decode_symbols leaves what lies past a lane's own entries, and their sum, open: for a caller that
+// heeds only its own and knows where the record starts.)
+__device__ __forceinline__ Symbols decode_symbols(LaneRecord rec, const Tables &T)
 {
     Symbols y{{0, 0, 0, 0}, {0, 0, 0, 0}, rec.n, wave_max(rec.n), 0};
     // (the masks in vector registers: an and-or takes one scalar operand)
     Tables V = T;
     asm("" : "+v"(V.vmask), "+v"(V.imask));
     decode_from<0>(rec, V, y);
+    return y;
+}
+
+__device__ __forceinline__ Symbols decode_record(LaneRecord rec, const Tables &T)
+{
+    Symbols y = decode_symbols(rec, T);
     // clear the bytes of entries a lane does not have: word w keeps its first
     // clamp(n - 4 w, 0, 4) bytes (the shift by 8 bits per byte is done in two halves,
     // so that four bytes shift everything out)
@@ -290,16 +317,22 @@ struct BlockGeom {
     int shift;        // log2(bwp) when bwp is a power of two, else -1
 };
 
-__device__ __forceinline__ BlockGeom block_geom(const LayerDev &L, uint32_t b)
+// block `bcol` of block row `brow`
+__device__ __forceinline__ BlockGeom block_geom(const LayerDev &L, int brow, int bcol)
 {
     BlockGeom g;
-    const int brow = (int)(b / (uint32_t)L.nbw);
     g.row_id = brow * L.bh;
-    g.col_id = (int)(b - (uint32_t)brow * (uint32_t)L.nbw) * L.bw;
+    g.col_id = bcol * L.bw;
     g.bhp = min(L.bh, L.M - g.row_id);
     g.bwp = min(L.bw, L.K - g.col_id);
     g.shift = (g.bwp & (g.bwp - 1)) == 0 ? (31 - __builtin_clz((uint32_t)g.bwp)) : -1;
     return g;
+}
+
+__device__ __forceinline__ BlockGeom block_geom(const LayerDev &L, uint32_t b)
+{
+    const int brow = (int)(b / (uint32_t)L.nbw);
+    return block_geom(L, brow, (int)(b - (uint32_t)brow * (uint32_t)L.nbw));
 }
 
 // Position inside a block -> (row, column) offsets; a block is flattened row by
@@ -359,10 +392,8 @@ __device__ __forceinline__ TableRegs fetch_tables(const LayerDev &L)
     TableRegs t;
     const uint4 *g = L.tables;
 #pragma unroll
-    for (int k = 0; k < kTableRows; ++k) {
-        const int i = (int)threadIdx.x + k * kThreads;
-        t.row[k] = i < L.table_rows ? g[i] : uint4{0, 0, 0, 0};
-    }
+    // (past the last row: that one again, not stored)
+    for (int k = 0; k < kTableRows; ++k) t.row[k] = g[min((int)threadIdx.x + k * kThreads, L.table_rows - 1)];
     return t;
 }
 

@@ -62,10 +62,12 @@ struct LayerDev {
     const uint32_t *chunk_half;          // null unless the blocks are at most 128 x 128 (with group_ptr)
     const uint32_t *group_ptr;
     const uint16_t *row_ptr;
+    const void *rec_pos;                 // null unless the small-batch kernel's wavefronts have tiles of their own
     const float *codebook;
     const uint4 *tables;                 // both decode tables and the codebook as they lie in LDS (carve)
     int M, K, bh, bw, nbw;
     int val_bits, idx_bits, ncode;       // index widths of the decode tables, codebook entries
+    int pos32;                           // rec_pos has 32 bits a record, not 16
     int block_slots, row_ptrs;           // slots of a block in `slot`, entries of a block in row_ptr
     int table_rows;                      // 16-byte rows of the table image (tables + codebook)
     uint32_t n_chunks;
@@ -94,6 +96,8 @@ static LayerDev make_dev(const cl_layer *L)
     d.group_ptr = L->dev.group_ptr;
     d.codebook = L->dev.codebook;
     d.row_ptr = L->dev.row_ptr;
+    d.rec_pos = L->dev.rec_pos;
+    d.pos32 = L->rec_pos32.empty() ? 0 : 1;
     d.tables = (const uint4 *)L->dev.tables;
     d.M = L->desc.M;
     d.K = L->desc.K;
@@ -259,7 +263,7 @@ try {
         std::memcpy(image.data() + (values_first ? vb : 0), L->idx_lut.data(), ib);
         std::memcpy(image.data() + ((vb + ib + 15) & ~(size_t)15), L->codebook.data(), L->codebook.size() * 4);
     }
-    Sec secs[10] = {
+    Sec secs[12] = {
         {L->records.data(), L->records.size() * 8, 0},
         {L->meta.data(), L->meta.size() * sizeof(cl_chunk_meta), 0},
         {L->block_ptr.data(), L->block_ptr.size() * 4, 0},
@@ -270,6 +274,8 @@ try {
         {L->chunk_half.data(), L->chunk_half.size() * 4, 0},
         {L->group_ptr.data(), L->group_ptr.size() * 4, 0},
         {L->row_ptr.data(), L->row_ptr.size() * 2, 0},
+        {L->rec_pos16.data(), L->rec_pos16.size() * 2, 0},
+        {L->rec_pos32.data(), L->rec_pos32.size() * 4, 0},
     };
     size_t total = 0;
     for (auto &s : secs) { s.off = total; total += (s.bytes + 255) / 256 * 256; }
@@ -295,6 +301,7 @@ try {
     L->dev.chunk_half = L->group_ptr.empty() ? nullptr : (const uint32_t *)(blob + secs[7].off);
     L->dev.group_ptr = L->group_ptr.empty() ? nullptr : (const uint32_t *)(blob + secs[8].off);
     L->dev.row_ptr = L->row_ptr.empty() ? nullptr : (const uint16_t *)(blob + secs[9].off);
+    L->dev.rec_pos = !L->rec_pos16.empty() ? blob + secs[10].off : !L->rec_pos32.empty() ? blob + secs[11].off : nullptr;
     L->dev.tables = blob + secs[4].off;
     L->dev.codebook = (const float *)(blob + secs[4].off + ((L->val_lut.size() + L->idx_lut.size()) * sizeof(lut_t) + 15) / 16 * 16);
     clear_error();
@@ -891,7 +898,7 @@ static int32_t forward_sparse(const cl_layer *L, const LayerDev &D, const Sparse
     do {                                                                                                           \
         if (lds > 64 * 1024)                                                                                       \
             HIP_TRY(hipFuncSetAttribute((const void *)fc_sparse_kernel<BTV, FOLDV>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)); \
-        hipLaunchKernelGGL((fc_sparse_kernel<BTV, FOLDV>), grid, dim3(kThreads), lds, st, D, x, part, P.wg_per_panel, xcap, from, nb); \
+        hipLaunchKernelGGL((fc_sparse_kernel<BTV, FOLDV>), grid, dim3(kThreads), lds, st, D, x, part, divisor((uint32_t)P.wg_per_panel), xcap, from, nb); \
     } while (0)
             switch (bt) {
             case 16: CL_LAUNCH_SPARSE(16, false); break;
@@ -1452,8 +1459,8 @@ extern "C" int32_t cl_compressed_fc_group_forward(const cl_layer_group *G, const
     do {                                                                                                            \
         if (P.lds > 64 * 1024)                                                                                      \
             HIP_TRY(hipFuncSetAttribute((const void *)fc_sparse_group_kernel<BTV>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)P.lds)); \
-        hipLaunchKernelGGL(fc_sparse_group_kernel<BTV>, grid, dim3(kThreads), P.lds, st, G->table, P.wgs_per_layer, d_X, x_stride, part, \
-                           P.part_stride, P.sp.wg_per_panel, P.xcap);                                               \
+        hipLaunchKernelGGL(fc_sparse_group_kernel<BTV>, grid, dim3(kThreads), P.lds, st, G->table, divisor(P.wgs_per_layer), d_X, x_stride, part, \
+                           P.part_stride, divisor((uint32_t)P.sp.wg_per_panel), P.xcap);                                               \
     } while (0)
         switch (bt) {
         case 16: CL_LAUNCH_GROUP(16); break;

@@ -10,6 +10,7 @@ namespace cl {
 
 constexpr int kLanes = CL_RECORDS_PER_CHUNK;        // one 64-bit record per lane of a wavefront
 constexpr int kCountBits = 4;                       // width of a record's entry-count field
+constexpr int kPrivateTileRows = 256;               // block rows up to which a wavefront of the small-batch kernel has an output tile of its own
 
 int32_t fail(int32_t code, const char *fmt, ...) noexcept;
 void clear_error() noexcept;
@@ -45,6 +46,7 @@ struct DeviceImage {
     const uint32_t *group_ptr = nullptr;
     const float *codebook = nullptr;
     const uint16_t *row_ptr = nullptr;
+    const void *rec_pos = nullptr;
     const void *tables = nullptr;      // decode tables and codebook, laid out as in LDS
 };
 
@@ -87,6 +89,10 @@ struct cl_layer {
                                                     //   number, so that a block's begin at a whole word
     std::vector<cl_chunk_meta> meta;                // n_chunks + 1
     std::vector<uint64_t> records;
+    // For layers with blocks of at most kPrivateTileRows rows: sum of (z + 1) over a block's entries before each of its
+    // records, which is where the small-batch kernel starts a lane; one of the two, by the block's number of cells (derived).
+    std::vector<uint16_t> rec_pos16;
+    std::vector<uint32_t> rec_pos32;
     std::vector<cl::lut_t> val_lut, idx_lut;        // indexed by the next val_lut_bits / idx_lut_bits stream bits
     int val_lut_bits = 1, idx_lut_bits = 1;         // longest codeword of each code
     cl::DeviceImage dev;

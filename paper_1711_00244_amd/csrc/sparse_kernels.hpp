@@ -180,7 +180,7 @@ struct PrevSlots {
 // batch kernel has an output tile of its own in LDS and writes each row sum once, with a
 // plain store (see fc_sparse_body); above, the workgroup shares one tile through float atomics
 // (8 x bh x BT floats would crowd the CU, and those batch sizes belong to the tile kernels).
-constexpr int kPrivateTileBT = 8, kPrivateTileRows = 256;
+constexpr int kPrivateTileBT = 8;
 __host__ __device__ constexpr bool private_tiles(int bh, int bt) { return bt <= kPrivateTileBT && bh <= kPrivateTileRows; }
 
 // Where a column's BT images lie in the LDS slab: as 16-byte groups of four, and for BT > 4 the
@@ -221,17 +221,57 @@ __device__ __forceinline__ void wave_segmented_sums(float (&v)[BT], bool start)
 #undef CL_SEG_STEP
 }
 
+// An entry of a record on its way to its row's sum: looked up, not yet waited for.
+template <int BT> struct Pending {
+    float w, x[BT];
+    uint32_t row;
+};
+
+// A record decoded and used in one pass: entry after entry, both codeword streams side by side.  The position of an
+// entry is where the record starts (a table, counted when the layer was loaded) plus what the entries before
+// it advance, so an entry is looked up - its weight, its column's activations - as soon as it is
+// decoded, and used one entry later, while the next one's table reads are on their way.
+// at: the position of the entry before (the record's start less one); in SHIFTED form it is in the bits from 8 up:
+// a table entry has its symbol in the second byte and its length below, and added up as they are, with 256 per
+// entry, they move the position on (fifteen lengths of at most twelve bits do not reach bit 8).  Every lane goes on
+// to the wavefront's longest record; use(entry number, entry) is for the lane's own entries to heed.
+template <int BT, bool SHIFTED, class Look, class Use>
+__device__ __forceinline__ void entries_in_one_pass(LaneRecord &rec, const Tables &T, uint32_t nmax, uint32_t at, Look look, Use use)
+{
+    auto next = [&](Pending<BT> &e) {
+        const uint32_t ez = next_entry(rec.ibuf, T.ibase, T.imask);
+        const uint32_t ev = next_entry(rec.vbuf, T.vbase, T.vmask);
+        at += SHIFTED ? ez + 256u : (ez >> 8) + 1u;
+        look(at, ev, e);
+    };
+    Pending<BT> a, b;                                       // (two take turns: nothing is moved)
+    uint32_t j = 0;
+    next(a);
+#pragma unroll 1
+    for (; j + 2 < nmax; j += 2) {                          // uniform
+        next(b);
+        use(j, a);
+        next(a);
+        use(j + 1, b);
+    }
+    if (j + 1 < nmax) {
+        next(b);
+        use(j, a);
+        use(j + 1, b);
+    } else use(j, a);
+}
+
 // (wg: the workgroup's number within the layer's share of the grid; nb <= BT: images that X
 // holds - the tile's other images are zeros; FOLD: the input may be the partial tiles of the
 // layer before - an instantiation of its own, so that the code for it does not weigh on the
-// registers of the others)
-template <int BT, bool FOLD>
-__device__ __forceinline__ void fc_sparse_body(const LayerDev &L, const float *__restrict__ X, float *part, int wg_per_panel,
+// registers of the others; ONE_PASS: see entries_private)
+template <int BT, bool FOLD, bool ONE_PASS>
+__device__ __forceinline__ void fc_sparse_body(const LayerDev &L, const float *__restrict__ X, float *part, const Divisor &wg_per_panel,
                                                int xcap, const PrevSlots &prev, uint32_t wg, int nb)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem_raw[];
     const Smem s = carve(smem_raw, L);
-    const int p = (int)(wg / (uint32_t)wg_per_panel), j = (int)(wg % (uint32_t)wg_per_panel);
+    const int p = (int)wg_per_panel.quotient(wg), j = (int)(wg - (uint32_t)p * wg_per_panel.d);
     const uint32_t pc1 = L.panel_chunk[p + 1];
     const uint32_t my0 = L.panel_chunk[p] + (uint32_t)j * (kWaves * kSparseChunksPerWave);
     if (my0 >= pc1) return;
@@ -242,19 +282,25 @@ __device__ __forceinline__ void fc_sparse_body(const LayerDev &L, const float *_
     bool have[kSparseChunksPerWave];
     ChunkHead h[kSparseChunksPerWave];
     LaneRecord rec[kSparseChunksPerWave];
+    uint32_t rec_pos[kSparseChunksPerWave];
+    const bool priv = private_tiles(L.bh, BT);
 #pragma unroll
     for (int i = 0; i < kSparseChunksPerWave; ++i) {
         const uint32_t c = my0 + (uint32_t)(i * kWaves + wave);
         have[i] = c < pc1;
         h[i] = ChunkHead{};
         rec[i] = LaneRecord{};
+        rec_pos[i] = 0;
         if (have[i]) {
             h[i] = load_head(L, c);
             rec[i] = load_record(L, h[i], lane);
+            if (priv && (uint32_t)lane < h[i].nrec) {
+                const size_t r = (size_t)h[i].m.rec_off + lane;
+                rec_pos[i] = L.pos32 ? ((const uint32_t *)L.rec_pos)[r] : ((const uint16_t *)L.rec_pos)[r];
+            }
         }
     }
     const TableRegs tr = fetch_tables(L);
-    const bool priv = private_tiles(L.bh, BT);
     const int n_tiles = priv ? kWaves : 1;
     float *ytile = s.extra;                  // [n_tiles][BT][bh]
     float *xs = ytile + (size_t)n_tiles * L.bh * BT;   // [xcap][BT]: a column's BT images side by side, one LDS read per entry
@@ -318,15 +364,15 @@ __device__ __forceinline__ void fc_sparse_body(const LayerDev &L, const float *_
 #pragma unroll
     for (int i = 0; i < kSparseChunksPerWave; ++i) {
         if (!have[i]) continue;
-        const Symbols y = decode_record(rec[i], s.T);
-        const LaneStart st = lane_starts(y, h[i].m.pos0);
-        const BlockGeom g = block_geom(L, h[i].m.blk);
+        const BlockGeom g = block_geom(L, p, (int)(h[i].m.blk - pb0));
         // The entries of the record in order, in every lane up to the wavefront's longest
         // record: a lane past its own entries multiplies codebook entry 0 with a column
         // of the block.  The instantiations differ in where the activations come from
         // (LDS stays LDS: no generic pointers) and in how a position splits into row and
         // column (shift and mask for a power-of-two block width).
         auto entries_shared = [&](auto load_x, auto split) {
+            const Symbols y = decode_record(rec[i], s.T);
+            const LaneStart st = lane_starts(y, h[i].m.pos0);
             uint32_t cur = 0;
             float acc[BT];
 #pragma unroll
@@ -359,18 +405,11 @@ __device__ __forceinline__ void fc_sparse_body(const LayerDev &L, const float *_
         // have nothing but that row is summed with a segmented scan - the row is then stored
         // once, by the lane where it ends.  No two lanes store the same row, and the tile
         // receives this chunk only, so plain stores do.
-        auto entries_private = [&](auto load_x, auto split) {
+        auto entries_private = [&](auto shifted, auto load_x, auto split) {
             static_assert(kSparseChunksPerWave == 1, "a wavefront's tile takes one chunk: plain stores");
             constexpr uint32_t kNone = 0xffffffffu;
             float *tile = ytile + (size_t)wave * L.bh * BT;
-            // the lane's first row is that of its first entry (kNone for a lane without a record)
-            uint32_t first_row = kNone;
-            if (y.n > 0) {
-                uint32_t unused;
-                split(st.sum + (y.z[0] & 0xffu), first_row, unused);
-            }
-            uint32_t cur = first_row;
-            bool several = false;                       // the lane has left its first row
+            uint32_t first_row = kNone, cur = kNone;    // the rows of the lane's first entry and of its last so far (kNone: no record)
             float acc[BT], head[BT];
 #pragma unroll
             for (int b = 0; b < BT; ++b) acc[b] = head[b] = 0.0f;
@@ -380,8 +419,9 @@ __device__ __forceinline__ void fc_sparse_body(const LayerDev &L, const float *_
             // that one is read back after the loop and written over with the sum over all its
             // lanes (one image: 33.9 -> 32.5 us per step of the
             // AlexNet-shaped stack; four images: 42.2 -> 43.2, so not there).
-            auto enter_row = [&](uint32_t r) {
-                if (r != cur) {
+            auto use = [&](const Pending<BT> &e) {
+                if (e.row != cur) {
+                    const bool several = cur != first_row;          // the lane had left its first row before
                     if (BT <= 2 || several) {
 #pragma unroll
                         for (int b = 0; b < BT; ++b) tile[b * L.bh + cur] = acc[b];
@@ -391,39 +431,53 @@ __device__ __forceinline__ void fc_sparse_body(const LayerDev &L, const float *_
                         if (BT > 2) head[b] = several ? head[b] : acc[b];
                         acc[b] = 0.0f;
                     }
-                    several = true;
-                    cur = r;
+                    cur = e.row;
                 }
+#pragma unroll
+                for (int b = 0; b < BT; ++b) acc[b] += e.w * e.x[b];
             };
-            constexpr int G = BT <= 2 || BT > 8 ? 1 : 3;
-            if constexpr (G == 1) {
-                for_each_entry<false>(y, st.sum, [&](uint32_t, uint32_t v, uint32_t, uint32_t pos) {
-                    uint32_t r, cc;
-                    split(pos, r, cc);
-                    enter_row(r);
-                    const float w = s.T.cb[v];
-                    float x[BT];
-                    load_x((int)cc, x);
-#pragma unroll
-                    for (int b = 0; b < BT; ++b) acc[b] += w * x[b];
-                });
-            } else {
-                // the codebook and activation reads of G entries go out together: the row logic
-                // is all branches, behind which the compiler leaves each read where it is used
-                uint32_t rows[G];
-                float ws[G], xv[G][BT];
-                for_each_entry_grouped<G>(y, st.sum, [&](int u, uint32_t v, uint32_t pos) {
+            // In one pass, but for a layer of its own at eight images: there a wavefront's time is the latency of its reads, of
+            // which one entry at a time (32 bytes of activations) is not enough to hide it, and a pass that decodes and one that
+            // takes three entries at a time are a little shorter; where many layers share the grid, instructions bound
+            // it (us a call, before / one pass / two passes: FC 4096 x 9216 at eight images 23.5 / 24.7 / 23.1, AlexNet-shaped
+            // stack at eight 49.9 / 51.9 / 49.7, at four 41.0 / 37.0 / -, at one 31.5 / 28.6 / -; sixteen layers of
+            // 4096 x 4096 in one grid at one image 59.7 / 50.2 / -, at four 80.3 / 66.2 / -, at eight 124.1 / 121.3 / 129.8).
+            if constexpr (ONE_PASS) {
+                const uint32_t n = rec[i].n;
+                bool first = true;                          // no entry looked up yet
+                auto look = [&](uint32_t at, uint32_t ev, Pending<BT> &e) {
                     uint32_t cc;
-                    split(pos, rows[u], cc);
-                    ws[u] = s.T.cb[v];
-                    load_x((int)cc, xv[u]);
-                }, [&](int u) {
-                    enter_row(rows[u]);
-#pragma unroll
-                    for (int b = 0; b < BT; ++b) acc[b] += ws[u] * xv[u][b];
-                });
+                    split(at, e.row, cc);
+                    e.w = *(const float *)((const char *)s.T.cb + (ev >> 6));       // (lengths are below 64: the symbol's word)
+                    if (first) first_row = cur = n > 0 ? e.row : kNone;
+                    first = false;
+                    load_x((int)cc, e.x);
+                };
+                Tables V = s.T;                             // (the masks in vector registers: an and-or takes one scalar operand)
+                asm("" : "+v"(V.vmask), "+v"(V.imask));
+                entries_in_one_pass<BT, shifted>(rec[i], V, wave_max(n), (rec_pos[i] - 1u) << (shifted ? 8 : 0), look,
+                                                 [&](uint32_t j, const Pending<BT> &e) { if (j < n) use(e); });
+            } else {
+                const Symbols y = decode_symbols(rec[i], s.T);
+                auto split_at = [&](uint32_t pos, uint32_t &r, uint32_t &cc) { split(shifted ? pos << 8 : pos, r, cc); };
+                if (y.n > 0) {
+                    uint32_t unused;
+                    split_at(rec_pos[i] + (y.z[0] & 0xffu), first_row, unused);
+                    cur = first_row;
+                }
+                // the codebook and activation reads of three entries go out together: the row logic
+                // is all branches, behind which the compiler leaves each read where it is used
+                constexpr int G = 3;
+                Pending<BT> e[G];
+                for_each_entry_grouped<G>(y, rec_pos[i], [&](int u, uint32_t v, uint32_t pos) {
+                    uint32_t cc;
+                    split_at(pos, e[u].row, cc);
+                    e[u].w = s.T.cb[v];
+                    load_x((int)cc, e[u].x);
+                }, [&](int u) { use(e[u]); });
             }
             // cur: the lane's last row (kNone for a lane without a record), acc its sum so far
+            const bool several = cur != first_row;
             // (every lane takes part in the exchange: a lane that sat it out would hand its
             // neighbour a zero)
             const uint32_t from_prev = (uint32_t)__shfl_up((int)cur, 1), from_next = (uint32_t)__shfl_down((int)first_row, 1);
@@ -446,22 +500,16 @@ __device__ __forceinline__ void fc_sparse_body(const LayerDev &L, const float *_
                 for (int b = 0; b < BT; ++b) tile[b * L.bh + cur] = acc[b];
             }
         };
-        auto entries = [&](auto load_x, auto split) {
-            if (priv) entries_private(load_x, split);
-            else entries_shared(load_x, split);
-        };
         auto with_split = [&](auto load_x) {
-            if (g.shift >= 0 && priv) {
-                // (rows are used for a lane's own entries only here, and those lie inside the block:
-                // checked when the layer was loaded)
-                const uint32_t sh = (uint32_t)g.shift, cmask = (uint32_t)g.bwp - 1u;
-                entries_private(load_x, [&](uint32_t pos, uint32_t &r, uint32_t &cc) { r = pos >> sh; cc = pos & cmask; });
-            } else if (g.shift >= 0) {
-                const uint32_t sh = (uint32_t)g.shift, cmask = (uint32_t)g.bwp - 1u, rmax = (uint32_t)g.bhp - 1u;
-                entries(load_x, [&](uint32_t pos, uint32_t &r, uint32_t &cc) { r = min(pos >> sh, rmax); cc = pos & cmask; });
-            } else {
-                entries(load_x, [&](uint32_t pos, uint32_t &r, uint32_t &cc) { split_pos(pos, g, r, cc); });
-            }
+            const uint32_t sh = (uint32_t)g.shift, cmask = (uint32_t)g.bwp - 1u, rmax = (uint32_t)g.bhp - 1u;
+            // (rows are used for a lane's own entries only in one pass, and those lie inside the block: checked when the
+            // layer was loaded)
+            if (priv && L.pos32) entries_private(std::false_type{}, load_x, [&](uint32_t pos, uint32_t &r, uint32_t &cc) { split_pos(pos, g, r, cc); });
+            else if (priv && g.shift >= 0)
+                entries_private(std::true_type{}, load_x, [&](uint32_t at, uint32_t &r, uint32_t &cc) { r = at >> (8u + sh); cc = __builtin_amdgcn_ubfe(at, 8u, sh); });
+            else if (priv) entries_private(std::true_type{}, load_x, [&](uint32_t at, uint32_t &r, uint32_t &cc) { split_pos(at >> 8, g, r, cc); });
+            else if (g.shift >= 0) entries_shared(load_x, [&](uint32_t pos, uint32_t &r, uint32_t &cc) { r = min(pos >> sh, rmax); cc = pos & cmask; });
+            else entries_shared(load_x, [&](uint32_t pos, uint32_t &r, uint32_t &cc) { split_pos(pos, g, r, cc); });
         };
         if (slab) {
             const int xoff = g.col_id - col_a;
@@ -504,9 +552,10 @@ __device__ __forceinline__ void fc_sparse_body(const LayerDev &L, const float *_
 
 template <int BT, bool FOLD>
 __global__ __launch_bounds__(kThreads) void fc_sparse_kernel(LayerDev L, const float *__restrict__ X, float *part,
-                                                             int wg_per_panel, int xcap, PrevSlots prev, int nb)
+                                                             Divisor wg_per_panel, int xcap, PrevSlots prev, int nb)
 {
-    fc_sparse_body<BT, FOLD>(L, X, part, wg_per_panel, xcap, prev, blockIdx.x, nb);
+    constexpr bool kOnePass = BT <= 4;
+    fc_sparse_body<BT, FOLD, kOnePass>(L, X, part, wg_per_panel, xcap, prev, blockIdx.x, nb);
 }
 
 // Several layers of one shape in one grid (the same layer of several models, or layers
@@ -514,13 +563,13 @@ __global__ __launch_bounds__(kThreads) void fc_sparse_kernel(LayerDev L, const f
 // wgs_per_layer (i + 1) - 1 do layer i's share of Algorithm 2, from its own input
 // (x_stride floats apart; 0: one input for all) into its own partial tiles.
 template <int BT>
-__global__ __launch_bounds__(kThreads) void fc_sparse_group_kernel(const LayerDev *__restrict__ table, uint32_t wgs_per_layer,
+__global__ __launch_bounds__(kThreads) void fc_sparse_group_kernel(const LayerDev *__restrict__ table, Divisor wgs_per_layer,
                                                                    const float *__restrict__ X, size_t x_stride, float *part,
-                                                                   size_t part_stride, int wg_per_panel, int xcap)
+                                                                   size_t part_stride, Divisor wg_per_panel, int xcap)
 {
-    const uint32_t job = blockIdx.x / wgs_per_layer, wg = blockIdx.x - job * wgs_per_layer;
+    const uint32_t job = wgs_per_layer.quotient(blockIdx.x), wg = blockIdx.x - job * wgs_per_layer.d;
     const LayerDev L = table[job];
-    fc_sparse_body<BT, false>(L, X + job * x_stride, part + job * part_stride, wg_per_panel, xcap,
+    fc_sparse_body<BT, false, true>(L, X + job * x_stride, part + job * part_stride, wg_per_panel, xcap,
                        PrevSlots{nullptr, nullptr, nullptr, 1, 0, 0, 0}, wg, BT);
 }
 
@@ -536,7 +585,7 @@ __device__ __forceinline__ void fc_reduce_body(const LayerDev &L, const float *_
                                                float *Y, int B, int part_b, int wg_per_panel, int relu, int wg)
 {
     __shared__ float slice_sum[kRedThreads];
-    const int p = wg / B, b = wg - p * B;
+    const int p = __builtin_amdgcn_readfirstlane(wg / B), b = wg - p * B;       // (uniform: said so, or its table entries come by vector loads)
     const int row_id = p * L.bh;
     const int bhp = min(L.bh, L.M - row_id);
     // the sparse kernel fills one slot per workgroup's worth of chunks of the block row
@@ -594,7 +643,7 @@ __global__ __launch_bounds__(kRedThreads) void fc_reduce_group_kernel(const Laye
                                                                       const float *__restrict__ bias, size_t bias_stride, float *Y,
                                                                       size_t y_stride, int B, int wg_per_panel, int relu)
 {
-    const int job = (int)blockIdx.x / wgs_per_layer, wg = (int)blockIdx.x - job * wgs_per_layer;
+    const int job = __builtin_amdgcn_readfirstlane((int)blockIdx.x / wgs_per_layer), wg = (int)blockIdx.x - job * wgs_per_layer;
     const LayerDev L = table[job];
     fc_reduce_body(L, part + job * part_stride, bias ? bias + job * bias_stride : nullptr, Y + job * y_stride, B, B, wg_per_panel, relu,
                    wg);

@@ -40,3 +40,14 @@ def test_decode_blocks(M, K, bh, bw, d, r, k):
             assert (got[:at] == 0xA5).all() and (got[at + size:] == 0xA5).all()
             np.testing.assert_array_equal(got[at:at + size], want[which].reshape(-1).view(np.uint8))
     L.free()
+
+
+def test_dense_matrix_past_the_caches():
+    """A dense matrix of more than 64 MiB (written past the caches), ragged blocks on both edges."""
+    rng = np.random.default_rng(64)
+    W = rand_pruned(rng, 4133, 4148, 0.01)
+    L = cl.compress_layer(W, 5, 4, 128, 128, upload=True)
+    dense = cl.decode_layer(L)[3].cpu().numpy()
+    assert dense.nbytes > 64 << 20
+    np.testing.assert_array_equal(dense, oracle.dense_weights(oracle.compress_layer(W, 5, 4, 128, 128)))
+    L.free()

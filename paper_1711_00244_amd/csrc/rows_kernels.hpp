@@ -122,22 +122,37 @@ __global__ __launch_bounds__(kRowsThreads) void fc_rows_kernel(LayerDev L, const
     ChunkSlot ch{};
     uint64_t rec = 0;
     int ch_blk = 0, ch_i = 0;                   // the chunk's block (of the block row) and its number within the group
+    auto slot_of = [&](int ph, int i) {
+        const int b0 = blk_lo + ph * G;
+        int g = 0;
+#pragma unroll
+        for (int q = 1; q < G; ++q) g += i >= q * slots ? 1 : 0;
+        ch_blk = b0 + g;
+        return L.slot[(size_t)(pb0 + (uint32_t)b0) * (uint32_t)slots + (uint32_t)i];
+    };
+    auto slots_of = [&](int ph) { return ph < phases ? min(G, blk_hi - (blk_lo + ph * G)) * slots : 0; };
     auto fetch_chunk = [&](int ph) {            // the next chunk with records from ch_i on, if any
-        const int b0 = blk_lo + ph * G, n = ph < phases ? min(G, blk_hi - b0) * slots : 0;
+        const int n = slots_of(ph);
         ch.nrec = 0;
         for (; ch_i < n; ch_i += NW) {
-            int g = 0;
-#pragma unroll
-            for (int q = 1; q < G; ++q) g += ch_i >= q * slots ? 1 : 0;
-            ch_blk = b0 + g;
-            ch = L.slot[(size_t)(pb0 + (uint32_t)b0) * (uint32_t)slots + (uint32_t)ch_i];
+            ch = slot_of(ph, ch_i);
             if (ch.nrec != 0) break;
         }
         if (ch.nrec != 0) rec = (uint32_t)lane < ch.nrec ? L.records[(size_t)ch.rec_off + lane] : 0ull;
     };
-    auto first_chunk = [&](int ph) {
+    // The first chunk of a group is asked for in two steps, so that neither waits: its slot, and
+    // some thousand cycles later (the products of a group) its record.
+    auto first_slot = [&](int ph) {
         ch_i = (wave + 4 * ph) & (NW - 1);
-        fetch_chunk(ph);
+        ch.nrec = 0;
+        if (ch_i < slots_of(ph)) ch = slot_of(ph, ch_i);
+    };
+    auto first_record = [&](int ph) {
+        if (ch.nrec != 0) rec = (uint32_t)lane < ch.nrec ? L.records[(size_t)ch.rec_off + lane] : 0ull;
+        else if (ch_i < slots_of(ph)) {
+            ch_i += NW;
+            fetch_chunk(ph);
+        }
     };
     auto decode = [&](int ph) {
         const Symbols y = decode_record(split_record(rec, (uint32_t)rec & 15u), s.T);
@@ -180,7 +195,6 @@ __global__ __launch_bounds__(kRowsThreads) void fc_rows_kernel(LayerDev L, const
     typedef float f4 __attribute__((ext_vector_type(4)));
     typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
     f4 stage[kPieces];
-    const bool ragged = L.nbw * L.bw > L.K || L.bw < kTile;           // (a fetch may run past the end of an image)
     auto piece = [&](int i, int &g, int &img, int &col) {
         const int t = (wave + i * NW) * 4;                              // four 16-byte columns, sixteen images per wavefront
         const int c = t & (kTile / 4 - 1), q = t / (kTile / 4);
@@ -190,14 +204,33 @@ __global__ __launch_bounds__(kRowsThreads) void fc_rows_kernel(LayerDev L, const
     };
     // (images past the batch read the last one: their sums are dropped; columns a block does not
     // have read the next block's or the row's last: no list names them)
+    // Where a lane's pieces lie does not change from group to group but for the first column, which all lanes share:
+    // a load takes that as its scalar offset, and a lane's own one, in bytes, is worked out here once.
+    const bool near = (uint64_t)kImages * (uint64_t)L.K < (uint64_t)1 << 29;        // a tile's images within a buffer's offsets
+    const __amdgpu_buffer_rsrc_t images = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(X + (size_t)img0 * L.K), 0, near ? (int)((uint32_t)min(kImages, B - img0) * (uint32_t)L.K * (uint32_t)sizeof(float)) : 0, 0x00020000);
+    uint32_t piece_off[kPieces];
+#pragma unroll
+    for (int i = 0; i < kPieces; ++i) {
+        int g, img, col;
+        piece(i, g, img, col);
+        piece_off[i] = ((uint32_t)(min(img0 + img, B - 1) - img0) * (uint32_t)L.K + (uint32_t)(min(g, G - 1) * L.bw + col)) * (uint32_t)sizeof(float);
+    }
     auto slab_fetch = [&](int ph) {
+        const int k0 = (blk_lo + ph * G) * L.bw;                        // uniform
+        if (near && k0 + (G - 1) * L.bw + kTile <= L.K) {
+#pragma unroll
+            for (int i = 0; i < kPieces; ++i)
+                stage[i] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(images, (int)piece_off[i], k0 * (int)sizeof(float), 0));
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < kPieces; ++i) {
             int g, img, col;
             piece(i, g, img, col);
             const int k = min(blk_lo + ph * G + g, L.nbw - 1) * L.bw + col;
             const float *row = X + (size_t)min(img0 + img, B - 1) * L.K;
-            if (!ragged || k + 4 <= L.K) stage[i] = *(const f4u *)(row + k);
+            if (k + 4 <= L.K) stage[i] = *(const f4u *)(row + k);
             else {
 #pragma unroll
                 for (int u = 0; u < 4; ++u) stage[i][u] = row[min(k + u, L.K - 1)];
@@ -221,19 +254,19 @@ __global__ __launch_bounds__(kRowsThreads) void fc_rows_kernel(LayerDev L, const
     const int row0 = wave * (kTile / NW) + (lane >> 4) * RQ;
     static_assert(RQ == 2, "a quarter's two rows are one word of row_ptr and the half after it");
     const int row_at = min(row0, L.row_ptrs - 2), row_end = min(row0 + RQ, L.row_ptrs - 1);
+    // (as they are loaded, and taken apart where they are used: a group's turn would otherwise begin with waiting for them)
     struct RowRange {
-        uint32_t at[RQ + 1];
+        uint32_t starts, end;
+        __device__ __forceinline__ uint32_t at(int i) const { return i == 0 ? starts & 0xffffu : i == 1 ? starts >> 16 : end; }
     };
     auto ranges_fetch = [&](int ph, RowRange (&r)[G]) {
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            const int blk = blk_lo + ph * G + g;
-            r[g] = RowRange{};
-            if (blk < blk_hi) {
-                const uint16_t *rp = L.row_ptr + (size_t)(pb0 + (uint32_t)blk) * (uint32_t)L.row_ptrs;
-                const uint32_t starts = *(const uint32_t *)(rp + row_at);
-                r[g] = RowRange{{starts & 0xffffu, starts >> 16, rp[row_end]}};
-            }
+            // (a block past the last: the last one's again, which multiply leaves out - a register set to zero here would have
+            // every load before it waited for)
+            const int blk = min(blk_lo + ph * G + g, blk_hi - 1);
+            const uint16_t *rp = L.row_ptr + (size_t)(pb0 + (uint32_t)blk) * (uint32_t)L.row_ptrs;
+            r[g] = RowRange{*(const uint32_t *)(rp + row_at), rp[row_end]};
         }
     };
 
@@ -247,13 +280,14 @@ __global__ __launch_bounds__(kRowsThreads) void fc_rows_kernel(LayerDev L, const
         // the first sixteen entries of all the rows, then their weights: requested together
         // (past a row's last entry: codebook entry 0 and the column of zeros)
         auto entry = [&](uint32_t at, int left) { return l16 < left ? (uint32_t)*(lds_u16)(uintptr_t)at : (uint32_t)kTile; };
-        auto list_at = [&](int g, int i) { return (uint32_t)(uintptr_t)(lds_u16)(lists + ((ph & 1) * G + g) * list_cap) + 2u * (r[g].at[i] + (uint32_t)l16); };
+        auto list_at = [&](int g, int i) { return (uint32_t)(uintptr_t)(lds_u16)(lists + ((ph & 1) * G + g) * list_cap) + 2u * (r[g].at(i) + (uint32_t)l16); };
+        auto count = [&](int g, int i) { return blk_lo + ph * G + g < blk_hi ? (int)(r[g].at(i + 1) - r[g].at(i)) : 0; };
         uint32_t ent[G][RQ];
         float w[G][RQ];
 #pragma unroll
         for (int g = 0; g < G; ++g)
 #pragma unroll
-            for (int i = 0; i < RQ; ++i) ent[g][i] = entry(list_at(g, i), (int)(r[g].at[i + 1] - r[g].at[i]));
+            for (int i = 0; i < RQ; ++i) ent[g][i] = entry(list_at(g, i), count(g, i));
 #pragma unroll
         for (int g = 0; g < G; ++g)
 #pragma unroll
@@ -264,7 +298,7 @@ __global__ __launch_bounds__(kRowsThreads) void fc_rows_kernel(LayerDev L, const
                                    (uint32_t)(l16 * IPL * 4);
 #pragma unroll
             for (int i = 0; i < RQ; ++i) {
-                int left = (int)(r[g].at[i + 1] - r[g].at[i]);
+                int left = count(g, i);
                 uint32_t at = list_at(g, i);
                 for (;;) {
                     const uint32_t off = (ent[g][i] & 255u) * (uint32_t)(kImages * 4);
@@ -286,25 +320,32 @@ __global__ __launch_bounds__(kRowsThreads) void fc_rows_kernel(LayerDev L, const
     if (phases > 0) {
         RowRange now[G], next[G];
         for (int i = (int)threadIdx.x; i < L.table_rows; i += kRowsThreads) s.tables[i] = L.tables[i];
-        first_chunk(0);
+        first_slot(0);
+        first_record(0);
         slab_fetch(0);
         ranges_fetch(0, now);
         for (int i = (int)threadIdx.x; i < 2 * G * kImages; i += kRowsThreads) slabs[(i / kImages) * kSlab + kTile * kImages + i % kImages] = 0.0f;
         __syncthreads();
         decode_group(0);
-        first_chunk(1);
+        first_slot(1);
         slab_store(0);
+        first_record(1);
         __syncthreads();
         for (int ph = 0; ph < phases; ++ph) {
             const bool more = ph + 1 < phases;
             if (more) {
+                // (a wavefront with a chunk has the longest way to the barrier: the others' products wait for it.  It decodes
+                // first: behind the loads that follow it would wait for them as well)
+                __builtin_amdgcn_s_setprio(3);
+                decode_group(ph + 1);
+                __builtin_amdgcn_s_setprio(0);
                 slab_fetch(ph + 1);
                 ranges_fetch(ph + 1, next);
-                decode_group(ph + 1);
-                first_chunk(ph + 2);
+                first_slot(ph + 2);
             }
             multiply(ph, now);
             if (more) {
+                first_record(ph + 2);
                 slab_store(ph + 1);
 #pragma unroll
                 for (int g = 0; g < G; ++g) now[g] = next[g];

@@ -452,8 +452,8 @@ bool plan_rows(const cl_layer *L, int batch, const DeviceLimits &dl, RowsPlan &P
     // Blocks to a group and split of the block rows, as on the other paths, in cycles per
     // workgroup: a start; per group of blocks a part that does not depend on what is in it
     // (latencies, the barrier), per block and per surviving weight; the partial tiles.  Fitted to
-    // the AlexNet- and VGG-shaped fc6 / fc7 / fc8 at 16, 32 and 64 images (fc6, us a call: 28.9,
-    // 32.6 and 45.8; one block to a group 34.6, 36.9 and 45.8).
+    // the AlexNet- and VGG-shaped fc6 / fc7 / fc8 at 16, 32 and 64 images (AlexNet-shaped fc6, us a call:
+    // 24.4, 28.2 and 40.7; one block to a group 30.0, 32.2 and 40.7).
     static const struct { int groups, block, weight_x20; } kFit[3] = {{3, 2150, 29}, {3, 3000, 34}, {1, 3900, 51}};
     const auto &fit = kFit[P.ipl / 2];
     const int64_t tiles = (int64_t)L->n_panels * (Bp / images);
@@ -739,16 +739,19 @@ int32_t launch_wide_mul(const LayerDev &D, int panels, const WidePlan &P, const 
 // kernel) and for blocks above 128 x 128; above, whichever of the sparse path's fc_rows_kernel,
 // the dense-tile path and the wide sparse path their launch models price lower (same units, all
 // fitted to measured launches; fc_rows_kernel saves a launch that lays the activations out or
-// decodes, 6 k cycles).  Measured on the AlexNet-shaped stack (fc6 / fc7 / fc8, us per layer
-// call): small-batch kernel 24 / 16 / 14 at 8 images; at 16 images fc_rows_kernel 29 / 18 / 18,
-// dense tiles 40 / 24 / 18; at 64 images 46 / 28 / 24 and 60 / 35 / 23; at 256 images wide
-// 97 / 58 / 50, dense tiles 166 / 89 / 41 - the dense tile multiplies eleven times the necessary
+// decodes, 9 k cycles with what the models leave out: from 6.3 k on fc8 below, at 65 to 128 images, is on
+// it - 24 us, dense tiles 29 - and above 9.7 k fc6 would be at these batches, where a stack is better off with it
+// on the wide path).  Measured on the
+// AlexNet-shaped stack (fc6 / fc7 / fc8, us per layer call): small-batch kernel 24 / 16 / 14 at 8 images; at
+// 16 images fc_rows_kernel 24 / 16 / 13, dense tiles 41 / 25 / 18; at 64 images 41 / 25 / 18 and
+// 60 / 35 / 24; at 128 images 71 / 40 / 24, wide 77 / 49 / 44; at 256 images 128 / 65 / 36, wide 97 / 57 / 50,
+// dense tiles 165 / 89 / 42 - the dense tile multiplies eleven times the necessary
 // products at a 9 % density but four at 25 %.  A layer of fewer than kAutoRowsBlocks blocks takes
 // 12 to 16 us on either, launches for the most part, and stays on dense tiles.  (Where the sparse path
 // runs the small-batch kernel instead, rows_kernel_pays, that is the cheaper one: the price is an upper bound.)
 constexpr int kAutoSparseBatch = 8;
 constexpr int kAutoRowsBlocks = 48;
-constexpr int64_t kAutoLaunch = 6000;
+constexpr int64_t kAutoLaunch = 9000;
 
 // How one layer runs for a batch: the path, and that path's launch shape.  Made once per call (what
 // the choice of a path has worked out for it is kept).
@@ -1154,9 +1157,9 @@ bool plain_rows(const cl_layer *L) { return L->desc.block_w == kTile && L->desc.
 // lays the activations out, or decodes - a layer between two on the other paths does not pay: its
 // neighbour hands the activations over, and one launch decodes all layers on the wide path.  So where
 // some layers run on fc_rows_kernel and some do not, the modelled cycles of the whole stack decide
-// whether the former do without it (us a step, AlexNet- and VGG-shaped stack: at 128 images, fc6 wide
-// either way, 148 and 167 with fc_rows_kernel for fc7, 135 and 156 without; at 64, all three layers on it, 87 and
-// 125, 114 and 136 without).
+// whether the former do without it (us a step, AlexNet- and VGG-shaped stack: at 128 images, fc6 wide either way,
+// 144 and 161 with fc_rows_kernel for fc7 and fc8, 136 and 156 without; at 64, all three layers on it, 81 and 106,
+// 115 and 136 without).
 constexpr int64_t kWideShared = 13000;          // the decoding launch's fixed part (plan_wide)
 
 void choose_stack_paths(const cl_layer *const *layers, int n, int batch, const DeviceLimits &dl, std::vector<FcPlan> &fc)

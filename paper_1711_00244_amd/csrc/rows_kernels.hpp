@@ -94,10 +94,12 @@ __device__ __forceinline__ void list_from(const Symbols &y, uint32_t pos, uint32
 // row's sum stays in a register from the first block to the last, and nothing is added in
 // memory.  Where a row's entries start in a block's list was counted when the layer was loaded
 // (row_ptr).
-// Bound by vector issue (52 % of the cycles at 16 images of the AlexNet-shaped fc6, 40 % over the
-// VGG-shaped stack at 64) and by the latencies of a group's turn, which is why small tiles take several blocks to a group.  There (us per
-// layer call, dense tiles before): 16 images 40 -> 29, 32 images 41 -> 32, 64 images 60 -> 46;
-// VGG-shaped fc6 91 -> 50, 92 -> 57, 139 -> 87.
+// Bound by vector issue (decode and multiply-adds) and by what is left of a group's turn, which is why small tiles
+// take several blocks to a group.  Nothing in a turn waits for loads it has just requested: the decode, which the
+// barrier waits for, comes first; ranges stay as loaded; a slot is asked for before the products and its record after
+// them (a turn of the VGG-shaped fc6 at 64 images 7.7 k -> 6.5 k cycles, the AlexNet-shaped 9.5 k -> 8.4 k).  us per
+// layer call at 16 / 32 / 64 images: AlexNet-shaped fc6 24 / 28 / 41, dense tiles 41 / 42 / 60; VGG-shaped fc6
+// 41 / 47 / 70, dense tiles 92 / 92 / 139.
 template <int IPL, int G>
 __global__ __launch_bounds__(kRowsThreads) void fc_rows_kernel(LayerDev L, const float *__restrict__ X, float *__restrict__ part, int B,
                                                                int panels, int splits, int Bp, int list_cap)

@@ -998,7 +998,7 @@ static int32_t launch_wide_expand(const cl_layer *const *layers, WideEntry *cons
     ExpandJobs jobs{};
     jobs.ipl = (uint32_t)ipl;
     size_t lds = xt_of ? kExpandTurnBytes : 0;
-    int64_t wgs = 0;
+    int64_t wgs = 0, t_wgs = 0;
     int used = 0;
     if (xt_of) {
         jobs.X = d_X;
@@ -1008,8 +1008,7 @@ static int32_t launch_wide_expand(const cl_layer *const *layers, WideEntry *cons
         jobs.Bp = bp;
         jobs.bw = xt_of->desc.block_w;
         jobs.rows = xt_of->nbw * kTile;
-        jobs.t_wgs = (uint32_t)(((int64_t)(jobs.rows / 32) * (bp / 32) + 1) / 2);
-        wgs = jobs.t_wgs;
+        t_wgs = ((int64_t)(jobs.rows / 32) * (bp / 32) + 1) / 2;
     }
     for (int i = 0; i < n; ++i) {
         const cl_layer *L = layers[i];
@@ -1018,10 +1017,11 @@ static int32_t launch_wide_expand(const cl_layer *const *layers, WideEntry *cons
         jobs.ent[used] = ents[i];
         jobs.wg0[used] = (uint32_t)wgs;
         wgs += (L->n_chunks + kWaves - 1) / kWaves;
-        lds = std::max(lds, table_image_bytes(L->val_lut_bits, L->idx_lut_bits, 1 << L->desc.weight_bits));
+        lds = std::max(lds, table_image_bytes(L->val_lut_bits, L->idx_lut_bits, 1 << L->desc.weight_bits) + kWaves * kExpandList * sizeof(uint32_t));
         ++used;
     }
-    if (!used && !jobs.t_wgs) return CL_OK;
+    if (!used && !t_wgs) return CL_OK;
+    jobs.t_wg0 = (uint32_t)wgs;
     for (int i = used; i <= kExpandJobs; ++i) jobs.wg0[i] = i == used ? (uint32_t)wgs : UINT32_MAX;
     if (!used) {
         // nothing to decode: the launch only lays the activations out (the job table names the
@@ -1033,7 +1033,7 @@ static int32_t launch_wide_expand(const cl_layer *const *layers, WideEntry *cons
     static LdsLimit seen;
     if (int32_t rc = ensure_lds((const void *)wide_expand_kernel, lds, seen)) return rc;
     dim3 egrid;
-    GRID_TRY(egrid, wgs);
+    GRID_TRY(egrid, wgs + t_wgs);
     hipLaunchKernelGGL(wide_expand_kernel, egrid, dim3(kThreads), lds, st, jobs);
     HIP_TRY(hipGetLastError());
     return CL_OK;

@@ -45,27 +45,33 @@ constexpr int kGroupPtrs = 2 * (kWideWaves + 1);        // group_ptr words per b
 // its own list: workgroups wg0[i] .. wg0[i + 1] - 1 belong to job i.)
 constexpr int kExpandJobs = 4;
 constexpr size_t kExpandTurnBytes = 2 * 32 * 33 * sizeof(float);       // LDS of a workgroup that lays activations out
+constexpr int kExpandList = 64 * kMaxEntries + 4;                      // LDS words of a wavefront's list: a chunk's weights, and a place nobody reads
 struct ExpandJobs {
     LayerDev L[kExpandJobs];
     WideEntry *ent[kExpandJobs];
     uint32_t wg0[kExpandJobs + 1];
     uint32_t ipl;                   // images per lane of the multiplying kernel: the row offsets count its sum registers
     // The same launch can lay out the activations of the first layer (what transpose_pad_kernel
-    // does: XT rows x Bp from X B x K): its first t_wgs workgroups do that, two 32 x 32 tiles
-    // each, and are through while the decoding workgroups wait for their records.
+    // does: XT rows x Bp from X B x K): its workgroups from t_wg0 on do that, two 32 x 32 tiles
+    // each, beside the decoding ones that are still at it (in front of them they left the decoding, which has
+    // the longer way to go, to the end of the launch: AlexNet-shaped fc6 at 256 images 92.9 -> 91.7 us a call).
     const float *X;
     float *XT;
     int B, K, Bp, bw, rows;
-    uint32_t t_wgs;
+    uint32_t t_wg0;
 };
 
+// A wavefront gathers its chunk's entries in LDS, in the order of the list, and writes them out side by side: bound by
+// the chain from the chunk's head over its records to their decode, and by what the vector unit has to do for each.
+// (Written where they belong straight from the decode, 4 bytes of a lane here and there, the stores took as long as the
+// rest: fc6 and fc7 of the AlexNet-shaped stack at 256 images 24.5 -> 19.6 us.)
 __global__ __launch_bounds__(kThreads) void wide_expand_kernel(ExpandJobs jobs)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem_raw[];
-    if (blockIdx.x < jobs.t_wgs) {
+    if (blockIdx.x >= jobs.t_wg0) {
         auto t = (float(*)[32][33])smem_raw;          // [2][32][33]
         const int half = (int)(threadIdx.x >> 8), tid = (int)(threadIdx.x & 255);
-        const int row_tiles = jobs.rows / 32, tile = (int)blockIdx.x * 2 + half;
+        const int row_tiles = jobs.rows / 32, tile = (int)(blockIdx.x - jobs.t_wg0) * 2 + half;
         const bool real = tile < row_tiles * (jobs.Bp / 32);
         const int r0 = (tile % row_tiles) * 32, b0 = (tile / row_tiles) * 32;
         const int tx = tid & 31, ty = tid >> 5;       // 32 x 8
@@ -102,26 +108,33 @@ __global__ __launch_bounds__(kThreads) void wide_expand_kernel(ExpandJobs jobs)
     store_tables(s, L, fetch_tables(L));
     __syncthreads();
     if (!have) return;
-    const BlockGeom g = block_geom(L, h.m.blk);
+    // (the division is vector arithmetic: what it gives is made uniform again, or the block's shape would be one per lane)
+    const int brow = __builtin_amdgcn_readfirstlane((int)(h.m.blk / (uint32_t)L.nbw));
+    const BlockGeom g = block_geom(L, brow, (int)h.m.blk - brow * L.nbw);
     const Symbols y = decode_record(rec, s.T);
     const LaneStart st = lane_starts(y, h.m.pos0);
-    // the lane's surviving weights per half, then where its first of each half goes
+    // the lane's surviving weights per half, then where its first of each half goes: byte offsets
+    // in the chunk's list, the first half's weights before the second's
     uint32_t mine = 0;
-    for_each_entry(y, st.sum, [&](uint32_t, uint32_t v, uint32_t, uint32_t pos) {
+    for_each_entry<true>(y, st.sum, [&](uint32_t, uint32_t v, uint32_t, uint32_t pos) {
         uint32_t r, cc;
         split_pos(pos, g, r, cc);
-        if (v != 0u) mine += cc >= (uint32_t)kHalf ? 0x10000u : 1u;
+        mine += (v != 0u ? 1u : 0u) << ((cc & (uint32_t)kHalf) >> 2);
     });
-    const uint32_t excl = wave_incl_scan(mine) - mine;
-    uint32_t at0 = base0 + (excl & 0xffffu), at1 = base1 + (excl >> 16);
-    for_each_entry(y, st.sum, [&](uint32_t, uint32_t v, uint32_t, uint32_t pos) {
+    const uint32_t incl = wave_incl_scan(mine), excl = incl - mine;
+    const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63), n0 = all & 0xffffu, n = n0 + (all >> 16);
+    uint32_t at = (excl + (n0 << 16)) << 2;
+    uint32_t *list = (uint32_t *)s.extra + wave * kExpandList;
+    for_each_entry<true>(y, st.sum, [&](uint32_t, uint32_t v, uint32_t, uint32_t pos) {
         uint32_t r, cc;
         split_pos(pos, g, r, cc);
-        if (v == 0u) return;
+        const uint32_t half = (cc & (uint32_t)kHalf) >> 2;              // 0 or 16
         const WideEntry e = (v << 16) | ((cc & (uint32_t)(kHalf - 1)) << 8) | ((r & (uint32_t)(kMulRows - 1)) * jobs.ipl);
-        if (cc >= (uint32_t)kHalf) ent[at1++] = e;
-        else ent[at0++] = e;
+        *(uint32_t *)((char *)list + (v != 0u ? (at >> half) & 0xffffu : (uint32_t)(kExpandList - 1) * 4u)) = e;
+        at += (v != 0u ? 4u : 0u) << half;
     });
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    for (uint32_t i = (uint32_t)lane; i < n; i += 64u) ent[i < n0 ? base0 + i : base1 + (i - n0)] = list[i];
 }
 
 // The multiply-add of up to 64 entries, one per lane of (entry word, weight) - lanes past

@@ -126,14 +126,16 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 // 32 (64 for NQ = 8) columns and as many of the 128 weight rows as it takes to share the
 // tile among four wavefronts: the multiplies are sixteen times faster, and columns read
 // once per workgroup instead of four times keep the activation loads off the critical
-// path (weights come from LDS).
+// path (weights come from LDS).  (Eight multipliers for NQ = 8, two to a SIMD with half the rows each, were no
+// faster: 53 us for 256 images of the AlexNet-shaped fc6, 52 with four.)
 template <int NQ> struct Bf16Shape {
-    static constexpr int kDecoders = 4;
-    static constexpr int kThreads = (4 + kDecoders) * 64;
+    static constexpr int kMultipliers = 4;
+    static constexpr int kDecoders = NQ == 8 ? 4 : 8;
+    static constexpr int kThreads = (kMultipliers + kDecoders) * 64;
     static constexpr int kAhead = 4;                           // groups of sixteen k in flight
     static constexpr int kImages = 32 * NQ;
     static constexpr int kIT = NQ == 8 ? 2 : 1;                // 32-column groups per wavefront
-    static constexpr int kWavesPerCols = NQ >= 4 ? 1 : 4 / NQ; // wavefronts sharing the same columns
+    static constexpr int kWavesPerCols = kMultipliers * kIT / NQ;   // wavefronts sharing the same columns
     static constexpr int kRT = 4 / kWavesPerCols;              // 32-row tiles per wavefront
 };
 
@@ -142,8 +144,14 @@ template <int NQ> struct Bf16Shape {
 // tiles; a multiplying wavefront reads the eight hi halves and the eight lo halves of a
 // row for a group of sixteen k with one 16-byte LDS read each (lanes 0-31 the first
 // eight k, lanes 32-63 the other eight) and feeds three multiplies per accumulator.
+// A used tile is cleared by the decoders while the multipliers are at the next one: they meet at a second barrier
+// behind a quarter of a block's multiplies.  (Cleared by the multipliers, between two barriers, a block of the AlexNet-shaped
+// fc6 at 256 images took 0.4 us longer.)  Bound by the multiplies for eight accumulators (2.9 us of the 4.1 a block takes;
+// start and partial tiles another 10 us of a launch), by the decode below: hence eight decoders there.  fc6 / fc7 / fc8 at 256
+// images 60 / 33.5 / 21 -> 49 / 28.5 / 16.5 us.
 constexpr int kHStride = kTile + 8;                       // bf16 per row of a half tile (16-byte rows, 4-bank skew)
 constexpr int kBf16BufFloats = 2 * kTile * kHStride / 2;  // floats per buffer: hi tile + lo tile
+constexpr int kClearGroups = 2;                           // groups of a block that are multiplied while the other buffer is cleared
 template <int NQ>
 __global__ __launch_bounds__(Bf16Shape<NQ>::kThreads) void fc_mfma_bf16_kernel(LayerDev L, const uint16_t *__restrict__ XB,
                                                                              float *part, int splits, int Bp, size_t plane_elems,
@@ -165,13 +173,13 @@ __global__ __launch_bounds__(Bf16Shape<NQ>::kThreads) void fc_mfma_bf16_kernel(L
     XB += (size_t)((pj / splits) / panels_per_x) * x_stride;            // one pair of planes per filter group
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = (int)(threadIdx.x & 63);
-    store_tables(s, L, fetch_tables(L));
+    if (threadIdx.x < kThreads) store_tables(s, L, fetch_tables(L));      // the table image is copied by kThreads threads
     for (int t = threadIdx.x; t < 2 * kBf16BufFloats / 4; t += kNThreads) ((uint4 *)tiles)[t] = uint4{0, 0, 0, 0};
     for (int t = threadIdx.x; t < L.ncode; t += kNThreads) cbp[t] = bf16_split(L.codebook[t]);
     const int blk_lo = (int)(((int64_t)L.nbw * j) / splits), blk_hi = (int)(((int64_t)L.nbw * (j + 1)) / splits);
     const uint32_t pb0 = (uint32_t)p * (uint32_t)L.nbw;
-    if (wave >= 4) {
-        decoder_role<kDec, true, kBf16BufFloats>(L, s, tiles, blk_lo, blk_hi, pb0, wave, lane,
+    if (wave >= S::kMultipliers) {
+        decoder_role<kDec, true, kBf16BufFloats>(L, s, tiles, blk_lo, blk_hi, pb0, wave - S::kMultipliers, lane,
                                                  [&](uint32_t v) { return cbp[v]; },
                                                  [&](float *tile, uint32_t r, uint32_t cc, uint32_t w) {
                                                      uint16_t *t16 = (uint16_t *)tile + __umul24(r, (uint32_t)kHStride) + cc;
@@ -189,17 +197,22 @@ __global__ __launch_bounds__(Bf16Shape<NQ>::kThreads) void fc_mfma_bf16_kernel(L
     const int kl = lane >> 5, m = lane & 31;
     const int col0 = (wave / S::kWavesPerCols) * kIT * 32;  // this wavefront's first column of the tile
     const int row0 = (wave % S::kWavesPerCols) * kRT * 32;  // and its first weight row
-    // group g, column c: 32 bytes at (g Bp + c) * 32, this lane's eight k at + 16 kl
-    const uint4 *ap = (const uint4 *)XB + ((size_t)blk_lo * 8 * Bp + (size_t)nb * kImages + col0 + m) * 2 + kl;
-    const size_t group_stride = (size_t)Bp * 2, plane_stride = plane_elems / 8;      // in 16-byte units
+    // group g, column c: 32 bytes at (g Bp + c) * 32, this lane's eight k at + 16 kl: a uniform address that moves from
+    // group to group, and a lane's offset that does not
+    const size_t group_bytes = (size_t)Bp * 32, plane_bytes = plane_elems * 2;
+    const char *hi = (const char *)XB + (size_t)blk_lo * 8 * group_bytes + ((size_t)nb * kImages + col0) * 32, *lo = hi + plane_bytes;
+    const uint32_t lane_at = (uint32_t)(m * 32 + kl * 16);
     uint4 ah[kAhead][kIT], al[kAhead][kIT];
     auto load_group = [&](int slot) {
 #pragma unroll
         for (int it = 0; it < kIT; ++it) {
-            ah[slot][it] = ap[it * 64];
-            al[slot][it] = ap[plane_stride + it * 64];
+            ah[slot][it] = *(const uint4 *)(hi + lane_at + it * 1024);
+            al[slot][it] = *(const uint4 *)(lo + lane_at + it * 1024);
         }
-        ap += group_stride;
+        hi += group_bytes;
+        lo += group_bytes;
+        // (the compiler would move the loads down to where they are used, three groups on, and wait there)
+        __builtin_amdgcn_sched_barrier(0);
     };
 #pragma unroll
     for (int i = 0; i < kAhead; ++i) load_group(i);
@@ -218,6 +231,8 @@ __global__ __launch_bounds__(Bf16Shape<NQ>::kThreads) void fc_mfma_bf16_kernel(L
         halves_at(0, bh, bl);
 #pragma unroll
         for (int g = 0; g < 8; ++g) {
+            // (by now the decoders have cleared the other buffer; they wait for each other, and not much for this)
+            if (g == kClearGroups && bi > blk_lo) __syncthreads();
             constexpr int kSlotMask = kAhead - 1;
             const int slot = g & kSlotMask;
 #pragma unroll
@@ -234,11 +249,7 @@ __global__ __launch_bounds__(Bf16Shape<NQ>::kThreads) void fc_mfma_bf16_kernel(L
             }
             load_group(slot);
         }
-        // every multiplier reads rows that others read too: all done, then each clears a quarter
-        __syncthreads();
-        uint4 *z = (uint4 *)buf + wave * (kBf16BufFloats / 16);
-        for (int t = lane; t < kBf16BufFloats / 16; t += 64) z[t] = uint4{0, 0, 0, 0};
-        __syncthreads();
+        __syncthreads();                                    // this block multiplied, the next one decoded
     }
     // accumulator (it, rt), element e of lane l: column col0 + 32 it + 8 (e / 4) + 4 (l / 32) + e % 4
     // of the tile, weight row row0 + 32 rt + l % 32; 32 lanes write 32 consecutive floats

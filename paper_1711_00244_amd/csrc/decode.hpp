@@ -329,9 +329,11 @@ __device__ __forceinline__ BlockGeom block_geom(const LayerDev &L, int brow, int
     return g;
 }
 
+// (b the same in all lanes.  A division is vector arithmetic, and what follows from its result would be one value per
+// lane to the compiler: the shape of the block, and every branch on it)
 __device__ __forceinline__ BlockGeom block_geom(const LayerDev &L, uint32_t b)
 {
-    const int brow = (int)(b / (uint32_t)L.nbw);
+    const int brow = __builtin_amdgcn_readfirstlane((int)(b / (uint32_t)L.nbw));
     return block_geom(L, brow, (int)(b - (uint32_t)brow * (uint32_t)L.nbw));
 }
 

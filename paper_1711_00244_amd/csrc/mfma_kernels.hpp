@@ -107,8 +107,8 @@ __global__ __launch_bounds__(256) void im2col_pad_kernel(const float *__restrict
 //   block").
 //   Multipliers (wavefronts 0-3) multiply block i on the matrix cores (step 12); how
 //   the tile and the images are divided among them is the kernel's own business.
-// Two weight tiles alternate; a used tile is cleared by the multipliers, so a tile
-// is always clean when the decoders get it back.
+// Two weight tiles alternate; a used tile is cleared by the multipliers (in the bf16 kernel by the decoders),
+// so a tile is always clean when the decoders write to it.
 constexpr int kWStride = kTile + 4;      // floats per weight row of a tile (16-byte rows, 4-bank skew)
 constexpr int kWTileBytes = kTile * kWStride * 4;
 // The decoder wavefronts' side of the dense-tile kernels: decode the blocks blk_lo ..
@@ -116,15 +116,16 @@ constexpr int kWTileBytes = kTile * kWStride * 4;
 // 32-bit words, one block ahead of the multipliers, meeting them at one barrier per
 // block.  The two buffers are BUF_FLOATS floats apart; look(v) reads what stands for
 // value index v (the codebook entry, or its two bf16 halves) and put(buffer, row,
-// column, that) places it (in the tile, or in two half tiles).  With CLEAR_BARRIER the multipliers clear a used tile between two barriers
-// (their rows are shared), else right after their last read of their own rows.
-// Called by wavefronts 4 .. 4 + DEC - 1.
-template <int DEC, bool CLEAR_BARRIER, int BUF_FLOATS, class Look, class Put>
+// column, that) places it (in the tile, or in two half tiles).  With CLEAR the decoders clear a used tile, the
+// multipliers' rows being shared, and meet them at a second barrier behind that; else a multiplier clears
+// its own rows as it reads them.
+// `wave` counts the decoders, 0 .. DEC - 1.
+template <int DEC, bool CLEAR, int BUF_FLOATS, class Look, class Put>
 __device__ __forceinline__ void decoder_role(const LayerDev &L, const Smem &s, float *tiles, int blk_lo, int blk_hi, uint32_t pb0,
                                              int wave, int lane, Look look, Put put)
 {
     // The chunks of this split's blocks are consecutive, [c_lo, c_hi); decoder
-    // d = wave - 4 takes c_lo + d, c_lo + d + DEC, ... and finds a block's
+    // d = wave takes c_lo + d, c_lo + d + DEC, ... and finds a block's
     // end at the first chunk head that names a later block.  Block -> chunk head ->
     // record is a chain of dependent loads, so the stream runs ahead of the decoding:
     // the heads of the next three chunks and the records of the next two are in
@@ -142,7 +143,7 @@ __device__ __forceinline__ void decoder_role(const LayerDev &L, const Smem &s, f
     uint32_t lane_zero;
     asm volatile("v_mov_b32 %0, 0" : "=v"(lane_zero));
     const uint32_t c_hi = blk_lo < blk_hi ? L.block_chunk[pb0 + (uint32_t)blk_hi] : 0u;
-    uint32_t c_tail = blk_lo < blk_hi ? L.block_chunk[pb0 + (uint32_t)blk_lo] + (uint32_t)(wave - 4) : 0u;   // next head to load
+    uint32_t c_tail = blk_lo < blk_hi ? L.block_chunk[pb0 + (uint32_t)blk_lo] + (uint32_t)wave : 0u;   // next head to load
     auto next_head = [&]() {
         Head h;
         h.valid = c_tail < c_hi;
@@ -160,10 +161,11 @@ __device__ __forceinline__ void decoder_role(const LayerDev &L, const Smem &s, f
     };
     Head h0 = next_head(), h1 = next_head(), h2 = next_head();
     uint64_t w0 = word_of(h0), w1 = word_of(h1);
+    const int brow = __builtin_amdgcn_readfirstlane((int)(pb0 / (uint32_t)L.nbw));
     // decode block bi into a weight tile (clean on entry): Algorithm 2 steps 5-9
     auto produce = [&](int bi, float *tile) {
         const uint32_t b = pb0 + (uint32_t)bi;
-        const BlockGeom g = block_geom(L, b);
+        const BlockGeom g = block_geom(L, brow, bi);
         while (h0.valid && (uint32_t)__builtin_amdgcn_readfirstlane((int)h0.blk) == b) {
             const LaneRecord rec = split_record(w0, (uint32_t)lane < h0.rec_end - h0.rec_off ? (uint32_t)w0 & 15u : 0u);
             const uint32_t pos0 = h0.pos0;
@@ -200,7 +202,13 @@ __device__ __forceinline__ void decoder_role(const LayerDev &L, const Smem &s, f
     for (int bi = blk_lo; bi < blk_hi; ++bi) {
         if (bi + 1 < blk_hi) produce(bi + 1, tiles + (((bi - blk_lo) & 1) ^ 1) * BUF_FLOATS);
         __syncthreads();
-        if (CLEAR_BARRIER) __syncthreads();
+        if (CLEAR && bi + 1 < blk_hi) {
+            constexpr int kShare = BUF_FLOATS / 4 / DEC;
+            static_assert(!CLEAR || BUF_FLOATS % (4 * DEC) == 0, "the decoders clear equal shares");
+            uint4 *z = (uint4 *)(tiles + ((bi - blk_lo) & 1) * BUF_FLOATS) + wave * kShare;
+            for (int t = lane; t < kShare; t += 64) z[t] = uint4{0, 0, 0, 0};
+            __syncthreads();
+        }
     }
 }
 
@@ -408,7 +416,7 @@ __global__ __launch_bounds__(MfmaShape<NQ>::kThreads) void fc_mfma_kernel(LayerD
     const uint32_t pb0 = (uint32_t)p * (uint32_t)L.nbw;
 
     if (producer) {
-        decoder_role<kMfmaDecoders, false, kWTileBytes / 4>(L, s, tiles, blk_lo, blk_hi, pb0, wave, lane,
+        decoder_role<kMfmaDecoders, false, kWTileBytes / 4>(L, s, tiles, blk_lo, blk_hi, pb0, wave - 4, lane,
                                                              [&](uint32_t v) { return s.T.cb[v]; },
                                                              [&](float *tile, uint32_t r, uint32_t cc, float w) { tile[__umul24(r, (uint32_t)kWStride) + cc] = w; });
         return;

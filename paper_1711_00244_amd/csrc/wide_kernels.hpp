@@ -108,9 +108,7 @@ __global__ __launch_bounds__(kThreads) void wide_expand_kernel(ExpandJobs jobs)
     store_tables(s, L, fetch_tables(L));
     __syncthreads();
     if (!have) return;
-    // (the division is vector arithmetic: what it gives is made uniform again, or the block's shape would be one per lane)
-    const int brow = __builtin_amdgcn_readfirstlane((int)(h.m.blk / (uint32_t)L.nbw));
-    const BlockGeom g = block_geom(L, brow, (int)h.m.blk - brow * L.nbw);
+    const BlockGeom g = block_geom(L, h.m.blk);
     const Symbols y = decode_record(rec, s.T);
     const LaneStart st = lane_starts(y, h.m.pos0);
     // the lane's surviving weights per half, then where its first of each half goes: byte offsets

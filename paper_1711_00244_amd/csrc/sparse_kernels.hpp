@@ -180,6 +180,17 @@ struct PrevSlots {
     int bh, wg_per_panel, part_b, relu;
 };
 
+// Where fc_sparse_whole_kernel's outputs go.
+struct WholeOut {
+    const float *bias;              // or null
+    float *Y;                       // of the first image of the batch tile
+    int relu;
+};
+
+// Threads of fc_reduce_body's workgroups, and slices they form beside each other for a block row of `rows` rows.
+constexpr int kRedThreads = 512;
+__host__ __device__ constexpr int reduce_slices(int rows) { return kRedThreads / (rows < kRedThreads ? (rows + 63) / 64 * 64 : kRedThreads); }
+
 // Up to this batch tile, and for block rows of up to 256 rows, every wavefront of the small-
 // batch kernel has an output tile of its own in LDS and writes each row sum once, with a
 // plain store (see fc_sparse_body); above, the workgroup shares one tile through float atomics
@@ -268,29 +279,30 @@ __device__ __forceinline__ void entries_in_one_pass(LaneRecord &rec, const Table
 // (wg: the workgroup's number within the layer's share of the grid; nb <= BT: images that X
 // holds - the tile's other images are zeros; FOLD: the input may be the partial tiles of the
 // layer before - an instantiation of its own, so that the code for it does not weigh on the
-// registers of the others; ONE_PASS: see entries_private)
-template <int BT, bool FOLD, bool ONE_PASS>
+// registers of the others; ONE_PASS: see entries_private; WHOLE: the workgroup, of NW wavefronts with R chunks each, has all
+// chunks of the block row and finishes the output itself, see fc_sparse_whole_kernel)
+template <int BT, bool FOLD, bool ONE_PASS, bool WHOLE = false, int NW = kWaves, int R = kSparseChunksPerWave>
 __device__ __forceinline__ void fc_sparse_body(const LayerDev &L, const float *__restrict__ X, float *part, const Divisor &wg_per_panel,
-                                               int xcap, const PrevSlots &prev, uint32_t wg, int nb)
+                                               int xcap, const PrevSlots &prev, uint32_t wg, int nb, const WholeOut &whole = WholeOut{nullptr, nullptr, 0})
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem_raw[];
     const Smem s = carve(smem_raw, L);
     const int p = (int)wg_per_panel.quotient(wg), j = (int)(wg - (uint32_t)p * wg_per_panel.d);
     const uint32_t pc1 = L.panel_chunk[p + 1];
-    const uint32_t my0 = L.panel_chunk[p] + (uint32_t)j * (kWaves * kSparseChunksPerWave);
-    if (my0 >= pc1) return;
+    const uint32_t my0 = L.panel_chunk[p] + (uint32_t)j * (NW * R);
+    if (!WHOLE && my0 >= pc1) return;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = (int)(threadIdx.x & 63);
     // wavefront w takes chunks my0 + w, my0 + 8 + w, ...: all their records are requested
     // before the tables are copied
-    bool have[kSparseChunksPerWave];
-    ChunkHead h[kSparseChunksPerWave];
-    LaneRecord rec[kSparseChunksPerWave];
-    uint32_t rec_pos[kSparseChunksPerWave];
+    bool have[R];
+    ChunkHead h[R];
+    LaneRecord rec[R];
+    uint32_t rec_pos[R];
     const bool priv = private_tiles(L.bh, BT);
 #pragma unroll
-    for (int i = 0; i < kSparseChunksPerWave; ++i) {
-        const uint32_t c = my0 + (uint32_t)(i * kWaves + wave);
+    for (int i = 0; i < R; ++i) {
+        const uint32_t c = my0 + (uint32_t)(i * NW + wave);
         have[i] = c < pc1;
         h[i] = ChunkHead{};
         rec[i] = LaneRecord{};
@@ -304,17 +316,19 @@ __device__ __forceinline__ void fc_sparse_body(const LayerDev &L, const float *_
             }
         }
     }
-    const TableRegs tr = fetch_tables(L);
-    const int n_tiles = priv ? kWaves : 1;
+    TableRegs tr;
+    const bool copies = NW == kWaves || threadIdx.x < kThreads;         // the table image is copied by kThreads threads
+    if (copies) tr = fetch_tables(L);
+    const int n_tiles = WHOLE ? (int)((pc1 - my0 + kWaves - 1) / kWaves * kWaves) : priv ? kWaves : 1;
     float *ytile = s.extra;                  // [n_tiles][BT][bh]
     float *xs = ytile + (size_t)n_tiles * L.bh * BT;   // [xcap][BT]: a column's BT images side by side, one LDS read per entry
     // activation columns of the blocks this workgroup's chunks belong to
     const uint32_t pb0 = (uint32_t)p * (uint32_t)L.nbw;
-    const uint32_t c_last = min(pc1, my0 + (uint32_t)(kWaves * kSparseChunksPerWave)) - 1u;
-    const int col_a = (int)(L.meta[my0].blk - pb0) * L.bw;
-    const int col_b = min(L.K, (int)(L.meta[c_last].blk - pb0 + 1u) * L.bw);
+    const uint32_t c_last = min(pc1, my0 + (uint32_t)(NW * R)) - 1u;
+    const int col_a = WHOLE ? 0 : (int)(L.meta[my0].blk - pb0) * L.bw;
+    const int col_b = WHOLE ? L.K : min(L.K, (int)(L.meta[c_last].blk - pb0 + 1u) * L.bw);
     const int width = col_b - col_a;
-    const bool slab = width <= xcap;
+    const bool slab = WHOLE || width <= xcap;
     if (FOLD && slab && prev.part) {
         // (the host takes this form only for layers whose every workgroup has a slab)
         constexpr uint32_t kPerWg = kWaves * kSparseChunksPerWave;
@@ -363,10 +377,10 @@ __device__ __forceinline__ void fc_sparse_body(const LayerDev &L, const float *_
     } else {
         for (int t = threadIdx.x; t < n_tiles * L.bh * BT; t += blockDim.x) ytile[t] = 0.0f;
     }
-    store_tables(s, L, tr);
+    if (copies) store_tables(s, L, tr);
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kSparseChunksPerWave; ++i) {
+    for (int i = 0; i < R; ++i) {
         if (!have[i]) continue;
         const BlockGeom g = block_geom(L, p, (int)(h[i].m.blk - pb0));
         // The entries of the record in order, in every lane up to the wavefront's longest
@@ -410,9 +424,8 @@ __device__ __forceinline__ void fc_sparse_body(const LayerDev &L, const float *_
         // once, by the lane where it ends.  No two lanes store the same row, and the tile
         // receives this chunk only, so plain stores do.
         auto entries_private = [&](auto shifted, auto load_x, auto split) {
-            static_assert(kSparseChunksPerWave == 1, "a wavefront's tile takes one chunk: plain stores");
             constexpr uint32_t kNone = 0xffffffffu;
-            float *tile = ytile + (size_t)wave * L.bh * BT;
+            float *tile = ytile + (size_t)(i * NW + wave) * L.bh * BT;     // (one chunk to a tile: plain stores)
             uint32_t first_row = kNone, cur = kNone;    // the rows of the lane's first entry and of its last so far (kNone: no record)
             float acc[BT], head[BT];
 #pragma unroll
@@ -508,7 +521,10 @@ __device__ __forceinline__ void fc_sparse_body(const LayerDev &L, const float *_
             const uint32_t sh = (uint32_t)g.shift, cmask = (uint32_t)g.bwp - 1u, rmax = (uint32_t)g.bhp - 1u;
             // (rows are used for a lane's own entries only in one pass, and those lie inside the block: checked when the
             // layer was loaded)
-            if (priv && L.pos32) entries_private(std::false_type{}, load_x, [&](uint32_t pos, uint32_t &r, uint32_t &cc) { split_pos(pos, g, r, cc); });
+            if (WHOLE && !L.pos32 && g.shift >= 0)
+                entries_private(std::true_type{}, load_x, [&](uint32_t at, uint32_t &r, uint32_t &cc) { r = at >> (8u + sh); cc = __builtin_amdgcn_ubfe(at, 8u, sh); });
+            else if (WHOLE) entries_private(std::false_type{}, load_x, [&](uint32_t pos, uint32_t &r, uint32_t &cc) { split_pos(pos, g, r, cc); });
+            else if (priv && L.pos32) entries_private(std::false_type{}, load_x, [&](uint32_t pos, uint32_t &r, uint32_t &cc) { split_pos(pos, g, r, cc); });
             else if (priv && g.shift >= 0)
                 entries_private(std::true_type{}, load_x, [&](uint32_t at, uint32_t &r, uint32_t &cc) { r = at >> (8u + sh); cc = __builtin_amdgcn_ubfe(at, 8u, sh); });
             else if (priv) entries_private(std::true_type{}, load_x, [&](uint32_t at, uint32_t &r, uint32_t &cc) { split_pos(at >> 8, g, r, cc); });
@@ -531,6 +547,30 @@ __device__ __forceinline__ void fc_sparse_body(const LayerDev &L, const float *_
         }
     }
     __syncthreads();
+    if constexpr (WHOLE) {
+        // the tiles eight by eight, then these sums as fc_reduce_body adds the workgroups' tiles up: to the last bit what
+        // the two launches give
+        const int slots = n_tiles / kWaves, slices = reduce_slices(min(L.bh, L.M - p * L.bh)), row_id = p * L.bh;
+        for (int t = threadIdx.x; t < L.bh * nb; t += blockDim.x) {
+            const int b = t / L.bh, m = row_id + t - b * L.bh;
+            if (m >= L.M) continue;
+            float y = 0.0f;
+            for (int sl = 0; sl < min(slices, max(slots, 1)); ++sl) {
+                float acc = 0.0f;
+                for (int k = sl; k < slots; k += slices) {
+                    const float *tile = ytile + (size_t)k * kWaves * L.bh * BT + t;
+                    float sum = tile[0];
+#pragma unroll
+                    for (int w = 1; w < kWaves; ++w) sum += tile[(size_t)w * L.bh * BT];
+                    acc += sum;
+                }
+                y = sl == 0 ? acc : y + acc;
+            }
+            if (whole.bias) y += whole.bias[m];
+            whole.Y[(size_t)b * L.M + m] = whole.relu ? fmaxf(y, 0.0f) : y;
+        }
+        return;
+    }
     float *mine = part + (size_t)wg * L.bh * BT;
     // (tiles added in wavefront order: the same every run; four outputs per thread where a tile's size allows)
     const int per_tile = L.bh * BT;
@@ -562,6 +602,22 @@ __global__ __launch_bounds__(kThreads) void fc_sparse_kernel(LayerDev L, const f
     fc_sparse_body<BT, FOLD, kOnePass>(L, X, part, wg_per_panel, xcap, prev, blockIdx.x, nb);
 }
 
+// A small layer in one launch: a workgroup of sixteen wavefronts takes a whole block row, up to three chunks a wavefront, each
+// into a tile of its own, stages all activations, and finishes the output, so that there are no partial tiles and
+// nothing to add up in a second launch - which took as long as the products of such a layer, and its launch
+// longer.  Bound by the latencies of a chunk, one after the other: 9.4 us for 1024 x 1024 at 10 % and one image (35 chunks to a
+// block row), 5.5 and 3.3 in two launches.  A call, which the host's work for its launches bounds: 13.4 -> 10.2 us; two images
+// 13.0 -> 10.1; 256 x 256 (4 chunks) 12.7 -> 9.7; 32768 x 1024, a block row to a CU, 13.8 -> 9.5.  A fourth chunk
+// to a wavefront would take as long as the launch that is saved.
+constexpr int kWholeWaves = 16, kWholeRounds = 3, kWholeBT = 4;
+
+template <int BT>
+__global__ __launch_bounds__(kWholeWaves * 64) void fc_sparse_whole_kernel(LayerDev L, const float *__restrict__ X, WholeOut out, int nb)
+{
+    fc_sparse_body<BT, false, true, true, kWholeWaves, kWholeRounds>(L, X, nullptr, Divisor{1, 0, 1}, 0, PrevSlots{nullptr, nullptr, nullptr, 1, 0, 0, 0},
+                                                                    blockIdx.x, nb, out);
+}
+
 // Several layers of one shape in one grid (the same layer of several models, or layers
 // whose inputs do not depend on each other): workgroups wgs_per_layer i ..
 // wgs_per_layer (i + 1) - 1 do layer i's share of Algorithm 2, from its own input
@@ -583,8 +639,6 @@ __global__ __launch_bounds__(kThreads) void fc_sparse_group_kernel(const LayerDe
 // nothing else, so it is laid out to have few links: the threads form as many groups
 // (slices) as fit next to one pass over the rows, slice s adds slots s, s + slices, ...
 // with twelve loads in flight, LDS adds the slices in order.
-constexpr int kRedThreads = 512;
-
 __device__ __forceinline__ void fc_reduce_body(const LayerDev &L, const float *__restrict__ part, const float *__restrict__ bias,
                                                float *Y, int B, int part_b, int wg_per_panel, int relu, int wg)
 {

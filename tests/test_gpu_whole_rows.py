@@ -1,0 +1,38 @@
+"""Small layers in one launch, a workgroup to a block row: block rows of no, one, sixteen, seventeen and 48 chunks (the most)
+and of 49 (two launches), ragged last blocks, widths that are no power of two, positions of 32 bits; to the
+last bit what the two launches give, which a group of layers in one grid still takes."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_1711_00244_amd as cl
+from gates import assert_close, fc_ref
+from test_host_library import rand_pruned
+
+pytestmark = pytest.mark.gpu
+
+# rows, columns, block height and width, density, value and index bits
+CASES = [(1024, 1024, 128, 128, 0.1, 5, 4), (300, 333, 128, 128, 0.3, 5, 4), (256, 256, 256, 256, 0.2, 5, 4), (257, 500, 128, 100, 0.05, 8, 5),
+         (1, 64, 1, 64, 0.5, 5, 4), (100, 3000, 64, 3000, 0.02, 5, 8), (512, 2048, 128, 128, 0.002, 5, 4)] + [
+             (100, 128 * n, 64, 128, 0.05, 5, 4) for n in (1, 16, 17, 32, 33, 48, 49)]
+
+
+@pytest.mark.parametrize("M,K,bh,bw,d,r,k", CASES)
+def test_whole_block_rows(M, K, bh, bw, d, r, k):
+    import torch
+    rng = np.random.default_rng(M + 3 * K)
+    W = rand_pruned(rng, M, K, d)
+    W[-(M % bh or bh):] = 0 if M > bh else W[-(M % bh or bh):]           # the last block row without a chunk
+    L = cl.compress_layer(W, r, k, bh, bw, upload=True)
+    oW = oracle.dense_weights(oracle.compress_layer(W, r, k, bh, bw))
+    bias = (rng.standard_normal(M) * 0.1).astype(np.float32)
+    G = cl.LayerGroup([L])
+    for B in (1, 2, 3, 4):
+        X = rng.standard_normal((B, K)).astype(np.float32)
+        Xd, bd = torch.from_numpy(X).cuda(), torch.from_numpy(bias).cuda()
+        for relu in (False, True):
+            Y = cl.compressed_fc_forward(L, Xd, bd, relu=relu, path=cl.PATH_SPARSE)
+            assert_close(Y.cpu().numpy(), fc_ref(oW, X, bias), relu)
+        if B != 3:
+            plain = cl.compressed_fc_forward(L, Xd, None, relu=False, path=cl.PATH_SPARSE)
+            assert torch.equal(plain, G.forward(Xd[None])[0])

@@ -280,15 +280,37 @@ try {
     size_t total = 0;
     for (auto &s : secs) { s.off = total; total += (s.bytes + 255) / 256 * 256; }
     total += 256;
-    std::vector<char> host(total, 0);
-    for (auto &s : secs)
-        if (s.bytes) std::memcpy(host.data() + s.off, s.src, s.bytes);
+    // The small sections travel together, with zeros between them; a section of 1 MB and more goes by itself from where it lies
+    // (what lies behind it up to the next one is read by nobody).  The AlexNet-shaped fc6, 7 MB: 430 us, 560 with all of
+    // them put together first in new memory.
+    constexpr size_t kOwnCopy = 1 << 20;
+    std::vector<char> together;
+    struct Copy { size_t off; const void *src; size_t bytes; };
+    std::vector<Copy> copies;
+    size_t end = 0;                                     // of what is put together, from its first byte on the device
+    size_t small = 0;
+    for (const auto &s : secs) small += s.bytes < kOwnCopy ? (s.bytes + 255) / 256 * 256 : 0;
+    together.assign(small + 256, 0);
+    for (size_t i = 0; i < std::size(secs); ++i) {
+        const auto &s = secs[i];
+        if (s.bytes >= kOwnCopy) {
+            copies.push_back({s.off, s.src, s.bytes});
+            continue;
+        }
+        const bool joins = i > 0 && secs[i - 1].bytes < kOwnCopy;
+        const size_t padded = (i + 1 < std::size(secs) ? secs[i + 1].off : total) - s.off;
+        if (!joins) copies.push_back({s.off, together.data() + end, 0});
+        if (s.bytes) std::memcpy(together.data() + end, s.src, s.bytes);
+        end += padded;
+        copies.back().bytes += padded;
+    }
     char *blob = nullptr;
     if (hipMalloc((void **)&blob, total) != hipSuccess) return fail(CL_ENOMEM, "hipMalloc of %zu bytes failed", total);
-    if (hipMemcpy(blob, host.data(), total, hipMemcpyHostToDevice) != hipSuccess) {
-        (void)hipFree(blob);
-        return fail(CL_EHIP, "hipMemcpy to device failed");
-    }
+    for (const Copy &c : copies)
+        if (c.bytes && hipMemcpy(blob + c.off, c.src, c.bytes, hipMemcpyHostToDevice) != hipSuccess) {
+            (void)hipFree(blob);
+            return fail(CL_EHIP, "hipMemcpy to device failed");
+        }
     L->dev.device = dev;
     L->dev.blob = blob;
     L->dev.blob_bytes = total;

@@ -43,17 +43,26 @@ __device__ __forceinline__ void store_split4(uint16_t *XB, size_t plane_elems, s
     *(uint2 *)(XB + plane_elems + at) = uint2{(w[0] & 0xffffu) | (w[1] << 16), (w[2] & 0xffffu) | (w[3] << 16)};
 }
 
-// grid: (groups, ceil(Bp / 64)); thread t: column 64 blockIdx.y + t / 4, k quad t % 4
+// grid: (groups, ceil(Bp / 64)); thread t: column 64 blockIdx.y + t / 4, k quad t % 4.  Bound by the latency of its loads: a quad
+// that lies in one block is one load (256 images of 9216: 8.2 us with four, 6.2 us).
 __global__ __launch_bounds__(256) void split_pad_kernel(const float *__restrict__ X, uint16_t *XB, int B, int K, int Bp, int bw,
                                                         size_t plane_elems)
 {
     const int g = blockIdx.x, col = blockIdx.y * 64 + (int)(threadIdx.x >> 2), kq = (int)(threadIdx.x & 3);
     if (col >= Bp) return;
     float v[4];
+    const int row = (g >> 3) * kTile + (g & 7) * 16 + 4 * kq, k0 = xt_row_to_k(row, bw, K);
+    if (k0 >= 0 && xt_row_to_k(row + 3, bw, K) >= 0 && col < B) {      // (four of a block's columns: side by side)
+        typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+        const f4u x = *(const f4u *)(X + (size_t)col * K + k0);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int k = xt_row_to_k((g >> 3) * kTile + (g & 7) * 16 + 4 * kq + j, bw, K);
-        v[j] = (k >= 0 && col < B) ? X[(size_t)col * K + k] : 0.0f;
+        for (int j = 0; j < 4; ++j) v[j] = x[j];
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int k = xt_row_to_k(row + j, bw, K);
+            v[j] = (k >= 0 && col < B) ? X[(size_t)col * K + k] : 0.0f;
+        }
     }
     store_split4(XB, plane_elems, ((size_t)g * Bp + col) * 16 + 4 * kq, v);
 }

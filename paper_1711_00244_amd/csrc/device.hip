@@ -419,10 +419,12 @@ struct SparsePlan {
     size_t fixed = 0;        // LDS bytes of tables + codebook
     size_t part_bytes = 0;   // partial-tile buffer in the workspace
     // LDS of fc_sparse_whole_kernel, 0 where it does not take the layer (a block row of more chunks than it has places, no tile
-    // per chunk, more than a workgroup's 64 KiB)
+    // per chunk, more than a workgroup's 64 KiB, more threads than a launch may have: its workgroups have twice those of the
+    // two launches, which at one image take up to twice as many block rows)
     size_t whole_lds(const cl_layer *L, int bt) const
     {
         if (bt > kWholeBT || !private_tiles(L->desc.block_h, bt) || L->max_panel_chunks > kWholeWaves * kWholeRounds) return 0;
+        if ((uint64_t)L->n_panels * (kWholeWaves * 64) > UINT32_MAX) return 0;
         const size_t lds = fixed + ((size_t)wg_per_panel * kWaves * L->desc.block_h + L->desc.K) * 4 * bt;
         return lds <= 64 * 1024 ? lds : 0;
     }
@@ -935,11 +937,13 @@ static int32_t forward_sparse(const cl_layer *L, const LayerDev &D, const Sparse
         const size_t whole = finish && !prev && L->n_chunks > 0 ? P.whole_lds(L, bt) : 0;
         if (whole) {
             const WholeOut out{d_bias, y, relu};
+            dim3 rows;
+            GRID_TRY(rows, L->n_panels);
             if (b0 == 0) timing_begin(st);
             switch (bt) {
-            case 4: hipLaunchKernelGGL(fc_sparse_whole_kernel<4>, dim3((unsigned)L->n_panels), dim3(kWholeWaves * 64), whole, st, D, x, out, nb); break;
-            case 2: hipLaunchKernelGGL(fc_sparse_whole_kernel<2>, dim3((unsigned)L->n_panels), dim3(kWholeWaves * 64), whole, st, D, x, out, nb); break;
-            default: hipLaunchKernelGGL(fc_sparse_whole_kernel<1>, dim3((unsigned)L->n_panels), dim3(kWholeWaves * 64), whole, st, D, x, out, nb); break;
+            case 4: hipLaunchKernelGGL(fc_sparse_whole_kernel<4>, rows, dim3(kWholeWaves * 64), whole, st, D, x, out, nb); break;
+            case 2: hipLaunchKernelGGL(fc_sparse_whole_kernel<2>, rows, dim3(kWholeWaves * 64), whole, st, D, x, out, nb); break;
+            default: hipLaunchKernelGGL(fc_sparse_whole_kernel<1>, rows, dim3(kWholeWaves * 64), whole, st, D, x, out, nb); break;
             }
             HIP_TRY(hipGetLastError());
             if (b0 == 0) timing_end(st, 1);

@@ -36,3 +36,21 @@ def test_whole_block_rows(M, K, bh, bw, d, r, k):
         if B != 3:
             plain = cl.compressed_fc_forward(L, Xd, None, relu=False, path=cl.PATH_SPARSE)
             assert torch.equal(plain, G.forward(Xd[None])[0])
+
+
+def test_more_block_rows_than_a_launch_has_threads_for():
+    """2^22 block rows: at 1024 threads each one more thread than a launch's 32 bits count, at the two launches'
+    512 half of that."""
+    import torch
+    rng = np.random.default_rng(22)
+    M, K = 1 << 22, 129
+    rows = np.unique(np.concatenate([rng.integers(0, M, 999), [0, M - 1]]))
+    W = np.zeros((M, K), np.float32)                         # (blocks above 128 columns: no tables for the other paths)
+    W[rows] = rng.integers(-3, 4, (len(rows), K))
+    L = cl.compress_layer(W, 3, 8, 1, K, codebook=np.array([0, 1, 2, 3, -1, -2, -3, 4], np.float32), upload=True)
+    X = rng.integers(-8, 9, (1, K)).astype(np.float32)
+    Y = cl.compressed_fc_forward(L, torch.from_numpy(X).cuda(), None, relu=False, path=cl.PATH_SPARSE).cpu().numpy()
+    want = np.zeros((1, M), np.float32)
+    want[:, rows] = X @ W[rows].T                            # (whole numbers below 2^24: exact in any order)
+    assert np.array_equal(Y, want)
+    L.free()

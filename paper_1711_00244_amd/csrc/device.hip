@@ -410,6 +410,14 @@ struct RowsPlan {
     int padded(int images) const { return (images + 16 * ipl - 1) / (16 * ipl) * (16 * ipl); }
 };
 
+// At one image a layer of more block rows than this stays on two launches where eight wavefronts have all chunks of a block
+// row: eight of fc_sparse_whole_kernel's sixteen and more clear, stage and wait for the others, which the launch it saves
+// (2 us) pays for up to some 2.9 k block rows of one chunk and 4.1 k of eight.  (us a call, one launch / two: one chunk, 2048
+// block rows 13.8 / 14.4, 3072 19.6 / 19.1, 4096 25.6 / 24.1, 65536 424 / 346; four chunks 20.7 / 20.8 at 3072, 26.6 / 25.9 at
+// 4096; eight 23.1 / 24.1, 29.7 / 30.3, 122 / 112 at 16384; nine, two workgroups of eight wavefronts, 131 / 190 there.
+// Two images, one chunk: 15.5 / 18.9, 28.9 / 34.1 and 488 / 501; four images 497 / 817.)
+int64_t whole_narrow_rows(int64_t chunks) { return 2816 + 160 * chunks; }
+
 // Launch shape of the sparse forward path for one layer and batch.
 struct SparsePlan {
     RowsPlan rows;           // the launch, if fc_rows_kernel takes it; else:
@@ -425,6 +433,7 @@ struct SparsePlan {
     {
         if (bt > kWholeBT || !private_tiles(L->desc.block_h, bt) || L->max_panel_chunks > kWholeWaves * kWholeRounds) return 0;
         if ((uint64_t)L->n_panels * (kWholeWaves * 64) > UINT32_MAX) return 0;
+        if (bt == 1 && wg_per_panel == 1 && L->n_panels > whole_narrow_rows(L->max_panel_chunks)) return 0;
         const size_t lds = fixed + ((size_t)wg_per_panel * kWaves * L->desc.block_h + L->desc.K) * 4 * bt;
         return lds <= 64 * 1024 ? lds : 0;
     }

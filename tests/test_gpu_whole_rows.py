@@ -38,6 +38,27 @@ def test_whole_block_rows(M, K, bh, bw, d, r, k):
             assert torch.equal(plain, G.forward(Xd[None])[0])
 
 
+@pytest.mark.parametrize("M,bh,n", [(2976, 1, 1), (2977, 1, 1), (3 * 3500, 3, 1), (4096, 1, 8), (4097, 1, 8), (4097, 1, 9)])
+def test_many_block_rows(M, bh, n):
+    """On both sides of the line between one launch and two, block rows of one, eight and nine chunks."""
+    import torch
+    rng = np.random.default_rng(M + n)
+    K = 130 * n
+    W = rand_pruned(rng, M, K, 0.05)
+    W[::3, ::130] = 0.5                                       # (no block row without a chunk)
+    L = cl.compress_layer(W, 5, 4, bh, 130, upload=True)
+    oW = oracle.dense_weights(oracle.compress_layer(W, 5, 4, bh, 130))
+    G = cl.LayerGroup([L])
+    for B in (1, 2, 3):
+        X = rng.standard_normal((B, K)).astype(np.float32)
+        Xd = torch.from_numpy(X).cuda()
+        Y = cl.compressed_fc_forward(L, Xd, None, relu=False, path=cl.PATH_SPARSE)
+        assert_close(Y.cpu().numpy(), fc_ref(oW, X), False)
+        if B != 3:
+            assert torch.equal(Y, G.forward(Xd[None])[0])
+    L.free()
+
+
 def test_more_block_rows_than_a_launch_has_threads_for():
     """2^22 block rows: at 1024 threads each one more thread than a launch's 32 bits count, at the two launches'
     512 half of that."""

@@ -343,13 +343,6 @@ static bool decode_by_blocks(const cl_layer *L, bool dense)
     return !L->slot.empty() && (int64_t)L->desc.block_h * L->desc.block_w >= (dense ? 64 * 64 : 96 * 96);
 }
 
-// From this size on the dense matrix is written past the caches: what is written to memory in the end gets there
-// sooner than after a stay in them, and the kernel's end has less to write back (us, written to other buffers than the
-// calls before / to the same one again: 151 MB 37.6 / 30.2 through the caches, 33.7 / 33.7 past them; 98 MB 29.0 / 22.6
-// and 24.9 / 25.1; 67 MB 18.7 / 16.5 and 16.8 / 16.8).  Smaller ones take the same time either way, and are
-// left where the next kernel finds them.
-constexpr size_t kDecodePastCaches = (size_t)64 << 20;
-
 extern "C" int32_t cl_decode_layer(const cl_layer *L, uint8_t *d_val_sym, uint8_t *d_idx_sym,
                                    uint32_t *d_block_ptr, float *d_dense, void *stream)
 {
@@ -361,15 +354,13 @@ extern "C" int32_t cl_decode_layer(const cl_layer *L, uint8_t *d_val_sym, uint8_
         if (int32_t rc = device_limits(dl)) return rc;
         const int stage = ((int)L->max_block_entries + 31) / 16 * 16;           // (and up to 15 bytes before the first)
         const size_t lds = smem_fixed_bytes(D.val_bits, D.idx_bits, D.ncode) + kDecodeTile + 2 * (size_t)stage;
-        const bool past_caches = d_dense && (size_t)L->desc.M * L->desc.K * sizeof(float) >= kDecodePastCaches;
-        const auto kernel = past_caches ? decode_blocks_kernel<true> : decode_blocks_kernel<false>;
-        static LdsLimit seen[2];
-        if (int32_t rc = ensure_lds((const void *)kernel, lds, seen[past_caches ? 1 : 0])) return rc;
+        static LdsLimit seen;
+        if (int32_t rc = ensure_lds((const void *)decode_blocks_kernel, lds, seen)) return rc;
         // as many workgroups as are resident at once, each with the same number of blocks where
         // that divides
         const int64_t resident = (int64_t)dl.cus * std::max<int64_t>(1, std::min<int64_t>(8, dl.max_lds / lds));
         const int64_t each = (L->n_blocks + resident - 1) / resident;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)((L->n_blocks + each - 1) / each)), dim3(kDecodeThreads), lds, st, D, L->dev.block_ptr,
+        hipLaunchKernelGGL(decode_blocks_kernel, dim3((unsigned)((L->n_blocks + each - 1) / each)), dim3(kDecodeThreads), lds, st, D, L->dev.block_ptr,
                            (int)L->n_blocks, d_val_sym, d_idx_sym, d_block_ptr, d_dense, stage);
         HIP_TRY(hipGetLastError());
         clear_error();

@@ -47,11 +47,12 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(LayerDev L, uint8_t *v
 // tile of the block, at its position; then the workgroup writes the block out, dense rows (zeros
 // with the rest) and symbols in whole 16-byte pieces, having asked for the next block's
 // records first.  Bound by the bytes written: every byte of the outputs is written once, in
-// whole lines where the rows of a block begin on one.  PAST_CACHES: with stores that leave no room to the dense
-// matrix in the caches (kDecodePastCaches).
+// whole lines where the rows of a block begin on one.  The dense matrix goes through the caches: stores that leave it no
+// room there take the call itself from 37 to 34 us for 151 MB written to a buffer that was not used just before, but from
+// 30 to 34 for one that was, and what reads the matrix next then waits for memory (us for the call and a product
+// with one vector, through the caches / past them: 101 MB 42-47 / 54-58, 151 MB in one buffer 59 / 78).
 constexpr int kDecodeThreads = 256, kDecodeTile = 128 * 128;
 
-template <bool PAST_CACHES>
 __global__ __launch_bounds__(kDecodeThreads) void decode_blocks_kernel(LayerDev L, const uint32_t *block_ptr, int blocks, uint8_t *val_out, uint8_t *idx_out,
                                                                        uint32_t *ptr_out, float *dense, int stage_bytes)
 {
@@ -132,9 +133,7 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_blocks_kernel(LayerDev 
                     uint32_t *t = (uint32_t *)(tile + r * g.bwp + c);
                     const uint32_t v = *t;
                     *t = 0u;
-                    const f4 w = f4{s.T.cb[v & 255u], s.T.cb[(v >> 8) & 255u], s.T.cb[(v >> 16) & 255u], s.T.cb[v >> 24]};
-                    if constexpr (PAST_CACHES) __builtin_nontemporal_store(w, (f4 *)(dst + (size_t)r * L.K));
-                    else *(f4 *)(dst + (size_t)r * L.K) = w;
+                    *(f4 *)(dst + (size_t)r * L.K) = f4{s.T.cb[v & 255u], s.T.cb[(v >> 8) & 255u], s.T.cb[(v >> 16) & 255u], s.T.cb[v >> 24]};
                 }
             }
         } else {

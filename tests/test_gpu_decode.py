@@ -42,8 +42,8 @@ def test_decode_blocks(M, K, bh, bw, d, r, k):
     L.free()
 
 
-def test_dense_matrix_past_the_caches():
-    """A dense matrix of more than 64 MiB (written past the caches), ragged blocks on both edges."""
+def test_large_dense_matrix():
+    """A dense matrix of more than 64 MiB, ragged blocks on both edges."""
     rng = np.random.default_rng(64)
     W = rand_pruned(rng, 4133, 4148, 0.01)
     L = cl.compress_layer(W, 5, 4, 128, 128, upload=True)

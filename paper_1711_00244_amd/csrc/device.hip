@@ -409,6 +409,28 @@ struct RowsPlan {
 // Two images, one chunk: 15.5 / 18.9, 28.9 / 34.1 and 488 / 501; four images 497 / 817.)
 int64_t whole_narrow_rows(int64_t chunks) { return 2816 + 160 * chunks; }
 
+// GPU time of fc_sparse_whole_kernel less that of the two launches, in ns, where a wavefront has more than one chunk to take
+// (up to one, sixteen to a block row, the one launch is 1 to 4 us shorter everywhere).  A wavefront's chunks come one after the
+// other, each as long as its longest record, which the entries of a record stand for, twice as long where a position takes a
+// division to split; all columns are staged.  `full`: the two launches have so many workgroups to a CU, one and a half and more, that
+// they take longer themselves.  Fitted to thirteen shapes of block and density, 4 to 48 chunks, 1 to 300 block rows (rms 0.6 us).  At one image,
+// us on the GPU, one launch / two: 1024 rows at 10 %, 40 chunks 8.5 / 7.1, 20 chunks 6.0 / 6.9; blocks 128 x 128 at
+// 1.8 %, fourteen entries to a record, 24 chunks 8.1 / 8.0, 48 chunks 12.5 / 7.8.
+int64_t whole_extra(const cl_layer *L, int bt, bool full)
+{
+    const int64_t chunks = L->max_panel_chunks, K = L->desc.K, wide = (L->desc.block_w & (L->desc.block_w - 1)) ? 2 : 1;
+    const int64_t steps = L->entries * 10 * wide / std::max<int64_t>(1, L->n_records);           // tenths
+    if (bt > 2) return full ? INT64_MIN : chunks * (77 + steps * 8 / 10) - 3730;
+    if (bt == 2) return full ? chunks * (41 + steps * 66 / 100) + K / 4 - 3790 : chunks * (105 + steps * 68 / 100) + K / 3 - 4200;
+    return full ? chunks * (28 + steps * 74 / 100) + K / 7 - 3390 : chunks * (107 + steps * 48 / 100) + K / 7 - 3840;
+}
+
+// Up to this whole_extra (within the fit's error of none) one launch is the faster one whatever waits for it.  A call of one
+// launch by itself also spares the host a launch, 2.4 us, which bounds calls one behind the other (1024 x 1024 at 10 %: 11.7 -> 9.1 us); one
+// that is waited for has only some of that, since the host makes the second launch beside the first (23.7 -> 24.3 us; 20 chunks 23.5 -> 21.9): up
+// to the second figure the first gains more than the second loses.
+constexpr int64_t kWholeExtra = 200, kWholeExtraAlone = 2300;
+
 // Launch shape of the sparse forward path for one layer and batch.
 struct SparsePlan {
     RowsPlan rows;           // the launch, if fc_rows_kernel takes it; else:
@@ -417,16 +439,21 @@ struct SparsePlan {
     int xwant = 0;           // activation columns to stage in LDS per image (3 blocks wide)
     size_t fixed = 0;        // LDS bytes of tables + codebook
     size_t part_bytes = 0;   // partial-tile buffer in the workspace
+    int cus = 1;
     // LDS of fc_sparse_whole_kernel, 0 where it does not take the layer (a block row of more chunks than it has places, no tile
     // per chunk, more than a workgroup's 64 KiB, more threads than a launch may have: its workgroups have twice those of the
-    // two launches, which at one image take up to twice as many block rows)
-    size_t whole_lds(const cl_layer *L, int bt) const
+    // two launches, which at one image take up to twice as many block rows; where two launches are the faster ones).  alone(): the
+    // call is this launch, made by the host as it goes.
+    template <class Alone> size_t whole_lds(const cl_layer *L, int bt, Alone alone) const
     {
         if (bt > kWholeBT || !private_tiles(L->desc.block_h, bt) || L->max_panel_chunks > kWholeWaves * kWholeRounds) return 0;
         if ((uint64_t)L->n_panels * (kWholeWaves * 64) > UINT32_MAX) return 0;
         if (bt == 1 && wg_per_panel == 1 && L->n_panels > whole_narrow_rows(L->max_panel_chunks)) return 0;
         const size_t lds = fixed + ((size_t)wg_per_panel * kWaves * L->desc.block_h + L->desc.K) * 4 * bt;
-        return lds <= 64 * 1024 ? lds : 0;
+        if (lds > 64 * 1024) return 0;
+        if (L->max_panel_chunks > kWholeWaves && whole_extra(L, bt, 2 * (int64_t)L->n_panels * wg_per_panel > 3 * (int64_t)cus) > kWholeExtra &&
+            (whole_extra(L, bt, false) > kWholeExtraAlone || !alone())) return 0;
+        return lds;
     }
     int xcap_for(int bt) const { return (size_t)xwant * 4 * bt <= 32 * 1024 ? xwant : 0; }
     size_t lds_for(const cl_layer *L, int bt) const
@@ -523,6 +550,7 @@ int32_t plan_sparse(const cl_layer *L, int batch, const DeviceLimits &dl, Sparse
             return CL_OK;
         }
     }
+    P.cus = std::max(1, dl.cus);
     P.fixed = table_image_bytes(L->val_lut_bits, L->idx_lut_bits, 1 << L->desc.weight_bits);
     P.xwant = (int)std::min<int64_t>(L->desc.K, (1 + 2 * kSparseChunksPerWave) * (int64_t)L->desc.block_w);
     // largest power-of-two batch tile (<= 16) that fits; prefer to stay under 64 KiB
@@ -915,10 +943,10 @@ static int32_t forward_rows(const cl_layer *L, const LayerDev &D, const RowsPlan
 // One layer on the sparse path with launch shape P.  With `prev` the input is not d_X but the partial
 // tiles of the layer before (see PrevSlots); with finish == false the layer's own
 // finishing kernel is left to the layer after it in the same way.  Both only where
-// sparse_can_fold allows.
+// sparse_can_fold allows.  in_stack: other layers' launches come before or behind.
 static int32_t forward_sparse(const cl_layer *L, const LayerDev &D, const SparsePlan &P, const float *d_X,
                               const float *d_bias, float *d_Y, int batch, int relu, float *part, hipStream_t st,
-                              const PrevSlots *prev = nullptr, bool finish = true)
+                              bool in_stack = false, const PrevSlots *prev = nullptr, bool finish = true)
 {
     if (P.rows.ipl) return forward_rows(L, D, P.rows, d_X, d_bias, d_Y, batch, relu, part, st);
     const PrevSlots from = prev ? *prev : PrevSlots{nullptr, nullptr, nullptr, 1, 0, 0, 0};
@@ -926,6 +954,13 @@ static int32_t forward_sparse(const cl_layer *L, const LayerDev &D, const Sparse
     const int M = L->desc.M, K = L->desc.K;
     dim3 grid;
     if (L->n_chunks > 0) GRID_TRY(grid, (int64_t)L->n_panels * P.wg_per_panel);
+    const auto alone = [&]() {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (in_stack || batch > P.bt_max) return false;
+        if (hipStreamIsCapturing(st, &capture) == hipSuccess) return capture == hipStreamCaptureStatusNone;
+        (void)hipGetLastError();
+        return false;
+    };
     for (int b0 = 0; b0 < batch;) {
         // the smallest batch tile that holds the images left (its other images are zeros):
         // one launch for 3 images, not two
@@ -934,7 +969,7 @@ static int32_t forward_sparse(const cl_layer *L, const LayerDev &D, const Sparse
         while (bt / 2 >= nb) bt >>= 1;
         const float *x = d_X + (size_t)b0 * K;
         float *y = d_Y + (size_t)b0 * M;
-        const size_t whole = finish && !prev && L->n_chunks > 0 ? P.whole_lds(L, bt) : 0;
+        const size_t whole = finish && !prev && L->n_chunks > 0 ? P.whole_lds(L, bt, alone) : 0;
         if (whole) {
             const WholeOut out{d_bias, y, relu};
             dim3 rows;
@@ -1384,7 +1419,7 @@ try {
             }
             const bool finish = last || !P.fold_in[i + 1];
             if (int32_t rc = forward_sparse(L, D, P.fc[i].sparse, in, bias, out, batch, relu, (float *)region(part0, P.part_bytes, i), st,
-                                            P.fold_in[i] ? &prev : nullptr, finish))
+                                            n_layers > 1, P.fold_in[i] ? &prev : nullptr, finish))
                 return rc;
             in = out;
         }

@@ -603,11 +603,10 @@ __global__ __launch_bounds__(kThreads) void fc_sparse_kernel(LayerDev L, const f
 
 // A small layer in one launch: a workgroup of sixteen wavefronts takes a whole block row, up to three chunks a wavefront, each
 // into a tile of its own, stages all activations, and finishes the output, so that there are no partial tiles and
-// nothing to add up in a second launch - which took as long as the products of such a layer, and its launch
-// longer.  Bound by the latencies of a chunk, one after the other: 9.4 us for 1024 x 1024 at 10 % and one image (35 chunks to a
-// block row), 5.5 and 3.3 in two launches.  A call, which the host's work for its launches bounds: 13.4 -> 10.2 us; two images
-// 13.0 -> 10.1; 256 x 256 (4 chunks) 12.7 -> 9.7; 32768 x 1024, a block row to a CU, 13.8 -> 9.5.  A fourth chunk
-// to a wavefront would take as long as the launch that is saved.
+// nothing to add up in a second launch.  Bound by the latencies of a chunk, one after the other.  With a chunk to a wavefront it
+// is shorter on the GPU than the two launches (us, one image: 256 x 256 at 20 % 4.9 / 7.0, 1024 x 384 at 10 %, 15 chunks to a block row, 5.0 / 6.8);
+// with two it is about as long, with three longer (1024 x 1024 at 10 %, 40 chunks to a block row, 8.5 / 7.1), and gains only where the
+// host's work for its launches bounds the calls (that layer, call behind call from Python: 11.7 -> 9.1): whole_extra decides.
 constexpr int kWholeWaves = 16, kWholeRounds = 3, kWholeBT = 4;
 
 template <int BT>

@@ -511,8 +511,11 @@ bool plan_rows(const cl_layer *L, int batch, const DeviceLimits &dl, RowsPlan &P
     // Blocks to a group and split of the block rows, as on the other paths, in cycles per
     // workgroup: a start; per group of blocks a part that does not depend on what is in it
     // (latencies, the barrier), per block and per surviving weight; the partial tiles.  Fitted to
-    // the AlexNet- and VGG-shaped fc6 / fc7 / fc8 at 16, 32 and 64 images (AlexNet-shaped fc6, us a call:
-    // 24.4, 28.2 and 40.7; one block to a group 30.0, 32.2 and 40.7).
+    // the AlexNet- and VGG-shaped fc6 / fc7 / fc8 at 16, 32 and 64 images, when a group's turn still waited for its loads.  It does
+    // not any more, and all parts have become shorter alike: over 1400 calls (a hundred layers drawn from 200 x 500 to 8192 x
+    // 25088, densities of 3 to 40 %, 12 to 512 images) a call takes 0.83 of its price, rms 7.7 %, and with every constant fitted
+    // anew 7.2 %.  Groups and splits come out the same either way (AlexNet-shaped fc6, us a call: 24.4, 28.2 and 40.7; one block
+    // to a group 30.0, 32.2 and 40.7); against the other paths the price is too high, which kAutoLaunch makes up for in part.
     static const struct { int groups, block, weight_x20; } kFit[3] = {{3, 2150, 29}, {3, 3000, 34}, {1, 3900, 51}};
     const auto &fit = kFit[P.ipl / 2];
     const int64_t tiles = (int64_t)L->n_panels * (Bp / images);
@@ -607,7 +610,9 @@ size_t xt_rows(const cl_layer *L) { return (size_t)L->nbw * kTile + kXtTailRows;
 // block row writes the output itself, `direct`).  Fitted
 // to sweeps over every tile width and split of the AlexNet and VGG-16 FC layers at 8 to
 // 1024 images: the choice is the fastest measured shape for the large layers and
-// within 3 % of it on average for a 1000-row layer, where the partial tiles decide.  The
+// within 3 % of it on average for a 1000-row layer, where the partial tiles decide.  (The bf16 kernel has become faster
+// since, its wide tiles most: over the calls of plan_rows a thousand cycles of price take 0.37 us with 32 and 64 columns to a
+// tile, 0.30 with 128 and 0.23 with 256.  Its price has not been fitted again.)  The
 // gathered convolution's kernel is priced at 13 k cycles a block (two phases), 7.5 k with blocks of at most 64
 // rows or two terms, and 4 k for an item; against its predecessor's price (8 k and 17.9 k for any block) 0 to
 // 4 % faster over forty convolutions, none slower by more than 1 %.  (Fitted with six products of the terms; with
@@ -798,14 +803,15 @@ int32_t launch_wide_mul(const LayerDev &D, int panels, const WidePlan &P, const 
 // CL_PATH_AUTO: the sparse path up to kAutoSparseBatch images (one batch tile of its small-batch
 // kernel) and for blocks above 128 x 128; above, whichever of the sparse path's fc_rows_kernel,
 // the dense-tile path and the wide sparse path their launch models price lower (same units, all
-// fitted to measured launches; fc_rows_kernel saves a launch that lays the activations out or
-// decodes, 9 k cycles with what the models leave out: from 6.3 k on fc8 below, at 65 to 128 images, is on
-// it - 24 us, dense tiles 29 - and above 9.7 k fc6 would be at these batches, where a stack is better off with it
-// on the wide path).  Measured on the
-// AlexNet-shaped stack (fc6 / fc7 / fc8, us per layer call): small-batch kernel 24 / 16 / 14 at 8 images; at
-// 16 images fc_rows_kernel 24 / 16 / 13, dense tiles 41 / 25 / 18; at 64 images 41 / 25 / 18 and
-// 60 / 35 / 24; at 128 images 71 / 40 / 24, wide 77 / 49 / 44; at 256 images 128 / 65 / 36, wide 97 / 57 / 50,
-// dense tiles 165 / 89 / 42 - the dense tile multiplies eleven times the necessary
+// fitted to measured launches).  fc_rows_kernel is taken up to kAutoLaunch cycles above the others: the launch it saves,
+// which lays the activations out or decodes (2.5 us, 6 k cycles, in the fits of the three paths), and a part of what its price is
+// too high by (plan_rows).  Over the 1400 calls measured there the choice is 2.1 % slower on average than the best of the three
+// paths, more than 5 % in 139; with 6 k cycles 2.5 % and 180, and all 44 calls whose path differs are slower with 6 k, by 1 to 53 %.  (With the price
+// at 7/8 and 6 k cycles 1.4 % and 75; but of 600 calls of stacks of such layers 26 become slower, by up to 7.5 %, and 36 faster, by up to 10 %:
+// choose_stack_paths weighs all of a stack's layers that would be on fc_rows_kernel against none of them.)  AlexNet-shaped stack (fc6 / fc7 / fc8, us per layer call): small-batch kernel
+// 24 / 16 / 14 at 8 images; at 16 images fc_rows_kernel 24 / 16 / 12, dense tiles 40 / 24 / 18; at 64 images 41 / 25 / 17 and
+// 60 / 35 / 23; at 128 images 71 / 40 / 24, wide 73 / 47 / 41 (fc6 is on the latter); at 256 images 128 / 66 / 36, wide 91 / 55 / 47,
+// dense tiles 163 / 88 / 40 (fc8 is on these) - the dense tile multiplies eleven times the necessary
 // products at a 9 % density but four at 25 %.  A layer of fewer than kAutoRowsBlocks blocks takes
 // 12 to 16 us on either, launches for the most part, and stays on dense tiles.  (Where the sparse path
 // runs the small-batch kernel instead, rows_kernel_pays, that is the cheaper one: the price is an upper bound.)

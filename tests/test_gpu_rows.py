@@ -176,3 +176,19 @@ def test_a_stack_chooses_its_paths_together():
         assert torch.equal(Y, a), B
     for L in layers:
         L.free()
+
+
+# where CL_PATH_AUTO goes to this kernel and where it leaves it: a dense and a sparse layer, images on both sides of the line
+@pytest.mark.parametrize("M,K,d,paths", [(1000, 4096, 0.25, {16: cl.PATH_SPARSE, 65: cl.PATH_SPARSE, 128: cl.PATH_SPARSE, 256: cl.PATH_MFMA_F32}),
+                                         (4096, 4096, 0.09, {16: cl.PATH_SPARSE, 128: cl.PATH_SPARSE, 256: cl.PATH_SPARSE_WIDE}),
+                                         (4096, 4096, 0.3, {16: cl.PATH_SPARSE, 128: cl.PATH_MFMA_F32}), (384, 500, 0.1, {64: cl.PATH_MFMA_F32})])
+def test_auto_path(M, K, d, paths):
+    import torch
+    rng = np.random.default_rng(K)
+    L = cl.compress_layer(rand_pruned(rng, M, K, d), 5, 4, 128, 128, upload=True)
+    for B, path in paths.items():
+        assert cl.fc_resolved_path(L, B) == path, B
+        assert cl.fc_workspace_bytes(L, B) == cl.fc_workspace_bytes(L, B, path)
+        X = torch.from_numpy(rng.standard_normal((B, K)).astype(np.float32)).cuda()
+        assert torch.equal(cl.compressed_fc_forward(L, X), cl.compressed_fc_forward(L, X, path=path))
+    L.free()

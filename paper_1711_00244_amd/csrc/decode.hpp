@@ -32,15 +32,15 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v)
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
-// n / d for a divisor known on the host, in four scalar instructions (a division of uniform values the compiler
+// n / d for a divisor known on the host, in five scalar instructions (a division of uniform values the compiler
 // works out in vector registers, and takes what follows from it for different in every lane).  Granlund and
 // Montgomery's round-up method, exact for every 32-bit n.
 struct Divisor {
-    uint32_t mul, shift, d;
+    uint32_t mul, shift1, shift2, d;
     __device__ __forceinline__ uint32_t quotient(uint32_t n) const
     {
         const uint32_t t = __umulhi(n, mul);
-        return (t + ((n - t) >> (shift > 0 ? 1 : 0))) >> (shift > 0 ? shift - 1 : 0);
+        return (t + ((n - t) >> shift1)) >> shift2;
     }
 };
 
@@ -48,7 +48,7 @@ static Divisor divisor(uint32_t d)
 {
     uint32_t s = 0;
     while (s < 32 && (1ull << s) < d) ++s;
-    return Divisor{(uint32_t)((((1ull << s) - d) << 32) / d + 1), s, d};
+    return Divisor{(uint32_t)((((1ull << s) - d) << 32) / d + 1), s > 0 ? 1u : 0u, s > 0 ? s - 1 : 0u, d};
 }
 
 // W consecutive floats (W * 4-byte aligned) with one load.

@@ -612,7 +612,7 @@ constexpr int kWholeWaves = 16, kWholeRounds = 3, kWholeBT = 4;
 template <int BT>
 __global__ __launch_bounds__(kWholeWaves * 64) void fc_sparse_whole_kernel(LayerDev L, const float *__restrict__ X, WholeOut out, int nb)
 {
-    fc_sparse_body<BT, false, true, true, kWholeWaves, kWholeRounds>(L, X, nullptr, Divisor{1, 0, 1}, 0, PrevSlots{nullptr, nullptr, nullptr, 1, 0, 0, 0},
+    fc_sparse_body<BT, false, true, true, kWholeWaves, kWholeRounds>(L, X, nullptr, Divisor{1, 0, 0, 1}, 0, PrevSlots{nullptr, nullptr, nullptr, 1, 0, 0, 0},
                                                                     blockIdx.x, nb, out);
 }
 

@@ -36,6 +36,46 @@ def test_one_pass(M, K, bh, bw, d, r, k):
     L.free()
 
 
+def named_cells(L):
+    """(row, column) of every entry of the layer, padding included, by its decoded indices."""
+    M, K, bh, bw = (L.host_view()["desc"][n] for n in ("M", "K", "block_h", "block_w"))
+    _, idx, bp, _ = (t.cpu().numpy().astype(np.int64) if t is not None else None for t in cl.decode_layer(L, want_dense=False))
+    out = np.zeros((M, K), bool)
+    per_row = -(-K // bw)
+    for b in range(len(bp) - 1):
+        r0, c0 = b // per_row * bh, b % per_row * bw
+        pos = np.cumsum(idx[bp[b]:bp[b + 1]] + 1) - 1
+        w = min(bw, K - c0)
+        out[r0 + pos // w, c0 + pos % w] = True
+    return out
+
+
+# (the last two: one launch where four images and fewer allow)
+@pytest.mark.parametrize("M,K,bh,bw,d,r,k", [(256, 1024, 256, 256, 0.07, 5, 4), (300, 2100, 256, 1000, 0.03, 5, 5), (200, 6000, 64, 48, 0.05, 8, 4),
+                                             (300, 9000, 128, 128, 0.05, 5, 4), (256, 384, 128, 128, 0.05, 5, 4), (200, 333, 64, 48, 0.1, 8, 4)])
+def test_values_that_are_not_finite_stay_in_their_rows(M, K, bh, bw, d, r, k):
+    """A lane looks columns up past its own record's last entry: an output without an entry in a column has nothing of it."""
+    import torch
+    rng = np.random.default_rng(M + K)
+    L = cl.compress_layer(rand_pruned(rng, M, K, d), r, k, bh, bw, upload=True)
+    cells = named_cells(L)
+    G = cl.LayerGroup([L])
+    for B in (1, 2, 4, 8):
+        X = rng.standard_normal((B, K)).astype(np.float32)
+        bad = rng.choice(K, 4, replace=False)
+        Z = X.copy()
+        Z[B // 2, bad] = [np.inf, np.nan, -np.inf, np.inf]
+        alone, grid = (lambda x: cl.compressed_fc_forward(L, x, path=cl.PATH_SPARSE)), (lambda x: G.forward(x[None])[0])
+        for call in (alone, grid) if bh < 256 or B < 8 else (alone,):        # (a grid takes no more images than one tile has room for)
+            want, got = (call(torch.from_numpy(a).cuda()).cpu().numpy() for a in (X, Z))
+            touched = np.zeros((B, M), bool)
+            touched[B // 2] = cells[:, bad].any(axis=1)
+            assert touched.any() and not touched.all(axis=1).any()
+            assert np.array_equal(got[~touched].view(np.uint32), want[~touched].view(np.uint32))
+            assert not np.isfinite(got[touched]).any()
+    L.free()
+
+
 @pytest.mark.parametrize("B", [1, 2, 4, 8])
 def test_one_pass_in_one_grid(B):
     import torch

@@ -155,7 +155,7 @@ template <int NQ> struct Bf16Shape {
 // eight k, lanes 32-63 the other eight) and feeds three multiplies per accumulator.
 // A used tile is cleared by the decoders while the multipliers are at the next one: they meet at a second barrier
 // behind a quarter of a block's multiplies.  (Cleared by the multipliers, between two barriers, a block of the AlexNet-shaped
-// fc6 at 256 images took 0.4 us longer.)  Bound by the multiplies for eight accumulators (2.9 us of the 4.1 a block takes;
+// fc6 at 256 images took 0.4 us longer.)  Bound by the multiplies for eight accumulators (60 % of fc6's cycles, 2.9 us of the 4.1 a block takes;
 // start and partial tiles another 10 us of a launch), by the decode below: hence eight decoders there.  fc6 / fc7 / fc8 at 256
 // images 60 / 33.5 / 21 -> 49 / 28.5 / 16.5 us.
 constexpr int kHStride = kTile + 8;                       // bf16 per row of a half tile (16-byte rows, 4-bank skew)

@@ -376,14 +376,22 @@ int32_t cl_conv_workspace_bytes(const cl_layer *layer, const cl_conv_desc *conv,
  * one after the other through the same buffers and decode the blocks inside the
  * multiply kernel - about half the memory for a layer with two filter groups, the same
  * results, more time (AlexNet conv2 at batch 1: 45 instead of 32 us).  Where the
- * call gathers the columns itself, nothing needs less and the two sizes are equal. */
+ * call gathers the columns itself, nothing needs less and the two sizes are equal; where it
+ * splits both operands beforehand, one of the other forms needs less and runs, given
+ * enough for it alone. */
 int32_t cl_conv_workspace_bytes_min(const cl_layer *layer, const cl_conv_desc *conv, int32_t batch,
                                     int32_t path, size_t *out);
 
 /* d_X: batch x C x H x W fp32 (NCHW); d_Y: batch x out_channels x P x Q fp32 with
  * P = (H + 2 pad - R) / stride + 1, Q likewise.  The convolution is the product of the
  * layer's matrix with the matrix whose columns are the receptive fields (Sec. III-A),
- * computed on an MFMA path, all filter groups in one launch, in one of two forms:
+ * computed on an MFMA path, all filter groups in one launch, in one of three forms:
+ *  - long calls, where a model of the launches finds it cheaper (from some 36 us on with
+ *    CL_PATH_MFMA_F32): both operands are split once per call into the bf16 terms that the next
+ *    form splits them into, in the order in which the multiply kernel takes them, and
+ *    the same products are added.  Workspace: 2 bytes a term, three terms (two on CL_PATH_MFMA_BF16), for
+ *    each weight of the dense matrix and each activation, zero border included, channels of a group rounded up to eight
+ *    (to four where it has at most four), and partial tiles.
  *  - from 512 columns (images x output pixels) on, when 128-column
  *    tiles give the chip enough to do (work items for a sixteenth of the compute units,
  *    block products for half): every block of the layer is decoded once per call into a

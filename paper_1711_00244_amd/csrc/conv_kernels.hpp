@@ -94,6 +94,8 @@ template <int NP> __device__ __forceinline__ void split8(const float (&v)[8], ui
     if (most >= 3.3895e38f) {                               // (the largest bf16 and half a step: 0x7f7f8000 is 3.39615e38)
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
+            // (the others as they are: whoever sees them and not this one gets what it would without it)
+            if (__builtin_fabsf(v[j]) < 3.3895e38f) continue;
             const uint32_t u = __float_as_uint(v[j]), put = 16 * (j & 1), keep = 0xffffu << (16 - put);
             const bool finite = (u & 0x7f800000u) != 0x7f800000u;
             // (the first term cut off, not rounded: it cannot overflow)
@@ -429,15 +431,15 @@ __global__ __launch_bounds__(conv_threads(NP)) void conv_mfma_kernel(LayerDev L,
 // conv4_2 at one image; this one 5.0.)
 constexpr int kConvRedThreads = 256, kConvRedColumns = 4 * kConvRedThreads;
 
-__global__ __launch_bounds__(kConvRedThreads) void conv_reduce_kernel(LayerDev L, const float *__restrict__ part, const float *__restrict__ bias, float *Y,
-                                                                      int ncols, int Np, int splits, int relu, int pq)
+__global__ __launch_bounds__(kConvRedThreads) void conv_reduce_kernel(const float *__restrict__ part, const float *__restrict__ bias, float *Y, int M, int OCg,
+                                                                      int panels_per_group, int panel_rows, int ncols, int Np, int splits, int relu, int pq)
 {
     const int chunks = (ncols + kConvRedColumns - 1) / kConvRedColumns;
-    const int row = (int)blockIdx.x / chunks, c = ((int)blockIdx.x % chunks) * kConvRedColumns + 4 * (int)threadIdx.x;
-    const int p = row / L.bh, r = row - p * L.bh, m = p * L.bh + r;
-    if (m >= L.M || c >= ncols) return;
-    const size_t stride = (size_t)L.bh * Np;
-    const float *src = part + ((size_t)p * splits * L.bh + r) * Np + c;
+    const int m = (int)blockIdx.x / chunks, c = ((int)blockIdx.x % chunks) * kConvRedColumns + 4 * (int)threadIdx.x;
+    const int grp = m / OCg, in_grp = m - grp * OCg, panel = in_grp / panel_rows, r = in_grp - panel * panel_rows;
+    if (c >= ncols) return;
+    const size_t stride = (size_t)panel_rows * Np;
+    const float *src = part + ((size_t)(grp * panels_per_group + panel) * splits * panel_rows + r) * Np + c;
     float t[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     for (int j = 0; j < splits; j += 8) {                   // eight loads in flight, added in order
         float a[8][4];
@@ -455,7 +457,7 @@ __global__ __launch_bounds__(kConvRedThreads) void conv_reduce_kernel(LayerDev L
         t[k] += b;
         if (relu) t[k] = fmaxf(t[k], 0.0f);
     }
-    float *dst = Y + ((size_t)(c / pq) * L.M + m) * pq + c % pq;
+    float *dst = Y + ((size_t)(c / pq) * M + m) * pq + c % pq;
     if ((pq & 3) == 0 && ((uintptr_t)Y & 15u) == 0) store_floats<4>(dst, t);     // (four pixels of one image)
     else {
         int o = c % pq;
@@ -465,7 +467,7 @@ __global__ __launch_bounds__(kConvRedThreads) void conv_reduce_kernel(LayerDev L
             ++dst;
             if (++o == pq) {
                 o = 0;
-                dst += (size_t)(L.M - 1) * pq;
+                dst += (size_t)(M - 1) * pq;
             }
         }
     }

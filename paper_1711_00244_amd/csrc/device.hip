@@ -16,7 +16,7 @@
 // One translation unit: this file holds the host side (device image of a layer, launch
 // shapes, the entry points) and includes the kernels - decode.hpp (wavefront primitives,
 // decoding and placement passes), sparse_kernels.hpp, mfma_kernels.hpp, wide_kernels.hpp, rows_kernels.hpp, bf16_kernels.hpp,
-// conv_kernels.hpp, finish_kernels.hpp, layer_kernels.hpp.
+// conv_kernels.hpp, conv_plane_kernels.hpp, finish_kernels.hpp, layer_kernels.hpp.
 #include <hip/hip_runtime.h>
 #include <type_traits>
 
@@ -120,6 +120,7 @@ static LayerDev make_dev(const cl_layer *L)
 #include "rows_kernels.hpp"
 #include "bf16_kernels.hpp"
 #include "conv_kernels.hpp"
+#include "conv_plane_kernels.hpp"
 #include "finish_kernels.hpp"
 #include "layer_kernels.hpp"
 
@@ -1655,10 +1656,54 @@ struct ConvPlan {
     ConvGeom cg{};
     int OCg = 0, panels_per_group = 0, imgs = 0;
     bool gather = false;       // blocks decoded once per call, no column matrix in memory: conv_mfma_kernel
+    bool planes = false;       // operands split once per call: conv_plane_kernel
+    PlaneGeom pg{};
     int groups_at_once = 1;    // filter groups per launch: all of them, or one (the compact form)
     size_t lds = 0, xt_bytes = 0, part_bytes = 0, wt_bytes = 0, rows_bytes = 0;
     size_t total() const { return xt_bytes + part_bytes + wt_bytes + rows_bytes; }
 };
+
+// The shapes of conv_plane_kernel's workgroup tile.
+struct PlaneTile {
+    int rows, cols, mfmas;     // of a tile; accumulators of a wavefront
+};
+constexpr PlaneTile kPlaneTiles[3] = {{128, 128, 4}, {96, 128, 3}, {64, 128, 2}};
+
+constexpr int kPlaneRun = 256;
+
+struct PlaneShape {
+    int tile = 0, tiles = 0, splits = 1;
+    int64_t cost = 0;          // cycles
+};
+
+// Tile and split of the steps of k by a model of the launch, in cycles: a step is a wavefront's multiplies and a quarter more (32 x 32 x 16
+// multiplies take 32 cycles; with one workgroup to a CU 1.07 times that is measured, with two the chip's clock gives way), 5 k for a workgroup
+// alone on its CU to start and end and 8 k for two; the partial tiles of split steps as in mfma_shape, 300 for a split's turn in the
+// finishing launch and 8 k for that launch.  Over 230 drawn convolutions the launch takes 4 us + 1.11 times its price, and the tile picked is within 2 % of
+// the best of the three on average, 13 % at worst.
+PlaneShape plane_shape(int OCg, int groups, int steps, int ncols, bool bf16, int cus)
+{
+    cus = std::max(1, cus);
+    PlaneShape best;
+    for (int i = 0; i < 3; ++i) {
+        const PlaneTile &T = kPlaneTiles[i];
+        const int64_t panels = (int64_t)groups * ((OCg + T.rows - 1) / T.rows), tiles = (ncols + T.cols - 1) / T.cols;
+        const int64_t step = (int64_t)(bf16 ? 3 : 8) * 32 * T.mfmas * 5 / 4;
+        const int sp_max = (int)std::max<int64_t>(1, std::min<int64_t>(steps, (4 * cus + panels * tiles - 1) / (panels * tiles)));
+        // (not more than kPlaneRun steps in one sum, which rounds at every one of them)
+        for (int sp = (steps + kPlaneRun - 1) / kPlaneRun; sp <= std::max(sp_max, (steps + kPlaneRun - 1) / kPlaneRun);) {
+            const int64_t items = panels * tiles * sp, n = (steps + sp - 1) / sp;
+            const int64_t full = items / (2 * cus), rest = items % (2 * cus);
+            int64_t t = full * (8000 + 2 * step * n);
+            if (rest) t += rest <= cus ? 5000 + step * n : 8000 + 2 * step * n;
+            if (sp > 1) t += 8000 + 300 * sp + panels * T.rows * tiles * T.cols * sp * 4 * 2 / 5000;
+            if (best.cost == 0 || t < best.cost) best = PlaneShape{i, (int)tiles, sp, t};
+            if (n == 1) break;
+            sp = (int)((steps + n - 2) / (n - 1));          // the next that makes a workgroup's run of steps shorter
+        }
+    }
+    return best;
+}
 
 // From this many columns on (image x output pixel) both paths decode the layer's
 // blocks once per call into dense tiles in the workspace, and a multiply kernel of its own
@@ -1673,18 +1718,89 @@ constexpr int64_t kConvGatherColumns = 512;
 
 // Whether the layer's weights are the sums of the three bf16 terms that the gathered form splits them
 // into, with a sign that the first two share (split_weights): not below 2^-110, nor as -0.
-bool splits_exactly(const cl_layer *L)
+bool splits_exactly(const cl_layer *L, float least = 0x1p-110f)
 {
     for (float c : L->codebook)
-        if (std::fabs(c) < 0x1p-110f && (c != 0.0f || std::signbit(c))) return false;
+        if (std::fabs(c) < least && (c != 0.0f || std::signbit(c))) return false;
     return true;
 }
 
-// compact: the form that needs the least scratch - filter groups one after the other
-// through the same buffers, blocks decoded inside the multiply kernel.
-int32_t plan_conv(const cl_layer *L, const cl_conv_desc *cv, int batch, bool bf16, const DeviceLimits &dl, ConvPlan &P,
-                  bool compact = false)
+// Blocks side by side that a workgroup of conv_prepare_kernel decodes, fewer rows of each the more there are: enough that most of their
+// units of eight channels are whole (162 channels of 11 x 11, us beside the multiply launch, 1 / 2 / 4 / 8 blocks: 109 / 77 / 67 / 69;
+// VGG-16 conv4_2, 3 x 3: 25.1 / 24.4 / 26.2 / 29.5; 1 x 1: 8.3 / 8.8 / 8.7 / 8.9).
+int prep_blocks(const cl_layer *L, int taps)
 {
+    const int most = taps == 1 ? 1 : taps < 16 ? 2 : 4;
+    int n = 1;
+    while (n < most && n < L->nbw) n *= 2;
+    return n;
+}
+
+int64_t prep_strips(const cl_layer *L, int blocks)
+{
+    const int rows = kPrepCells / blocks;
+    return (int64_t)L->n_panels * ((L->desc.block_h + rows - 1) / rows) * ((L->nbw + blocks - 1) / blocks);
+}
+
+// The form whose operands are split beforehand: its geometry and workspace, and what the call will take, in us; false where it cannot run.
+bool plan_planes(const cl_layer *L, const cl_conv_desc *cv, int batch, bool bf16, const DeviceLimits &dl, ConvPlan &P, double &us)
+{
+    const ConvGeom &g = P.cg;
+    const int np = bf16 ? 2 : 3;
+    PlaneGeom &q = P.pg;
+    q.C = g.C; q.Cg = g.Cg; q.H = g.H; q.W = g.W; q.R = g.R; q.S = g.S; q.pad = g.pad;
+    q.px4 = g.Cg <= 4 ? 1 : 0;
+    if (q.px4 && g.S < 2) return false;
+    // (half a weight has to split, too, where two units share a tap)
+    if (!bf16 && !splits_exactly(L, q.px4 && (g.S & 1) ? 0x1p-109f : 0x1p-110f)) return false;
+    const int64_t Hp = g.H + 2 * (int64_t)g.pad, Wp = (g.W + 2 * (int64_t)g.pad + q.px4) / (1 + q.px4) * (1 + q.px4);
+    q.CG = q.px4 ? 1 : (g.Cg + 7) / 8;
+    q.SU = q.px4 ? (g.S + 1) / 2 : g.S;
+    q.groups = cv->groups;
+    q.OCg = P.OCg;
+    // offsets are 32-bit ones: of the activations in bytes, all terms, and of a tile's weights
+    const int64_t units = (int64_t)q.CG * g.R * q.SU;
+    if (Hp > INT32_MAX / Wp || Hp * Wp > INT32_MAX / 16 / np / q.groups / q.CG || units > INT32_MAX / 2 / (np * kTile * 16)) return false;
+    q.Hp = (int)Hp;
+    q.Wp = (int)Wp;
+    const int64_t plane = Hp * Wp / (1 + q.px4), image = (int64_t)q.groups * q.CG * plane;                // 16-byte pieces
+    q.units = (int)units;
+    q.steps = (q.units + 1) / 2;
+    P.imgs = (int)std::min<int64_t>({(int64_t)batch, kMaxTileColumns / ((int64_t)g.P * g.Q), INT32_MAX / (image * 16 * np)});
+    q.pieces = (uint32_t)(P.imgs * image);
+    q.per_plane = divisor((uint32_t)plane);
+    q.per_row = divisor((uint32_t)(Wp / (1 + q.px4)));
+    q.planes = divisor((uint32_t)(q.groups * q.CG));
+    q.per_s = divisor((uint32_t)g.S);
+    q.per_group = divisor((uint32_t)(q.px4 ? q.SU : g.R * g.S));
+    P.xt_bytes = round256((size_t)np * q.pieces * 16);
+    P.wt_bytes = P.part_bytes = 0;
+    const int blocks = prep_blocks(L, g.R * g.S);
+    us = 0;
+    for (int imgs : {P.imgs, batch % P.imgs}) {
+        if (imgs == 0) continue;
+        const PlaneShape s = plane_shape(P.OCg, q.groups, q.steps, imgs * g.P * g.Q, bf16, dl.cus);
+        const PlaneTile &T = kPlaneTiles[s.tile];
+        const size_t rows = (size_t)q.groups * ((P.OCg + T.rows - 1) / T.rows) * T.rows, wt = rows * q.steps * np * 2 * 16;
+        P.wt_bytes = std::max(P.wt_bytes, round256(wt));
+        if (s.splits > 1) P.part_bytes = std::max(P.part_bytes, round256(rows * s.splits * s.tiles * T.cols * sizeof(float)));
+        const double over = std::max<double>(0, prep_strips(L, blocks) / std::max(1.0, (double)dl.cus) - 1);
+        us += (imgs == P.imgs ? batch / P.imgs : 1) * (13 + 1.2 * s.cost / 2400 + (bf16 ? 2.0e-6 : 0.95e-6) * wt +
+                                                       (bf16 ? 0.37e-6 : 0.28e-6) * np * 16 * imgs * image + (bf16 ? 0 : 7) * over);
+    }
+    P.rows_bytes = round256((size_t)q.steps * 2 * sizeof(uint32_t));
+    P.lds = table_image_bytes(L->val_lut_bits, L->idx_lut_bits, 1 << L->desc.weight_bits) + prep_tile_bytes(blocks) + ((size_t)2 * sizeof(uint2) << L->desc.weight_bits);
+    return P.lds <= dl.max_lds;
+}
+
+// any: whichever is the fastest.  not_planes: operands not split beforehand, which takes less scratch.  compact: the form that needs the
+// least - filter groups one after the other through the same buffers, blocks decoded inside the multiply kernel.
+enum class ConvForm { any, not_planes, compact };
+
+int32_t plan_conv(const cl_layer *L, const cl_conv_desc *cv, int batch, bool bf16, const DeviceLimits &dl, ConvPlan &P,
+                  ConvForm form = ConvForm::any)
+{
+    const bool compact = form == ConvForm::compact;
     if (!cv) return fail(CL_EINVAL, "null convolution descriptor");
     if (cv->C < 1 || cv->H < 1 || cv->W < 1 || cv->R < 1 || cv->S < 1 || cv->stride < 1 || cv->pad < 0 || cv->groups < 1 ||
         cv->out_channels < 1)
@@ -1728,13 +1844,33 @@ int32_t plan_conv(const cl_layer *L, const cl_conv_desc *cv, int batch, bool bf1
     P.rows_bytes = P.gather ? round256((size_t)L->nbw * kTile * sizeof(uint2)) : 0;
     // workspace for the larger of a full image group and the last, smaller one
     P.xt_bytes = P.part_bytes = 0;
+    // What the call will take, in us, to be compared with plan_planes'.  Over 230 calls drawn from 3 to 512 channels, filters of 3 x 3, 5 x 5 and 11 x 11
+    // and 2e7 to 4e10 operations these are 11 % (bf16 16-19 %) off the measured times, plan_planes' 7 % (12 %).
+    double us = 0;
     for (int imgs : {P.imgs, batch % P.imgs}) {
         if (imgs == 0) continue;
         int nq, np, splits;
-        mfma_shape(L, launch_panels, imgs * g.P * g.Q, dl.cus, bf16, nq, np, splits, P.gather, P.gather || !bf16);
-        if (!P.gather) P.xt_bytes = std::max(P.xt_bytes, (size_t)P.groups_at_once * xt_bytes_for(L, np, bf16));
+        int64_t cost;
+        mfma_shape(L, launch_panels, imgs * g.P * g.Q, dl.cus, bf16, nq, np, splits, P.gather, P.gather || !bf16, &cost);
+        const double cycles_us = cost / 2400.0, xt = P.gather ? 0 : (double)P.groups_at_once * xt_bytes_for(L, np, bf16);
+        us += (imgs == P.imgs ? batch / P.imgs : 1) * (P.gather ? 14.5 + (bf16 ? 1.0 : 1.11) * cycles_us + (bf16 ? 1.9e-6 : 1.1e-6) * P.wt_bytes
+                                                                : bf16 ? 4.2 + 1.66 * cycles_us + 0.68e-6 * xt : 2.1 * cycles_us);
+        if (!P.gather) P.xt_bytes = std::max(P.xt_bytes, (size_t)xt);
         if (!(P.gather && splits == 1))
             P.part_bytes = std::max(P.part_bytes, (size_t)launch_panels * splits * np * L->desc.block_h * sizeof(float));
+    }
+    // Both operands split beforehand, where that is cheaper by a twentieth and the call a long one.  What it saves is in proportion to
+    // the multiplies, what it costs to the weights (VGG-16 conv4_2 at one image, 14 MB of terms: 19 us to split them and 30 to multiply, gathered 9
+    // and 36).  Of 148 drawn fp32 calls 55 take it, 1.30 times as fast on average as the other two forms, one of them slower by more than 3 % (12 %); of
+    // 80 bf16 ones 57, 1.36 times, five slower (16 % at worst).  Without the limit of 36 us 28 more fp32 calls would, for 1.08 times the speed and
+    // several times the scratch.
+    if (form == ConvForm::any && us > (bf16 ? 0 : 36)) {
+        ConvPlan F = P;
+        double planes_us;
+        if (plan_planes(L, cv, batch, bf16, dl, F, planes_us) && 1.05 * planes_us < us) {
+            P = F;
+            P.planes = true;
+        }
     }
     return CL_OK;
 }
@@ -1762,9 +1898,11 @@ extern "C" int32_t cl_conv_workspace_bytes_min(const cl_layer *L, const cl_conv_
     DeviceLimits dl;
     if (int32_t rc = device_limits(dl)) return rc;
     ConvPlan P, F;
-    if (int32_t rc = plan_conv(L, cv, batch, path == CL_PATH_MFMA_BF16, dl, P, true)) return rc;
+    if (int32_t rc = plan_conv(L, cv, batch, path == CL_PATH_MFMA_BF16, dl, P, ConvForm::compact)) return rc;
     if (int32_t rc = plan_conv(L, cv, batch, path == CL_PATH_MFMA_BF16, dl, F)) return rc;
-    *out = std::min(P.total(), F.total());      // the fast form's launch shape can happen to need less
+    ConvPlan G;
+    if (int32_t rc = plan_conv(L, cv, batch, path == CL_PATH_MFMA_BF16, dl, G, ConvForm::not_planes)) return rc;
+    *out = std::min({P.total(), F.total(), G.total()});      // the faster forms' launch shapes can happen to need less
     return CL_OK;
 }
 
@@ -1824,8 +1962,70 @@ int32_t conv_gathered(const ConvCall &c, bool bf16, const float *wt, const uint2
     HIP_TRY(hipGetLastError());
     if (!*c.timed) { timing_end(c.st, 1); *c.timed = true; }
     if (direct) return CL_OK;
-    GRID_TRY(grid, (int64_t)c.launch_panels * bh * ((c.ncols + kConvRedColumns - 1) / kConvRedColumns));
-    hipLaunchKernelGGL(conv_reduce_kernel, grid, dim3(kConvRedThreads), 0, c.st, c.D, c.part, c.bias, c.y, c.ncols, c.Np, c.splits, c.relu, c.pq);
+    GRID_TRY(grid, (int64_t)c.L->desc.M * ((c.ncols + kConvRedColumns - 1) / kConvRedColumns));
+    hipLaunchKernelGGL(conv_reduce_kernel, grid, dim3(kConvRedThreads), 0, c.st, c.part, c.bias, c.y, c.L->desc.M, P.OCg, P.panels_per_group, bh, c.ncols,
+                       c.Np, c.splits, c.relu, c.pq);
+    HIP_TRY(hipGetLastError());
+    return CL_OK;
+}
+
+template <int NP, int RT, int CT, int WR, int WC>
+int32_t launch_plane(dim3 grid, const uint4 *wt, const uint4 *xs, const uint32_t *unit_off, float *part, const PlaneConv &pc, hipStream_t st)
+{
+    hipLaunchKernelGGL((conv_plane_kernel<NP, RT, CT, WR, WC>), grid, dim3(256), 0, st, wt, xs, unit_off, part, pc);
+    HIP_TRY(hipGetLastError());
+    return CL_OK;
+}
+
+// The form with both operands split beforehand: one launch to split them, one to multiply, one to add up
+// where the steps are split.
+int32_t conv_planes(const ConvCall &c, bool bf16, int imgs, void *xs, void *wt, uint32_t *unit_off)
+{
+    const ConvPlan &P = *c.P;
+    PlaneGeom g = P.pg;
+    const PlaneShape s = plane_shape(P.OCg, g.groups, g.steps, c.ncols, bf16, c.cus);
+    const PlaneTile &T = kPlaneTiles[s.tile];
+    g.tile_rows = T.rows;
+    g.ppg = (P.OCg + T.rows - 1) / T.rows;
+    const uint32_t image = g.planes.d * g.per_plane.d;
+    g.pieces = (uint32_t)imgs * image;
+    const int blocks = prep_blocks(c.L, P.cg.R * P.cg.S);
+    const int64_t n_strips = prep_strips(c.L, blocks);
+    dim3 grid;
+    // (few strips: several workgroups decode the same one and each writes some of its units)
+    const int parts = (int)std::max<int64_t>(1, std::min<int64_t>(8, std::max(1, c.cus) / n_strips));
+    GRID_TRY(grid, n_strips * parts + std::min<int64_t>(1024, (g.pieces + kPrepThreads - 1) / kPrepThreads));
+    using Prepare = void (*)(LayerDev, PlaneGeom, const float *, uint4 *, uint4 *, uint32_t *, int, int, int);
+    static const Prepare prepare[2] = {conv_prepare_kernel<3>, conv_prepare_kernel<2>};
+    static LdsLimit seen[2];
+    if (int32_t rc = ensure_lds((const void *)prepare[bf16], P.lds, seen[bf16])) return rc;
+    hipLaunchKernelGGL(prepare[bf16], grid, dim3(kPrepThreads), P.lds, c.st, c.D, g, c.x, (uint4 *)wt, (uint4 *)xs, unit_off, (int)n_strips, parts, blocks);
+    HIP_TRY(hipGetLastError());
+    PlaneConv pc{};
+    pc.steps = g.steps; pc.splits = s.splits; pc.panels = g.groups * g.ppg; pc.ppg = g.ppg; pc.tiles = s.tiles;
+    pc.n_cols = c.ncols; pc.Np = s.tiles * T.cols; pc.pq = c.pq; pc.Q = P.cg.Q; pc.stride = P.cg.stride;
+    pc.Wp = g.Wp; pc.px_bytes = g.px4 ? 8 : 16;
+    pc.image_bytes = image * 16; pc.group_bytes = (uint32_t)g.CG * g.per_plane.d * 16; pc.term_bytes = g.pieces * 16;
+    pc.M = c.L->desc.M; pc.OCg = P.OCg;
+    const bool direct = s.splits == 1;
+    pc.Y = direct ? c.y : nullptr; pc.bias = c.bias; pc.relu = c.relu;
+    GRID_TRY(grid, (int64_t)pc.panels * pc.tiles * pc.splits);
+    if (!*c.timed) timing_begin(c.st);
+    const uint4 *w = (const uint4 *)wt, *x = (const uint4 *)xs;
+    int32_t rc;
+    switch (s.tile + (bf16 ? 3 : 0)) {
+    case 0: rc = launch_plane<3, 2, 2, 2, 2>(grid, w, x, unit_off, c.part, pc, c.st); break;
+    case 1: rc = launch_plane<3, 3, 1, 1, 4>(grid, w, x, unit_off, c.part, pc, c.st); break;
+    case 2: rc = launch_plane<3, 2, 1, 1, 4>(grid, w, x, unit_off, c.part, pc, c.st); break;
+    case 3: rc = launch_plane<2, 2, 2, 2, 2>(grid, w, x, unit_off, c.part, pc, c.st); break;
+    case 4: rc = launch_plane<2, 3, 1, 1, 4>(grid, w, x, unit_off, c.part, pc, c.st); break;
+    default: rc = launch_plane<2, 2, 1, 1, 4>(grid, w, x, unit_off, c.part, pc, c.st); break;
+    }
+    if (rc) return rc;
+    if (!*c.timed) { timing_end(c.st, 1); *c.timed = true; }
+    if (direct) return CL_OK;
+    GRID_TRY(grid, (int64_t)pc.M * ((c.ncols + kConvRedColumns - 1) / kConvRedColumns));
+    hipLaunchKernelGGL(conv_reduce_kernel, grid, dim3(kConvRedThreads), 0, c.st, c.part, c.bias, c.y, pc.M, P.OCg, g.ppg, T.rows, c.ncols, pc.Np, s.splits, c.relu, c.pq);
     HIP_TRY(hipGetLastError());
     return CL_OK;
 }
@@ -1881,13 +2081,17 @@ extern "C" int32_t cl_compressed_conv_forward(const cl_layer *L, const cl_conv_d
     DeviceLimits dl;
     if (int32_t rc = device_limits(dl)) return rc;
     const bool bf16 = path == CL_PATH_MFMA_BF16;
-    // the fast form if the workspace holds it, else the compact one
+    // the fast form if the workspace holds it, then the gathered one, else the compact one
     ConvPlan P;
     if (int32_t rc = plan_conv(L, cv, batch, bf16, dl, P)) return rc;
-    if (workspace_bytes < P.total() || !d_workspace) {
-        const size_t fast = P.total();
+    const size_t fast = P.total();
+    if (P.planes && (workspace_bytes < fast || !d_workspace)) {
         P = ConvPlan{};
-        if (int32_t rc = plan_conv(L, cv, batch, bf16, dl, P, true)) return rc;
+        if (int32_t rc = plan_conv(L, cv, batch, bf16, dl, P, ConvForm::not_planes)) return rc;
+    }
+    if (workspace_bytes < P.total() || !d_workspace) {
+        P = ConvPlan{};
+        if (int32_t rc = plan_conv(L, cv, batch, bf16, dl, P, ConvForm::compact)) return rc;
         if (workspace_bytes < P.total() || !d_workspace)
             return fail(CL_EINVAL, "workspace too small: %zu < %zu (%zu for the fast form)", workspace_bytes, P.total(), fast);
     }
@@ -1900,7 +2104,7 @@ extern "C" int32_t cl_compressed_conv_forward(const cl_layer *L, const cl_conv_d
     float *wt = (float *)(ws + P.xt_bytes + P.part_bytes);
     uint2 *rows = (uint2 *)(ws + P.xt_bytes + P.part_bytes + P.wt_bytes);
     const bool combined = g.R * g.S <= 32;      // one tap mask per column instead of one per filter row and one per filter column
-    if (P.gather) {
+    if (P.gather && !P.planes) {
         const size_t lds = table_image_bytes(L->val_lut_bits, L->idx_lut_bits, 1 << L->desc.weight_bits) + (size_t)kWTileBytes;
         static LdsLimit seen;
         if (int32_t rc = ensure_lds((const void *)decode_tiles_kernel, lds, seen)) return rc;
@@ -1914,9 +2118,13 @@ extern "C" int32_t cl_compressed_conv_forward(const cl_layer *L, const cl_conv_d
     for (int b0 = 0; b0 < batch; b0 += P.imgs) {
         const int nb = std::min(P.imgs, batch - b0);
         c.ncols = nb * c.pq;
-        mfma_shape(L, c.launch_panels, c.ncols, dl.cus, bf16, c.nq, c.Np, c.splits, P.gather, P.gather || !bf16);
         c.x = d_X + (size_t)b0 * g.C * g.H * g.W;
         c.y = d_Y + (size_t)b0 * L->desc.M * c.pq;
+        if (P.planes) {
+            if (int32_t rc = conv_planes(c, bf16, nb, xt, wt, (uint32_t *)rows)) return rc;
+            continue;
+        }
+        mfma_shape(L, c.launch_panels, c.ncols, dl.cus, bf16, c.nq, c.Np, c.splits, P.gather, P.gather || !bf16);
         if (int32_t rc = P.gather ? conv_gathered(c, bf16, wt, rows, combined) : conv_columns(c, cv->groups, bf16, xt)) return rc;
     }
     clear_error();

@@ -1,0 +1,148 @@
+"""The convolution form whose operands are split beforehand (conv_prepare_kernel, conv_plane_kernel): where its
+tiles, units of k and blocks end, which calls take it, and what is not finite."""
+import numpy as np
+import pytest
+
+import paper_1711_00244_amd as cl
+from gates import assert_close, conv_ref
+
+pytestmark = pytest.mark.gpu
+
+
+def _geom(C, H, R, OC, groups=1, stride=1, pad=None, S=None, W=None):
+    return dict(C=C, H=H, W=W or H, R=R, S=S or R, stride=stride, pad=R // 2 if pad is None else pad, groups=groups, OC=OC)
+
+
+def _layer(rng, geom, block_h, block_w, density=0.4, codebook=None):
+    K = geom["C"] // geom["groups"] * geom["R"] * geom["S"]
+    W = (rng.standard_normal((geom["OC"], K)) * (rng.random((geom["OC"], K)) < density)).astype(np.float32)
+    L = cl.compress_layer(W, 8, 8, block_h, block_w, codebook=codebook, upload=True)
+    return L, cl.decode_layer(L)[3].cpu().numpy()
+
+
+def _terms_bytes(geom, batch, terms):
+    """The least that a call of this form asks for: the activations' terms."""
+    Cg = geom["C"] // geom["groups"]
+    H, W = geom["H"] + 2 * geom["pad"], geom["W"] + 2 * geom["pad"]
+    channels = 4 if Cg <= 4 else -(-Cg // 8) * 8
+    return 2 * terms * batch * geom["groups"] * channels * H * (W + (W & 1 if Cg <= 4 else 0))
+
+
+def _check(rng, geom, block, batch, path, density=0.4):
+    import torch
+    L, W = _layer(rng, geom, *block, density=density)
+    terms = 2 if path == "bf16" else 3
+    p = cl.PATH_MFMA_BF16 if path == "bf16" else cl.PATH_MFMA_F32
+    assert cl.conv_workspace_bytes(L, geom, batch, p) >= _terms_bytes(geom, batch, terms)
+    X = rng.standard_normal((batch, geom["C"], geom["H"], geom["W"])).astype(np.float32)
+    bias = rng.standard_normal(geom["OC"]).astype(np.float32)
+    Xd, bd = torch.from_numpy(X).cuda(), torch.from_numpy(bias).cuda()
+    Y = cl.compressed_conv_forward(L, geom, Xd, bd, relu=True, path=p)
+    again = cl.compressed_conv_forward(L, geom, Xd, bd, relu=True, path=p)
+    assert torch.equal(Y, again)
+    Y = Y.cpu().numpy()
+    # filters of the first and last rows of tiles and groups, the first and last image and one between
+    OC, g, Cg = geom["OC"], geom["groups"], geom["C"] // geom["groups"]
+    per = OC // g
+    imgs = sorted({0, batch // 2, batch - 1})
+    for grp in range(g):
+        rows = sorted({r for r in (0, 31, 63, 64, 95, 96, 127, 128, per - 1) if r < per})
+        sub = dict(geom, C=Cg, OC=len(rows), groups=1)
+        at = np.array(rows) + grp * per
+        ref = conv_ref(np.ascontiguousarray(W[at]), np.ascontiguousarray(X[imgs][:, grp * Cg:(grp + 1) * Cg]), sub, bias[at])
+        # (two bf16 terms each: what is dropped is below 3 * 2^-16 of each product)
+        assert_close(Y[imgs][:, at], ref, True, product_rel=3 * 2.0 ** -16 if path == "bf16" else 0.0)
+    L.free()
+
+
+CASES = [
+    # tiles of 128, 96 and 64 filters, whole and not; channels that fill their last group of eight, and not
+    (_geom(40, 56, 3, 128), (128, 128), 16), (_geom(41, 56, 3, 130), (128, 128), 16), (_geom(33, 56, 3, 96), (96, 128), 20),
+    (_geom(63, 57, 3, 64), (64, 128), 24), (_geom(65, 40, 3, 200), (128, 128), 24),
+    # an odd number of units (25 taps of one group of eight, 9 of three), taps by rows and columns
+    (_geom(8, 64, 5, 130), (128, 128), 24), (_geom(24, 56, 3, 250), (128, 128), 16),
+    (_geom(24, 48, 1, 190, S=7, pad=3), (128, 128), 24),
+    # four channels to a pixel: odd and even numbers of taps, odd and even widths, two filter groups
+    (_geom(3, 129, 11, 96, stride=2, pad=0), (96, 128), 48), (_geom(4, 65, 3, 250), (128, 128), 64), (_geom(3, 80, 4, 250, pad=1), (128, 128), 40),
+    (_geom(8, 61, 5, 256, groups=2), (128, 128), 32),
+    # filter groups with filters of their own tiles; strides; blocks of other widths and heights
+    (_geom(96, 27, 5, 256, groups=2), (128, 128), 16), (_geom(384, 13, 3, 384, groups=2), (96, 128), 48), (_geom(48, 90, 3, 160, stride=2), (128, 128), 24),
+    (_geom(40, 56, 3, 128), (64, 48), 20), (_geom(40, 56, 3, 120), (24, 128), 20), (_geom(20, 40, 11, 96), (96, 128), 16),
+    # few columns, many units: steps split among workgroups
+    (_geom(512, 28, 3, 512), (128, 128), 2), (_geom(505, 15, 11, 70), (72, 128), 8),
+]
+
+
+@pytest.mark.parametrize("geom,block,batch", CASES)
+@pytest.mark.parametrize("path", ["f32", "bf16"])
+def test_edges(geom, block, batch, path):
+    _check(np.random.default_rng(geom["C"] * geom["OC"] + batch), geom, block, batch, path)
+
+
+@pytest.mark.parametrize("density", [0.0, 0.02, 1.0])
+def test_densities(density):
+    """Blocks without a chunk, of one, and of many (the chunks that a workgroup takes are counted from their carries)."""
+    _check(np.random.default_rng(7), _geom(41, 56, 3, 130), (128, 128), 16, "f32", density)
+
+
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+@pytest.mark.parametrize("geom,batch", [(_geom(41, 56, 3, 130), 16), (_geom(3, 80, 5, 250), 40)])
+def test_not_finite(geom, batch, bad):
+    """What is not finite gives what fp32 gives over the dense block (a tap shared between two units once, not twice),
+    and outputs that do not see it are as without it (slots and units that are not there are zeros on both sides)."""
+    import torch
+    rng = np.random.default_rng(6)
+    L, W = _layer(rng, geom, 128, 128)
+    R, pad, OC = geom["R"], geom["pad"], geom["OC"]
+    X = rng.standard_normal((batch, geom["C"], geom["H"], geom["W"])).astype(np.float32)
+    assert cl.conv_workspace_bytes(L, geom, batch) >= _terms_bytes(geom, batch, 3)
+    clean = cl.compressed_conv_forward(L, geom, torch.from_numpy(X).cuda(), relu=False).cpu().numpy()
+    X[4, geom["C"] - 1, 17, 11] = bad
+    Y = cl.compressed_conv_forward(L, geom, torch.from_numpy(X).cuda(), relu=False).cpu().numpy()
+    taps = W.reshape(OC, geom["C"], R, R)[:, -1]
+    seen = np.zeros(Y.shape, bool)
+    for r in range(R):
+        for s in range(R):
+            y, x = 17 + pad - r, 11 + pad - s
+            seen[4, :, y, x] = True
+            with np.errstate(invalid="ignore"):
+                want = np.float32(bad) * taps[:, r, s]
+            assert np.array_equal(Y[4, :, y, x], want, equal_nan=True), (r, s)
+    assert np.array_equal(Y[~seen], clean[~seen])
+    L.free()
+
+
+def test_codebooks_that_do_not_split():
+    """Half a weight of 2^-110 is below what three terms hold: where two units share a tap such a layer goes the other way."""
+    import torch
+    rng = np.random.default_rng(8)
+    cb = np.concatenate([[0.0], np.linspace(1, 2, 255) * 2.0 ** -110 * (1 + 2.0 ** -20)]).astype(np.float32)
+    geom, batch = _geom(3, 80, 5, 250), 40
+    L, W = _layer(rng, geom, 128, 128, codebook=cb)
+    assert cl.conv_workspace_bytes(L, geom, batch) < _terms_bytes(geom, batch, 3)
+    X = (rng.standard_normal((batch, 3, 80, 80)) * 2.0 ** 100).astype(np.float32)
+    Y = cl.compressed_conv_forward(L, geom, torch.from_numpy(X).cuda()).cpu().numpy()
+    up = np.float32(2.0 ** 20)
+    rows, imgs = np.array([0, 249]), [0, batch - 1]
+    assert_close(Y[imgs][:, rows] * up, conv_ref(np.ascontiguousarray(W[rows]) * up, np.ascontiguousarray(X[imgs]), dict(geom, OC=2)), False)
+    L.free()
+
+
+def test_scratch_of_the_other_forms():
+    """With less scratch than this form takes the call runs in the gathered form, and with less than that in the compact one;
+    below the least it is refused."""
+    import torch
+    rng = np.random.default_rng(9)
+    geom, batch = _geom(96, 27, 5, 256, groups=2), 16
+    L, W = _layer(rng, geom, 128, 128)
+    X = torch.from_numpy(rng.standard_normal((batch, 96, 27, 27)).astype(np.float32)).cuda()
+    full, least = cl.conv_workspace_bytes(L, geom, batch), cl.conv_workspace_bytes(L, geom, batch, compact=True)
+    assert least < full
+    rows, imgs = np.array([0, 127]), [0, batch - 1]
+    ref = conv_ref(np.ascontiguousarray(W[rows]), np.ascontiguousarray(X.cpu().numpy()[imgs][:, :48]), dict(geom, C=48, OC=2, groups=1))
+    for n in (full, full - 256, least):
+        Y = cl.compressed_conv_forward(L, geom, X, workspace=torch.empty(n, dtype=torch.uint8, device="cuda")).cpu().numpy()
+        assert_close(Y[imgs][:, rows], ref, False)
+    with pytest.raises(cl.CLError):
+        cl.compressed_conv_forward(L, geom, X, workspace=torch.empty(least - 256, dtype=torch.uint8, device="cuda"))
+    L.free()

@@ -516,16 +516,18 @@ bool plan_rows(const cl_layer *L, int batch, const DeviceLimits &dl, RowsPlan &P
     // not any more, and all parts have become shorter alike: over 1400 calls (a hundred layers drawn from 200 x 500 to 8192 x
     // 25088, densities of 3 to 40 %, 12 to 512 images) a call takes 0.83 of its price, rms 7.7 %, and with every constant fitted
     // anew 7.2 %.  Groups and splits come out the same either way (AlexNet-shaped fc6, us a call: 24.4, 28.2 and 40.7; one block
-    // to a group 30.0, 32.2 and 40.7); against the other paths the price is too high, which kAutoLaunch makes up for in part.
-    static const struct { int groups, block, weight_x20; } kFit[3] = {{3, 2150, 29}, {3, 3000, 34}, {1, 3900, 51}};
+    // to a group 30.0, 32.2 and 40.7 - at 16 images before four lanes had a row); against the other paths the price is too high, which kAutoLaunch makes up for in part.
+    // With 16 images (four lanes to a row, groups of one, two or four blocks) its parts are those of 4096-row layers of 4096 to 25088 columns
+    // and 3 to 30 %, to the same 0.83.
+    static const struct { int groups, group, block, weight_x20; } kFit[3] = {{4, 4400, 630, 29}, {3, 2200, 3000, 34}, {1, 2200, 3900, 51}};
     const auto &fit = kFit[P.ipl / 2];
     const int64_t tiles = (int64_t)L->n_panels * (Bp / images);
     const int cus = std::max(1, dl.cus);
     const int64_t nnz_block = L->n_blocks ? L->nnz / L->n_blocks : 0;
-    const int64_t per_block = fit.block + nnz_block * fit.weight_x20 / 20, per_group = 2200, start = 12000;
+    const int64_t per_block = fit.block + nnz_block * fit.weight_x20 / 20, per_group = fit.group, start = 12000;
     const int sp_max = (int)std::max<int64_t>(1, std::min<int64_t>({L->nbw, (3 * (int64_t)cus + tiles - 1) / tiles, (int64_t)(kRowsScratch / (image_bytes * Bp))}));
     int64_t best = -1;
-    for (int group = 1; group <= fit.groups && lds_of(group) <= dl.max_lds; ++group)
+    for (int group = 1; group <= fit.groups && lds_of(group) <= dl.max_lds; group += P.ipl == 1 ? group : 1)
         for (int sp = 1; sp <= sp_max; ++sp) {
             const int64_t rounds = (tiles * sp + cus - 1) / cus, blocks = (L->nbw + sp - 1) / sp;
             const int64_t t = rounds * (start + (blocks + group - 1) / group * per_group + blocks * per_block) +
@@ -931,7 +933,7 @@ static int32_t forward_rows(const cl_layer *L, const LayerDev &D, const RowsPlan
         switch (P.ipl * 8 + P.group) {
         case 1 * 8 + 1: rc = launch_rows<1, 1>(D, L->n_panels, P, x, part, nb, st); break;
         case 1 * 8 + 2: rc = launch_rows<1, 2>(D, L->n_panels, P, x, part, nb, st); break;
-        case 1 * 8 + 3: rc = launch_rows<1, 3>(D, L->n_panels, P, x, part, nb, st); break;
+        case 1 * 8 + 4: rc = launch_rows<1, 4>(D, L->n_panels, P, x, part, nb, st); break;
         case 2 * 8 + 1: rc = launch_rows<2, 1>(D, L->n_panels, P, x, part, nb, st); break;
         case 2 * 8 + 2: rc = launch_rows<2, 2>(D, L->n_panels, P, x, part, nb, st); break;
         case 2 * 8 + 3: rc = launch_rows<2, 3>(D, L->n_panels, P, x, part, nb, st); break;

@@ -1,5 +1,5 @@
 // Batches of a few up to some dozens of images: decode to entry lists in LDS, multiply row by
-// row with sixteen images across the lanes of a quarter wavefront.  fc_rows_kernel.
+// row, the images across a few lanes.  fc_rows_kernel.
 // Part of the device translation unit: included by device.hip inside namespace cl,
 // in the order given there.
 #pragma once
@@ -19,15 +19,17 @@ template <int K> __device__ __forceinline__ uint32_t row_bcast(uint32_t v)
 // its k-th entry with its sixteen (times IPL) images.  The reads of all eight go out together;
 // the multiply-adds take the weight from lane k of the quarter themselves (written out: the
 // compiler keeps the move apart).
-template <int IPL, int K>
-__device__ __forceinline__ void rows_read(float (&x)[8][IPL], uint32_t off, uint32_t xbase)
+template <int IPL, int K, int N>
+__device__ __forceinline__ void rows_read(float (&x)[N][IPL], uint32_t off, uint32_t xbase)
 {
     typedef typename WideVec<IPL>::type vec_t;
     typedef const __attribute__((address_space(3))) vec_t *lds_vec;
-    const uint32_t at[8] = {row_bcast<K>(off) + xbase,     row_bcast<K + 1>(off) + xbase, row_bcast<K + 2>(off) + xbase, row_bcast<K + 3>(off) + xbase,
-                            row_bcast<K + 4>(off) + xbase, row_bcast<K + 5>(off) + xbase, row_bcast<K + 6>(off) + xbase, row_bcast<K + 7>(off) + xbase};
+    uint32_t at[N];
+    at[0] = row_bcast<K>(off) + xbase, at[1] = row_bcast<K + 1>(off) + xbase, at[2] = row_bcast<K + 2>(off) + xbase, at[3] = row_bcast<K + 3>(off) + xbase;
+    if constexpr (N == 8)
+        at[4] = row_bcast<K + 4>(off) + xbase, at[5] = row_bcast<K + 5>(off) + xbase, at[6] = row_bcast<K + 6>(off) + xbase, at[7] = row_bcast<K + 7>(off) + xbase;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < N; ++u) {
         const vec_t v = *(lds_vec)(uintptr_t)at[u];
         if constexpr (IPL == 1) x[u][0] = v;
         else {
@@ -37,23 +39,72 @@ __device__ __forceinline__ void rows_read(float (&x)[8][IPL], uint32_t off, uint
     }
 }
 
-template <int IPL, int K>
-__device__ __forceinline__ void rows_add(float (&acc)[IPL], const float (&x)[8][IPL], float w)
+template <int IPL, int K, int N>
+__device__ __forceinline__ void rows_add(float (&acc)[IPL], const float (&x)[N][IPL], float w)
 {
     // (s_nop: two wait states between a vector write of w and its use as another lane's operand)
 #pragma unroll
-    for (int m = 0; m < IPL; ++m)
+    for (int m = 0; m < IPL; ++m) {
+        if constexpr (N == 8)
+            asm("s_nop 1\n"
+                "v_fmac_f32_dpp %0, %1, %2 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n"
+                "v_fmac_f32_dpp %0, %1, %3 row_newbcast:%10+1 row_mask:0xf bank_mask:0xf\n"
+                "v_fmac_f32_dpp %0, %1, %4 row_newbcast:%10+2 row_mask:0xf bank_mask:0xf\n"
+                "v_fmac_f32_dpp %0, %1, %5 row_newbcast:%10+3 row_mask:0xf bank_mask:0xf\n"
+                "v_fmac_f32_dpp %0, %1, %6 row_newbcast:%10+4 row_mask:0xf bank_mask:0xf\n"
+                "v_fmac_f32_dpp %0, %1, %7 row_newbcast:%10+5 row_mask:0xf bank_mask:0xf\n"
+                "v_fmac_f32_dpp %0, %1, %8 row_newbcast:%10+6 row_mask:0xf bank_mask:0xf\n"
+                "v_fmac_f32_dpp %0, %1, %9 row_newbcast:%10+7 row_mask:0xf bank_mask:0xf"
+                : "+v"(acc[m])
+                : "v"(w), "v"(x[0][m]), "v"(x[1][m]), "v"(x[2][m]), "v"(x[3][m]), "v"(x[4][m]), "v"(x[5][m]), "v"(x[6][m]), "v"(x[7][m]), "n"(K));
+        else
+            asm("s_nop 1\n"
+                "v_fmac_f32_dpp %0, %1, %2 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n"
+                "v_fmac_f32_dpp %0, %1, %3 row_newbcast:%6+1 row_mask:0xf bank_mask:0xf\n"
+                "v_fmac_f32_dpp %0, %1, %4 row_newbcast:%6+2 row_mask:0xf bank_mask:0xf\n"
+                "v_fmac_f32_dpp %0, %1, %5 row_newbcast:%6+3 row_mask:0xf bank_mask:0xf"
+                : "+v"(acc[m])
+                : "v"(w), "v"(x[0][m]), "v"(x[1][m]), "v"(x[2][m]), "v"(x[3][m]), "n"(K));
+    }
+}
+
+// The value of lane K of each group of four lanes, in all four.
+template <int K> __device__ __forceinline__ uint32_t quad_bcast(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, K * 0x55, 0xf, 0xf, true);          // quad_perm:[K,K,K,K]
+}
+
+// Four entries of a row, held by its four lanes one each (byte offset of the entry's column in the activations, and its weight),
+// times the lane's four (H = 1) or eight images: images 4 t .. 4 t + 3 of lane t, and those 16 further on.
+template <int H>
+__device__ __forceinline__ void quad_read(float (&x)[4][4 * H], uint32_t off, uint32_t xbase)
+{
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    typedef const __attribute__((address_space(3))) f4 *lds_f4;
+    const uint32_t at[4] = {quad_bcast<0>(off) + xbase, quad_bcast<1>(off) + xbase, quad_bcast<2>(off) + xbase, quad_bcast<3>(off) + xbase};
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+            const f4 v = ((lds_f4)(uintptr_t)at[u])[4 * h];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) x[u][4 * h + m] = v[m];
+        }
+}
+
+template <int H>
+__device__ __forceinline__ void quad_add(float (&acc)[4 * H], const float (&x)[4][4 * H], float w)
+{
+    // (s_nop: two wait states between a vector write of w and its use as another lane's operand)
+#pragma unroll
+    for (int m = 0; m < 4 * H; ++m)
         asm("s_nop 1\n"
-            "v_fmac_f32_dpp %0, %1, %2 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n"
-            "v_fmac_f32_dpp %0, %1, %3 row_newbcast:%10+1 row_mask:0xf bank_mask:0xf\n"
-            "v_fmac_f32_dpp %0, %1, %4 row_newbcast:%10+2 row_mask:0xf bank_mask:0xf\n"
-            "v_fmac_f32_dpp %0, %1, %5 row_newbcast:%10+3 row_mask:0xf bank_mask:0xf\n"
-            "v_fmac_f32_dpp %0, %1, %6 row_newbcast:%10+4 row_mask:0xf bank_mask:0xf\n"
-            "v_fmac_f32_dpp %0, %1, %7 row_newbcast:%10+5 row_mask:0xf bank_mask:0xf\n"
-            "v_fmac_f32_dpp %0, %1, %8 row_newbcast:%10+6 row_mask:0xf bank_mask:0xf\n"
-            "v_fmac_f32_dpp %0, %1, %9 row_newbcast:%10+7 row_mask:0xf bank_mask:0xf"
+            "v_fmac_f32_dpp %0, %1, %2 quad_perm:[0,0,0,0] row_mask:0xf bank_mask:0xf\n"
+            "v_fmac_f32_dpp %0, %1, %3 quad_perm:[1,1,1,1] row_mask:0xf bank_mask:0xf\n"
+            "v_fmac_f32_dpp %0, %1, %4 quad_perm:[2,2,2,2] row_mask:0xf bank_mask:0xf\n"
+            "v_fmac_f32_dpp %0, %1, %5 quad_perm:[3,3,3,3] row_mask:0xf bank_mask:0xf"
             : "+v"(acc[m])
-            : "v"(w), "v"(x[0][m]), "v"(x[1][m]), "v"(x[2][m]), "v"(x[3][m]), "v"(x[4][m]), "v"(x[5][m]), "v"(x[6][m]), "v"(x[7][m]), "n"(K));
+            : "v"(w), "v"(x[0][m]), "v"(x[1][m]), "v"(x[2][m]), "v"(x[3][m]));
 }
 
 // Bytes of v that are not zero, added to n.
@@ -88,18 +139,24 @@ __device__ __forceinline__ void list_from(const Symbols &y, uint32_t pos, uint32
 // wavefronts, one to a CU.  The blocks are taken G at a time.  While a group is multiplied the
 // next one is decoded, by the same wavefronts: each decodes its chunk of the next group (one
 // record per lane), puts the surviving weights of the chunk in block order into that block's
-// list in LDS and then multiplies its eight rows of the present group, two per quarter
-// wavefront: a quarter takes sixteen entries of a row, one per lane, and goes through them as
-// above.  So an entry costs a quarter of (one address, one LDS read, IPL multiply-adds), a
-// row's sum stays in a register from the first block to the last, and nothing is added in
-// memory.  Where a row's entries start in a block's list was counted when the layer was loaded
-// (row_ptr).
-// Bound by vector issue (decode and multiply-adds: 60 % of the cycles at 16 images of the AlexNet-shaped fc6, 53 % at 64 of
-// the VGG-shaped one, LDS 46 and 37 %) and by what is left of a group's turn, which is why small tiles take several blocks to a group.  Nothing in a turn waits for loads it has just requested: the decode, which the
+// list in LDS and then multiplies its rows of the present group.  A row's sum stays in a register from the first block to the last, and
+// nothing is added in memory.  Where a row's entries start in a block's list was counted when the layer was loaded (row_ptr).
+//   From 17 images on (IPL 2 and 4) a quarter wavefront has two rows, one after the other: it takes sixteen entries of a
+//   row, one per lane, and goes through them with row broadcasts, sixteen images, IPL to a lane, across its lanes.
+//   Up to 16 images four lanes have a row, four images each: they take four entries, one per lane, and go through them with quad
+//   broadcasts.  So a wavefront has sixteen rows at a time, an address and a read serve sixteen entries and not four, and the reads are of
+//   16 bytes; a step is as long as the longest of sixteen rows, not of four.  Eight wavefronts have a block's rows; the
+//   other eight have the next block's, and the two halves' sums are added at the end.  (us a call at 16 images, two rows to a quarter and
+//   this: 4096 x 9216 at 9 % 25.6 and 22.8, 4096 x 25088 at 4 % 42.6 and 31.6, 4096 x 16384 at 3 / 16 / 30 % 32.3 / 53.3 / 80.5 and 22.7 / 38.1 /
+//   58.1.  At 32 images, eight to a lane, 28.6 and 29.8, 46.9 and 44.5 for the first two: left as it was.)
+// Bound by vector issue (decode and multiply-adds; at 64 images of the VGG-shaped fc6 53 % of the cycles, LDS 37 %) and by what is left of a group's
+// turn, which is why small tiles take several blocks to a group.  At 16 images of the AlexNet-shaped fc6, two rows to a quarter, leaving out
+// the products took 24 us to 13, leaving out the decode to 21, the activations nothing.  Nothing in a turn waits for loads it has just requested: the decode, which the
 // barrier waits for, comes first; ranges stay as loaded; a slot is asked for before the products and its record after
-// them (a turn of the VGG-shaped fc6 at 64 images 7.7 k -> 6.5 k cycles, the AlexNet-shaped 9.5 k -> 8.4 k).  us per
-// layer call at 16 / 32 / 64 images: AlexNet-shaped fc6 24 / 28 / 41, dense tiles 41 / 42 / 60; VGG-shaped fc6
-// 41 / 47 / 70, dense tiles 92 / 92 / 139.
+// them (a turn of the VGG-shaped fc6 at 64 images 7.7 k -> 6.5 k cycles).  us per
+// layer call at 32 / 64 images: AlexNet-shaped fc6 28 / 41, dense tiles 42 / 60; VGG-shaped fc6 47 / 70, dense tiles 92 / 139.
+// (A turn that decodes the symbols of the group after next and places the next group's - half the chain each - 0 to 2 % slower up to 32
+// images, 2 % faster at 64 at 4 %, nothing at 9 %.)
 template <int IPL, int G>
 __global__ __launch_bounds__(kRowsThreads) void fc_rows_kernel(LayerDev L, const float *__restrict__ X, float *__restrict__ part, int B,
                                                                int panels, int splits, int Bp, int list_cap)
@@ -251,76 +308,151 @@ __global__ __launch_bounds__(kRowsThreads) void fc_rows_kernel(LayerDev L, const
         }
     };
 
-    // ---- where the quarter's rows start in the lists of a group of blocks, and where the last ends ----
+    // ---- where the lane's rows start in the lists of a group of blocks, and where the last ends ----
     // (rows the blocks do not have start and end where the last row ends: the table's last two entries)
-    const int row0 = wave * (kTile / NW) + (lane >> 4) * RQ;
+    // (QUADS: up to 16 images, four lanes to a row)
+    constexpr bool QUADS = IPL == 1;
+    constexpr int GW = QUADS ? (G + 1) / 2 : G;             // blocks of a group to a wavefront
+    const int g_first = QUADS ? wave >> 3 : 0;              // the first of them
+    constexpr int g_step = QUADS ? 2 : 1;
+    const int row0 = QUADS ? (wave & 7) * 16 + (lane >> 2) : wave * (kTile / NW) + (lane >> 4) * RQ;
     static_assert(RQ == 2, "a quarter's two rows are one word of row_ptr and the half after it");
-    const int row_at = min(row0, L.row_ptrs - 2), row_end = min(row0 + RQ, L.row_ptrs - 1);
+    const int row_at = min(row0, L.row_ptrs - 2), row_end = min(row0 + (QUADS ? 1 : RQ), L.row_ptrs - 1);
     // (as they are loaded, and taken apart where they are used: a group's turn would otherwise begin with waiting for them)
     struct RowRange {
         uint32_t starts, end;
         __device__ __forceinline__ uint32_t at(int i) const { return i == 0 ? starts & 0xffffu : i == 1 ? starts >> 16 : end; }
     };
-    auto ranges_fetch = [&](int ph, RowRange (&r)[G]) {
+    auto ranges_fetch = [&](int ph, RowRange (&r)[GW]) {
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
+        for (int i = 0; i < GW; ++i) {
+            const int g = g_first + i * g_step;
             // (a block past the last: the last one's again, which multiply leaves out - a register set to zero here would have
             // every load before it waited for)
             const int blk = min(blk_lo + ph * G + g, blk_hi - 1);
             const uint16_t *rp = L.row_ptr + (size_t)(pb0 + (uint32_t)blk) * (uint32_t)L.row_ptrs;
-            r[g] = RowRange{*(const uint32_t *)(rp + row_at), rp[row_end]};
+            r[i] = QUADS ? RowRange{rp[row_at], rp[row_end]} : RowRange{*(const uint32_t *)(rp + row_at), rp[row_end]};
         }
     };
 
-    float acc[RQ][IPL];
+    constexpr int AR = QUADS ? 1 : RQ, AI = QUADS ? 4 * IPL : IPL;      // rows and images of a lane
+    float acc[AR][AI];
 #pragma unroll
-    for (int i = 0; i < RQ; ++i)
+    for (int i = 0; i < AR; ++i)
 #pragma unroll
-        for (int m = 0; m < IPL; ++m) acc[i][m] = 0.0f;
+        for (int m = 0; m < AI; ++m) acc[i][m] = 0.0f;
 
-    auto multiply = [&](int ph, const RowRange (&r)[G]) {
-        // the first sixteen entries of all the rows, then their weights: requested together
-        // (past a row's last entry: codebook entry 0 and the column of zeros)
-        auto entry = [&](uint32_t at, int left) { return l16 < left ? (uint32_t)*(lds_u16)(uintptr_t)at : (uint32_t)kTile; };
-        auto list_at = [&](int g, int i) { return (uint32_t)(uintptr_t)(lds_u16)(lists + ((ph & 1) * G + g) * list_cap) + 2u * (r[g].at(i) + (uint32_t)l16); };
-        auto count = [&](int g, int i) { return blk_lo + ph * G + g < blk_hi ? (int)(r[g].at(i + 1) - r[g].at(i)) : 0; };
-        uint32_t ent[G][RQ];
-        float w[G][RQ];
+    auto multiply_quads = [&](int ph, const RowRange (&r)[GW]) {
+        if constexpr (QUADS) {
+            // The first sixteen entries of the wavefront's rows of all its blocks, four to a lane, then their weights: requested together
+            // (past a row's last entry: codebook entry 0 and the column of zeros).  The activations of four entries of each row are
+            // requested while the four before them are multiplied.
+            const uint32_t t = (uint32_t)lane & 3u;
+            auto entry = [&](uint32_t at, int left) { return (int)t < left ? (uint32_t)*(lds_u16)(uintptr_t)at : (uint32_t)kTile; };
+            uint32_t ent[GW][4], at[GW];
+            int left[GW];
+            float w[GW][4];
 #pragma unroll
-        for (int g = 0; g < G; ++g)
+            for (int i = 0; i < GW; ++i) {
+                const int g = g_first + i * g_step;
+                left[i] = g < G && blk_lo + ph * G + g < blk_hi ? (int)(r[i].end - r[i].starts) : 0;
+                at[i] = (uint32_t)(uintptr_t)(lds_u16)(lists + ((ph & 1) * G + min(g, G - 1)) * list_cap) + 2u * (r[i].starts + t);
 #pragma unroll
-            for (int i = 0; i < RQ; ++i) ent[g][i] = entry(list_at(g, i), count(g, i));
+                for (int q = 0; q < 4; ++q) ent[i][q] = entry(at[i] + 8u * q, left[i] - 4 * q);
+            }
 #pragma unroll
-        for (int g = 0; g < G; ++g)
+            for (int i = 0; i < GW; ++i)
 #pragma unroll
-            for (int i = 0; i < RQ; ++i) w[g][i] = s.T.cb[ent[g][i] >> 8];
+                for (int q = 0; q < 4; ++q) w[i][q] = s.T.cb[ent[i][q] >> 8];
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const uint32_t xbase = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) float *)(slabs + ((ph & 1) * G + g) * kSlab) +
-                                   (uint32_t)(l16 * IPL * 4);
-#pragma unroll
-            for (int i = 0; i < RQ; ++i) {
-                int left = count(g, i);
-                uint32_t at = list_at(g, i);
+            for (int i = 0; i < GW; ++i) {
+                const uint32_t xbase = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) float *)(slabs + ((ph & 1) * G + min(g_first + i * g_step, G - 1)) * kSlab) + 16u * t;
+                auto off = [&](uint32_t e) { return (e & 255u) * (uint32_t)(kImages * 4); };
+                if (!__any(left[i] > 0)) continue;                          // (all conditions here are uniform)
                 for (;;) {
-                    const uint32_t off = (ent[g][i] & 255u) * (uint32_t)(kImages * 4);
-                    const bool half = __any(left > 8), more = __any(left > 16);      // uniform
-                    float x0[8][IPL], x1[8][IPL];
-                    rows_read<IPL, 0>(x0, off, xbase);
-                    if (half) rows_read<IPL, 8>(x1, off, xbase);
-                    const float wv = w[g][i];
-                    if (more) ent[g][i] = entry(at += 32u, left -= 16);
-                    rows_add<IPL, 0>(acc[i], x0, wv);
-                    if (more) w[g][i] = s.T.cb[ent[g][i] >> 8];
-                    if (half) rows_add<IPL, 8>(acc[i], x1, wv);
+                    float x0[4][AI], x1[4][AI];
+                    const bool two = __any(left[i] > 4), three = __any(left[i] > 8), four = __any(left[i] > 12), more = __any(left[i] > 16);
+                    quad_read<IPL>(x0, off(ent[i][0]), xbase);
+                    if (two) quad_read<IPL>(x1, off(ent[i][1]), xbase);
+                    quad_add<IPL>(acc[0], x0, w[i][0]);
+                    if (two) {
+                        if (three) quad_read<IPL>(x0, off(ent[i][2]), xbase);
+                        quad_add<IPL>(acc[0], x1, w[i][1]);
+                        if (three) {
+                            if (four) quad_read<IPL>(x1, off(ent[i][3]), xbase);
+                            quad_add<IPL>(acc[0], x0, w[i][2]);
+                            if (four) quad_add<IPL>(acc[0], x1, w[i][3]);
+                        }
+                    }
                     if (!more) break;
+                    left[i] -= 16;
+                    at[i] += 32u;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) ent[i][q] = entry(at[i] + 8u * q, left[i] - 4 * q);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) w[i][q] = s.T.cb[ent[i][q] >> 8];
+                }
+            }
+        }
+    };
+    auto multiply_rows = [&](int ph, const RowRange (&r)[GW]) {
+        if constexpr (!QUADS) {
+            // the first sixteen entries of all the rows, then their weights: requested together
+            // (past a row's last entry: codebook entry 0 and the column of zeros)
+            auto entry = [&](uint32_t at, int left) { return l16 < left ? (uint32_t)*(lds_u16)(uintptr_t)at : (uint32_t)kTile; };
+            auto list_at = [&](int g, int i) { return (uint32_t)(uintptr_t)(lds_u16)(lists + ((ph & 1) * G + g) * list_cap) + 2u * (r[g].at(i) + (uint32_t)l16); };
+            auto count = [&](int g, int i) { return blk_lo + ph * G + g < blk_hi ? (int)(r[g].at(i + 1) - r[g].at(i)) : 0; };
+            uint32_t ent[G][RQ];
+            float w[G][RQ];
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+                for (int i = 0; i < RQ; ++i) ent[g][i] = entry(list_at(g, i), count(g, i));
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+                for (int i = 0; i < RQ; ++i) w[g][i] = s.T.cb[ent[g][i] >> 8];
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                const uint32_t xbase = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) float *)(slabs + ((ph & 1) * G + g) * kSlab) +
+                                       (uint32_t)(l16 * IPL * 4);
+#pragma unroll
+                for (int i = 0; i < RQ; ++i) {
+                    int left = count(g, i);
+                    uint32_t at = list_at(g, i);
+                    for (;;) {
+                        const uint32_t off = (ent[g][i] & 255u) * (uint32_t)(kImages * 4);
+                        const bool half = __any(left > 8), more = __any(left > 16);      // uniform
+                        float x0[8][IPL], x1[IPL == 4 ? 4 : 8][IPL];
+                        rows_read<IPL, 0>(x0, off, xbase);
+                        if (half) rows_read<IPL, 8>(x1, off, xbase);
+                        const float wv = w[g][i];
+                        // (with four images a lane the eight behind the first eight go four at a time: rows differ, and it is these lanes'
+                        // multiply-adds and reads that count.  With fewer, the wait for the last four does.)
+                        const bool rest = IPL == 4 && __any(left > 12);
+                        if (more) ent[g][i] = entry(at += 32u, left -= 16);
+                        rows_add<IPL, 0>(acc[i], x0, wv);
+                        if (more) w[g][i] = s.T.cb[ent[g][i] >> 8];
+                        if (half) {
+                            float x2[4][IPL];
+                            if (rest) rows_read<IPL, 12>(x2, off, xbase);
+                            rows_add<IPL, 8>(acc[i], x1, wv);
+                            if (rest) rows_add<IPL, 12>(acc[i], x2, wv);
+                        }
+                        if (!more) break;
+                    }
                 }
             }
         }
     };
 
+    auto multiply = [&](int ph, const RowRange (&r)[GW]) {
+        multiply_quads(ph, r);
+        multiply_rows(ph, r);
+    };
+
     if (phases > 0) {
-        RowRange now[G], next[G];
+        RowRange now[GW], next[GW];
         for (int i = (int)threadIdx.x; i < L.table_rows; i += kRowsThreads) s.tables[i] = L.tables[i];
         first_slot(0);
         first_record(0);
@@ -350,15 +482,33 @@ __global__ __launch_bounds__(kRowsThreads) void fc_rows_kernel(LayerDev L, const
                 first_record(ph + 2);
                 slab_store(ph + 1);
 #pragma unroll
-                for (int g = 0; g < G; ++g) now[g] = next[g];
+                for (int g = 0; g < GW; ++g) now[g] = next[g];
             }
             __syncthreads();
         }
     }
-    // the quarter's rows of the workgroup's partial tile, part[block row][split][row][Bp]
+    // the wavefront's rows of the workgroup's partial tile, part[block row][split][row][Bp]
+    float *to = part + (((size_t)p * splits + j) * kTile + row0) * (size_t)Bp + img0;
+    if constexpr (QUADS) {
+        // (the two halves of the workgroup have every second block's sums each; every wavefront has passed its last barrier)
+        float *sums = slabs + (wave & 7) * (64 * AI) + lane * AI;
+        if (G > 1 && wave >= 8) store_floats<4>(sums, acc[0]);
+        if constexpr (AI == 8)
+            if (G > 1 && wave >= 8) store_floats<4>(sums + 4, acc[0] + 4);
+        if (G > 1) __syncthreads();
+        if (wave >= 8) return;
 #pragma unroll
-    for (int i = 0; i < RQ; ++i)
-        store_floats<IPL>(part + (((size_t)p * splits + j) * kTile + row0 + i) * (size_t)Bp + img0 + l16 * IPL, acc[i]);
+        for (int h = 0; h < IPL; ++h) {
+            float y[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+            if (G > 1) load_floats<4>(sums + 4 * h, y);
+#pragma unroll
+            for (int m = 0; m < 4; ++m) y[m] += acc[0][4 * h + m];
+            store_floats<4>(to + 16 * h + 4 * (lane & 3), y);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < RQ; ++i) store_floats<IPL>(to + (size_t)i * Bp + l16 * IPL, acc[i]);
+    }
 }
 
 // Finishes fc_rows_kernel: Y[image][row] = act(sum over the splits + bias) from part[block row][split][row][Bp].  The

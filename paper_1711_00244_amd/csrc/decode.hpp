@@ -98,6 +98,20 @@ __device__ __forceinline__ LaneRecord split_record(uint64_t w, uint32_t n)
     return LaneRecord{{(uint32_t)v, (uint32_t)(v >> 32)}, {(uint32_t)i, (uint32_t)(i >> 32)}, n};
 }
 
+// A layer's description read from memory: the compiler takes its pointers for ones that could point anywhere (flat loads, which wait
+// for LDS as well, and values that differ from lane to lane), unless it is told that they point to device memory.  (By way of a number: a cast there and back is taken for nothing.)
+template <class T> __device__ __forceinline__ const T *in_global(const T *p) { return (const T *)(const __attribute__((address_space(1))) T *)(uintptr_t)p; }
+
+__device__ __forceinline__ LayerDev in_global(LayerDev L)
+{
+    L.records = in_global(L.records);
+    L.meta = in_global(L.meta);
+    L.panel_chunk = in_global(L.panel_chunk);
+    L.rec_pos = in_global((const uint16_t *)L.rec_pos);
+    L.tables = in_global(L.tables);
+    return L;
+}
+
 struct ChunkHead {
     cl_chunk_meta m;
     uint32_t nrec;

@@ -959,7 +959,7 @@ static int32_t forward_sparse(const cl_layer *L, const LayerDev &D, const Sparse
                               bool in_stack = false, const PrevSlots *prev = nullptr, bool finish = true)
 {
     if (P.rows.ipl) return forward_rows(L, D, P.rows, d_X, d_bias, d_Y, batch, relu, part, st);
-    const PrevSlots from = prev ? *prev : PrevSlots{nullptr, nullptr, nullptr, 1, 0, 0, 0};
+    const PrevSlots from = prev ? *prev : PrevSlots{};
     if ((prev || !finish) && !sparse_can_fold(L, P, batch)) return fail(CL_EINVAL, "internal: layer cannot take or leave partial tiles");
     const int M = L->desc.M, K = L->desc.K;
     dim3 grid;
@@ -1424,7 +1424,7 @@ try {
             if (P.fold_in[i]) {
                 const cl_layer *Lp = layers[i - 1];
                 prev = PrevSlots{(const float *)region(part0, P.part_bytes, i - 1), make_dev(Lp).panel_chunk,
-                                 d_bias_or_null ? d_bias_or_null[i - 1] : nullptr, Lp->desc.block_h, P.fc[i - 1].sparse.wg_per_panel,
+                                 d_bias_or_null ? d_bias_or_null[i - 1] : nullptr, divisor((uint32_t)Lp->desc.block_h), P.fc[i - 1].sparse.wg_per_panel,
                                  batch, relu_hidden};
             }
             const bool finish = last || !P.fold_in[i + 1];

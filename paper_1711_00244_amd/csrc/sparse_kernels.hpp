@@ -176,7 +176,8 @@ struct PrevSlots {
     const float *part;              // null: the input is X
     const uint32_t *panel_chunk;    // of the layer before: how many slots each of its block rows filled
     const float *bias;              // of the layer before, or null
-    int bh, wg_per_panel, part_b, relu;
+    Divisor bh;
+    int wg_per_panel, part_b, relu;
 };
 
 // Where fc_sparse_whole_kernel's outputs go.
@@ -286,17 +287,25 @@ __device__ __forceinline__ void fc_sparse_body(const LayerDev &L, const float *_
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem_raw[];
     const Smem s = carve(smem_raw, L);
+    // Everything the prologue waits for is requested before anything of it is touched: the table image, which needs nothing,
+    // then chunk heads, records and their positions, then activations.  (Many layers in one grid gain
+    // by it, one layer's launch 1 %: its other workgroups fill the time.)
+    TableRegs tr;
+    const bool copies = NW == kWaves || threadIdx.x < kThreads;         // the table image is copied by kThreads threads
+    if (copies) tr = fetch_tables(L);
     const int p = (int)wg_per_panel.quotient(wg), j = (int)(wg - (uint32_t)p * wg_per_panel.d);
     const uint32_t pc1 = L.panel_chunk[p + 1];
     const uint32_t my0 = L.panel_chunk[p] + (uint32_t)j * (NW * R);
     if (!WHOLE && my0 >= pc1) return;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = (int)(threadIdx.x & 63);
-    // wavefront w takes chunks my0 + w, my0 + 8 + w, ...: all their records are requested
-    // before the tables are copied
+    // activation columns of the blocks this workgroup's chunks belong to
+    const uint32_t pb0 = (uint32_t)p * (uint32_t)L.nbw;
+    const uint32_t blk_a = WHOLE ? 0 : L.meta[my0].blk, blk_b = WHOLE ? 0 : L.meta[min(pc1, my0 + (uint32_t)(NW * R)) - 1u].blk;
+    // wavefront w takes chunks my0 + w, my0 + 8 + w, ...
     bool have[R];
     ChunkHead h[R];
-    LaneRecord rec[R];
+    uint64_t word[R];                                                   // the lane's records, as they are stored
     uint32_t rec_pos[R];
     const bool priv = private_tiles(L.bh, BT);
 #pragma unroll
@@ -304,38 +313,43 @@ __device__ __forceinline__ void fc_sparse_body(const LayerDev &L, const float *_
         const uint32_t c = my0 + (uint32_t)(i * NW + wave);
         have[i] = c < pc1;
         h[i] = ChunkHead{};
-        rec[i] = LaneRecord{};
+        word[i] = 0;
         rec_pos[i] = 0;
+        // (a chunk past the block row's last: that one's head, so that heads are asked for without a branch; a block row always has one but where
+        // a workgroup has the whole of it)
+        if (!WHOLE || have[i]) h[i] = load_head(L, WHOLE ? c : min(c, pc1 - 1u));
         if (have[i]) {
-            h[i] = load_head(L, c);
-            rec[i] = load_record(L, h[i], lane);
-            if (priv && (uint32_t)lane < h[i].nrec) {
+            if ((uint32_t)lane < h[i].nrec) {
                 const size_t r = (size_t)h[i].m.rec_off + lane;
-                rec_pos[i] = L.pos32 ? ((const uint32_t *)L.rec_pos)[r] : ((const uint16_t *)L.rec_pos)[r];
+                word[i] = L.records[r];
+                if (priv) rec_pos[i] = L.pos32 ? ((const uint32_t *)L.rec_pos)[r] : ((const uint16_t *)L.rec_pos)[r];
             }
         }
     }
-    TableRegs tr;
-    const bool copies = NW == kWaves || threadIdx.x < kThreads;         // the table image is copied by kThreads threads
-    if (copies) tr = fetch_tables(L);
     const int n_tiles = WHOLE ? (int)((pc1 - my0 + kWaves - 1) / kWaves * kWaves) : priv ? kWaves : 1;
     float *ytile = s.extra;                  // [n_tiles][BT][bh]
     float *xs = ytile + (size_t)n_tiles * L.bh * BT;   // [xcap][BT]: a column's BT images side by side, one LDS read per entry
-    // activation columns of the blocks this workgroup's chunks belong to
-    const uint32_t pb0 = (uint32_t)p * (uint32_t)L.nbw;
-    const uint32_t c_last = min(pc1, my0 + (uint32_t)(NW * R)) - 1u;
-    const int col_a = WHOLE ? 0 : (int)(L.meta[my0].blk - pb0) * L.bw;
-    const int col_b = WHOLE ? L.K : min(L.K, (int)(L.meta[c_last].blk - pb0 + 1u) * L.bw);
+    const int col_a = WHOLE ? 0 : (int)(blk_a - pb0) * L.bw;
+    const int col_b = WHOLE ? L.K : min(L.K, (int)(blk_b - pb0 + 1u) * L.bw);
     const int width = col_b - col_a;
     const bool slab = WHOLE || width <= xcap;
-    if (FOLD && slab && prev.part) {
+    const bool fold = FOLD && slab && prev.part;
+    float x0[BT];                                                       // the thread's first column of the slab
+#pragma unroll
+    for (int b = 0; b < BT; ++b) x0[b] = 0.0f;
+    if (slab && !fold && (int)threadIdx.x < width) {
+#pragma unroll
+        for (int b = 0; b < BT; ++b)
+            if (b < nb) x0[b] = X[(size_t)b * L.K + col_a + threadIdx.x];
+    }
+    if (fold) {
         // (the host takes this form only for layers whose every workgroup has a slab)
         constexpr uint32_t kPerWg = kWaves * kSparseChunksPerWave;
         for (int t = threadIdx.x; t < width; t += blockDim.x) {
-            const int k = col_a + t, pp = k / prev.bh, r = k - pp * prev.bh;
+            const uint32_t k = (uint32_t)(col_a + t), pp = prev.bh.quotient(k), r = k - pp * prev.bh.d;
             const int active = (int)((prev.panel_chunk[pp + 1] - prev.panel_chunk[pp] + kPerWg - 1) / kPerWg);
-            const float *src = prev.part + (size_t)pp * prev.wg_per_panel * prev.part_b * prev.bh + r;
-            const size_t step = (size_t)prev.part_b * prev.bh;
+            const float *src = prev.part + (size_t)pp * prev.wg_per_panel * prev.part_b * prev.bh.d + r;
+            const size_t step = (size_t)prev.part_b * prev.bh.d;
             const float bv = prev.bias ? prev.bias[k] : 0.0f;
 #pragma unroll
             for (int b = 0; b < BT; ++b) {
@@ -343,7 +357,7 @@ __device__ __forceinline__ void fc_sparse_body(const LayerDev &L, const float *_
                 for (int j = 0; j < active; j += 12) {      // twelve loads in flight, added in slot order
                     float a[12];
 #pragma unroll
-                    for (int u = 0; u < 12; ++u) a[u] = src[(size_t)(j + u < active ? j + u : j) * step + (size_t)b * prev.bh];
+                    for (int u = 0; u < 12; ++u) a[u] = src[(size_t)(j + u < active ? j + u : j) * step + (size_t)b * prev.bh.d];
 #pragma unroll
                     for (int u = 0; u < 12; ++u)
                         if (j + u < active) acc += a[u];
@@ -351,20 +365,6 @@ __device__ __forceinline__ void fc_sparse_body(const LayerDev &L, const float *_
                 acc += bv;
                 xs[t * BT + b] = prev.relu ? fmaxf(acc, 0.0f) : acc;
             }
-        }
-    } else if (slab && BT < 4) {
-#pragma unroll
-        for (int b = 0; b < BT; ++b)
-            for (int t = threadIdx.x; t < width; t += blockDim.x) xs[t * BT + b] = b < nb ? X[(size_t)b * L.K + col_a + t] : 0.0f;
-    } else if (slab) {
-        // a column's images are requested together and stored together
-        for (int t = threadIdx.x; t < width; t += blockDim.x) {
-            float v[BT];
-#pragma unroll
-            for (int b = 0; b < BT; ++b) v[b] = b < nb ? X[(size_t)b * L.K + col_a + t] : 0.0f;
-            constexpr int kW = BT < 4 ? BT : 4;
-#pragma unroll
-            for (int q = 0; q < BT / kW; ++q) store_floats<kW>(xs + t * BT + x_group<BT>(t, q) * kW, v + q * kW);
         }
     }
     // (16 bytes at a time, and four outputs per thread at the end, pay from four images on -
@@ -377,18 +377,36 @@ __device__ __forceinline__ void fc_sparse_body(const LayerDev &L, const float *_
         for (int t = threadIdx.x; t < n_tiles * L.bh * BT; t += blockDim.x) ytile[t] = 0.0f;
     }
     if (copies) store_tables(s, L, tr);
+    if (slab && !fold) {
+        // a column's images are stored together
+        auto store_column = [&](int t, const float (&v)[BT]) {
+            constexpr int kW = BT < 4 ? BT : 4;
+#pragma unroll
+            for (int q = 0; q < BT / kW; ++q) store_floats<kW>(xs + t * BT + x_group<BT>(t, q) * kW, v + q * kW);
+        };
+        if ((int)threadIdx.x < width) store_column((int)threadIdx.x, x0);
+        for (int t = threadIdx.x + blockDim.x; t < width; t += blockDim.x) {
+            float v[BT];
+#pragma unroll
+            for (int b = 0; b < BT; ++b) v[b] = b < nb ? X[(size_t)b * L.K + col_a + t] : 0.0f;
+            store_column(t, v);
+        }
+    }
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < R; ++i) {
         if (!have[i]) continue;
         const BlockGeom g = block_geom(L, p, (int)(h[i].m.blk - pb0));
+        LaneRecord rec = split_record(word[i], (uint32_t)word[i] & 15u);
         // The entries of the record in order, in every lane up to the wavefront's longest
         // record: a lane past its own entries multiplies codebook entry 0 with a column
         // of the block.  The instantiations differ in where the activations come from
         // (LDS stays LDS: no generic pointers) and in how a position splits into row and
         // column (shift and mask for a power-of-two block width).
         auto entries_shared = [&](auto load_x, auto split) {
-            const Symbols y = decode_record(rec[i], s.T);
+            // (a count of its own: what the decode makes of it would otherwise be worked out ahead of every form)
+            asm volatile("" : "+v"(rec.n));
+            const Symbols y = decode_record(rec, s.T);
             const LaneStart st = lane_starts(y, h[i].m.pos0);
             uint32_t cur = 0;
             float acc[BT];
@@ -459,7 +477,7 @@ __device__ __forceinline__ void fc_sparse_body(const LayerDev &L, const float *_
             // stack at eight 49.9 / 51.9 / 49.7, at four 41.0 / 37.0 / -, at one 31.5 / 28.6 / -; sixteen layers of
             // 4096 x 4096 in one grid at one image 59.7 / 50.2 / -, at four 80.3 / 66.2 / -, at eight 124.1 / 121.3 / 129.8).
             if constexpr (ONE_PASS) {
-                const uint32_t n = rec[i].n;
+                const uint32_t n = rec.n;
                 bool first = true;                          // no entry looked up yet
                 auto look = [&](uint32_t at, uint32_t ev, Pending<BT> &e) {
                     uint32_t cc;
@@ -471,10 +489,10 @@ __device__ __forceinline__ void fc_sparse_body(const LayerDev &L, const float *_
                 };
                 Tables V = s.T;                             // (the masks in vector registers: an and-or takes one scalar operand)
                 asm("" : "+v"(V.vmask), "+v"(V.imask));
-                entries_in_one_pass<BT, shifted>(rec[i], V, wave_max(n), (rec_pos[i] - 1u) << (shifted ? 8 : 0), look,
+                entries_in_one_pass<BT, shifted>(rec, V, wave_max(n), (rec_pos[i] - 1u) << (shifted ? 8 : 0), look,
                                                  [&](uint32_t j, const Pending<BT> &e) { if (j < n) use(e); });
             } else {
-                const Symbols y = decode_symbols(rec[i], s.T);
+                const Symbols y = decode_symbols(rec, s.T);
                 auto split_at = [&](uint32_t pos, uint32_t &r, uint32_t &cc) { split(shifted ? pos << 8 : pos, r, cc); };
                 if (y.n > 0) {
                     uint32_t unused;
@@ -612,23 +630,25 @@ constexpr int kWholeWaves = 16, kWholeRounds = 3, kWholeBT = 4;
 template <int BT>
 __global__ __launch_bounds__(kWholeWaves * 64) void fc_sparse_whole_kernel(LayerDev L, const float *__restrict__ X, WholeOut out, int nb)
 {
-    fc_sparse_body<BT, false, true, true, kWholeWaves, kWholeRounds>(L, X, nullptr, Divisor{1, 0, 0, 1}, 0, PrevSlots{nullptr, nullptr, nullptr, 1, 0, 0, 0},
+    fc_sparse_body<BT, false, true, true, kWholeWaves, kWholeRounds>(L, X, nullptr, Divisor{1, 0, 0, 1}, 0, PrevSlots{},
                                                                     blockIdx.x, nb, out);
 }
 
 // Several layers of one shape in one grid (the same layer of several models, or layers
 // whose inputs do not depend on each other): workgroups wgs_per_layer i ..
 // wgs_per_layer (i + 1) - 1 do layer i's share of Algorithm 2, from its own input
-// (x_stride floats apart; 0: one input for all) into its own partial tiles.
+// (x_stride floats apart; 0: one input for all) into its own partial tiles.  Bound by vector issue, so what every lane need not work out
+// for itself weighs: with the layer's pointers as they come from `table` (in_global) chunk heads and block geometry were vector values,
+// and each load waited for the one before (sixteen layers of 4096 x 4096 at 9 %, one image: 49.9 -> 43.6 us a call).
 template <int BT>
 __global__ __launch_bounds__(kThreads) void fc_sparse_group_kernel(const LayerDev *__restrict__ table, Divisor wgs_per_layer,
                                                                    const float *__restrict__ X, size_t x_stride, float *part,
                                                                    size_t part_stride, Divisor wg_per_panel, int xcap)
 {
     const uint32_t job = wgs_per_layer.quotient(blockIdx.x), wg = blockIdx.x - job * wgs_per_layer.d;
-    const LayerDev L = table[job];
+    const LayerDev L = in_global(table[job]);
     fc_sparse_body<BT, false, true>(L, X + job * x_stride, part + job * part_stride, wg_per_panel, xcap,
-                       PrevSlots{nullptr, nullptr, nullptr, 1, 0, 0, 0}, wg, BT);
+                       PrevSlots{}, wg, BT);
 }
 
 // Finishes the sparse path: adds up the partial tiles of each block row in a fixed
@@ -700,7 +720,7 @@ __global__ __launch_bounds__(kRedThreads) void fc_reduce_group_kernel(const Laye
                                                                       size_t y_stride, int B, int wg_per_panel, int relu)
 {
     const int job = __builtin_amdgcn_readfirstlane((int)blockIdx.x / wgs_per_layer), wg = (int)blockIdx.x - job * wgs_per_layer;
-    const LayerDev L = table[job];
+    const LayerDev L = in_global(table[job]);
     fc_reduce_body(L, part + job * part_stride, bias ? bias + job * bias_stride : nullptr, Y + job * y_stride, B, B, wg_per_panel, relu,
                    wg);
 }

@@ -119,9 +119,15 @@ struct ChunkHead {
 
 __device__ __forceinline__ ChunkHead load_head(const LayerDev &L, uint32_t c)
 {
+    // (as constant memory, which a launch never writes: one scalar load where c is the same in all lanes, whatever the kernel stores before)
+    typedef const __attribute__((address_space(4))) cl_chunk_meta *const_meta;
+    const const_meta m = (const_meta)(uintptr_t)L.meta + c;
     ChunkHead h;
-    h.m = L.meta[c];
-    h.nrec = L.meta[c + 1].rec_off - h.m.rec_off;
+    h.m.sym_off = m->sym_off;
+    h.m.rec_off = m->rec_off;
+    h.m.blk = m->blk;
+    h.m.pos0 = m->pos0;
+    h.nrec = m[1].rec_off - h.m.rec_off;
     return h;
 }
 

@@ -95,42 +95,48 @@ __global__ __launch_bounds__(kThreads) void wide_expand_kernel(ExpandJobs jobs)
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = (int)(threadIdx.x & 63);
     const uint32_t c = (blockIdx.x - jobs.wg0[job]) * kWaves + (uint32_t)wave;
+    // (Everything is requested before anything is touched; a wavefront past the last chunk asks for that one's.  Head, record, places and tables
+    // were four trips to memory in turn: fc6 and fc7 of the AlexNet-shaped stack at 256 images, with the branch below, 20.1 -> 18.5 us.)
+    const TableRegs tables = fetch_tables(L);
     const bool have = c < L.n_chunks;
-    ChunkHead h{};
-    LaneRecord rec{};
-    uint32_t base0 = 0, base1 = 0;
-    if (have) {
-        h = load_head(L, c);
-        rec = load_record(L, h, lane);
-        base0 = L.chunk_half[2 * (size_t)c];
-        base1 = L.chunk_half[2 * (size_t)c + 1];
-    }
-    store_tables(s, L, fetch_tables(L));
+    const uint32_t mine_c = min(c, L.n_chunks - 1u);
+    const ChunkHead h = load_head(L, mine_c);
+    const uint64_t word = (uint32_t)lane < h.nrec ? L.records[(size_t)h.m.rec_off + lane] : 0ull;
+    const uint32_t base0 = L.chunk_half[2 * (size_t)mine_c], base1 = L.chunk_half[2 * (size_t)mine_c + 1];
+    store_tables(s, L, tables);
     __syncthreads();
     if (!have) return;
     const BlockGeom g = block_geom(L, h.m.blk);
-    const Symbols y = decode_record(rec, s.T);
+    const Symbols y = decode_record(split_record(word, (uint32_t)word & 15u), s.T);
     const LaneStart st = lane_starts(y, h.m.pos0);
-    // the lane's surviving weights per half, then where its first of each half goes: byte offsets
-    // in the chunk's list, the first half's weights before the second's
-    uint32_t mine = 0;
-    for_each_entry<true>(y, st.sum, [&](uint32_t, uint32_t v, uint32_t, uint32_t pos) {
-        uint32_t r, cc;
-        split_pos(pos, g, r, cc);
-        mine += (v != 0u ? 1u : 0u) << ((cc & (uint32_t)kHalf) >> 2);
-    });
-    const uint32_t incl = wave_incl_scan(mine), excl = incl - mine;
-    const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63), n0 = all & 0xffffu, n = n0 + (all >> 16);
-    uint32_t at = (excl + (n0 << 16)) << 2;
     uint32_t *list = (uint32_t *)s.extra + wave * kExpandList;
-    for_each_entry<true>(y, st.sum, [&](uint32_t, uint32_t v, uint32_t, uint32_t pos) {
-        uint32_t r, cc;
-        split_pos(pos, g, r, cc);
-        const uint32_t half = (cc & (uint32_t)kHalf) >> 2;              // 0 or 16
-        const WideEntry e = (v << 16) | ((cc & (uint32_t)(kHalf - 1)) << 8) | ((r & (uint32_t)(kMulRows - 1)) * jobs.ipl);
-        *(uint32_t *)((char *)list + (v != 0u ? (at >> half) & 0xffffu : (uint32_t)(kExpandList - 1) * 4u)) = e;
-        at += (v != 0u ? 4u : 0u) << half;
-    });
+    uint32_t n0 = 0, n = 0;
+    auto expand = [&](auto split) {
+        // the lane's surviving weights per half, then where its first of each half goes: byte offsets
+        // in the chunk's list, the first half's weights before the second's
+        uint32_t mine = 0;
+        for_each_entry<true>(y, st.sum, [&](uint32_t, uint32_t v, uint32_t, uint32_t pos) {
+            uint32_t r, cc;
+            split(pos, r, cc);
+            mine += (v != 0u ? 1u : 0u) << ((cc & (uint32_t)kHalf) >> 2);
+        });
+        const uint32_t incl = wave_incl_scan(mine), excl = incl - mine;
+        const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        n0 = all & 0xffffu;
+        n = n0 + (all >> 16);
+        uint32_t at = (excl + (n0 << 16)) << 2;
+        for_each_entry<true>(y, st.sum, [&](uint32_t, uint32_t v, uint32_t, uint32_t pos) {
+            uint32_t r, cc;
+            split(pos, r, cc);
+            const uint32_t half = (cc & (uint32_t)kHalf) >> 2;          // 0 or 16
+            const WideEntry e = (v << 16) | ((cc & (uint32_t)(kHalf - 1)) << 8) | ((r & (uint32_t)(kMulRows - 1)) * jobs.ipl);
+            *(uint32_t *)((char *)list + (v != 0u ? (at >> half) & 0xffffu : (uint32_t)(kExpandList - 1) * 4u)) = e;
+            at += (v != 0u ? 4u : 0u) << half;
+        });
+    };
+    // (the form of the split is chosen once: a branch for every entry kept each behind the one before)
+    if (g.shift >= 0) expand([&](uint32_t pos, uint32_t &r, uint32_t &cc) { r = pos >> g.shift; cc = pos & ((uint32_t)g.bwp - 1u); });
+    else expand([&](uint32_t pos, uint32_t &r, uint32_t &cc) { split_pos(pos, g, r, cc); });
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     for (uint32_t i = (uint32_t)lane; i < n; i += 64u) ent[i < n0 ? base0 + i : base1 + (i - n0)] = list[i];
 }

@@ -234,6 +234,27 @@ constexpr int kTileDecodeThreads = kTileDecodeWaves * 64;
 __global__ __launch_bounds__(kTileDecodeThreads) void decode_tiles_kernel(LayerDev L, float *tiles_out, ConvGeom cg, int n_rows, int combined,
                                                                 uint2 *rows)
 {
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem_raw[];
+    const Smem s = carve(smem_raw, L);
+    float *tile = s.extra;                                  // [kTile][kWStride]
+    const uint32_t b = blockIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int lane = (int)(threadIdx.x & 63);
+    TableRegs tr;
+    if (threadIdx.x < kThreads) tr = fetch_tables(L);           // the table image is copied by kThreads threads
+    const uint32_t c0 = L.block_chunk[b], c1 = L.block_chunk[b + 1];
+    uint32_t c = c0 + (uint32_t)wave;
+    uint32_t pos0 = 0;
+    uint64_t word = 0;
+    auto fetch = [&]() {                                        // chunk c, if the block has it
+        if (c >= c1) return;
+        const ChunkHead h = load_head(L, c);
+        pos0 = h.m.pos0;
+        word = (uint32_t)lane < h.nrec ? L.records[(size_t)h.m.rec_off + lane] : 0ull;
+    };
+    fetch();
+    for (int t = threadIdx.x; t < kTile * kWStride / 4; t += kTileDecodeThreads) ((uint4 *)tile)[t] = uint4{0, 0, 0, 0};
+    if (threadIdx.x < kThreads) store_tables(s, L, tr);
     {
         const int t = (int)(blockIdx.x * kTileDecodeThreads + threadIdx.x);
         if (t < n_rows) {
@@ -247,29 +268,27 @@ __global__ __launch_bounds__(kTileDecodeThreads) void decode_tiles_kernel(LayerD
             rows[t] = e;
         }
     }
-    extern __shared__ __attribute__((aligned(16))) uint8_t smem_raw[];
-    const Smem s = carve(smem_raw, L);
-    float *tile = s.extra;                                  // [kTile][kWStride]
-    const uint32_t b = blockIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int lane = (int)(threadIdx.x & 63);
-    const uint32_t c0 = L.block_chunk[b], c1 = L.block_chunk[b + 1];
-    TableRegs tr;
-    if (threadIdx.x < kThreads) tr = fetch_tables(L);           // the table image is copied by kThreads threads
-    for (int t = threadIdx.x; t < kTile * kWStride / 4; t += kTileDecodeThreads) ((uint4 *)tile)[t] = uint4{0, 0, 0, 0};
-    if (threadIdx.x < kThreads) store_tables(s, L, tr);
     __syncthreads();
     const BlockGeom g = block_geom(L, b);
-    for (uint32_t c = c0 + (uint32_t)wave; c < c1; c += kTileDecodeWaves) {       // uniform per wavefront
-        const ChunkHead h = load_head(L, c);
-        const Symbols y = decode_record(load_record(L, h, lane), s.T);
-        const LaneStart st = lane_starts(y, h.m.pos0);
-        for_each_entry(y, st.sum, [&](uint32_t, uint32_t v, uint32_t, uint32_t pos) {
-            uint32_t r, cc;
-            split_pos(pos, g, r, cc);
-            if (v != 0 && cc < (uint32_t)kTile) tile[r * kWStride + cc] = s.T.cb[v];
-        });
-    }
+    auto place = [&](auto split) {
+        while (c < c1) {                                        // uniform per wavefront
+            const LaneRecord rec = split_record(word, (uint32_t)word & 15u);
+            const uint32_t from = pos0;
+            c += kTileDecodeWaves;
+            fetch();                                            // the next one's record is on its way while this one is decoded
+            const Symbols y = decode_record(rec, s.T);
+            const LaneStart st = lane_starts(y, from);
+            // (padding writes a zero at a place of its own; the weights of four entries are looked up together)
+            place_entries(y, st.sum, [&](uint32_t v) { return s.T.cb[v]; }, [&](uint32_t pos, float w) {
+                uint32_t r, cc;
+                split(pos, r, cc);
+                tile[r * kWStride + cc] = w;
+            });
+        }
+    };
+    // (records are checked when the layer is loaded: a position lies inside its block, and blocks are at most 128 x 128)
+    if (g.shift >= 0) place([&](uint32_t pos, uint32_t &r, uint32_t &cc) { r = pos >> g.shift; cc = pos & ((uint32_t)g.bwp - 1u); });
+    else place([&](uint32_t pos, uint32_t &r, uint32_t &cc) { split_pos(pos, g, r, cc); });
     __syncthreads();
     uint4 *dst = (uint4 *)(tiles_out + (size_t)b * kTile * kTile);
     const uint4 *src = (const uint4 *)tile;

@@ -391,7 +391,8 @@ int32_t cl_conv_workspace_bytes_min(const cl_layer *layer, const cl_conv_desc *c
  *    form splits them into, in the order in which the multiply kernel takes them, and
  *    the same products are added.  Workspace: 2 bytes a term, three terms (two on CL_PATH_MFMA_BF16), for
  *    each weight of the dense matrix and each activation, zero border included, channels of a group rounded up to eight
- *    (to four where it has at most four), and partial tiles.
+ *    (to four where it has at most four), and partial tiles.  Above 256 MB of activations' terms and partial tiles the images are
+ *    taken in groups that need no more (of one image at least), the weights split with the first.
  *  - from 512 columns (images x output pixels) on, when 128-column
  *    tiles give the chip enough to do (work items for a sixteenth of the compute units,
  *    block products for half): every block of the layer is decoded once per call into a

@@ -1660,6 +1660,7 @@ struct ConvPlan {
     bool gather = false;       // blocks decoded once per call, no column matrix in memory: conv_mfma_kernel
     bool planes = false;       // operands split once per call: conv_plane_kernel
     PlaneGeom pg{};
+    int tile = 0;              // its tile, the same for all image groups (the order of the split weights)
     int groups_at_once = 1;    // filter groups per launch: all of them, or one (the compact form)
     size_t lds = 0, xt_bytes = 0, part_bytes = 0, wt_bytes = 0, rows_bytes = 0;
     size_t total() const { return xt_bytes + part_bytes + wt_bytes + rows_bytes; }
@@ -1673,6 +1674,12 @@ constexpr PlaneTile kPlaneTiles[3] = {{128, 128, 4}, {96, 128, 3}, {64, 128, 2}}
 
 constexpr int kPlaneRun = 256;
 
+// Split activations and partial tiles of a launch together: the images of a call are taken in groups that stay below this (one
+// image at least), weights split with the first.  (VGG-16 conv1_2 at 64 images, 1.26 GB at once: us in 2 / 5 / 11 / 22 groups 1786 / 1796 / 1777 /
+// 1880; conv2_2 in 1 / 3 / 5 / 11 1393 / 1444 / 1378 / 1568.  Of 8600 drawn fp32 calls that take the form eight are slower by more than 5 % with this limit than
+// without any, and 137 with half of it.)
+constexpr size_t kPlaneScratch = (size_t)256 << 20;
+
 struct PlaneShape {
     int tile = 0, tiles = 0, splits = 1;
     int64_t cost = 0;          // cycles
@@ -1682,12 +1689,13 @@ struct PlaneShape {
 // multiplies take 32 cycles; with one workgroup to a CU 1.07 times that is measured, with two the chip's clock gives way), 5 k for a workgroup
 // alone on its CU to start and end and 8 k for two; the partial tiles of split steps as in mfma_shape, 300 for a split's turn in the
 // finishing launch and 8 k for that launch.  Over 230 drawn convolutions the launch takes 4 us + 1.11 times its price, and the tile picked is within 2 % of
-// the best of the three on average, 13 % at worst.
-PlaneShape plane_shape(int OCg, int groups, int steps, int ncols, bool bf16, int cus)
+// the best of the three on average, 13 % at worst.  (only: this tile, not the best of the three.)
+PlaneShape plane_shape(int OCg, int groups, int steps, int ncols, bool bf16, int cus, int only = -1)
 {
     cus = std::max(1, cus);
     PlaneShape best;
     for (int i = 0; i < 3; ++i) {
+        if (only >= 0 && i != only) continue;
         const PlaneTile &T = kPlaneTiles[i];
         const int64_t panels = (int64_t)groups * ((OCg + T.rows - 1) / T.rows), tiles = (ncols + T.cols - 1) / T.cols;
         const int64_t step = (int64_t)(bf16 ? 3 : 8) * 32 * T.mfmas * 5 / 4;
@@ -1768,27 +1776,47 @@ bool plan_planes(const cl_layer *L, const cl_conv_desc *cv, int batch, bool bf16
     const int64_t plane = Hp * Wp / (1 + q.px4), image = (int64_t)q.groups * q.CG * plane;                // 16-byte pieces
     q.units = (int)units;
     q.steps = (q.units + 1) / 2;
-    P.imgs = (int)std::min<int64_t>({(int64_t)batch, kMaxTileColumns / ((int64_t)g.P * g.Q), INT32_MAX / (image * 16 * np)});
+    const int pq = g.P * g.Q;
+    auto panels_of = [&](int tile) { return q.groups * ((P.OCg + kPlaneTiles[tile].rows - 1) / kPlaneTiles[tile].rows); };
+    auto xs_of = [&](int imgs) { return round256((size_t)np * 16 * imgs * image); };
+    auto part_of = [&](const PlaneShape &s) {
+        const PlaneTile &T = kPlaneTiles[s.tile];
+        return s.splits == 1 ? 0 : round256((size_t)panels_of(s.tile) * T.rows * s.splits * s.tiles * T.cols * sizeof(float));
+    };
+    // groups of equal size, as few as the launch's offsets and kPlaneScratch allow
+    int most = (int)std::min<int64_t>({(int64_t)batch, kMaxTileColumns / pq, INT32_MAX / (image * 16 * np), std::max<int64_t>(1, kPlaneScratch / (image * 16 * np))});
+    PlaneShape s;
+    for (;;) {
+        const int runs = (batch + most - 1) / most;
+        P.imgs = (batch + runs - 1) / runs;
+        s = plane_shape(P.OCg, q.groups, q.steps, P.imgs * pq, bf16, dl.cus);
+        const size_t bytes = xs_of(P.imgs) + part_of(s);
+        if (bytes <= kPlaneScratch || P.imgs == 1) break;
+        most = std::max(1, std::min(P.imgs - 1, (int)(P.imgs * (double)kPlaneScratch / bytes)));
+    }
+    P.tile = s.tile;
     q.pieces = (uint32_t)(P.imgs * image);
     q.per_plane = divisor((uint32_t)plane);
     q.per_row = divisor((uint32_t)(Wp / (1 + q.px4)));
     q.planes = divisor((uint32_t)(q.groups * q.CG));
     q.per_s = divisor((uint32_t)g.S);
     q.per_group = divisor((uint32_t)(q.px4 ? q.SU : g.R * g.S));
-    P.xt_bytes = round256((size_t)np * q.pieces * 16);
-    P.wt_bytes = P.part_bytes = 0;
+    const size_t wt = (size_t)panels_of(P.tile) * kPlaneTiles[P.tile].rows * q.steps * np * 2 * 16;
+    P.xt_bytes = xs_of(P.imgs);
+    P.wt_bytes = round256(wt);
+    P.part_bytes = part_of(s);
     const int blocks = prep_blocks(L, g.R * g.S);
-    us = 0;
+    const int64_t strips = prep_strips(L, blocks);
+    if (strips > UINT32_MAX / kPrepThreads - 1024) return false;             // (a launch's threads are counted in 32 bits)
+    const double over = std::max<double>(0, strips / std::max(1.0, (double)dl.cus) - 1);
+    us = (bf16 ? 2.0e-6 : 0.95e-6) * wt + (bf16 ? 0 : 7) * over;
     for (int imgs : {P.imgs, batch % P.imgs}) {
         if (imgs == 0) continue;
-        const PlaneShape s = plane_shape(P.OCg, q.groups, q.steps, imgs * g.P * g.Q, bf16, dl.cus);
-        const PlaneTile &T = kPlaneTiles[s.tile];
-        const size_t rows = (size_t)q.groups * ((P.OCg + T.rows - 1) / T.rows) * T.rows, wt = rows * q.steps * np * 2 * 16;
-        P.wt_bytes = std::max(P.wt_bytes, round256(wt));
-        if (s.splits > 1) P.part_bytes = std::max(P.part_bytes, round256(rows * s.splits * s.tiles * T.cols * sizeof(float)));
-        const double over = std::max<double>(0, prep_strips(L, blocks) / std::max(1.0, (double)dl.cus) - 1);
-        us += (imgs == P.imgs ? batch / P.imgs : 1) * (13 + 1.2 * s.cost / 2400 + (bf16 ? 2.0e-6 : 0.95e-6) * wt +
-                                                       (bf16 ? 0.37e-6 : 0.28e-6) * np * 16 * imgs * image + (bf16 ? 0 : 7) * over);
+        if (imgs != P.imgs) {
+            s = plane_shape(P.OCg, q.groups, q.steps, imgs * pq, bf16, dl.cus, P.tile);
+            P.part_bytes = std::max(P.part_bytes, part_of(s));
+        }
+        us += (imgs == P.imgs ? batch / P.imgs : 1) * (13 + 1.2 * s.cost / 2400 + (bf16 ? 0.37e-6 : 0.28e-6) * np * 16 * imgs * image);
     }
     P.rows_bytes = round256((size_t)q.steps * 2 * sizeof(uint32_t));
     P.lds = table_image_bytes(L->val_lut_bits, L->idx_lut_bits, 1 << L->desc.weight_bits) + prep_tile_bytes(blocks) + ((size_t)2 * sizeof(uint2) << L->desc.weight_bits);
@@ -1979,23 +2007,23 @@ int32_t launch_plane(dim3 grid, const uint4 *wt, const uint4 *xs, const uint32_t
     return CL_OK;
 }
 
-// The form with both operands split beforehand: one launch to split them, one to multiply, one to add up
-// where the steps are split.
-int32_t conv_planes(const ConvCall &c, bool bf16, int imgs, void *xs, void *wt, uint32_t *unit_off)
+// The form with both operands split beforehand: one launch to split them (of the first images the weights too), one to multiply, one
+// to add up where the steps are split.
+int32_t conv_planes(const ConvCall &c, bool bf16, int imgs, bool first, void *xs, void *wt, uint32_t *unit_off)
 {
     const ConvPlan &P = *c.P;
     PlaneGeom g = P.pg;
-    const PlaneShape s = plane_shape(P.OCg, g.groups, g.steps, c.ncols, bf16, c.cus);
-    const PlaneTile &T = kPlaneTiles[s.tile];
+    const PlaneShape s = plane_shape(P.OCg, g.groups, g.steps, c.ncols, bf16, c.cus, P.tile);
+    const PlaneTile &T = kPlaneTiles[P.tile];
     g.tile_rows = T.rows;
     g.ppg = (P.OCg + T.rows - 1) / T.rows;
     const uint32_t image = g.planes.d * g.per_plane.d;
     g.pieces = (uint32_t)imgs * image;
     const int blocks = prep_blocks(c.L, P.cg.R * P.cg.S);
-    const int64_t n_strips = prep_strips(c.L, blocks);
+    const int64_t n_strips = first ? prep_strips(c.L, blocks) : 0;
     dim3 grid;
     // (few strips: several workgroups decode the same one and each writes some of its units)
-    const int parts = (int)std::max<int64_t>(1, std::min<int64_t>(8, std::max(1, c.cus) / n_strips));
+    const int parts = first ? (int)std::max<int64_t>(1, std::min<int64_t>(8, std::max(1, c.cus) / n_strips)) : 1;
     GRID_TRY(grid, n_strips * parts + std::min<int64_t>(1024, (g.pieces + kPrepThreads - 1) / kPrepThreads));
     using Prepare = void (*)(LayerDev, PlaneGeom, const float *, uint4 *, uint4 *, uint32_t *, int, int, int);
     static const Prepare prepare[2] = {conv_prepare_kernel<3>, conv_prepare_kernel<2>};
@@ -2123,7 +2151,7 @@ extern "C" int32_t cl_compressed_conv_forward(const cl_layer *L, const cl_conv_d
         c.x = d_X + (size_t)b0 * g.C * g.H * g.W;
         c.y = d_Y + (size_t)b0 * L->desc.M * c.pq;
         if (P.planes) {
-            if (int32_t rc = conv_planes(c, bf16, nb, xt, wt, (uint32_t *)rows)) return rc;
+            if (int32_t rc = conv_planes(c, bf16, nb, b0 == 0, xt, wt, (uint32_t *)rows)) return rc;
             continue;
         }
         mfma_shape(L, c.launch_panels, c.ncols, dl.cus, bf16, c.nq, c.Np, c.splits, P.gather, P.gather || !bf16);

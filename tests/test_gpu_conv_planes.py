@@ -28,12 +28,36 @@ def _terms_bytes(geom, batch, terms):
     return 2 * terms * batch * geom["groups"] * channels * H * (W + (W & 1 if Cg <= 4 else 0))
 
 
-def _check(rng, geom, block, batch, path, density=0.4):
+def _round256(n):
+    return -(-n // 256) * 256
+
+
+def _shapes(geom, batch, terms, workspace):
+    """(rows of a tile, splits of the steps, images of a launch) for which a call of this form asks for `workspace` bytes.  (Tiles that cut
+    a filter group into as many rows, whole tiles counted, cannot be told apart.)"""
+    Cg, g, R, S = geom["C"] // geom["groups"], geom["groups"], geom["R"], geom["S"]
+    P, Q = ((geom[n] + 2 * geom["pad"] - geom[f]) // geom["stride"] + 1 for n, f in (("H", "R"), ("W", "S")))
+    steps = ((R * -(-S // 2) if Cg <= 4 else -(-Cg // 8) * R * S) + 1) // 2
+    found = set()
+    for rows in (128, 96, 64):
+        tiles = g * -(-(geom["OC"] // g) // rows)
+        left = workspace - _round256(tiles * rows * steps * terms * 32) - _round256(8 * steps)
+        for imgs in {-(-batch // runs) for runs in range(1, batch + 1)}:
+            part = left - _round256(_terms_bytes(geom, imgs, terms))
+            one = tiles * rows * -(-imgs * P * Q // 128) * 128 * 4          # (a multiple of 256)
+            if part == 0:
+                found.add((rows, 1, imgs))
+            elif part > 0 and part % one == 0 and 2 <= part // one <= steps:
+                found.add((rows, part // one, imgs))
+    return found
+
+
+def _check(rng, geom, block, batch, path, density=0.4, imgs=None):
     import torch
     L, W = _layer(rng, geom, *block, density=density)
     terms = 2 if path == "bf16" else 3
     p = cl.PATH_MFMA_BF16 if path == "bf16" else cl.PATH_MFMA_F32
-    assert cl.conv_workspace_bytes(L, geom, batch, p) >= _terms_bytes(geom, batch, terms)
+    assert cl.conv_workspace_bytes(L, geom, batch, p) >= _terms_bytes(geom, imgs or batch, terms)
     X = rng.standard_normal((batch, geom["C"], geom["H"], geom["W"])).astype(np.float32)
     bias = rng.standard_normal(geom["OC"]).astype(np.float32)
     Xd, bd = torch.from_numpy(X).cuda(), torch.from_numpy(bias).cuda()
@@ -44,14 +68,14 @@ def _check(rng, geom, block, batch, path, density=0.4):
     # filters of the first and last rows of tiles and groups, the first and last image and one between
     OC, g, Cg = geom["OC"], geom["groups"], geom["C"] // geom["groups"]
     per = OC // g
-    imgs = sorted({0, batch // 2, batch - 1})
+    some = sorted({0, batch // 2, batch - 1})
     for grp in range(g):
         rows = sorted({r for r in (0, 31, 63, 64, 95, 96, 127, 128, per - 1) if r < per})
         sub = dict(geom, C=Cg, OC=len(rows), groups=1)
         at = np.array(rows) + grp * per
-        ref = conv_ref(np.ascontiguousarray(W[at]), np.ascontiguousarray(X[imgs][:, grp * Cg:(grp + 1) * Cg]), sub, bias[at])
+        ref = conv_ref(np.ascontiguousarray(W[at]), np.ascontiguousarray(X[some][:, grp * Cg:(grp + 1) * Cg]), sub, bias[at])
         # (two bf16 terms each: what is dropped is below 3 * 2^-16 of each product)
-        assert_close(Y[imgs][:, at], ref, True, product_rel=3 * 2.0 ** -16 if path == "bf16" else 0.0)
+        assert_close(Y[some][:, at], ref, True, product_rel=3 * 2.0 ** -16 if path == "bf16" else 0.0)
     L.free()
 
 
@@ -77,6 +101,21 @@ CASES = [
 @pytest.mark.parametrize("path", ["f32", "bf16"])
 def test_edges(geom, block, batch, path):
     _check(np.random.default_rng(geom["C"] * geom["OC"] + batch), geom, block, batch, path)
+
+
+@pytest.mark.parametrize("geom,block,batch,imgs", [
+    # terms of all images 300 MB; one image's terms 290 MB; images of 2^18 pixels, at most eight to a launch; a last launch of fewer images
+    (_geom(64, 112, 3, 128), (128, 128), 60, 30), (_geom(480, 316, 1, 64, pad=0), (64, 128), 2, 1), (_geom(4, 512, 3, 96), (96, 128), 10, 5),
+    (_geom(72, 200, 3, 64), (64, 128), 25, 13)])
+def test_images_in_groups(geom, block, batch, imgs):
+    """Scratch that grows with the images stays below 256 MB, or one image's; the images are taken in groups, the weights split with the
+    first."""
+    rng = np.random.default_rng(imgs)
+    L, _ = _layer(rng, geom, *block)
+    assert {s[2] for s in _shapes(geom, batch, 3, cl.conv_workspace_bytes(L, geom, batch))} == {imgs}
+    assert _terms_bytes(geom, imgs, 3) <= 256 << 20 or imgs == 1
+    L.free()
+    _check(rng, geom, block, batch, "f32", imgs=imgs)
 
 
 @pytest.mark.parametrize("density", [0.0, 0.02, 1.0])

@@ -387,7 +387,7 @@ int32_t cl_conv_workspace_bytes_min(const cl_layer *layer, const cl_conv_desc *c
  * layer's matrix with the matrix whose columns are the receptive fields (Sec. III-A),
  * computed on an MFMA path, all filter groups in one launch, in one of three forms:
  *  - long calls, where a model of the launches finds it cheaper (from some 36 us on with
- *    CL_PATH_MFMA_F32): both operands are split once per call into the bf16 terms that the next
+ *    CL_PATH_MFMA_F32, 17 us with CL_PATH_MFMA_BF16): both operands are split once per call into the bf16 terms that the next
  *    form splits them into, in the order in which the multiply kernel takes them, and
  *    the same products are added.  Workspace: 2 bytes a term, three terms (two on CL_PATH_MFMA_BF16), for
  *    each weight of the dense matrix and each activation, zero border included, channels of a group rounded up to eight

@@ -1752,6 +1752,20 @@ int64_t prep_strips(const cl_layer *L, int blocks)
     return (int64_t)L->n_panels * ((L->desc.block_h + rows - 1) / rows) * ((L->nbw + blocks - 1) / blocks);
 }
 
+// What a call of that form takes, in us: the call; each launch of a group of images; a CU's pair of workgroups, or one alone, to start and
+// end, and a step of theirs by the tile; a MB of split weights, of filters of fewer than 16 taps and of others (which end more of their units in other workgroups); rounds of
+// strips behind the first; a MB of split activations, of outputs, of partial tiles, the finishing launch and a split's turn in it; and, of
+// strides above one, whose 64 pixels of a request lie that far apart, a MB requested (stride 2 by whether the terms of a launch exceed
+// 90 MB, wider ones).  [bf16][four channels to a pixel], fitted to 32 k drawn calls of 25 us (bf16 18) and longer: 5.2 % off them (bf16 5.9 %).
+struct PlanePrice {
+    double call, run, pair, alone, step2[3], step1[3], weights[2], over, terms, outputs, part, split, turn, near, far, wide;
+};
+constexpr PlanePrice kPlanePrice[2][2] = {
+    {{13.5, 25, 1.75, 2.2, {.599, .461, .299}, {.624, .485, .309}, {.97, 1.18}, 3.6, .17, .209, .23, 3.8, .124, .006, .023, .025},
+     {12.2, 7, 2.9, 3.15, {.628, .477, .284}, {.644, .489, .309}, {2.65, 2.65}, 0, .20, .119, .73, .26, 0, .003, .003, .008}},
+    {{14.5, 25, .05, 0, {.238, .196, .124}, {.285, .257, .210}, {1.07, 1.50}, 3.6, .216, .200, .31, 2.4, .163, .003, .052, .026},
+     {13, 7, 1.17, 0, {.238, .200, .109}, {.326, .321, .251}, {3.5, 3.5}, 0, .15, .154, 0, 0, 0, .010, .010, .027}}};
+
 // The form whose operands are split beforehand: its geometry and workspace, and what the call will take, in us; false where it cannot run.
 bool plan_planes(const cl_layer *L, const cl_conv_desc *cv, int batch, bool bf16, const DeviceLimits &dl, ConvPlan &P, double &us)
 {
@@ -1808,20 +1822,43 @@ bool plan_planes(const cl_layer *L, const cl_conv_desc *cv, int batch, bool bf16
     const int blocks = prep_blocks(L, g.R * g.S);
     const int64_t strips = prep_strips(L, blocks);
     if (strips > UINT32_MAX / kPrepThreads - 1024) return false;             // (a launch's threads are counted in 32 bits)
-    const double over = std::max<double>(0, strips / std::max(1.0, (double)dl.cus) - 1);
-    us = (bf16 ? 2.0e-6 : 0.95e-6) * wt + (bf16 ? 0 : 7) * over;
+    const int cus = std::max(1, dl.cus);
+    const PlanePrice &p = kPlanePrice[bf16][q.px4];
+    us = p.call - p.run + p.weights[g.R * g.S >= 16] * 1e-6 * cv->out_channels * q.steps * np * 2 * 16 + p.over * std::max(0.0, (double)strips / cus - 1);
     for (int imgs : {P.imgs, batch % P.imgs}) {
         if (imgs == 0) continue;
         if (imgs != P.imgs) {
             s = plane_shape(P.OCg, q.groups, q.steps, imgs * pq, bf16, dl.cus, P.tile);
             P.part_bytes = std::max(P.part_bytes, part_of(s));
         }
-        us += (imgs == P.imgs ? batch / P.imgs : 1) * (13 + 1.2 * s.cost / 2400 + (bf16 ? 0.37e-6 : 0.28e-6) * np * 16 * imgs * image);
+        const int panels = panels_of(P.tile), n = (q.steps + s.splits - 1) / s.splits;
+        const int64_t items = (int64_t)panels * s.tiles * s.splits, rest = items % (2 * cus);
+        const int64_t pairs = items / (2 * cus) + (rest > cus ? 1 : 0);
+        const double xs = 1e-6 * np * 16 * imgs * image, out = 4e-6 * imgs * cv->out_channels * pq;
+        const double fetched = 1e-6 * np * 16 * 2 * q.steps * panels * imgs * pq;
+        double t = p.run + pairs * (p.pair + 2 * n * p.step2[P.tile]) + (rest > 0 && rest <= cus ? p.alone + n * p.step1[P.tile] : 0) +
+                   p.terms * xs + p.outputs * out;
+        if (s.splits > 1) t += p.split + p.turn * (s.splits - 1) + p.part * 1e-6 * part_of(s);
+        if (g.stride > 2) t += p.wide * fetched;
+        else if (g.stride == 2) t += (xs > 90 ? p.far : p.near) * fetched;
+        us += (imgs == P.imgs ? batch / P.imgs : 1) * t;
     }
     P.rows_bytes = round256((size_t)q.steps * 2 * sizeof(uint32_t));
     P.lds = table_image_bytes(L->val_lut_bits, L->idx_lut_bits, 1 << L->desc.weight_bits) + prep_tile_bytes(blocks) + ((size_t)2 * sizeof(uint2) << L->desc.weight_bits);
     return P.lds <= dl.max_lds;
 }
+
+// What a call of the other two forms takes, in us: the call; a workgroup's item (without a column matrix) or a cycle of mfma_shape's price (with
+// one); a 64-wide half of a block, by the blocks' height in thirty-twos (with a column matrix: a block of a row's share); a MB of decoded blocks, of column matrix, of
+// inputs, of outputs; the finishing launch and a MB of partial tiles where block rows are split.  Fitted to the same calls as PlanePrice:
+// 6 % off them (bf16 8 %).  [bf16][filters of up to 32 taps] and [bf16].
+struct OtherPrice {
+    double call, item, half[4], weights, columns, inputs, outputs, split, part;
+};
+constexpr OtherPrice kGatherPrice[2][2] = {
+    {{12.3, .9, {1.91, 2.20, 2.71, 2.87}, .54, 0, .57, .44, 4.4, .45}, {14, 1.3, {1.71, 1.93, 2.75, 2.88}, .50, 0, .09, .25, 2.6, .385}},
+    {{12.7, .65, {1.19, 1.35, 1.55, 1.62}, .67, 0, .78, .35, 2.4, .56}, {11.7, 1.4, {1.03, 1.17, 1.54, 1.59}, .79, 0, .16, .23, 2.2, .46}}};
+constexpr OtherPrice kColumnsPrice[2] = {{7.1, 1.13, {1.2}, 0, .28, 0, .35, 3.1, .23}, {4.7, 1.33, {0}, 0, .58, 0, 1.7, 0, .53}};
 
 // any: whichever is the fastest.  not_planes: operands not split beforehand, which takes less scratch.  compact: the form that needs the
 // least - filter groups one after the other through the same buffers, blocks decoded inside the multiply kernel.
@@ -1874,30 +1911,42 @@ int32_t plan_conv(const cl_layer *L, const cl_conv_desc *cv, int batch, bool bf1
     P.rows_bytes = P.gather ? round256((size_t)L->nbw * kTile * sizeof(uint2)) : 0;
     // workspace for the larger of a full image group and the last, smaller one
     P.xt_bytes = P.part_bytes = 0;
-    // What the call will take, in us, to be compared with plan_planes'.  Over 230 calls drawn from 3 to 512 channels, filters of 3 x 3, 5 x 5 and 11 x 11
-    // and 2e7 to 4e10 operations these are 11 % (bf16 16-19 %) off the measured times, plan_planes' 7 % (12 %).
-    double us = 0;
+    double us = 0, cycles = 0;                              // what the call will take, to be compared with plan_planes'; mfma_shape's price
+    const OtherPrice &p = P.gather ? kGatherPrice[bf16][g.R * g.S <= 32] : kColumnsPrice[bf16];
+    const int nh = conv_halves(L->desc.block_w), height = std::min(3, (L->desc.block_h - 1) / 32);
     for (int imgs : {P.imgs, batch % P.imgs}) {
         if (imgs == 0) continue;
         int nq, np, splits;
         int64_t cost;
         mfma_shape(L, launch_panels, imgs * g.P * g.Q, dl.cus, bf16, nq, np, splits, P.gather, P.gather || !bf16, &cost);
-        const double cycles_us = cost / 2400.0, xt = P.gather ? 0 : (double)P.groups_at_once * xt_bytes_for(L, np, bf16);
-        us += (imgs == P.imgs ? batch / P.imgs : 1) * (P.gather ? 14.5 + (bf16 ? 1.0 : 1.11) * cycles_us + (bf16 ? 1.9e-6 : 1.1e-6) * P.wt_bytes
-                                                                : bf16 ? 4.2 + 1.66 * cycles_us + 0.68e-6 * xt : 2.1 * cycles_us);
-        if (!P.gather) P.xt_bytes = std::max(P.xt_bytes, (size_t)xt);
-        if (!(P.gather && splits == 1))
-            P.part_bytes = std::max(P.part_bytes, (size_t)launch_panels * splits * np * L->desc.block_h * sizeof(float));
+        const size_t xt = P.gather ? 0 : (size_t)P.groups_at_once * xt_bytes_for(L, np, bf16);
+        const size_t part = (size_t)launch_panels * splits * np * L->desc.block_h * sizeof(float);
+        double t = p.columns * 1e-6 * xt + 4e-6 * imgs * ((double)p.inputs * g.C * g.H * g.W + p.outputs * cv->out_channels * g.P * g.Q);
+        if (splits > 1) t += p.split + p.part * 1e-6 * part;
+        if (P.gather) {
+            const int rounds = (int)(((int64_t)launch_panels * splits * (np / kConvColumns) + std::max(1, dl.cus) - 1) / std::max(1, dl.cus));
+            const int halves = splits > 1 ? (L->nbw + splits - 1) / splits * nh
+                                          : (L->nbw - 1) * nh + conv_halves(L->desc.K - (L->nbw - 1) * L->desc.block_w);
+            t += rounds * (p.item + halves * p.half[height]);
+        } else t += p.item * cost / 2400 + p.half[0] * L->nbw / splits;
+        const int runs = imgs == P.imgs ? batch / P.imgs : 1;
+        us += runs * t;
+        cycles += runs * (double)cost;
+        P.xt_bytes = std::max(P.xt_bytes, xt);
+        if (!(P.gather && splits == 1)) P.part_bytes = std::max(P.part_bytes, part);
     }
-    // Both operands split beforehand, where that is cheaper by a twentieth and the call a long one.  What it saves is in proportion to
+    us += p.call + p.weights * 1e-6 * P.wt_bytes;
+    // Both operands split beforehand, where that is cheaper by a twenty-fifth and the call a long one.  What it saves is in proportion to
     // the multiplies, what it costs to the weights (VGG-16 conv4_2 at one image, 14 MB of terms: 19 us to split them and 30 to multiply, gathered 9
-    // and 36).  Of 148 drawn fp32 calls 55 take it, 1.30 times as fast on average as the other two forms, one of them slower by more than 3 % (12 %); of
-    // 80 bf16 ones 57, 1.36 times, five slower (16 % at worst).  Without the limit of 36 us 28 more fp32 calls would, for 1.08 times the speed and
-    // several times the scratch.
-    if (form == ConvForm::any && us > (bf16 ? 0 : 36)) {
+    // and 36).  Of 14200 fp32 calls drawn anew 6250 take it, 1.30 times as fast on average as the other two forms, 0.3 % of them slower by more than 5 % (14 % at
+    // worst); of 4800 bf16 ones 3330, 1.37 times, 0.8 % slower (23 %).  (With one price for all of a form's calls, without launches that add up, strides and
+    // halves of blocks, 0.7 % and 6 % were, up to 27 % and 59 %, and AlexNet's conv1 and conv5 at 64 images, 1.25 and 1.08 times as fast in this form, did not take it.)
+    // Long: some 36 us by mfma_shape's price, below which several times the scratch would buy some 8 %; in bf16, 17 us, below which there is nothing to gain.
+    const bool long_call = bf16 ? us > 17 : P.gather ? 1.11 * cycles / 2400 + 1.1e-6 * P.wt_bytes > 21.5 : 2.1 * cycles / 2400 > 36;
+    if (form == ConvForm::any && long_call) {
         ConvPlan F = P;
         double planes_us;
-        if (plan_planes(L, cv, batch, bf16, dl, F, planes_us) && 1.05 * planes_us < us) {
+        if (plan_planes(L, cv, batch, bf16, dl, F, planes_us) && 1.04 * planes_us < us) {
             P = F;
             P.planes = true;
         }

@@ -52,6 +52,22 @@ def _shapes(geom, batch, terms, workspace):
     return found
 
 
+@pytest.mark.parametrize("geom,batch,path,takes", [
+    # (us in this form and in the faster of the others)
+    (_geom(3, 227, 11, 96, stride=4, pad=0), 64, "f32", True),              # 138, 170
+    (_geom(384, 13, 3, 256, groups=2), 64, "f32", True),                    # 84, 90
+    (_geom(102, 44, 11, 190, stride=4), 2, "f32", False),                   # 60, 47
+    (_geom(379, 11, 11, 433, stride=4), 33, "f32", False),                  # 293, 245
+    (_geom(508, 16, 11, 410), 2, "bf16", False),                            # 320, 201
+    (_geom(32, 180, 5, 50, stride=4), 1, "bf16", False),                    # 31, 23
+    (_geom(7, 95, 3, 42, stride=2), 13, "bf16", False)])                    # 16, 13
+def test_which_calls_take_it(geom, batch, path, takes):
+    L, _ = _layer(np.random.default_rng(1), geom, cl.conv_block_h(geom["OC"], geom["groups"], 128), 128)
+    n = cl.conv_workspace_bytes(L, geom, batch, cl.PATH_MFMA_BF16 if path == "bf16" else cl.PATH_MFMA_F32)
+    assert bool(_shapes(geom, batch, 2 if path == "bf16" else 3, n)) == takes
+    L.free()
+
+
 def _check(rng, geom, block, batch, path, density=0.4, imgs=None):
     import torch
     L, W = _layer(rng, geom, *block, density=density)

@@ -24,7 +24,7 @@ EXPORTS = [
     "cl_layer_host_view", "cl_layer_serialize", "cl_layer_deserialize", "cl_decode_layer",
     "cl_fc_workspace_bytes", "cl_fc_resolved_path", "cl_compressed_fc_forward", "cl_compressed_fc_forward_static", "cl_fc_stack_workspace_bytes",
     "cl_compressed_fc_stack_forward", "cl_layer_group_create", "cl_layer_group_free", "cl_fc_group_workspace_bytes",
-    "cl_compressed_fc_group_forward", "cl_conv_workspace_bytes", "cl_conv_workspace_bytes_min",
+    "cl_compressed_fc_group_forward", "cl_conv_workspace_bytes", "cl_conv_workspace_bytes_min", "cl_conv_workspace_bytes_unsplit",
     "cl_compressed_conv_forward", "cl_plan_batches", "cl_maxpool_forward", "cl_lrn_forward",
     "cl_set_kernel_timing", "cl_last_kernel_ms",
 ]
@@ -107,6 +107,7 @@ def lib():
     L.cl_compressed_fc_group_forward.argtypes = [p, p, sz, p, sz, p, i32, i32, p, sz, p]
     L.cl_conv_workspace_bytes.argtypes = [p, C.POINTER(ConvDesc), i32, i32, C.POINTER(sz)]
     L.cl_conv_workspace_bytes_min.argtypes = [p, C.POINTER(ConvDesc), i32, i32, C.POINTER(sz)]
+    L.cl_conv_workspace_bytes_unsplit.argtypes = [p, C.POINTER(ConvDesc), i32, i32, C.POINTER(sz)]
     L.cl_compressed_conv_forward.argtypes = [p, C.POINTER(ConvDesc), p, p, p, i32, i32, i32, p, sz, p]
     L.cl_plan_batches.argtypes = [i32, p, i32, p, p, p, p, i64, i64, C.c_double, p, C.POINTER(C.c_double)]
     L.cl_maxpool_forward.argtypes = [p, p] + [i32] * 6 + [p]
@@ -421,11 +422,12 @@ class LayerGroup:
         return Y
 
 
-def conv_workspace_bytes(layer: Layer, conv: dict, batch: int, path: int = PATH_AUTO, compact: bool = False) -> int:
-    """Scratch for the fast form of the call, or (compact) the least it works with."""
+def conv_workspace_bytes(layer: Layer, conv: dict, batch: int, path: int = PATH_AUTO, compact: bool = False, unsplit: bool = False) -> int:
+    """Scratch for the fastest form of the call, for the fastest whose operands are not split beforehand (unsplit), or
+    (compact) the least it works with."""
     cd = ConvDesc(conv["C"], conv["H"], conv["W"], conv["R"], conv["S"], conv["stride"], conv["pad"], conv["groups"], conv["OC"])
     n = C.c_size_t(0)
-    fn = lib().cl_conv_workspace_bytes_min if compact else lib().cl_conv_workspace_bytes
+    fn = lib().cl_conv_workspace_bytes_min if compact else lib().cl_conv_workspace_bytes_unsplit if unsplit else lib().cl_conv_workspace_bytes
     _check(fn(layer.handle, C.byref(cd), batch, path, C.byref(n)))
     return n.value
 

@@ -26,6 +26,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <initializer_list>
 #include <memory>
 #include <vector>
 
@@ -1956,33 +1957,37 @@ int32_t plan_conv(const cl_layer *L, const cl_conv_desc *cv, int batch, bool bf1
 
 }  // namespace
 
-extern "C" int32_t cl_conv_workspace_bytes(const cl_layer *L, const cl_conv_desc *cv, int32_t batch, int32_t path, size_t *out)
+static int32_t conv_scratch(const cl_layer *L, const cl_conv_desc *cv, int32_t batch, int32_t path, size_t *out, std::initializer_list<ConvForm> forms)
 {
     if (!L || !out) return fail(CL_EINVAL, "null argument");
     if (batch < 1) return fail(CL_EINVAL, "batch must be positive");
     if (path != CL_PATH_AUTO && !is_mfma(path)) return fail(CL_EUNSUPPORTED, "convolution runs on the MFMA paths only");
     DeviceLimits dl;
     if (int32_t rc = device_limits(dl)) return rc;
-    ConvPlan P;
-    if (int32_t rc = plan_conv(L, cv, batch, path == CL_PATH_MFMA_BF16, dl, P)) return rc;
-    *out = P.total();
+    size_t least = SIZE_MAX;
+    for (ConvForm form : forms) {
+        ConvPlan P;
+        if (int32_t rc = plan_conv(L, cv, batch, path == CL_PATH_MFMA_BF16, dl, P, form)) return rc;
+        least = std::min(least, P.total());
+    }
+    *out = least;
     return CL_OK;
 }
 
+extern "C" int32_t cl_conv_workspace_bytes(const cl_layer *L, const cl_conv_desc *cv, int32_t batch, int32_t path, size_t *out)
+{
+    return conv_scratch(L, cv, batch, path, out, {ConvForm::any});
+}
+
+extern "C" int32_t cl_conv_workspace_bytes_unsplit(const cl_layer *L, const cl_conv_desc *cv, int32_t batch, int32_t path, size_t *out)
+{
+    return conv_scratch(L, cv, batch, path, out, {ConvForm::not_planes});
+}
+
+// (the faster forms' launch shapes can happen to need less than the compact one's)
 extern "C" int32_t cl_conv_workspace_bytes_min(const cl_layer *L, const cl_conv_desc *cv, int32_t batch, int32_t path, size_t *out)
 {
-    if (!L || !out) return fail(CL_EINVAL, "null argument");
-    if (batch < 1) return fail(CL_EINVAL, "batch must be positive");
-    if (path != CL_PATH_AUTO && !is_mfma(path)) return fail(CL_EUNSUPPORTED, "convolution runs on the MFMA paths only");
-    DeviceLimits dl;
-    if (int32_t rc = device_limits(dl)) return rc;
-    ConvPlan P, F;
-    if (int32_t rc = plan_conv(L, cv, batch, path == CL_PATH_MFMA_BF16, dl, P, ConvForm::compact)) return rc;
-    if (int32_t rc = plan_conv(L, cv, batch, path == CL_PATH_MFMA_BF16, dl, F)) return rc;
-    ConvPlan G;
-    if (int32_t rc = plan_conv(L, cv, batch, path == CL_PATH_MFMA_BF16, dl, G, ConvForm::not_planes)) return rc;
-    *out = std::min({P.total(), F.total(), G.total()});      // the faster forms' launch shapes can happen to need less
-    return CL_OK;
+    return conv_scratch(L, cv, batch, path, out, {ConvForm::compact, ConvForm::any, ConvForm::not_planes});
 }
 
 namespace {

@@ -45,11 +45,12 @@ class FcOp:
 
 class ConvOp:
     """compact: run with the least scratch the library works with (filter groups one
-    after the other, blocks decoded inside the multiply kernel) instead of the fast form."""
+    after the other, blocks decoded inside the multiply kernel) instead of the fast form.
+    unsplit: with the scratch of the fastest form whose operands are not split beforehand."""
 
-    def __init__(self, name, layer, geom, block, relu=True, compact=False):
+    def __init__(self, name, layer, geom, block, relu=True, compact=False, unsplit=False):
         self.name, self.layer, self.geom, self.relu, self.block = name, layer, geom, relu, tuple(block)
-        self.compact = compact
+        self.compact, self.unsplit = compact, unsplit
         self._ws = {}
 
     def out_shape(self, in_shape):
@@ -59,7 +60,7 @@ class ConvOp:
         return (g["OC"], P, Q)
 
     def ws_bytes(self, B, in_shape):
-        return cl.conv_workspace_bytes(self.layer, self.geom, B, compact=self.compact)
+        return cl.conv_workspace_bytes(self.layer, self.geom, B, compact=self.compact, unsplit=self.unsplit)
 
     def forward(self, X, out=None):
         import torch
@@ -176,10 +177,19 @@ class NetworkRunner(StackRunner):
         return best
 
 
+def _conv_copy(net, **form):
+    ops = [ConvOp(op.name, op.layer, op.geom, op.block, op.relu, **form) if isinstance(op, ConvOp) else op for op in net.layers]
+    return NetworkRunner(ops, net.in_shape)
+
+
 def compact_copy(net):
     """The same network (the same compressed layers) with its convolutions in the compact form."""
-    ops = [ConvOp(op.name, op.layer, op.geom, op.block, op.relu, compact=True) if isinstance(op, ConvOp) else op for op in net.layers]
-    return NetworkRunner(ops, net.in_shape)
+    return _conv_copy(net, compact=True)
+
+
+def unsplit_copy(net):
+    """The same network with its convolutions in the fastest form that does not split operands beforehand."""
+    return _conv_copy(net, unsplit=True)
 
 
 def alexnet(block=(128, 128), density=None):
@@ -222,14 +232,14 @@ def main(argv=None):
                               ms_per_layer={op.name: round(float(x), 5) for op, x in zip(fast.layers, t)},
                               ms_total=round(float(t.sum()), 4))), flush=True)
         return 0
-    nets = {"fast": fast, "compact": compact_copy(fast)}
+    nets = {"fast": fast, "unsplit": unsplit_copy(fast), "compact": compact_copy(fast)}
     model_bytes = sum(op.layer.stats()["model_bytes"] for op in fast.layers if hasattr(op, "layer"))
     for K in args.images:
         batch_set = [b for b in range(1, K + 1) if K % b == 0]
         times = {name: n.measure_times(batch_set, graphs=args.graphs) for name, n in nets.items()}
         for mult in args.budgets:
             tot = int(mult * model_bytes)
-            # the convolutions' scratch is part of the budget: both forms of the network are
+            # the convolutions' scratch is part of the budget: all forms of the network are
             # planned, the faster feasible plan (and the faster feasible fixed batch) is reported
             plans = {name: n.plan(batch_set, tot, time_ms=times[name]) for name, n in nets.items()}
             fixeds = {name: n.fixed_batch(batch_set, tot, times[name]) for name, n in nets.items()}

@@ -201,3 +201,29 @@ def test_scratch_of_the_other_forms():
     with pytest.raises(cl.CLError):
         cl.compressed_conv_forward(L, geom, X, workspace=torch.empty(least - 256, dtype=torch.uint8, device="cuda"))
     L.free()
+
+
+def test_scratch_without_split_operands():
+    """The gathered form can be asked for by its scratch - decoded blocks, the row table, partial tiles - and is what then runs; a call
+    that splits nothing asks for the same either way."""
+    import torch
+    from paper_1711_00244_amd import network
+    rng = np.random.default_rng(10)
+    geom, batch = _geom(96, 27, 5, 256, groups=2), 16
+    L, W = _layer(rng, geom, 128, 128)
+    full, n = cl.conv_workspace_bytes(L, geom, batch), cl.conv_workspace_bytes(L, geom, batch, unsplit=True)
+    blocks, columns = 2 * 10, -(-batch * 27 * 27 // 128) * 128
+    part = n - blocks * 128 * 128 * 4 - 10 * 128 * 8
+    assert n != full and part % (256 * columns * 4) == 0 and part // (256 * columns * 4) in range(11)
+    assert cl.conv_workspace_bytes(L, geom, 1) == cl.conv_workspace_bytes(L, geom, 1, unsplit=True)
+    X = torch.from_numpy(rng.standard_normal((batch, 96, 27, 27)).astype(np.float32)).cuda()
+    fast = network.ConvOp("conv", L, geom, (128, 128))
+    op = network.unsplit_copy(network.NetworkRunner([fast], (96, 27, 27))).layers[0]
+    assert op.ws_bytes(batch, None) == n
+    Y = op.forward(X)
+    assert torch.equal(Y, cl.compressed_conv_forward(L, geom, X, relu=True, workspace=torch.empty(n, dtype=torch.uint8, device="cuda")))
+    assert not torch.equal(Y, fast.forward(X))               # (the sums run in another order)
+    rows, imgs = np.array([0, 127]), [0, batch - 1]
+    sub = dict(geom, C=48, OC=2, groups=1)
+    assert_close(Y.cpu().numpy()[imgs][:, rows], conv_ref(np.ascontiguousarray(W[rows]), np.ascontiguousarray(X.cpu().numpy()[imgs][:, :48]), sub), True)
+    L.free()

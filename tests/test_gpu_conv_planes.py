@@ -44,11 +44,12 @@ def _shapes(geom, batch, terms, workspace):
         left = workspace - _round256(tiles * rows * steps * terms * 32) - _round256(8 * steps)
         for imgs in {-(-batch // runs) for runs in range(1, batch + 1)}:
             part = left - _round256(_terms_bytes(geom, imgs, terms))
-            one = tiles * rows * -(-imgs * P * Q // 128) * 128 * 4          # (a multiple of 256)
             if part == 0:
                 found.add((rows, 1, imgs))
-            elif part > 0 and part % one == 0 and 2 <= part // one <= steps:
-                found.add((rows, part // one, imgs))
+            for last in {imgs, batch % imgs or imgs}:                           # (the last launch can split more)
+                one = tiles * rows * -(-last * P * Q // 128) * 128 * 4          # (a multiple of 256)
+                if part > 0 and part % one == 0 and 2 <= part // one <= steps:
+                    found.add((rows, part // one, imgs))
     return found
 
 
@@ -68,12 +69,17 @@ def test_which_calls_take_it(geom, batch, path, takes):
     L.free()
 
 
-def _check(rng, geom, block, batch, path, density=0.4, imgs=None):
+def _check(rng, geom, block, batch, path, density=0.4, imgs=None, tile=None):
+    """tile: the rows of the call's tiles, its steps split among workgroups."""
     import torch
     L, W = _layer(rng, geom, *block, density=density)
     terms = 2 if path == "bf16" else 3
     p = cl.PATH_MFMA_BF16 if path == "bf16" else cl.PATH_MFMA_F32
-    assert cl.conv_workspace_bytes(L, geom, batch, p) >= _terms_bytes(geom, imgs or batch, terms)
+    n = cl.conv_workspace_bytes(L, geom, batch, p)
+    assert n >= _terms_bytes(geom, imgs or batch, terms)
+    # (the other forms' scratch can be larger than the terms: what this form asks for, to the byte)
+    shapes = {(rows, splits > 1) for rows, splits, launch in _shapes(geom, batch, terms, n) if launch == (imgs or batch)}
+    assert shapes == {(tile, True)} if tile else shapes
     X = rng.standard_normal((batch, geom["C"], geom["H"], geom["W"])).astype(np.float32)
     bias = rng.standard_normal(geom["OC"]).astype(np.float32)
     Xd, bd = torch.from_numpy(X).cuda(), torch.from_numpy(bias).cuda()
@@ -108,8 +114,6 @@ CASES = [
     # filter groups with filters of their own tiles; strides; blocks of other widths and heights
     (_geom(96, 27, 5, 256, groups=2), (128, 128), 16), (_geom(384, 13, 3, 384, groups=2), (96, 128), 48), (_geom(48, 90, 3, 160, stride=2), (128, 128), 24),
     (_geom(40, 56, 3, 128), (64, 48), 20), (_geom(40, 56, 3, 120), (24, 128), 20), (_geom(20, 40, 11, 96), (96, 128), 16),
-    # few columns, many units: steps split among workgroups
-    (_geom(512, 28, 3, 512), (128, 128), 2), (_geom(505, 15, 11, 70), (72, 128), 8),
 ]
 
 
@@ -119,10 +123,20 @@ def test_edges(geom, block, batch, path):
     _check(np.random.default_rng(geom["C"] * geom["OC"] + batch), geom, block, batch, path)
 
 
+@pytest.mark.parametrize("geom,block,batch,tile", [
+    (_geom(520, 14, 3, 440), (128, 128), 20, 128), (_geom(505, 15, 11, 70), (72, 128), 8, 96), (_geom(1000, 12, 3, 540, groups=2), (90, 128), 24, 96),
+    (_geom(470, 14, 3, 270), (128, 128), 16, 64)])
+@pytest.mark.parametrize("path", ["f32", "bf16"])
+def test_steps_split_among_workgroups(geom, block, batch, tile, path):
+    """Few columns and many units: each tile with its partial tiles added up, also of two filter groups."""
+    _check(np.random.default_rng(tile), geom, block, batch, path, tile=tile)
+
+
 @pytest.mark.parametrize("geom,block,batch,imgs", [
     # terms of all images 300 MB; one image's terms 290 MB; images of 2^18 pixels, at most eight to a launch; a last launch of fewer images
     (_geom(64, 112, 3, 128), (128, 128), 60, 30), (_geom(480, 316, 1, 64, pad=0), (64, 128), 2, 1), (_geom(4, 512, 3, 96), (96, 128), 10, 5),
-    (_geom(72, 200, 3, 64), (64, 128), 25, 13)])
+    # (twice; then also in three splits of the steps where the first launch has two)
+    (_geom(72, 200, 3, 64), (64, 128), 25, 13), (_geom(520, 80, 3, 64), (64, 128), 17, 9)])
 def test_images_in_groups(geom, block, batch, imgs):
     """Scratch that grows with the images stays below 256 MB, or one image's; the images are taken in groups, the weights split with the
     first."""
@@ -150,7 +164,7 @@ def test_not_finite(geom, batch, bad):
     L, W = _layer(rng, geom, 128, 128)
     R, pad, OC = geom["R"], geom["pad"], geom["OC"]
     X = rng.standard_normal((batch, geom["C"], geom["H"], geom["W"])).astype(np.float32)
-    assert cl.conv_workspace_bytes(L, geom, batch) >= _terms_bytes(geom, batch, 3)
+    assert _shapes(geom, batch, 3, cl.conv_workspace_bytes(L, geom, batch))
     clean = cl.compressed_conv_forward(L, geom, torch.from_numpy(X).cuda(), relu=False).cpu().numpy()
     X[4, geom["C"] - 1, 17, 11] = bad
     Y = cl.compressed_conv_forward(L, geom, torch.from_numpy(X).cuda(), relu=False).cpu().numpy()
@@ -174,7 +188,8 @@ def test_codebooks_that_do_not_split():
     cb = np.concatenate([[0.0], np.linspace(1, 2, 255) * 2.0 ** -110 * (1 + 2.0 ** -20)]).astype(np.float32)
     geom, batch = _geom(3, 80, 5, 250), 40
     L, W = _layer(rng, geom, 128, 128, codebook=cb)
-    assert cl.conv_workspace_bytes(L, geom, batch) < _terms_bytes(geom, batch, 3)
+    n = cl.conv_workspace_bytes(L, geom, batch)
+    assert n < _terms_bytes(geom, batch, 3) and not _shapes(geom, batch, 3, n)
     X = (rng.standard_normal((batch, 3, 80, 80)) * 2.0 ** 100).astype(np.float32)
     Y = cl.compressed_conv_forward(L, geom, torch.from_numpy(X).cuda()).cpu().numpy()
     up = np.float32(2.0 ** 20)
@@ -192,7 +207,7 @@ def test_scratch_of_the_other_forms():
     L, W = _layer(rng, geom, 128, 128)
     X = torch.from_numpy(rng.standard_normal((batch, 96, 27, 27)).astype(np.float32)).cuda()
     full, least = cl.conv_workspace_bytes(L, geom, batch), cl.conv_workspace_bytes(L, geom, batch, compact=True)
-    assert least < full
+    assert least < full and _shapes(geom, batch, 3, full)
     rows, imgs = np.array([0, 127]), [0, batch - 1]
     ref = conv_ref(np.ascontiguousarray(W[rows]), np.ascontiguousarray(X.cpu().numpy()[imgs][:, :48]), dict(geom, C=48, OC=2, groups=1))
     for n in (full, full - 256, least):

@@ -519,7 +519,8 @@ bool plan_rows(const cl_layer *L, int batch, const DeviceLimits &dl, RowsPlan &P
     // anew 7.2 %.  Groups and splits come out the same either way (AlexNet-shaped fc6, us a call: 24.4, 28.2 and 40.7; one block
     // to a group 30.0, 32.2 and 40.7 - at 16 images before four lanes had a row); against the other paths the price is too high, which kAutoLaunch makes up for in part.
     // With 16 images (four lanes to a row, groups of one, two or four blocks) its parts are those of 4096-row layers of 4096 to 25088 columns
-    // and 3 to 30 %, to the same 0.83.
+    // and 3 to 30 %, to the same 0.83.  It holds for other heights: of 281 calls at 9 to 16 images drawn from 96 to 8192 rows, 128 to 25088 columns and 2 to
+    // 40 % none is slower than with two rows to a quarter wavefront and that form's price (1.007 times at most), 0.96 times on average.
     static const struct { int groups, group, block, weight_x20; } kFit[3] = {{4, 4400, 630, 29}, {3, 2200, 3000, 34}, {1, 2200, 3900, 51}};
     const auto &fit = kFit[P.ipl / 2];
     const int64_t tiles = (int64_t)L->n_panels * (Bp / images);
@@ -1992,7 +1993,7 @@ extern "C" int32_t cl_conv_workspace_bytes_min(const cl_layer *L, const cl_conv_
 
 namespace {
 
-// One group of images of a convolution call: what the two forms share.
+// One group of images of a convolution call: what the forms share.
 struct ConvCall {
     const cl_layer *L;
     const ConvPlan *P;

@@ -16,7 +16,7 @@ template <int K> __device__ __forceinline__ uint32_t row_bcast(uint32_t v)
 
 // Eight of the sixteen entries a quarter wavefront holds, one per lane (byte offset of the
 // entry's column in the activations, and its weight), K .. K + 7: every quarter multiplies
-// its k-th entry with its sixteen (times IPL) images.  The reads of all eight go out together;
+// its k-th entry with its sixteen times IPL (2 or 4) images.  The reads of all eight (or, of N = 4, four) go out together;
 // the multiply-adds take the weight from lane k of the quarter themselves (written out: the
 // compiler keeps the move apart).
 template <int IPL, int K, int N>
@@ -31,11 +31,8 @@ __device__ __forceinline__ void rows_read(float (&x)[N][IPL], uint32_t off, uint
 #pragma unroll
     for (int u = 0; u < N; ++u) {
         const vec_t v = *(lds_vec)(uintptr_t)at[u];
-        if constexpr (IPL == 1) x[u][0] = v;
-        else {
 #pragma unroll
-            for (int m = 0; m < IPL; ++m) x[u][m] = v[m];
-        }
+        for (int m = 0; m < IPL; ++m) x[u][m] = v[m];
     }
 }
 
@@ -75,29 +72,27 @@ template <int K> __device__ __forceinline__ uint32_t quad_bcast(uint32_t v)
 }
 
 // Four entries of a row, held by its four lanes one each (byte offset of the entry's column in the activations, and its weight),
-// times the lane's four (H = 1) or eight images: images 4 t .. 4 t + 3 of lane t, and those 16 further on.
-template <int H>
-__device__ __forceinline__ void quad_read(float (&x)[4][4 * H], uint32_t off, uint32_t xbase)
+// times the lane's four images: 4 t .. 4 t + 3 of lane t.
+constexpr int kQuadImages = 4;
+
+__device__ __forceinline__ void quad_read(float (&x)[4][kQuadImages], uint32_t off, uint32_t xbase)
 {
     typedef float f4 __attribute__((ext_vector_type(4)));
     typedef const __attribute__((address_space(3))) f4 *lds_f4;
     const uint32_t at[4] = {quad_bcast<0>(off) + xbase, quad_bcast<1>(off) + xbase, quad_bcast<2>(off) + xbase, quad_bcast<3>(off) + xbase};
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+    for (int u = 0; u < 4; ++u) {
+        const f4 v = *(lds_f4)(uintptr_t)at[u];
 #pragma unroll
-        for (int h = 0; h < H; ++h) {
-            const f4 v = ((lds_f4)(uintptr_t)at[u])[4 * h];
-#pragma unroll
-            for (int m = 0; m < 4; ++m) x[u][4 * h + m] = v[m];
-        }
+        for (int m = 0; m < kQuadImages; ++m) x[u][m] = v[m];
+    }
 }
 
-template <int H>
-__device__ __forceinline__ void quad_add(float (&acc)[4 * H], const float (&x)[4][4 * H], float w)
+__device__ __forceinline__ void quad_add(float (&acc)[kQuadImages], const float (&x)[4][kQuadImages], float w)
 {
     // (s_nop: two wait states between a vector write of w and its use as another lane's operand)
 #pragma unroll
-    for (int m = 0; m < 4 * H; ++m)
+    for (int m = 0; m < kQuadImages; ++m)
         asm("s_nop 1\n"
             "v_fmac_f32_dpp %0, %1, %2 quad_perm:[0,0,0,0] row_mask:0xf bank_mask:0xf\n"
             "v_fmac_f32_dpp %0, %1, %3 quad_perm:[1,1,1,1] row_mask:0xf bank_mask:0xf\n"
@@ -335,7 +330,7 @@ __global__ __launch_bounds__(kRowsThreads) void fc_rows_kernel(LayerDev L, const
         }
     };
 
-    constexpr int AR = QUADS ? 1 : RQ, AI = QUADS ? 4 * IPL : IPL;      // rows and images of a lane
+    constexpr int AR = QUADS ? 1 : RQ, AI = QUADS ? kQuadImages : IPL;  // rows and images of a lane
     float acc[AR][AI];
 #pragma unroll
     for (int i = 0; i < AR; ++i)
@@ -370,18 +365,18 @@ __global__ __launch_bounds__(kRowsThreads) void fc_rows_kernel(LayerDev L, const
                 auto off = [&](uint32_t e) { return (e & 255u) * (uint32_t)(kImages * 4); };
                 if (!__any(left[i] > 0)) continue;                          // (all conditions here are uniform)
                 for (;;) {
-                    float x0[4][AI], x1[4][AI];
+                    float x0[4][kQuadImages], x1[4][kQuadImages];
                     const bool two = __any(left[i] > 4), three = __any(left[i] > 8), four = __any(left[i] > 12), more = __any(left[i] > 16);
-                    quad_read<IPL>(x0, off(ent[i][0]), xbase);
-                    if (two) quad_read<IPL>(x1, off(ent[i][1]), xbase);
-                    quad_add<IPL>(acc[0], x0, w[i][0]);
+                    quad_read(x0, off(ent[i][0]), xbase);
+                    if (two) quad_read(x1, off(ent[i][1]), xbase);
+                    quad_add(acc[0], x0, w[i][0]);
                     if (two) {
-                        if (three) quad_read<IPL>(x0, off(ent[i][2]), xbase);
-                        quad_add<IPL>(acc[0], x1, w[i][1]);
+                        if (three) quad_read(x0, off(ent[i][2]), xbase);
+                        quad_add(acc[0], x1, w[i][1]);
                         if (three) {
-                            if (four) quad_read<IPL>(x1, off(ent[i][3]), xbase);
-                            quad_add<IPL>(acc[0], x0, w[i][2]);
-                            if (four) quad_add<IPL>(acc[0], x1, w[i][3]);
+                            if (four) quad_read(x1, off(ent[i][3]), xbase);
+                            quad_add(acc[0], x0, w[i][2]);
+                            if (four) quad_add(acc[0], x1, w[i][3]);
                         }
                     }
                     if (!more) break;
@@ -491,20 +486,15 @@ __global__ __launch_bounds__(kRowsThreads) void fc_rows_kernel(LayerDev L, const
     float *to = part + (((size_t)p * splits + j) * kTile + row0) * (size_t)Bp + img0;
     if constexpr (QUADS) {
         // (the two halves of the workgroup have every second block's sums each; every wavefront has passed its last barrier)
-        float *sums = slabs + (wave & 7) * (64 * AI) + lane * AI;
+        float *sums = slabs + (wave & 7) * (64 * kQuadImages) + lane * kQuadImages;
         if (G > 1 && wave >= 8) store_floats<4>(sums, acc[0]);
-        if constexpr (AI == 8)
-            if (G > 1 && wave >= 8) store_floats<4>(sums + 4, acc[0] + 4);
         if (G > 1) __syncthreads();
         if (wave >= 8) return;
+        float y[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (G > 1) load_floats<4>(sums, y);
 #pragma unroll
-        for (int h = 0; h < IPL; ++h) {
-            float y[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-            if (G > 1) load_floats<4>(sums + 4 * h, y);
-#pragma unroll
-            for (int m = 0; m < 4; ++m) y[m] += acc[0][4 * h + m];
-            store_floats<4>(to + 16 * h + 4 * (lane & 3), y);
-        }
+        for (int m = 0; m < kQuadImages; ++m) y[m] += acc[0][m];
+        store_floats<4>(to + 4 * (lane & 3), y);
     } else {
 #pragma unroll
         for (int i = 0; i < RQ; ++i) store_floats<IPL>(to + (size_t)i * Bp + l16 * IPL, acc[i]);

@@ -6,7 +6,7 @@
 
 // (The third form of a convolution, for long calls; the launcher says when.)
 // conv_mfma_kernel gathers and splits each activation anew for every filter tap, block row and tile of
-// columns.  Here one launch per call (conv_prepare_kernel) splits weights and activations once into the terms
+// columns.  Here a launch (conv_prepare_kernel; one for each group of images, the weights with the first) splits weights and activations once into the terms
 // that the matrix cores multiply, and writes both so that the multiply kernel's operands are
 // plain 16-byte pieces, eight k side by side:
 //   activations: planes of pixels, eight channels of a pixel to a piece, term by term, with the image's
@@ -52,13 +52,14 @@ __device__ __forceinline__ Unit unit_at(const PlaneGeom &g, int u)
 // behind a group's last channel, and the second unit of the last step where there is none, are zero (an
 // activation times what is not written could be a NaN); rows behind a group's last filter stay as they are, and so do
 // the outputs that they reach, which nobody reads.
-// The workgroups behind the layer's blocks split the activations (split8), xs[term][image][plane][pixel][8 or 4 channels].
+// The workgroups behind the layer's blocks (no strips: all of them) split the activations (split8), xs[term][image][plane][pixel][8 or 4 channels].
 // unit_off[u]: bytes from a receptive field's corner to unit u's piece, 0xffffffff for the second unit of a last step that has
 // none.
 // A workgroup takes kPrepCells / `blocks` rows of `blocks` neighbouring blocks, finds the chunks that reach into them by the chunks' position
 // carries, and splits the codebook once, so that a weight's terms are looked up.  Strips that are fewer than the CUs are decoded by
 // several workgroups, each of which writes some of the units.
-// Bound by what is written, 6 bytes a weight and an activation (AlexNet's five convolutions at 64 images 17, 17, 14, 14 and 12 us, conv1 120 MB of them)
+// Bound by what is written, 6 bytes a weight and an activation (AlexNet's five convolutions at 64 images 17, 17, 14, 14 and 12 us of a call less the multiply launch, 24, 20, 16, 18 and 18 in a
+// trace, wavefronts waiting 57-60 % of their time, vector issue 31-40 %; conv1 80 MB written)
 // and, for a small call, by the chain carries -> record -> decode -> terms -> stores (VGG-16 conv4_2 at one image 19 us, of which decoding 8 and
 // storing 14 MB of weights 7).  With whole blocks of 128 x 128, split as they were stored slot by slot, these six were 40, 31, 21, 19, 22 and 20 us.
 template <int NP>
@@ -286,10 +287,11 @@ struct PlaneConv {
 // before they are read; a wavefront's pieces of the next step are read into registers while the present one is multiplied.
 // So a step has one barrier, and next to its multiplies nothing but LDS reads, loads with a scalar offset each, and scalar
 // arithmetic.  Two workgroups to a CU: one's barrier, start and end are the other's multiplies.
-// Bound by the multiplies: a step of 32 of them takes 1101 cycles with one workgroup to a CU (1024 of them multiplies; 1627 with reads
-// and requests in a bunch behind the barrier, and two buffers), and with the chip full the clock gives way: a loop of nothing but these
-// multiplies on random operands reaches 1.6-1.9 PFLOP/s here, on zeros 2.45.  AlexNet conv1 to conv5, 64 images, us, this launch (conv_mfma_kernel's):
-// 117 (150), 147 (182), 98 (118), 80 (118), 56 (72); VGG-16 conv4_2 at one image 29.7 (36.6).
+// Bound by the multiplies: of AlexNet's convolutions at 64 images they are 74 (conv1), 82, 84, 81 and 75 % of the launch's busy cycles (vector issue 13-20 %, LDS
+// 14-23 %, no bank conflicts; with one workgroup to a CU a step of 32 of them, 1024 cycles, took 1101 by stamps in a copy, 1627 with reads and requests in a bunch
+// behind the barrier and two buffers), and with the chip full the clock gives way: a loop of nothing but these
+// multiplies on random operands reaches 1.6-1.9 PFLOP/s here, on zeros 2.45.  conv1 to conv5, 64 images, us of this launch in the network (conv_mfma_kernel's):
+// 114 (163), 148 (187), 95 (114), 75 (125), 54 (71), of preparing 24, 20, 16, 18, 18 (of decoding 7-8); VGG-16 conv4_2 at one image 29.7 (36.6).
 template <int NP, int RT, int CT, int WR, int WC>
 __global__ __launch_bounds__(256, 2) void conv_plane_kernel(const uint4 *__restrict__ wt, const uint4 *__restrict__ xs, const uint32_t *__restrict__ unit_off,
                                                             float *part, PlaneConv g)
